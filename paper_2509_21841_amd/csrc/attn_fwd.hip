@@ -1,12 +1,11 @@
 // Causal attention forward over a work list of (query block, key run) tiles: bf16 MFMA for K Q^T and V^T P^T,
 // K/V tiles staged through LDS, online softmax kept per lane.
 //
-// Orientation. Scores are computed transposed, S^T = K Q^T with the 32x32x16 MFMA: the accumulator lane
-// (l%32, l/32) then holds ONE query (column l%32) and 16 keys per 32-key block (rows 8b + 4(l/32) + c),
-// so the row maximum and row sum of the softmax are in-lane reductions plus one exchange with lane l^32,
-// and the rescale factor is a per-lane scalar. The bf16 probabilities are already laid out as the B
-// operand of O^T += V^T P^T (k-slot i of MFMA m <-> accumulator register 8m+i), and V^T comes from the
-// row-major V tile in LDS through the transposing LDS read with the matching key order.
+// Orientation. Scores are computed transposed, S^T = K Q^T with the 16x16x32 MFMA: accumulator lane l then holds ONE
+// query (column l%16) and 4 keys per 16-key block (rows 4(l/16) + c). A wave owns two 16-query sub-blocks, so every K
+// operand read from LDS feeds two MFMAs. The bf16 probabilities are already laid out as the B operand of
+// O^T += V^T P^T (k-slots 0-3 of a lane are its keys of one 16-key block, 4-7 those of the next), and V^T comes from
+// the row-major V tile in LDS through the transposing LDS read with the matching key order (zp_lds16).
 #include <type_traits>
 #include "zp_common.h"
 
@@ -21,93 +20,116 @@ struct FwdCfg {
   static constexpr int TILEB = BN * D * 2;  // bytes per K (or V) tile
 };
 
-// One 64-key tile for one wave of 32 query rows. Kb, Vb: byte offsets of the K and V tile from the LDS base that
-// the lane offsets in `lo` carry (compile-time at the call sites, so every read is a register plus an immediate).
-// With PIECES, `piece(integral_constant<int, kk>)` is called once per 16-wide k-step of the score MFMAs: the caller
-// issues one asynchronous copy of the next tile there. The steps are fenced, so the copies stay one MFMA pair apart
-// -- far enough that none waits for the address unit behind the copies of the other waves, which is what issuing
-// them back to back in front of the tile costs.
-template <int D, bool MASK, bool PIECES, class Piece>
-__device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[D / 16],
-                                         f32x16 (&o_acc)[D / 32], float &mc, float &l_sum, float c_log2, int j0,
-                                         int hi, int nvis_lane, const zp_lds_offsets<D> &lo, Piece &&piece) {
-  constexpr int KK = D / 16, DB = D / 32;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  f32x16 s0 = zero, s1 = zero;
-  if constexpr (PIECES) {
-    // the K row operands stay two k-steps ahead of the MFMAs that use them
-    bf16x8 k0[KK], k1[KK];
-    k0[0] = lo.rows_at(Kb, 0, 0); k1[0] = lo.rows_at(Kb, 1, 0);
-    k0[1] = lo.rows_at(Kb, 0, 1); k1[1] = lo.rows_at(Kb, 1, 1);
-    zp_static_for<KK>([&](auto kk) {
-      constexpr int k = kk.value;
+// The partial sum of a lane's probabilities of a tile above which the reference maximum of its rows has to move.
+constexpr float P_SUM_MAX = 4096.0f;
+
+// One 64-key tile for one wave of two 16-query sub-blocks. Kb, Vb: byte offsets of the K and V tile from the LDS base
+// that the lane offsets in `lo` carry (compile-time at the call sites, so every read is a register plus an immediate).
+// ONLY1: no query of sub-block 0 sees a key of this tile. Both products run as fenced steps of one LDS operand and the
+// two MFMAs it feeds, operands requested two (K) and three (V) steps ahead, the first two V operands in front of the
+// softmax arithmetic. With PIECES, `piece(integral_constant<int, n>)` is called in every second step of the score
+// product: the caller issues one asynchronous copy of the next tile there, far enough apart that none waits for the
+// address unit behind the copies of the other waves.
+//
+// Bound: the power limit. The 16x16x32 MFMA accumulates twice as many products per accumulator access as the 32x32x16;
+// a register-only loop on random operands holds 1920-2000 TFLOP/s with it against 1520-1800, at the price of twice the
+// issue slots. On four 16384-token sequences (GQA 32/8, d = 128) the 32x32x16 form of this kernel took 7.66 ms and
+// this one takes 7.11 (on zeros, where power does not bind, 5.72 and 5.91: it issues more and waits more).
+//
+// The probabilities are taken against the reference the rows already have, nm = -(reference) in scaled log2 units, and
+// only their sum is looked at: a maximum per tile costs 20 of 136 vector operations and puts a cross-lane exchange in
+// front of the first exp2, while all that it protects against is a reference so far below the scores that the
+// probabilities grow out of range. When a lane's 16 probabilities add up to more than P_SUM_MAX (or to NaN), the rows'
+// maxima are worked out and the tile's probabilities taken again. A row without a reference has nm = +inf, which makes
+// its first tile end there. Probabilities, sums and O are floating point throughout, so the reference's distance
+// from the row maximum costs no precision.
+template <int D, bool MASK, bool ONLY1, bool PIECES, class Piece>
+__device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2][D / 32], f32x4 (&o_acc)[2][D / 16],
+                                         float (&nm)[2], float (&l_sum)[2], float c_log2, int j0, int q4,
+                                         const int (&nvis_lane)[2], const zp_lds16<D> &lo, Piece &&piece) {
+  constexpr int KK = D / 32, DB = D / 16, QB0 = ONLY1 ? 1 : 0;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 s[2][4];
+  {
+    constexpr int N = 4 * KK;  // operand n: key block n % 4, k-step n / 4
+    bf16x8 a[N];
+    a[0] = lo.rows_at(Kb, 0, 0);
+    a[1] = lo.rows_at(Kb, 1, 0);
+    zp_static_for<N>([&](auto nn) {
+      constexpr int n = nn.value, kb = n % 4, k = n / 4;
       __builtin_amdgcn_sched_barrier(0);
-      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[k], qreg[k], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[k], qreg[k], s1, 0, 0, 0);
-      if constexpr (k + 2 < KK) { k0[k + 2] = lo.rows_at(Kb, 0, k + 2); k1[k + 2] = lo.rows_at(Kb, 1, k + 2); }
-      piece(kk);
+#pragma unroll
+      for (int qb = QB0; qb < 2; qb++)
+        s[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], qreg[qb][k], k == 0 ? zero : s[qb][kb], 0, 0, 0);
+      if constexpr (n + 2 < N) a[n + 2] = lo.rows_at(Kb, (n + 2) % 4, (n + 2) / 4);
+      if constexpr (PIECES && n % 2 == 0) piece(std::integral_constant<int, n / 2>{});
     });
     __builtin_amdgcn_sched_barrier(0);
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < KK; kk++) {
-      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows_at(Kb, 0, kk), qreg[kk], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows_at(Kb, 1, kk), qreg[kk], s1, 0, 0, 0);
-    }
   }
+  bf16x8 va[2 * DB];  // operand n of the second product: 32 keys n / DB, 16 columns n % DB
+  va[0] = lo.tr_at(Vb, 0, 0);
+  va[1] = lo.tr_at(Vb, 0, 1);
+  __builtin_amdgcn_sched_barrier(0);
   if (MASK) {
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int j = j0 + 8 * (r >> 2) + 4 * hi + (r & 3);
-      if (j >= nvis_lane) s0[r] = -INFINITY;
-      if (j + 32 >= nvis_lane) s1[r] = -INFINITY;
+    for (int qb = QB0; qb < 2; qb++)
+#pragma unroll
+      for (int kb = 0; kb < 4; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+          if (j0 + 16 * kb + q4 + r >= nvis_lane[qb]) s[qb][kb][r] = -INFINITY;
+  }
+  // probabilities as the B operands of the second product: operand kp covers key blocks 2 kp and 2 kp + 1
+  bf16x8 pb[2][2];
+  float t[2] = {0.f, 0.f};
+  auto take = [&](int qb, float ref) {
+    float ta = 0.f, tb = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 4; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const float p = zp_exp2(__builtin_fmaf(s[qb][kb][r], c_log2, ref));
+        // the row sum is taken over the unrounded probabilities: LSE has to hold to 1e-3 also for rows with few keys
+        if (kb & 1) tb += p; else ta += p;
+        pb[qb][kb >> 1][(kb & 1) * 4 + r] = (__bf16)p;
+      }
+    t[qb] = ta + tb;
+  };
+#pragma unroll
+  for (int qb = QB0; qb < 2; qb++) take(qb, nm[qb]);
+  if (__builtin_amdgcn_ballot_w64(!(t[QB0] <= P_SUM_MAX && t[1] <= P_SUM_MAX)) != 0) {
+#pragma unroll
+    for (int qb = QB0; qb < 2; qb++) {
+      float m = s[qb][0][0];
+#pragma unroll
+      for (int kb = 0; kb < 4; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) m = fmaxf(m, s[qb][kb][r]);
+      m = zp_quad_max(m) * c_log2;
+      const float mc_old = -nm[qb], mc = fmaxf(mc_old, m);
+      const bool none = mc == -INFINITY;  // no key seen yet: keep waiting, every probability of this tile is zero
+      const float alpha = none ? 1.0f : zp_exp2(mc_old - mc);
+      nm[qb] = -mc;
+      l_sum[qb] *= alpha;
+#pragma unroll
+      for (int i = 0; i < DB; i++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) o_acc[qb][i][r] *= alpha;
+      take(qb, none ? 0.f : -mc);
     }
   }
-  // Two chains of three-operand maxima over the lane's 32 scores. The compiler does not check the inline-assembly
-  // v_max3 against the "MFMA result read too early" hazard, so both chains start from t0, an ordinary fmaxf of one
-  // register of each accumulator: the wait states the compiler inserts before t0 cover every later read.
-  const float t0 = fmaxf(s0[15], s1[15]);
-  float ta = zp_max3(t0, s0[0], s0[1]);
-  float tb = zp_max3(t0, s1[0], s1[1]);
 #pragma unroll
-  for (int r = 2; r < 14; r += 2) {
-    ta = zp_max3(ta, s0[r], s0[r + 1]);
-    tb = zp_max3(tb, s1[r], s1[r + 1]);
-  }
-  const float tmax = zp_pair_max(zp_max3(ta, tb, fmaxf(s0[14], s1[14])));
-  const float tmc = tmax * c_log2;
-  // the reference maximum moves only when the tile maximum exceeds it by more than 2^8
-  if (__builtin_amdgcn_ballot_w64(tmc > mc + 8.0f) != 0) {
-    const bool mv = tmc > mc + 8.0f;
-    const float alpha = mv ? zp_exp2(mc - tmc) : 1.0f;
-    mc = mv ? tmc : mc;
-    l_sum *= alpha;
+  for (int qb = QB0; qb < 2; qb++) l_sum[qb] += t[qb];
+  va[2] = lo.tr_at(Vb, 0, 2);
+  zp_static_for<2 * DB>([&](auto nn) {
+    constexpr int n = nn.value, kp = n / DB, db = n % DB;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < DB; i++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) o_acc[i][r] *= alpha;
-  }
-  const float neg_mc = (mc == -INFINITY) ? 0.f : -mc;
-  // the row sum is taken over the unrounded probabilities: LSE has to hold to 1e-3 also for rows with few keys
-  bf16x8 pb[2][2];
-  float l1 = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; r++) {
-    const float p0 = zp_exp2(__builtin_fmaf(s0[r], c_log2, neg_mc));
-    const float p1 = zp_exp2(__builtin_fmaf(s1[r], c_log2, neg_mc));
-    l_sum += p0;
-    l1 += p1;
-    pb[0][r >> 3][r & 7] = (__bf16)p0;
-    pb[1][r >> 3][r & 7] = (__bf16)p1;
-  }
-  l_sum += l1;
-#pragma unroll
-  for (int kb = 0; kb < 2; kb++)
-#pragma unroll
-    for (int m = 0; m < 2; m++)
-#pragma unroll
-      for (int db = 0; db < DB; db++)
-        o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.tr_at(Vb, kb, m, db), pb[kb][m], o_acc[db], 0, 0, 0);
+    for (int qb = QB0; qb < 2; qb++)
+      o_acc[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[n], pb[qb][kp], o_acc[qb][db], 0, 0, 0);
+    if constexpr (n + 3 < 2 * DB) va[n + 3] = lo.tr_at(Vb, (n + 3) / DB, (n + 3) % DB);
+  });
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 template <int D, int NW, bool PARTIAL>
@@ -128,46 +150,51 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const zp_tile t = p.tiles[tile_idx];
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int ql = lane & 31, hi = lane >> 5;
-  const int row = w * 32 + ql;  // this lane's query row inside the block
-  const bool row_ok = row < t.q_rows;
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  // A wave's two sub-blocks of 16 query rows are the w-th from the front and the w-th from the back of the block, so
+  // that all four waves see about the same number of keys and meet the barriers together.
+  const int rb[2] = {16 * w, 16 * (7 - w)};
+  const int row[2] = {rb[0] + c16, rb[1] + c16};  // this lane's query rows inside the block
 
   // number of keys of the run visible to a query row r: clamp(q_pos0 + r - k_pos0 + 1, 0, k_len)
   auto nvis_of = [&](int r) {
     int n = t.q_pos0 + r - t.k_pos0 + 1;
     return n < 0 ? 0 : (n > t.k_len ? t.k_len : n);
   };
-  const int nvis_lane = nvis_of(row);
-  const int nvis_w_min = nvis_of(w * 32), nvis_w_max = nvis_of(w * 32 + 31);
+  const int nvis_lane[2] = {nvis_of(row[0]), nvis_of(row[1])};
+  // fewest and most keys a sub-block's rows see (none if the block ends before it)
+  const int nvis0_min = nvis_of(rb[0]), nvis1_min = nvis_of(rb[1]);
+  const int nvis0_max = rb[0] < t.q_rows ? nvis_of(rb[0] + 15) : 0, nvis1_max = rb[1] < t.q_rows ? nvis_of(rb[1] + 15) : 0;
   const int n_kt = (nvis_of(t.q_rows - 1) + BN - 1) / BN;
 
-  // Q^T operand: 8 consecutive head-dim elements of this lane's query per 16-wide k-step
-  bf16x8 qreg[D / 16];
-  {
-    const __bf16 *qp = p.q + (int64_t)(t.q_tok0 + row) * p.q_stride + (int64_t)h * D + 8 * hi;
+  // Q^T operands: 8 consecutive head-dim elements of this lane's queries per 32-wide k-step
+  bf16x8 qreg[2][D / 32];
 #pragma unroll
-    for (int kk = 0; kk < D / 16; kk++) {
-      if (row_ok) qreg[kk] = *(const bf16x8 *)(qp + 16 * kk);
-      else qreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  for (int qb = 0; qb < 2; qb++) {
+    const __bf16 *qp = p.q + (int64_t)(t.q_tok0 + row[qb]) * p.q_stride + (int64_t)h * D + 2 * q4;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) {
+      if (row[qb] < t.q_rows) qreg[qb][kk] = *(const bf16x8 *)(qp + 32 * kk);
+      else qreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
     }
   }
   // No wait here: the first tile copy is issued right behind these loads so that the two memory latencies of the
   // prologue overlap; the explicit wait in front of the first barrier covers both (and tells the compiler that the
   // register operands have arrived: a wait of its own inside the key loop would drain the copies in flight).
 
-  zp_stager<D> kst, vst;
+  zp_stager<D, 4, true> kst, vst;
   kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
   vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
-  zp_lds_offsets<D> lo;
+  zp_lds16<D> lo;
   lo.init_abs(lane, smem);
 
-  f32x16 o_acc[D / 32];
+  f32x4 o_acc[2][D / 16];
 #pragma unroll
-  for (int i = 0; i < D / 32; i++)
+  for (int qb = 0; qb < 2; qb++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) o_acc[i][r] = 0.f;
-  float mc = -INFINITY;  // running reference maximum, in scaled log2 units
-  float l_sum = 0.f;     // this lane's share of the row sum
+    for (int i = 0; i < D / 16; i++) o_acc[qb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float nm[2] = {INFINITY, INFINITY};  // minus the running reference maximum, in scaled log2 units
+  float l_sum[2] = {0.f, 0.f};         // this lane's share of the row sums
   const float c_log2 = p.scale_log2;
 
   if (n_kt > 0) {
@@ -177,17 +204,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   zp_wait_async();
   __syncthreads();
 
-  constexpr int PW = zp_stager<D>::PER_WAVE;
+  constexpr int PW = zp_stager<D, 4, true>::PER_WAVE;
   // one key tile out of LDS buffer BUF (a compile-time constant, so every LDS address is register + immediate)
   auto key_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
     const int j0 = it * BN;
-    const bool compute = j0 < nvis_w_max;  // otherwise every key of this tile is masked for the whole wave
-    const bool masked = j0 + BN > nvis_w_min;
+    // which sub-blocks have a row that sees a key of this tile, and whether some row sees only a part of it
+    const bool act0 = j0 < nvis0_max, act1 = j0 < nvis1_max;
+    const bool compute = act0 || act1;
+    const bool masked = j0 + BN > (act0 ? nvis0_min : nvis1_min);
     // the next tile is fetched inside this tile's score MFMAs when it has 64 valid keys and this wave computes an
     // unmasked tile (the common case), else in front of it
     const bool fetch = it + 1 < n_kt;
-    const bool fused = fetch && compute && !masked && j0 + 2 * BN <= t.k_len;
+    const bool fused = fetch && act0 && !masked && j0 + 2 * BN <= t.k_len;
     if (fetch && !fused) {
       kst.issue(Ks + (buf ^ 1) * C::TILEB, j0 + BN, t.k_len);
       vst.issue(Vs + (buf ^ 1) * C::TILEB, j0 + BN, t.k_len);
@@ -198,7 +227,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const void *pc_v = zp_uniform_ptr(vst.base + (int64_t)(j0 + BN) * vst.stride);
     auto stage_piece = [&](auto n) {
       constexpr int N = decltype(n)::value, i = N / 2;
-      static_assert(2 * PW == D / 16, "one copy per k-step");
+      static_assert(2 * PW == 2 * (D / 32), "one copy per two K operands");
       if constexpr (N % 2 == 0)
         zp_dma16_so(pc_k, kst.off[i], __builtin_amdgcn_readfirstlane(zp_lds_addr(Ks + (buf ^ 1) * C::TILEB) + (kst.w * PW + i) * 1024));
       else
@@ -206,26 +235,27 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     };
     if (compute) {
       constexpr int Kb = buf * C::TILEB, Vb = (2 + buf) * C::TILEB;  // byte offsets of the tiles from smem
-      if (masked) fwd_tile<D, true, false>(Kb, Vb, qreg, o_acc, mc, l_sum, c_log2, j0, hi, nvis_lane, lo, stage_piece);
-      else if (fused) fwd_tile<D, false, true>(Kb, Vb, qreg, o_acc, mc, l_sum, c_log2, j0, hi, nvis_lane, lo, stage_piece);
-      else fwd_tile<D, false, false>(Kb, Vb, qreg, o_acc, mc, l_sum, c_log2, j0, hi, nvis_lane, lo, stage_piece);
+      if (!act0) fwd_tile<D, true, true, false>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
+      else if (masked) fwd_tile<D, true, false, false>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
+      else if (fused) fwd_tile<D, false, false, true>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
+      else fwd_tile<D, false, false, false>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
     }
     zp_wait_async();
     __syncthreads();
   };
-  int it = 0;
-  for (; it + 1 < n_kt; it += 2) {
+  for (int it = 0; it < n_kt; it += 2) {
     key_tile(it, std::integral_constant<int, 0>{});
-    key_tile(it + 1, std::integral_constant<int, 1>{});
+    if (it + 1 < n_kt) key_tile(it + 1, std::integral_constant<int, 1>{});
   }
-  if (it < n_kt) key_tile(it, std::integral_constant<int, 0>{});
 
   // epilogue: normalise, write O and LSE
-  const float l_tot = zp_pair_sum(l_sum);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  const float lse = l_tot > 0.f ? (mc * 0.6931471805599453f + __logf(l_tot)) : -INFINITY;
-  if (row_ok) {
-    const int64_t orow = (int64_t)t.out_row0 + row;
+#pragma unroll
+  for (int qb = 0; qb < 2; qb++) {
+    const float l_tot = zp_quad_sum(l_sum[qb]);
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    const float lse = l_tot > 0.f ? (__logf(l_tot) - nm[qb] * 0.6931471805599453f) : -INFINITY;
+    if (row[qb] >= t.q_rows) continue;
+    const int64_t orow = (int64_t)t.out_row0 + row[qb];
     if (PARTIAL) {
       // weights of the running row (w_old) and of this partial (w_new, its 1/l folded in); without update: 0 and 1/l
       float w_old = 0.f, w_new = inv, lse_out = lse;
@@ -242,31 +272,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           w_new = e_new / tot * inv;
         }
       }
-      if (hi == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse_out;
-      float *op = (float *)p.o + orow * p.o_stride + (int64_t)h * D + 4 * hi;
+      if (q4 == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse_out;
+      float *op = (float *)p.o + orow * p.o_stride + (int64_t)h * D + q4;
 #pragma unroll
-      for (int db = 0; db < D / 32; db++)
-#pragma unroll
-        for (int b = 0; b < 4; b++) {
-          f32x4 v4 = {o_acc[db][4 * b] * w_new, o_acc[db][4 * b + 1] * w_new, o_acc[db][4 * b + 2] * w_new,
-                      o_acc[db][4 * b + 3] * w_new};
-          if (w_old > 0.f) {  // a row that has seen no key yet may hold anything
-            const f32x4 old = *(const f32x4 *)(op + db * 32 + b * 8);
-            v4[0] += w_old * old[0]; v4[1] += w_old * old[1]; v4[2] += w_old * old[2]; v4[3] += w_old * old[3];
-          }
-          *(f32x4 *)(op + db * 32 + b * 8) = v4;
+      for (int db = 0; db < D / 16; db++) {
+        f32x4 v4 = {o_acc[qb][db][0] * w_new, o_acc[qb][db][1] * w_new, o_acc[qb][db][2] * w_new, o_acc[qb][db][3] * w_new};
+        if (w_old > 0.f) {  // a row that has seen no key yet may hold anything
+          const f32x4 old = *(const f32x4 *)(op + db * 16);
+          v4[0] += w_old * old[0]; v4[1] += w_old * old[1]; v4[2] += w_old * old[2]; v4[3] += w_old * old[3];
         }
+        *(f32x4 *)(op + db * 16) = v4;
+      }
     } else {
-      if (hi == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse;
-      __bf16 *op = (__bf16 *)p.o + orow * p.o_stride + (int64_t)h * D + 4 * hi;
+      if (q4 == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse;
+      __bf16 *op = (__bf16 *)p.o + orow * p.o_stride + (int64_t)h * D + q4;
 #pragma unroll
-      for (int db = 0; db < D / 32; db++)
-#pragma unroll
-        for (int b = 0; b < 4; b++) {
-          bf16x4 v4 = {(__bf16)(o_acc[db][4 * b] * inv), (__bf16)(o_acc[db][4 * b + 1] * inv),
-                       (__bf16)(o_acc[db][4 * b + 2] * inv), (__bf16)(o_acc[db][4 * b + 3] * inv)};
-          *(bf16x4 *)(op + db * 32 + b * 8) = v4;
-        }
+      for (int db = 0; db < D / 16; db++) {
+        bf16x4 v4 = {(__bf16)(o_acc[qb][db][0] * inv), (__bf16)(o_acc[qb][db][1] * inv),
+                     (__bf16)(o_acc[qb][db][2] * inv), (__bf16)(o_acc[qb][db][3] * inv)};
+        *(bf16x4 *)(op + db * 16) = v4;
+      }
     }
   }
 }

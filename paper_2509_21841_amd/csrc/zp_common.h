@@ -124,6 +124,16 @@ __device__ __forceinline__ float zp_pair_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// max / sum across the four lanes l%16, +16, +32, +48 that hold one column of a 16x16 MFMA accumulator.
+__device__ __forceinline__ float zp_quad_max(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return zp_pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float zp_quad_sum(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return zp_pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
 // 16-byte LDS read and the gfx950 transposing 8-byte LDS read.
 __device__ __forceinline__ bf16x8 zp_lds_read16(const char *smem, int off) {
   return *(const ZP_LDS bf16x8 *)((const ZP_LDS char *)smem + off);
@@ -152,6 +162,21 @@ __device__ __forceinline__ int zp_swz(int row, int chunk) {
 template <int D>
 __device__ __forceinline__ int zp_swz_col(int row, int col) {
   return zp_swz<D>(row, col >> 3) + ((col & 7) << 1);
+}
+
+// The swizzle of tiles read as operands of the 16x16x32 MFMA: what the 16-byte chunk index of row `row` (r3 r2 r1 r0 in
+// binary) is XORed with. Both read patterns touch each of the 64 banks once per phase of the LDS pipe:
+//  - row-wise ds_read_b128 (lane l: row l%16, chunk c + l/16): a phase serves lanes 0-3, 12-15 and 20-27 (or the other
+//    half of 0-31), that is eight rows with r2 == r3 at chunk c and the other eight at chunk c ^ 1; the map has to be
+//    one-to-one both as it is and with r2 ^ r3 added to its lowest bit. (Rows 0-7 on the chunk pairs in order and rows
+//    8-15 with the chunks exchanged is one-to-one only as it is: twice the LDS cycles, by counter.)
+//  - transposing ds_read_b64_tr_b16 (32 lanes: 8 consecutive rows x 2 chunks): eight different chunk pairs (D = 64: four
+//    in each 128-byte half).
+template <int D>
+__device__ __forceinline__ int zp_swz16_mask(int row) {
+  const int x = ((row >> 2) ^ (row >> 3)) & 1, r3 = (row >> 3) & 1;
+  if (D == 128) return (x << 3) | ((row & 3) << 1) | r3;
+  return (x << 2) | (row & 2) | r3;
 }
 
 // ---- asynchronous global -> LDS copies -------------------------------------------------------------
@@ -210,7 +235,7 @@ __device__ __forceinline__ const void *zp_uniform_ptr(const void *p) {
 // out once (they carry the LDS swizzle); issuing a tile is then scalar address arithmetic plus the loads.
 // `init` takes the tensor base of the row run and the token stride (64 * stride * 2 bytes must fit 32 bits);
 // `issue` copies rows row0 .. row0+63 (rows past rows_total clamp to the last valid row).
-template <int D, int NW = 4>
+template <int D, int NW = 4, bool T16 = false>
 struct zp_stager {
   static constexpr int PER_WAVE = 64 * D * 2 / 1024 / NW;  // 1 KiB wave-loads per wave (NW = 4: the four waves share a 64-row tile; NW = 8: they cover its first 32 rows)
   static constexpr int LOADS = PER_WAVE;
@@ -219,7 +244,10 @@ struct zp_stager {
   const __bf16 *base;
   int w, lane;
   __device__ __forceinline__ static void row_chunk(int blk, int lane, int &r, int &c) {
-    if (D == 128) {
+    if (T16) {
+      r = D == 128 ? blk * 4 + (lane >> 4) : blk * 8 + (lane >> 3);
+      c = (lane & (D / 8 - 1)) ^ zp_swz16_mask<D>(r);
+    } else if (D == 128) {
       r = blk * 4 + (lane >> 4);
       c = (lane & 15) ^ (((r & 3) << 2) | ((r >> 2) & 3));
     } else {
@@ -247,10 +275,12 @@ struct zp_stager {
 #pragma unroll
       for (int n = 0; n < PER_WAVE; n++) zp_dma16_so(sb, off[n], lds0 + (w * PER_WAVE + n) * 1024);
     } else {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));  // keeps the rare path's addresses out of the registers of the loop around it
 #pragma unroll
       for (int n = 0; n < PER_WAVE; n++) {
         int r, c;
-        row_chunk(w * PER_WAVE + n, lane, r, c);
+        row_chunk(w * PER_WAVE + n, ln, r, c);
         int gr = row0 + r;
         if (gr > rows_total - 1) gr = rows_total - 1;
         zp_dma16(base + (int64_t)gr * stride + c * 8 + extra, lds0 + (w * PER_WAVE + n) * 1024);
@@ -314,6 +344,43 @@ struct zp_lds_offsets {
   __device__ __forceinline__ bf16x8 tr(const char *tile, int kb, int m, int db) const {
     const int o = (kb * 32 + m * 16) * ROWB;
     return zp_cat(zp_lds_read_tr(tile, tr_off[0][db] + o), zp_lds_read_tr(tile, tr_off[1][db] + o));
+  }
+};
+
+// LDS read addresses of one lane for the two operand patterns of the 16x16x32 MFMA on a [64][D] zp_swz16 tile. Lane l
+// holds row (or column) l % 16 and the k-slots 8 (l / 16) .. + 7.
+// rows_at(kb, kk): 16 bytes of row 16*kb + l%16, head-dim elements 32*kk + 8*(l/16) ..+7  (row-major operand)
+// tr_at(kp, db): the transposed operand of 32 rows and 16 columns: column 16*db + l%16; k-slots 0-3 of the lane are rows
+//   32*kp + 4*(l/16) ..+3, k-slots 4-7 the rows 16 further -- the order in which two accumulators of 16 rows each hold
+//   their rows, so that a product's accumulators are the next product's other operand without moving between lanes.
+template <int D>
+struct zp_lds16 {
+  static constexpr int ROWB = D * 2;
+  int row_off[D / 32];
+  int tr_off[D / 16];
+  __device__ __forceinline__ void init_abs(int lane, const char *base) {
+    const int r16 = lane & 15, q = lane >> 4;
+    const int b = (int)(unsigned)(unsigned long long)(const ZP_LDS char *)base;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) {
+      row_off[kk] = b + r16 * ROWB + (((4 * kk + q) ^ zp_swz16_mask<D>(r16)) << 4);
+      asm volatile("" : "+v"(row_off[kk]));  // opaque from here on: see zp_lds_offsets
+    }
+    const int tr = 4 * q + (r16 >> 2);
+#pragma unroll
+    for (int db = 0; db < D / 16; db++) {
+      tr_off[db] = b + tr * ROWB + (((2 * db + ((r16 >> 1) & 1)) ^ zp_swz16_mask<D>(tr)) << 4) + ((r16 & 1) << 3);
+      asm volatile("" : "+v"(tr_off[db]));
+    }
+  }
+  __device__ __forceinline__ bf16x8 rows_at(int tile_off, int kb, int kk) const {
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(unsigned)(row_off[kk] + tile_off + kb * 16 * ROWB);
+  }
+  __device__ __forceinline__ bf16x8 tr_at(int tile_off, int kp, int db) const {
+    const int o = tile_off + kp * 32 * ROWB;
+    s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(unsigned)(tr_off[db] + o));
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(unsigned)(tr_off[db] + o + 16 * ROWB));
+    return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
   }
 };
 
