@@ -59,51 +59,83 @@ __device__ __forceinline__ void add_acc_rows(float *dst, const f32x16 (&acc)[D /
     }
 }
 
+// the same for accumulators of the 16x16x32 MFMA: 4 consecutive columns per 16-column block
+template <int D>
+__device__ __forceinline__ void store_acc_rows16(__bf16 *dst, const f32x4 (&acc)[D / 16], float mul) {
+#pragma unroll
+  for (int db = 0; db < D / 16; db++)
+    *(bf16x4 *)(dst + db * 16) = bf16x4{(__bf16)(acc[db][0] * mul), (__bf16)(acc[db][1] * mul), (__bf16)(acc[db][2] * mul), (__bf16)(acc[db][3] * mul)};
+}
+template <int D>
+__device__ __forceinline__ void add_acc_rows16(float *dst, const f32x4 (&acc)[D / 16], float mul) {
+#pragma unroll
+  for (int db = 0; db < D / 16; db++) {
+    f32x4 cur = *(const f32x4 *)(dst + db * 16);
+    cur[0] += acc[db][0] * mul; cur[1] += acc[db][1] * mul; cur[2] += acc[db][2] * mul; cur[3] += acc[db][3] * mul;
+    *(f32x4 *)(dst + db * 16) = cur;
+  }
+}
+
 // ------------------------------------------------------------------------------------------- dQ
-// One 32-key half of a K/V tile for one wave: S^T and dP^T chains, dS^T, then dQ^T += K^T dS^T.
-// `piece(integral_constant<int, kk>)` is called once per 16-wide k-step of the chains when PIECES is set: the caller
-// issues one asynchronous copy of the next tile there. Every step is fenced and the copies are ordered against every
-// LDS access, so they end up one per MFMA pair -- far enough apart that none waits for the address unit behind the
-// copies of the other waves. Kb, Vb: byte offsets of the K and V tile from the base the lane offsets carry.
-template <int D, bool MASK, bool PIECES, class Piece>
-__device__ __forceinline__ void dq_half(int Kb, int Vb, int kb, const bf16x8 (&qreg)[D / 16],
-                                        const bf16x8 (&doreg)[D / 16], f32x16 (&dq_acc)[D / 32], float c_log2,
-                                        float lse2, const f32x16 &negD, int j0, int hi, int nvis_lane,
-                                        const zp_lds_offsets<D> &lo, Piece &&piece) {
-  constexpr int KK = D / 16, DB = D / 32;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // the dP^T chain starts from -D (a lane holds one query, so the seed is the same in all 16 registers and lives in
-  // registers for the whole kernel): the accumulator then holds dP - D
-  // the LDS operand reads stay two k-steps ahead of the MFMAs that use them; every step is fenced so that the
-  // copies keep their distance
-  f32x16 s = zero, dp = negD;
-  bf16x8 ka[KK], va[KK];
-  ka[0] = lo.rows_at(Kb, kb, 0); va[0] = lo.rows_at(Vb, kb, 0);
-  ka[1] = lo.rows_at(Kb, kb, 1); va[1] = lo.rows_at(Vb, kb, 1);
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value;
+// 32 of a tile's 64 keys (half `half`) for one wave of two 16-query sub-blocks: S^T and dP^T, dS^T, dQ^T += K^T dS^T, all on the
+// 16x16x32 MFMA (attn_fwd.hip has the orientation and the layouts; zp_lds16 the LDS side). Steps of one LDS operand
+// and the two MFMAs it feeds are fenced, operands requested two (rows) and three (transposed) steps ahead, the first two
+// transposed ones in front of the dS arithmetic. ONLY1: no query of sub-block 0 sees a key of this half.
+// `piece(integral_constant<int, n>)` is called in every second step of the first two products when PIECES is set: the
+// caller issues one asynchronous copy of the next tile there, far enough apart that none waits for the address unit
+// behind the copies of the other waves. Kb, Vb: byte offsets of the K and V tile from the base the lane offsets carry.
+template <int D, bool MASK, bool ONLY1, bool PIECES, class Piece>
+__device__ __forceinline__ void dq_half(int Kb, int Vb, int half, const bf16x8 (&qreg)[2][D / 32],
+                                        const bf16x8 (&doreg)[2][D / 32], f32x4 (&dq_acc)[2][D / 16], float c_log2,
+                                        const float (&lse2)[2], const f32x4 (&negD)[2], int j0, int q4,
+                                        const int (&nvis_lane)[2], const zp_lds16<D> &lo, Piece &&piece) {
+  constexpr int KK = D / 32, DB = D / 16, N = 4 * KK, QB0 = ONLY1 ? 1 : 0;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  // the dP^T chains start from -D (a lane holds one query per sub-block): the accumulator then holds dP - D
+  f32x4 s[2][2], dp[2][2];
+  bf16x8 x[N];  // operand n: K and V alternating, key block n / 2 % 2 of the half, k-step n / 4
+  auto load = [&](auto nn) {
+    constexpr int n = decltype(nn)::value;
+    if constexpr (n < N) x[n] = lo.rows_at(n % 2 ? Vb : Kb, 2 * half + n / 2 % 2, n / 4);
+  };
+  load(std::integral_constant<int, 0>{});
+  load(std::integral_constant<int, 1>{});
+  zp_static_for<N>([&](auto nn) {
+    constexpr int n = nn.value, kb = n / 2 % 2, k = n / 4;
     __builtin_amdgcn_sched_barrier(0);
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[k], qreg[k], s, 0, 0, 0);
-    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[k], doreg[k], dp, 0, 0, 0);
-    if constexpr (k + 2 < KK) { ka[k + 2] = lo.rows_at(Kb, kb, k + 2); va[k + 2] = lo.rows_at(Vb, kb, k + 2); }
-    if constexpr (PIECES) piece(kk);
+#pragma unroll
+    for (int qb = QB0; qb < 2; qb++) {
+      if constexpr (n % 2 == 0) s[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], qreg[qb][k], k == 0 ? zero : s[qb][kb], 0, 0, 0);
+      else dp[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], doreg[qb][k], k == 0 ? negD[qb] : dp[qb][kb], 0, 0, 0);
+    }
+    load(std::integral_constant<int, n + 2>{});
+    if constexpr (PIECES && n % 2 == 0) piece(std::integral_constant<int, n / 2>{});
   });
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8 xt[DB];
+  xt[0] = lo.tr_at(Kb, half, 0);
+  xt[1] = lo.tr_at(Kb, half, 1);
   __builtin_amdgcn_sched_barrier(0);
   bf16x8 dsb[2];
 #pragma unroll
-  for (int r = 0; r < 16; r++) {
-    float pv = zp_exp2(__builtin_fmaf(s[r], c_log2, -lse2));
-    if (MASK) {
-      const int j = j0 + kb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-      if (j >= nvis_lane) pv = 0.f;
-    }
-    dsb[r >> 3][r & 7] = (__bf16)(pv * dp[r]);
-  }
+  for (int qb = QB0; qb < 2; qb++)
 #pragma unroll
-  for (int m = 0; m < 2; m++)
+    for (int kb = 0; kb < 2; kb++)
 #pragma unroll
-    for (int db = 0; db < DB; db++)
-      dq_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.tr_at(Kb, kb, m, db), dsb[m], dq_acc[db], 0, 0, 0);
+      for (int r = 0; r < 4; r++) {
+        float pv = zp_exp2(__builtin_fmaf(s[qb][kb][r], c_log2, -lse2[qb]));
+        if (MASK && j0 + 32 * half + 16 * kb + q4 + r >= nvis_lane[qb]) pv = 0.f;
+        dsb[qb][4 * kb + r] = (__bf16)(pv * dp[qb][kb][r]);
+      }
+  xt[2] = lo.tr_at(Kb, half, 2);
+  zp_static_for<DB>([&](auto nn) {
+    constexpr int n = nn.value;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qb = QB0; qb < 2; qb++)
+      dq_acc[qb][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[n], dsb[qb], dq_acc[qb][n], 0, 0, 0);
+    if constexpr (n + 3 < DB) xt[n + 3] = lo.tr_at(Kb, half, n + 3);
+  });
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -114,7 +146,6 @@ __device__ __forceinline__ void dq_half(int Kb, int Vb, int kb, const bf16x8 (&q
 template <int D>
 __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(zp_bwd_params p) {
   constexpr int TILEB = 64 * D * 2;
-  constexpr int LOADS = 2 * zp_stager<D>::LOADS;  // async loads one wave issues per staged K/V tile pair
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char *Ks = smem;               // [2][64][D]
   char *Vs = smem + 2 * TILEB;   // [2][64][D]
@@ -129,92 +160,98 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const zp_tile t = p.dq_tiles[tile_idx];
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int ql = lane & 31, hi = lane >> 5;
-  const int row = w * 32 + ql;
-  const bool row_ok = row < t.q_rows;
-  const int64_t tok = (int64_t)t.q_tok0 + row;
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  // the wave's two sub-blocks of 16 query rows, the w-th from the front and the w-th from the back of the block, so that
+  // all four waves see about the same number of keys
+  const int rb[2] = {16 * w, 16 * (7 - w)};
+  const int row[2] = {rb[0] + c16, rb[1] + c16};
 
   auto nvis_of = [&](int r) {
     int n = t.q_pos0 + r - t.k_pos0 + 1;
     return n < 0 ? 0 : (n > t.k_len ? t.k_len : n);
   };
-  const int nvis_lane = nvis_of(row);
-  const int nvis_w_min = nvis_of(w * 32), nvis_w_max = nvis_of(w * 32 + 31);
+  const int nvis_lane[2] = {nvis_of(row[0]), nvis_of(row[1])};
+  const int nvis0_min = nvis_of(rb[0]), nvis1_min = nvis_of(rb[1]);
+  const int nvis0_max = rb[0] < t.q_rows ? nvis_of(rb[0] + 15) : 0, nvis1_max = rb[1] < t.q_rows ? nvis_of(rb[1] + 15) : 0;
   const int n_kt = (nvis_of(t.q_rows - 1) + 63) / 64;
 
-  zp_stager<D> kst, vst;
+  zp_stager<D, 4, true> kst, vst;
   kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
   vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
-  zp_lds_offsets<D> lo;
+  zp_lds16<D> lo;
   lo.init_abs(lane, smem);
 
   // Row operands first, the first tile copy right behind them (the two memory latencies overlap), their first use
   // after that. The explicit wait before the first barrier covers all of it and tells the compiler that the register
   // operands have arrived (a wait of its own inside the key loop would drain the copies in flight every iteration).
-  bf16x8 qreg[D / 16], doreg[D / 16], oreg[D / 16];
-  {
-    const __bf16 *qp = p.q + tok * p.q_stride + (int64_t)h * D + 8 * hi;
-    const __bf16 *dop = p.dout + tok * p.do_stride + (int64_t)h * D + 8 * hi;
-    const __bf16 *op = p.o + tok * p.o_stride + (int64_t)h * D + 8 * hi;
+  bf16x8 qreg[2][D / 32], doreg[2][D / 32], oreg[2][D / 32];
+  float lse_nat[2] = {0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < D / 16; kk++) {
-      if (row_ok) {
-        qreg[kk] = *(const bf16x8 *)(qp + 16 * kk);
-        doreg[kk] = *(const bf16x8 *)(dop + 16 * kk);
-        oreg[kk] = *(const bf16x8 *)(op + 16 * kk);
+  for (int qb = 0; qb < 2; qb++) {
+    const int64_t tok = (int64_t)t.q_tok0 + row[qb];
+    const __bf16 *qp = p.q + tok * p.q_stride + (int64_t)h * D + 2 * q4;
+    const __bf16 *dop = p.dout + tok * p.do_stride + (int64_t)h * D + 2 * q4;
+    const __bf16 *op = p.o + tok * p.o_stride + (int64_t)h * D + 2 * q4;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) {
+      if (row[qb] < t.q_rows) {
+        qreg[qb][kk] = *(const bf16x8 *)(qp + 32 * kk);
+        doreg[qb][kk] = *(const bf16x8 *)(dop + 32 * kk);
+        oreg[qb][kk] = *(const bf16x8 *)(op + 32 * kk);
       } else {
-        qreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        doreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        oreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        qreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        doreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        oreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
       }
     }
+    if (row[qb] < t.q_rows) lse_nat[qb] = p.lse[(int64_t)h * p.T + tok];
   }
-  float lse_nat = 0.f;
-  if (row_ok) lse_nat = p.lse[(int64_t)h * p.T + tok];
   if (n_kt > 0) {
     kst.issue(Ks, 0, t.k_len);
     vst.issue(Vs, 0, t.k_len);
   }
-  float dsum = 0.f;
+  float lse2[2];
+  f32x4 negD[2];
 #pragma unroll
-  for (int kk = 0; kk < D / 16; kk++)
+  for (int qb = 0; qb < 2; qb++) {
+    float dsum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; e++) dsum += (float)doreg[kk][e] * (float)oreg[kk][e];
-  const float Dq = zp_pair_sum(dsum);
-  float lse2 = 0.f;
-  if (row_ok) {
-    lse2 = lse_nat * LOG2E;
-    if (hi == 0) {
+    for (int kk = 0; kk < D / 32; kk++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) dsum += (float)doreg[qb][kk][e] * (float)oreg[qb][kk][e];
+    const float Dq = zp_quad_sum(dsum);
+    lse2[qb] = lse_nat[qb] * LOG2E;
+    negD[qb] = f32x4{-Dq, -Dq, -Dq, -Dq};
+    if (row[qb] < t.q_rows && q4 == 0) {
       // negated and pre-divided so that the second kernel can seed its MFMA accumulators with them
-      p.dvec[(int64_t)h * p.T + tok] = -Dq;
-      p.lse2[(int64_t)h * p.T + tok] = -lse_nat / p.scale;
+      const int64_t at = (int64_t)h * p.T + t.q_tok0 + row[qb];
+      p.dvec[at] = -Dq;
+      p.lse2[at] = -lse_nat[qb] / p.scale;
     }
   }
 
-  f32x16 dq_acc[D / 32];
+  f32x4 dq_acc[2][D / 16];
 #pragma unroll
-  for (int i = 0; i < D / 32; i++)
+  for (int qb = 0; qb < 2; qb++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) dq_acc[i][r] = 0.f;
+    for (int i = 0; i < D / 16; i++) dq_acc[qb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float c_log2 = p.scale_log2;
 
   zp_wait_async();
   __syncthreads();
 
-  f32x16 negD;
-#pragma unroll
-  for (int r = 0; r < 16; r++) negD[r] = -Dq;
-  constexpr int PW = zp_stager<D>::PER_WAVE;
+  constexpr int PW = zp_stager<D, 4, true>::PER_WAVE;
   // one key tile out of LDS buffer BUF (compile-time, so that every LDS address is a register plus an immediate)
   auto key_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
     const int j0 = it * 64;
-    const bool compute = j0 < nvis_w_max;
-    const bool masked = j0 + 64 > nvis_w_min;
+    const bool act0 = j0 < nvis0_max, act1 = j0 < nvis1_max;  // sub-blocks with a row that sees a key of this tile
+    const bool compute = act0 || act1;
+    const bool masked = j0 + 64 > (act0 ? nvis0_min : nvis1_min);
     // the next tile is fetched inside the first half of this tile's arithmetic when it has 64 valid keys and this
     // wave computes an unmasked tile (the common case), else in front of it
     const bool fetch = it + 1 < n_kt;
-    const bool fused = fetch && compute && !masked && j0 + 128 <= t.k_len;
+    const bool fused = fetch && act0 && !masked && j0 + 128 <= t.k_len;
     if (fetch && !fused) {
       kst.issue(Ks + (buf ^ 1) * TILEB, j0 + 64, t.k_len);
       vst.issue(Vs + (buf ^ 1) * TILEB, j0 + 64, t.k_len);
@@ -225,7 +262,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const void *pc_v = zp_uniform_ptr(vst.base + (int64_t)(j0 + 64) * vst.stride);
     auto stage_piece = [&](auto n) {
       constexpr int N = decltype(n)::value, i = N / 2;
-      static_assert(2 * PW == D / 16, "one copy per k-step");
+      static_assert(2 * PW == 2 * (D / 32), "one copy per two steps");
       if constexpr (N % 2 == 0)
         zp_dma16_so(pc_k, kst.off[i], __builtin_amdgcn_readfirstlane(zp_lds_addr(Ks + (buf ^ 1) * TILEB) + (kst.w * PW + i) * 1024));
       else
@@ -233,15 +270,18 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
     if (compute) {
       constexpr int Kb = buf * TILEB, Vb = (2 + buf) * TILEB;  // byte offsets of the tiles from smem
-      if (masked) {
-        dq_half<D, true, false>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, hi, nvis_lane, lo, stage_piece);
-        dq_half<D, true, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, hi, nvis_lane, lo, stage_piece);
+      if (masked || !act0) {
+        // the halves of a tile on the diagonal one by one: a half that none of the wave's rows sees is left out
+        if (act0) dq_half<D, true, false, false>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
+        else dq_half<D, true, true, false>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
+        if (j0 + 32 < nvis0_max) dq_half<D, true, false, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
+        else if (j0 + 32 < nvis1_max) dq_half<D, true, true, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
       } else if (fused) {
-        dq_half<D, false, true>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, hi, nvis_lane, lo, stage_piece);
-        dq_half<D, false, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, hi, nvis_lane, lo, stage_piece);
+        dq_half<D, false, false, true>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
+        dq_half<D, false, false, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
       } else {
-        dq_half<D, false, false>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, hi, nvis_lane, lo, stage_piece);
-        dq_half<D, false, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, hi, nvis_lane, lo, stage_piece);
+        dq_half<D, false, false, false>(Kb, Vb, 0, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
+        dq_half<D, false, false, false>(Kb, Vb, 1, qreg, doreg, dq_acc, c_log2, lse2, negD, j0, q4, nvis_lane, lo, stage_piece);
       }
     }
     zp_wait_async();
@@ -252,9 +292,12 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if (it + 1 < n_kt) key_tile(it + 1, std::integral_constant<int, 1>{});
   }
 
-  if (row_ok) {
-    if (p.accumulate) add_acc_rows<D>((float *)p.dq + tok * p.dq_stride + (int64_t)h * D + 4 * hi, dq_acc, p.scale);
-    else store_acc_rows<D>(p.dq + tok * p.dq_stride + (int64_t)h * D + 4 * hi, dq_acc, p.scale);
+#pragma unroll
+  for (int qb = 0; qb < 2; qb++) {
+    if (row[qb] >= t.q_rows) continue;
+    const int64_t at = ((int64_t)t.q_tok0 + row[qb]) * p.dq_stride + (int64_t)h * D + q4;
+    if (p.accumulate) add_acc_rows16<D>((float *)p.dq + at, dq_acc[qb], p.scale);
+    else store_acc_rows16<D>(p.dq + at, dq_acc[qb], p.scale);
   }
 }
 
