@@ -157,7 +157,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   if (unit >= p.n_dq_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = p.dq_tiles[tile_idx];
+  const zp_tile t = zp_load_tile(p.dq_tiles + tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
@@ -310,14 +310,13 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // pipelined -- LDS operands are fetched a phase ahead, the exp/scale arithmetic of one block is interleaved
 // with the MFMAs of the other.
 
-// Two neighbouring elements (registers r, r + 1 of the accumulators) of P and dS of a 32-query block, packed as bf16.
-// The accumulators were seeded with -LSE/scale and -D, so P = exp2(S c) and dS = P dP.
+// Two neighbouring elements (registers r, r + 1 of an accumulator; the queries at positions qpos and qpos + 1) of P and
+// dS, packed as bf16. The accumulators were seeded with -LSE/scale and -D, so P = exp2(S c) and dS = P dP.
 template <bool MASK>
-__device__ __forceinline__ void dkdv_pair(const f32x16 &s, const f32x16 &dp, int r, int qb, int hi, int qpos0,
-                                          int kpos, int qpos_end, float c_log2, unsigned &p_pk, unsigned &ds_pk) {
+__device__ __forceinline__ void dkdv_pair(const f32x4 &s, const f32x4 &dp, int r, int qpos, int kpos, int qpos_end,
+                                          float c_log2, unsigned &p_pk, unsigned &ds_pk) {
   float p0 = zp_exp2(s[r] * c_log2), p1 = zp_exp2(s[r + 1] * c_log2);
   if (MASK) {
-    const int qpos = qpos0 + qb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
     if (qpos < kpos || qpos >= qpos_end) p0 = 0.f;
     if (qpos + 1 < kpos || qpos + 1 >= qpos_end) p1 = 0.f;
   }
@@ -325,99 +324,111 @@ __device__ __forceinline__ void dkdv_pair(const f32x16 &s, const f32x16 &dp, int
   const bf16x2 dd = {(__bf16)(p0 * dp[r]), (__bf16)(p1 * dp[r + 1])};
   p_pk = __builtin_bit_cast(unsigned, pp);
   ds_pk = __builtin_bit_cast(unsigned, dd);
+  asm volatile("" : "+v"(p_pk), "+v"(ds_pk));  // keeps the arithmetic in the step it is written in
 }
 
-// One 64-query tile = two 32-query blocks in four phases of D / 16 steps, two MFMAs per step:
+__device__ __forceinline__ bf16x8 dkdv_operand(const unsigned (&v)[4]) {
+  return __builtin_bit_cast(bf16x8, (u32x4){v[0], v[1], v[2], v[3]});
+}
+
+// One 64-query tile = two 32-query blocks in four phases of D / 16 steps, two LDS operands and the four MFMAs (one per
+// 16-key sub-block) they feed in a step:
 //   A: S,dP(0) | B: S,dP(1) || P,dS(0) | C: dV,dK(0) || P,dS(1) | D: dV,dK(1) || the caller's copies
-// A wave issues in order, so the overlap is written into the program order: every step is fenced, its two LDS
-// operands are requested two steps ahead (each phase thereby reads what its own MFMAs consume, 1/4 of the tile's
-// LDS traffic), and an empty volatile asm that takes the step's results as in/out operands pins its MFMAs and vector
-// arithmetic to the step. `piece(integral_constant<int, n>)` is called after the n-th MFMA of phase D
-// (n = 0 .. 4 * D / 32 - 1): the caller's asynchronous copies of a later tile are issued there, one load between two
-// MFMAs.
-template <int D, bool MASK, class Piece>
-__device__ __forceinline__ void dkdv_tile(const char *Qb, const char *Ob, const float *Lb, const float *Db,
-                                          const bf16x8 (&kreg)[D / 16], const bf16x8 (&vreg)[D / 16],
-                                          f32x16 (&dk_acc)[D / 32], f32x16 (&dv_acc)[D / 32], int qpos0, int kpos,
-                                          int qpos_end, float c_log2, int hi, const zp_lds_offsets<D> &lo,
+// A wave issues in order, so the overlap is written into the program order: every step is fenced and its LDS operands
+// are requested two steps ahead. ONLY0: no query of the tile sees a key of sub-block 1.
+// `piece(integral_constant<int, n>)` is called after each half of a step of phase D (n = 0 .. 2 * D / 16 - 1): the
+// caller's asynchronous copies of a later tile are issued there, one load at a time.
+// `lo` carries the addresses of the tile's Q rows; its dO rows are ZP_TILEB behind; seed: LDS address of the tile's
+// -LSE/scale plus the lane's 4 (l / 16) floats, -D is D_OFF bytes behind.
+template <int D, int D_OFF, bool MASK, bool ONLY0, class Piece>
+__device__ __forceinline__ void dkdv_tile(unsigned seed, const bf16x8 (&kreg)[2][D / 32], const bf16x8 (&vreg)[2][D / 32],
+                                          f32x4 (&dk_acc)[2][D / 16], f32x4 (&dv_acc)[2][D / 16], int qpos0,
+                                          const int (&kpos)[2], int qpos_end, float c_log2, const zp_lds16<D> &lo,
                                           Piece &&piece) {
-  constexpr int KK = D / 16, DB = D / 32, PPS = 8 / KK;  // steps per phase; pairs of P/dS elements per step
-  f32x16 s[2], dp[2];
-  auto load_seed = [&](int qb) {  // -LSE/scale and -D of the 16 query rows this lane holds
+  constexpr int QN = D / 16, PPS = 8 / QN, CB = ONLY0 ? 1 : 2;  // steps per phase; pairs of P/dS elements per step
+  constexpr int TILEB = 64 * D * 2;
+  f32x4 ls[2][2], ds[2][2];  // seeds: [32-query block][16 rows], the 4 query rows this lane holds
+  f32x4 s[2][2][2], dp[2][2][2];
+  auto load_seed = [&](int blk) {
 #pragma unroll
-    for (int b = 0; b < 4; b++) {
-      const f32x4 l4 = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)Lb + (qb * 32 + 8 * b + 4 * hi) * 4);
-      const f32x4 d4 = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)Db + (qb * 32 + 8 * b + 4 * hi) * 4);
-#pragma unroll
-      for (int c = 0; c < 4; c++) { s[qb][4 * b + c] = l4[c]; dp[qb][4 * b + c] = d4[c]; }
+    for (int rb = 0; rb < 2; rb++) {
+      ls[blk][rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + (blk * 32 + rb * 16) * 4);
+      ds[blk][rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + (blk * 32 + rb * 16) * 4);
     }
   };
-  // operand pair of global step t (phase t / KK, step t % KK): rows of Q,dO for A and B, transposed pieces of dO,Q
-  // for C and D
-  bf16x8 x[4 * KK], y[4 * KK];
-  auto load_ops = [&](auto tt) {
-    constexpr int t = decltype(tt)::value, ph = t / KK, k = t % KK;
-    if constexpr (ph < 2) { x[t] = lo.rows(Qb, ph, k); y[t] = lo.rows(Ob, ph, k); }
-    else { x[t] = lo.tr(Ob, ph - 2, k / DB, k % DB); y[t] = lo.tr(Qb, ph - 2, k / DB, k % DB); }
+  // operand pair of global step t (phase t / QN): rows of Q,dO for A and B (16 rows i % 2, k-step i / 2), transposed
+  // pieces of dO,Q for C and D (16 columns i)
+  bf16x8 x[4 * QN + 2], y[4 * QN + 2];
+  // (y before x: the wait for x then covers both)
+  auto load_ops = [&](auto tt, auto yy) {
+    constexpr int t = decltype(tt)::value, ph = t / QN, i = t % QN;
+    constexpr bool is_y = decltype(yy)::value;
+    if constexpr (ph < 2) (is_y ? y[t] : x[t]) = lo.rows_at(is_y ? TILEB : 0, 2 * ph + i % 2, i / 2);
+    else if constexpr (ph < 4) (is_y ? y[t] : x[t]) = lo.tr_at(is_y ? 0 : TILEB, ph - 2, i);
   };
-  unsigned ppk[2][8], dpk[2][8];
-
+  unsigned ppk[2][2][4], dpk[2][2][4];  // [block][sub-block][elements 2j, 2j + 1]
+  // element pair e of a block: 16 rows e / 4, sub-block e / 2 % 2, registers 2 (e % 2) and + 1; worked out in four stages,
+  // one behind each MFMA of a step
+  float e0[PPS], e1[PPS], d0[PPS], d1[PPS];
+  auto pair_stage = [&](int blk, int e, int u, int stage) {
+    const int rb = e / 4, cb = e / 2 % 2, r = 2 * (e % 2);
+    if (cb >= CB) return;
+    if (stage == 0) {
+      e0[u] = s[blk][rb][cb][r] * c_log2;
+      e1[u] = s[blk][rb][cb][r + 1] * c_log2;
+    } else if (stage == 1) {
+      e0[u] = zp_exp2(e0[u]);
+      e1[u] = zp_exp2(e1[u]);
+    } else if (stage == 2) {
+      if (MASK) {
+        const int qpos = qpos0 + blk * 32 + rb * 16 + r;
+        if (qpos < kpos[cb] || qpos >= qpos_end) e0[u] = 0.f;
+        if (qpos + 1 < kpos[cb] || qpos + 1 >= qpos_end) e1[u] = 0.f;
+      }
+      d0[u] = e0[u] * dp[blk][rb][cb][r];
+      d1[u] = e1[u] * dp[blk][rb][cb][r + 1];
+    } else {
+      unsigned pp = __builtin_bit_cast(unsigned, (bf16x2){(__bf16)e0[u], (__bf16)e1[u]});
+      unsigned dd = __builtin_bit_cast(unsigned, (bf16x2){(__bf16)d0[u], (__bf16)d1[u]});
+      asm volatile("" : "+v"(pp), "+v"(dd));
+      ppk[blk][cb][2 * rb + e % 2] = pp;
+      dpk[blk][cb][2 * rb + e % 2] = dd;
+      return;
+    }
+    asm volatile("" : "+v"(e0[u]), "+v"(e1[u]));
+    if (stage == 2) asm volatile("" : "+v"(d0[u]), "+v"(d1[u]));
+  };
   load_seed(0);
-  load_ops(std::integral_constant<int, 0>{});
-  load_ops(std::integral_constant<int, 1>{});
-  // A
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value, t = k;
-    __builtin_amdgcn_sched_barrier(0);
-    s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[t], kreg[k], s[0], 0, 0, 0);
-    dp[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[t], vreg[k], dp[0], 0, 0, 0);
-    load_ops(std::integral_constant<int, t + 2>{});
-    if constexpr (k == KK / 2) load_seed(1);
-    asm volatile("" : "+v"(s[0]), "+v"(dp[0]));
-  });
-  // B
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value, t = KK + k;
-    __builtin_amdgcn_sched_barrier(0);
-    s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[t], kreg[k], s[1], 0, 0, 0);
-    dp[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[t], vreg[k], dp[1], 0, 0, 0);
+  load_ops(std::integral_constant<int, 0>{}, std::true_type{});
+  load_ops(std::integral_constant<int, 0>{}, std::false_type{});
+  load_ops(std::integral_constant<int, 1>{}, std::true_type{});
+  load_ops(std::integral_constant<int, 1>{}, std::false_type{});
+  zp_static_for<4 * QN>([&](auto tt) {
+    constexpr int t = tt.value, ph = t / QN, i = t % QN;
+    // the MFMAs of a step: the x operand with each sub-block, then the y operand; what else belongs to the step goes
+    // between them a little at a time
+    zp_static_for<4>([&](auto mm) {
+      constexpr int m = mm.value, cb = m % 2;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (cb < CB) {
+        if constexpr (ph < 2) {
+          constexpr int rb = i % 2, k = i / 2;
+          if constexpr (m < 2) s[ph][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t], kreg[cb][k], k == 0 ? ls[ph][rb] : s[ph][rb][cb], 0, 0, 0);
+          else dp[ph][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[t], vreg[cb][k], k == 0 ? ds[ph][rb] : dp[ph][rb][cb], 0, 0, 0);
+        } else {
+          if constexpr (m < 2) dv_acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t], dkdv_operand(ppk[ph - 2][cb]), dv_acc[cb][i], 0, 0, 0);
+          else dk_acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[t], dkdv_operand(dpk[ph - 2][cb]), dk_acc[cb][i], 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (m % 2 == 0) load_ops(std::integral_constant<int, t + 2>{}, std::integral_constant<bool, m == 0>{});
+      if constexpr (ph == 1 || ph == 2) {
 #pragma unroll
-    for (int q = 0; q < PPS; q++)
-      dkdv_pair<MASK>(s[0], dp[0], 2 * (PPS * k + q), 0, hi, qpos0, kpos, qpos_end, c_log2, ppk[0][PPS * k + q], dpk[0][PPS * k + q]);
-    load_ops(std::integral_constant<int, t + 2>{});
-    if constexpr (PPS == 1) asm volatile("" : "+v"(s[1]), "+v"(dp[1]), "+v"(ppk[0][k]), "+v"(dpk[0][k]));
-    else asm volatile("" : "+v"(s[1]), "+v"(dp[1]), "+v"(ppk[0][2 * k]), "+v"(dpk[0][2 * k]), "+v"(ppk[0][2 * k + 1]), "+v"(dpk[0][2 * k + 1]));
-  });
-  auto pack4 = [](const unsigned (&v)[8], int m) {
-    return __builtin_bit_cast(bf16x8, (u32x4){v[4 * m], v[4 * m + 1], v[4 * m + 2], v[4 * m + 3]});
-  };
-  const bf16x8 pb0[2] = {pack4(ppk[0], 0), pack4(ppk[0], 1)}, dsb0[2] = {pack4(dpk[0], 0), pack4(dpk[0], 1)};
-  // C
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value, t = 2 * KK + k, m = k / DB, db = k % DB;
-    __builtin_amdgcn_sched_barrier(0);
-    dv_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[t], pb0[m], dv_acc[db], 0, 0, 0);
-    dk_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[t], dsb0[m], dk_acc[db], 0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < PPS; q++)
-      dkdv_pair<MASK>(s[1], dp[1], 2 * (PPS * k + q), 1, hi, qpos0, kpos, qpos_end, c_log2, ppk[1][PPS * k + q], dpk[1][PPS * k + q]);
-    load_ops(std::integral_constant<int, t + 2>{});
-    if constexpr (PPS == 1) asm volatile("" : "+v"(dv_acc[db]), "+v"(dk_acc[db]), "+v"(ppk[1][k]), "+v"(dpk[1][k]));
-    else asm volatile("" : "+v"(dv_acc[db]), "+v"(dk_acc[db]), "+v"(ppk[1][2 * k]), "+v"(dpk[1][2 * k]), "+v"(ppk[1][2 * k + 1]), "+v"(dpk[1][2 * k + 1]));
-  });
-  const bf16x8 pb1[2] = {pack4(ppk[1], 0), pack4(ppk[1], 1)}, dsb1[2] = {pack4(dpk[1], 0), pack4(dpk[1], 1)};
-  // D
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value, t = 3 * KK + k, m = k / DB, db = k % DB;
-    __builtin_amdgcn_sched_barrier(0);
-    dv_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[t], pb1[m], dv_acc[db], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    piece(std::integral_constant<int, 2 * k>{});
-    __builtin_amdgcn_sched_barrier(0);
-    dk_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[t], dsb1[m], dk_acc[db], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    piece(std::integral_constant<int, 2 * k + 1>{});
-    if constexpr (k + 2 < KK) load_ops(std::integral_constant<int, t + 2>{});
+        for (int u = 0; u < PPS; u++) pair_stage(ph - 1, i * PPS + u, u, m);
+      }
+      if constexpr (t == QN / 2 && m == 1) load_seed(1);
+      if constexpr (ph == 3 && m % 2 == 1) piece(std::integral_constant<int, 2 * i + m / 2>{});
+    });
   });
   __builtin_amdgcn_sched_barrier(0);
 }
@@ -428,88 +439,84 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
   constexpr int NBUF = 4;                       // tiles are fetched three iterations ahead
   constexpr int LOADS = 2 * (TILEB / 4096) + 2; // async loads one wave issues per staged tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char *Qs = smem;                              // [NBUF][64][D]
-  char *Os = smem + NBUF * TILEB;               // [NBUF][64][D]  (dO)
+  char *Qs = smem;                              // [NBUF][2][64][D]: a tile's Q rows and, behind them, its dO rows
   float *Ls = (float *)(smem + 2 * NBUF * TILEB);  // [NBUF][64] -LSE / scale
   float *Ds = Ls + NBUF * 64;                   // [NBUF][64] -D
 
   const int unit = zp_item_of_block(p.work_kv, (int *)(Ds + NBUF * 64));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
-  const zp_tile t = p.kv_tiles[tile_idx];
+  const zp_tile t = zp_load_tile(p.kv_tiles + tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int kl = lane & 31, hi = lane >> 5;
-  const int krow = w * 32 + kl;
-  const bool key_ok = krow < t.k_len;
-  const int64_t ktok = (int64_t)t.k_tok0 + krow;
-  const int kpos = t.k_pos0 + krow;
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  // the wave's two sub-blocks of 16 key rows, the w-th from the front and the w-th from the back of the block, so that
+  // all four waves are seen by about the same number of queries
+  const int kb[2] = {16 * w, 16 * (7 - w)};
+  const int krow[2] = {kb[0] + c16, kb[1] + c16};
+  const int kpos[2] = {t.k_pos0 + krow[0] - q4, t.k_pos0 + krow[1] - q4};  // less the lane's first query row: see dkdv_pair
 
-  bf16x8 kreg[D / 16], vreg[D / 16];
-  {
-    const __bf16 *kp = p.k + ktok * p.k_stride + (int64_t)g * D + 8 * hi;
-    const __bf16 *vp = p.v + ktok * p.v_stride + (int64_t)g * D + 8 * hi;
+  bf16x8 kreg[2][D / 32], vreg[2][D / 32];
 #pragma unroll
-    for (int kk = 0; kk < D / 16; kk++) {
-      if (key_ok) {
-        kreg[kk] = *(const bf16x8 *)(kp + 16 * kk);
-        vreg[kk] = *(const bf16x8 *)(vp + 16 * kk);
+  for (int cb = 0; cb < 2; cb++) {
+    const int64_t ktok = (int64_t)t.k_tok0 + krow[cb];
+    const __bf16 *kp = p.k + ktok * p.k_stride + (int64_t)g * D + 2 * q4;
+    const __bf16 *vp = p.v + ktok * p.v_stride + (int64_t)g * D + 2 * q4;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) {
+      if (krow[cb] < t.k_len) {
+        kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
+        vreg[cb][kk] = *(const bf16x8 *)(vp + 32 * kk);
       } else {
-        kreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        vreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        kreg[cb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        vreg[cb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
       }
     }
   }
 
-  f32x16 dk_acc[D / 32], dv_acc[D / 32];
+  f32x4 dk_acc[2][D / 16], dv_acc[2][D / 16];
 #pragma unroll
-  for (int i = 0; i < D / 32; i++)
+  for (int cb = 0; cb < 2; cb++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) { dk_acc[i][r] = 0.f; dv_acc[i][r] = 0.f; }
+    for (int i = 0; i < D / 16; i++) dk_acc[cb][i] = dv_acc[cb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float c_log2 = p.scale_log2;
 
   const int n_qt = (t.q_rows + 63) / 64;
   const int n_it = n_qt * p.grp;  // iterations: query tiles outermost (last tile first), heads of the group innermost
 
-  zp_stager<D> qst, ost;
+  zp_stager<D, 4, true> qst, ost;
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
   ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, tid);
-  zp_lds_offsets<D> lo;
-  lo.init(lane);
+  zp_lds16<D> lo;  // of the tile in hand: moved on by a buffer after every tile
+  lo.init_abs(lane, smem);
+  unsigned seed = zp_lds_addr(Ls) + q4 * 4;
   // Iteration order: query tiles from the END of the sequence backwards, the heads of the group innermost.
   // Workgroups of one sequence that start together then read the same (tile, head) at the same time and
   // share it in L2; the diagonal (masked) tiles come last.
-  int st_hh = 0, st_qt = n_qt - 1;
+  int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
+  auto staged = [&] { if (++st_hh == p.grp) { st_hh = 0; st_qt--; } };
   auto stage = [&](int buf) {
     const int hh = st_hh, i0 = st_qt * 64;
     const int h = g * p.grp + hh;
-    if (++st_hh == p.grp) { st_hh = 0; st_qt--; }
-    qst.issue(Qs + buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
-    ost.issue(Os + buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
+    qst.issue(Qs + 2 * buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
+    ost.issue(Qs + (2 * buf + 1) * TILEB, i0, t.q_rows, (int64_t)hh * D);
     const int64_t base = (int64_t)h * p.T + t.q_tok0;
     zp_stage_async_f32x64(Ls + buf * 64, p.lse2 + base, i0, t.q_rows - 1, lane);
     zp_stage_async_f32x64(Ds + buf * 64, p.dvec + base, i0, t.q_rows - 1, lane);
   };
   // The same copies for a tile of 64 valid rows, cut into pieces that dkdv_tile issues between the MFMAs of its
-  // last phase: piece 0 is the scalar address arithmetic, every later piece one load (same order as `stage`).
-  constexpr int PW = zp_stager<D>::PER_WAVE;
-  const void *pc_q = nullptr, *pc_o = nullptr, *pc_l = nullptr, *pc_d = nullptr;
+  // last phase: every piece but the first one load (same order as `stage`).
+  constexpr int PW = zp_stager<D, 4, true>::PER_WAVE;
+  const void *pc_q, *pc_o, *pc_l, *pc_d;
   unsigned pc_buf = 0;
   auto stage_piece = [&](auto n) {
     constexpr int N = decltype(n)::value;
     if constexpr (N == 0) {
-      const int hh = st_hh, i0 = st_qt * 64;
-      const int h = g * p.grp + hh;
-      if (++st_hh == p.grp) { st_hh = 0; st_qt--; }
-      pc_q = zp_uniform_ptr(qst.base + (int64_t)i0 * qst.stride + (int64_t)hh * D);
-      pc_o = zp_uniform_ptr(ost.base + (int64_t)i0 * ost.stride + (int64_t)hh * D);
-      const int64_t base = (int64_t)h * p.T + t.q_tok0 + i0;
-      pc_l = zp_uniform_ptr(p.lse2 + base);
-      pc_d = zp_uniform_ptr(p.dvec + base);
+      return;
     } else if constexpr (N <= PW) {
-      zp_dma16_so(pc_q, qst.off[N - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + pc_buf * TILEB + (qst.w * PW + N - 1) * 1024));
+      zp_dma16_so(pc_q, qst.off[N - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + 2 * pc_buf * TILEB + (qst.w * PW + N - 1) * 1024));
     } else if constexpr (N <= 2 * PW) {
-      zp_dma16_so(pc_o, ost.off[N - PW - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Os) + pc_buf * TILEB + (ost.w * PW + N - PW - 1) * 1024));
+      zp_dma16_so(pc_o, ost.off[N - PW - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + (2 * pc_buf + 1) * TILEB + (ost.w * PW + N - PW - 1) * 1024));
     } else if constexpr (N == 2 * PW + 1) {
       zp_dma4_so(pc_l, lane * 4, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + pc_buf * 256));
     } else if constexpr (N == 2 * PW + 2) {
@@ -522,13 +529,18 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
   // one explicit wait covers both -- it also tells the compiler that the register operands have arrived (a wait of
   // its own inside the loop would drain the copies in flight every iteration); tiles 1 and 2 follow and stay in flight
   if (n_it > 0) stage(0);
+  staged();
   zp_wait_async();
   if (n_it > 1) stage(1);
+  staged();
   if (n_it > 2) stage(2);
+  staged();
   __syncthreads();
 
-  const int kpos_w_min = t.k_pos0 + w * 32, kpos_w_max = t.k_pos0 + w * 32 + 31;
+  const int k0_min = t.k_pos0 + kb[0], k1_min = t.k_pos0 + kb[1];  // first positions of the sub-blocks
   const int qpos_end = t.q_pos0 + t.q_rows;
+  const int qpos_end_l = qpos_end - q4;
+  constexpr int D_OFF = NBUF * 256;
 
   int buf = 0, cur_qt = n_qt - 1, cur_hh = 0;
   for (int it = 0; it < n_it; it++) {
@@ -536,132 +548,154 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
     if (++cur_hh == p.grp) { cur_hh = 0; cur_qt--; }
     const int ahead = n_it - 1 - it;  // tiles after this one
     const int qpos0 = t.q_pos0 + i0;  // position of the tile's first query
-    const bool compute = qpos0 + 63 >= kpos_w_min;  // otherwise every query of the tile precedes every key of this wave
-    const bool masked = qpos0 < kpos_w_max || qpos0 + 64 > qpos_end;
+    // sub-blocks with a key that some query of the tile sees
+    const bool act0 = qpos0 + 63 >= k0_min, act1 = qpos0 + 63 >= k1_min && kb[1] < t.k_len;
+    const bool masked = qpos0 < (act1 ? k1_min : k0_min) + 15 || qpos0 + 64 > qpos_end;
     // the tile three iterations ahead is fetched inside this tile's arithmetic when it is a full tile and this
     // wave computes an unmasked one (the common case), else in front of it
     const bool fetch = ahead >= NBUF - 1;
-    const bool fused = fetch && compute && !masked && st_qt * 64 + 64 <= t.q_rows;
+    const bool fused = fetch && act1 && !masked && st_qt * 64 + 64 <= t.q_rows;
     pc_buf = (buf + NBUF - 1) & (NBUF - 1);
+    // the sources of that tile are worked out unconditionally (and, past the end, in vain): values defined under a
+    // wave's branch would not stay in scalar registers
+    {
+      const int i0n = st_qt * 64;
+      pc_q = zp_uniform_ptr(qst.base + (int64_t)i0n * qst.stride + (int64_t)st_hh * D);
+      pc_o = zp_uniform_ptr(ost.base + (int64_t)i0n * ost.stride + (int64_t)st_hh * D);
+      const int64_t base = (int64_t)(g * p.grp + st_hh) * p.T + t.q_tok0 + i0n;
+      pc_l = zp_uniform_ptr(p.lse2 + base);
+      pc_d = zp_uniform_ptr(p.dvec + base);
+    }
     if (fetch && !fused) stage(pc_buf);
 
-    if (compute) {
-      const char *Qb = Qs + buf * TILEB;
-      const char *Ob = Os + buf * TILEB;
-      if (masked)
-        dkdv_tile<D, true>(Qb, Ob, Ls + buf * 64, Ds + buf * 64, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end, c_log2, hi, lo, no_piece);
-      else if (fused)
-        dkdv_tile<D, false>(Qb, Ob, Ls + buf * 64, Ds + buf * 64, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end, c_log2, hi, lo, stage_piece);
-      else
-        dkdv_tile<D, false>(Qb, Ob, Ls + buf * 64, Ds + buf * 64, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end, c_log2, hi, lo, no_piece);
+    if (act1) {
+      if (masked) dkdv_tile<D, D_OFF, true, false>(seed, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, lo, no_piece);
+      else if (fused) dkdv_tile<D, D_OFF, false, false>(seed, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, lo, stage_piece);
+      else dkdv_tile<D, D_OFF, false, false>(seed, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, lo, no_piece);
+    } else if (act0) {
+      dkdv_tile<D, D_OFF, true, true>(seed, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, lo, no_piece);
     }
     // the next tile must have landed; the ones behind it may stay in flight
     if (ahead >= NBUF - 1) zp_wait_async_upto<(NBUF - 2) * LOADS>();
     else if (ahead == 2) zp_wait_async_upto<LOADS>();
     else zp_wait_async();
     __syncthreads();
+    staged();
     buf = (buf + 1) & (NBUF - 1);
+    lo.move(buf ? 2 * TILEB : -2 * (NBUF - 1) * TILEB);
+    seed += buf ? 256 : -(NBUF - 1) * 256;
   }
 
-  if (key_ok) {
+#pragma unroll
+  for (int cb = 0; cb < 2; cb++) {
+    if (krow[cb] >= t.k_len) continue;
+    const int64_t at = ((int64_t)t.k_tok0 + krow[cb]) * p.dkv_stride + (int64_t)g * D + q4;
     if (p.accumulate) {
-      add_acc_rows<D>((float *)p.dk + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dk_acc, p.scale);
-      add_acc_rows<D>((float *)p.dv + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dv_acc, 1.0f);
+      add_acc_rows16<D>((float *)p.dk + at, dk_acc[cb], p.scale);
+      add_acc_rows16<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
     } else {
-      store_acc_rows<D>(p.dk + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dk_acc, p.scale);
-      store_acc_rows<D>(p.dv + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dv_acc, 1.0f);
+      store_acc_rows16<D>(p.dk + at, dk_acc[cb], p.scale);
+      store_acc_rows16<D>(p.dv + at, dv_acc[cb], 1.0f);
     }
   }
 }
 
 // ---------------------------------------------------------------------------- dK, dV at head dimension 128
-// The LDS read addresses of zp_lds_offsets with three registers instead of sixteen: the swizzle XORs the 16-byte
-// chunk index with a function of the row, so the offsets of the k-steps (row pattern) and of the 32-column blocks
-// (transposed pattern) differ from the first one by an XOR with a constant -- also after a multiple of 256 bytes
-// (tile, row block) has been added.
+// The LDS read addresses of zp_lds16 with two registers instead of twelve: the swizzle XORs the 16-byte chunk index with
+// a function of the row, so the offsets of the k-steps (row pattern) and of the 16-column blocks (transposed pattern)
+// differ from the first one by an XOR with a constant -- also after a multiple of 256 bytes (tile, row block) has been
+// added.
 struct dkdv_lds_addr {
-  unsigned row0, tr0[2];
+  unsigned row0, tr0;
   __device__ __forceinline__ void init(int lane) {
-    zp_lds_offsets<128> lo;
-    lo.init(lane);
-    row0 = lo.row_off[0]; tr0[0] = lo.tr_off[0][0]; tr0[1] = lo.tr_off[1][0];
+    const int r16 = lane & 15, q = lane >> 4, tr = 4 * q + (r16 >> 2);
+    row0 = r16 * 256 + ((q ^ zp_swz16_mask<128>(r16)) << 4);
+    tr0 = tr * 256 + ((((r16 >> 1) & 1) ^ zp_swz16_mask<128>(tr)) << 4) + ((r16 & 1) << 3);
   }
-  // base = LDS address of the tile + the lane's first offset + the row block, see rows_base / tr_base
-  __device__ __forceinline__ unsigned rows_base(const char *tile, int blk) const { return zp_lds_addr(tile) + row0 + blk * 32 * 256; }
-  static __device__ __forceinline__ bf16x8 rows(unsigned base, int kk) {
-    return *(const ZP_LDS bf16x8 *)(unsigned long long)(base ^ (unsigned)(kk << 5));
+  // base = LDS address of the tile + the lane's first offset
+  __device__ __forceinline__ unsigned rows_base(const char *tile) const { return zp_lds_addr(tile) + row0; }
+  static __device__ __forceinline__ bf16x8 rows(unsigned base, int blk16, int kk) {
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)((base ^ (unsigned)(kk << 6)) + blk16 * 16 * 256);
   }
-  __device__ __forceinline__ unsigned tr_base(const char *tile, int blk, int j) const { return zp_lds_addr(tile) + tr0[j] + blk * 32 * 256; }
-  static __device__ __forceinline__ bf16x8 tr(unsigned b0, unsigned b1, int m, int db) {
-    const unsigned o = (unsigned)(db << 6);
-    s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)((b0 ^ o) + m * 16 * 256));
-    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)((b1 ^ o) + m * 16 * 256));
+  __device__ __forceinline__ unsigned tr_base(const char *tile) const { return zp_lds_addr(tile) + tr0; }
+  static __device__ __forceinline__ bf16x8 tr(unsigned base, int db) {
+    const unsigned o = base ^ (unsigned)(db << 5);
+    s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)o);
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + 16 * 256));
     return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
   }
 };
 
-template <int D, bool MASK, bool PIECES, class Piece>
-__device__ __forceinline__ void dkdv_block(const char *Qb, const char *Ob, const float *Lb, const float *Db, int qb,
-                                           const bf16x8 (&kreg)[D / 16], const char *Vt, int vkb,
-                                           f32x16 (&dk_acc)[D / 32], f32x16 (&dv_acc)[D / 32], int qpos0, int kpos,
-                                           int qpos_end, float c_log2, int hi, const dkdv_lds_addr &la,
+// One 32-query tile. Four runs of eight steps of one LDS operand (the dP run: one of dO, and both of V every second step)
+// and two MFMAs -- S, dP, dV^T, dK^T -- each a fenced pipeline with its operands two steps ahead; the last two steps of
+// a run request the first operands of the next one. One run at a time keeps the operands in flight within 28 registers
+// (all four streams two steps ahead would not fit beside the accumulators). The empty asm in every step keeps the
+// compiler from working out all the addresses of a run ahead of it. v0, v1: LDS addresses of the wave's V rows.
+// ONLY0: no query of the tile sees a key of sub-block 1.
+template <bool MASK, bool ONLY0, bool PIECES, class Piece>
+__device__ __forceinline__ void dkdv_block(const char *Qb, const char *Ob, unsigned seed, int d_off,
+                                           const bf16x8 (&kreg)[2][4], unsigned v0, unsigned v1,
+                                           f32x4 (&dk_acc)[2][8], f32x4 (&dv_acc)[2][8], int qpos0,
+                                           const int (&kpos)[2], int qpos_end, float c_log2, const dkdv_lds_addr &la,
                                            Piece &&piece) {
-  constexpr int KK = D / 16, DB = D / 32;
-  f32x16 s, dp;
+  constexpr int N = 8, CB = ONLY0 ? 1 : 2;
+  f32x4 s[2][2], dp[2][2], ls[2], ds[2];
 #pragma unroll
-  for (int b = 0; b < 4; b++) {  // -LSE/scale and -D of the 16 query rows this lane holds
-    const f32x4 l4 = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)Lb + (qb * 32 + 8 * b + 4 * hi) * 4);
-    const f32x4 d4 = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)Db + (qb * 32 + 8 * b + 4 * hi) * 4);
-#pragma unroll
-    for (int c = 0; c < 4; c++) { s[4 * b + c] = l4[c]; dp[4 * b + c] = d4[c]; }
+  for (int rb = 0; rb < 2; rb++) {  // -LSE/scale and -D of the 4 query rows this lane holds of each 16
+    ls[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + rb * 64);
+    ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + d_off + rb * 64);
   }
-  // Four runs of eight MFMAs -- S, dP, dV^T, dK^T -- each a fenced pipeline with its LDS operands two steps ahead;
-  // the last two steps of a run request the first operands of the next one. One run at a time keeps the operands in
-  // flight at 24 registers (all four streams two steps ahead would not fit beside the accumulators). The empty asm
-  // in every step keeps the compiler from working out all the addresses of a run ahead of it.
-  unsigned xb = la.rows_base(Qb, qb), yb = la.rows_base(Ob, qb), vb = la.rows_base(Vt, vkb);
-  unsigned xt0 = la.tr_base(Ob, qb, 0), xt1 = la.tr_base(Ob, qb, 1), yt0 = la.tr_base(Qb, qb, 0), yt1 = la.tr_base(Qb, qb, 1);
-  bf16x8 x[KK], y[KK], v[KK], xt[2 * DB], yt[2 * DB];
-  x[0] = la.rows(xb, 0); x[1] = la.rows(xb, 1);
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value;
+  unsigned xb = la.rows_base(Qb), yb = la.rows_base(Ob), xt = la.tr_base(Ob), yt = la.tr_base(Qb);
+  bf16x8 x[N], y[N], v[4][2], xo[N], yo[N];  // step i: 16 rows i % 2, k-step i / 2 (S, dP); 16 columns i (dV^T, dK^T)
+  auto load_v = [&](int k) {
+    v[k][0] = la.rows(v0, 0, k);
+    if (CB > 1) v[k][1] = la.rows(v1, 0, k);
+  };
+  x[0] = la.rows(xb, 0, 0); x[1] = la.rows(xb, 1, 0);
+  zp_static_for<N>([&](auto ii) {
+    constexpr int i = ii.value, rb = i % 2, k = i / 2;
     __builtin_amdgcn_sched_barrier(0);
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[k], kreg[k], s, 0, 0, 0);
-    asm volatile("" : "+v"(xb), "+v"(yb), "+v"(vb));
-    if constexpr (k + 2 < KK) x[k + 2] = la.rows(xb, k + 2);
-    else { y[k + 2 - KK] = la.rows(yb, k + 2 - KK); v[k + 2 - KK] = la.rows(vb, k + 2 - KK); }
-    if constexpr (PIECES) piece(kk);
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) s[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], kreg[cb][k], k == 0 ? ls[rb] : s[rb][cb], 0, 0, 0);
+    asm volatile("" : "+v"(xb), "+v"(yb), "+v"(v0), "+v"(v1));
+    if constexpr (i + 2 < N) x[i + 2] = la.rows(xb, i % 2, k + 1);
+    else y[i + 2 - N] = la.rows(yb, i % 2, 0);
+    if constexpr (i == N - 2) load_v(0);
+    if constexpr (PIECES) piece(ii);
   });
-  zp_static_for<KK>([&](auto kk) {
-    constexpr int k = kk.value;
+  zp_static_for<N>([&](auto ii) {
+    constexpr int i = ii.value, rb = i % 2, k = i / 2;
     __builtin_amdgcn_sched_barrier(0);
-    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y[k], v[k], dp, 0, 0, 0);
-    asm volatile("" : "+v"(yb), "+v"(vb), "+v"(xt0), "+v"(xt1));
-    if constexpr (k + 2 < KK) { y[k + 2] = la.rows(yb, k + 2); v[k + 2] = la.rows(vb, k + 2); }
-    else xt[k + 2 - KK] = la.tr(xt0, xt1, (k + 2 - KK) / DB, (k + 2 - KK) % DB);
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) dp[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[i], v[k][cb], k == 0 ? ds[rb] : dp[rb][cb], 0, 0, 0);
+    asm volatile("" : "+v"(yb), "+v"(v0), "+v"(v1), "+v"(xt));
+    if constexpr (i + 2 < N) y[i + 2] = la.rows(yb, i % 2, k + 1);
+    else xo[i + 2 - N] = la.tr(xt, i + 2 - N);
+    if constexpr (rb == 0 && k + 1 < 4) load_v(k + 1);
   });
   __builtin_amdgcn_sched_barrier(0);
-  unsigned ppk[8], dpk[8];
+  unsigned ppk[2][4], dpk[2][4];
 #pragma unroll
-  for (int q = 0; q < 8; q++) dkdv_pair<MASK>(s, dp, 2 * q, qb, hi, qpos0, kpos, qpos_end, c_log2, ppk[q], dpk[q]);
-  const bf16x8 pb[2] = {__builtin_bit_cast(bf16x8, (u32x4){ppk[0], ppk[1], ppk[2], ppk[3]}),
-                        __builtin_bit_cast(bf16x8, (u32x4){ppk[4], ppk[5], ppk[6], ppk[7]})};
-  const bf16x8 dsb[2] = {__builtin_bit_cast(bf16x8, (u32x4){dpk[0], dpk[1], dpk[2], dpk[3]}),
-                         __builtin_bit_cast(bf16x8, (u32x4){dpk[4], dpk[5], dpk[6], dpk[7]})};
-  zp_static_for<2 * DB>([&](auto ii) {
-    constexpr int i = ii.value, m = i / DB, db = i % DB;
+  for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      dkdv_pair<MASK>(s[e / 2][cb], dp[e / 2][cb], 2 * (e % 2), qpos0 + 16 * (e / 2) + 2 * (e % 2), kpos[cb], qpos_end, c_log2, ppk[cb][e], dpk[cb][e]);
+  zp_static_for<N>([&](auto ii) {
+    constexpr int i = ii.value;
     __builtin_amdgcn_sched_barrier(0);
-    dv_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xt[i], pb[m], dv_acc[db], 0, 0, 0);
-    asm volatile("" : "+v"(xt0), "+v"(xt1), "+v"(yt0), "+v"(yt1));
-    if constexpr (i + 2 < 2 * DB) xt[i + 2] = la.tr(xt0, xt1, (i + 2) / DB, (i + 2) % DB);
-    else yt[i + 2 - 2 * DB] = la.tr(yt0, yt1, (i + 2 - 2 * DB) / DB, (i + 2 - 2 * DB) % DB);
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) dv_acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[i], dkdv_operand(ppk[cb]), dv_acc[cb][i], 0, 0, 0);
+    asm volatile("" : "+v"(xt), "+v"(yt));
+    if constexpr (i + 2 < N) xo[i + 2] = la.tr(xt, i + 2);
+    else yo[i + 2 - N] = la.tr(yt, i + 2 - N);
   });
-  zp_static_for<2 * DB>([&](auto ii) {
-    constexpr int i = ii.value, m = i / DB, db = i % DB;
+  zp_static_for<N>([&](auto ii) {
+    constexpr int i = ii.value;
     __builtin_amdgcn_sched_barrier(0);
-    dk_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yt[i], dsb[m], dk_acc[db], 0, 0, 0);
-    asm volatile("" : "+v"(yt0), "+v"(yt1));
-    if constexpr (i + 2 < 2 * DB) yt[i + 2] = la.tr(yt0, yt1, (i + 2) / DB, (i + 2) % DB);
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) dk_acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yo[i], dkdv_operand(dpk[cb]), dk_acc[cb][i], 0, 0, 0);
+    asm volatile("" : "+v"(yt));
+    if constexpr (i + 2 < N) yo[i + 2] = la.tr(yt, i + 2);
   });
   __builtin_amdgcn_sched_barrier(0);
 }
@@ -680,7 +714,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   constexpr int D = 128, QT = 32;
   constexpr int TILEB = QT * D * 2;                // a staged tile: 32 query rows
   constexpr int NBUF = ZP_DKDV_NBUF;               // staging buffers (three would not fit two workgroups per CU with the seeds)
-  typedef zp_stager<D, 8> stager;                  // 4 waves x 2 wave-loads = the first 32 rows of its 64-row pattern
+  typedef zp_stager<D, 8, true> stager;                  // 4 waves x 2 wave-loads = the first 32 rows of its 64-row pattern
   constexpr int PW = stager::PER_WAVE;
   constexpr int LOADS = 2 * PW + 2;                // async loads one wave issues per staged tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -693,32 +727,33 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int unit = zp_item_of_block(p.work_kv_short, (int *)(Ds + NBUF * QT));
   if (unit < 0 || unit >= p.n_kv_tiles_short * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
-  const zp_tile t = p.kv_tiles_short[tile_idx];
+  const zp_tile t = zp_load_tile(p.kv_tiles_short + tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int kl = lane & 31, hi = lane >> 5;
-  const int krow = w * 32 + kl;
-  const bool key_ok = krow < t.k_len;
-  const int64_t ktok = (int64_t)t.k_tok0 + krow;
-  const int kpos = t.k_pos0 + krow;
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  // the wave's two sub-blocks of 16 key rows: see attn_bwd_dkdv_kernel
+  const int kb[2] = {16 * w, 16 * (7 - w)};
+  const int krow[2] = {kb[0] + c16, kb[1] + c16};
+  const int kpos[2] = {t.k_pos0 + krow[0] - q4, t.k_pos0 + krow[1] - q4};
 
   // K operands in registers; V operands from LDS (rows past the block's last key repeat it: a key column never
   // mixes with another, and those columns are not stored)
-  bf16x8 kreg[D / 16];
-  {
-    const __bf16 *kp = p.k + ktok * p.k_stride + (int64_t)g * D + 8 * hi;
+  bf16x8 kreg[2][D / 32];
 #pragma unroll
-    for (int kk = 0; kk < D / 16; kk++) {
-      if (key_ok) kreg[kk] = *(const bf16x8 *)(kp + 16 * kk);
-      else kreg[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  for (int cb = 0; cb < 2; cb++) {
+    const __bf16 *kp = p.k + ((int64_t)t.k_tok0 + krow[cb]) * p.k_stride + (int64_t)g * D + 2 * q4;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) {
+      if (krow[cb] < t.k_len) kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
+      else kreg[cb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
     }
   }
 
-  f32x16 dk_acc[D / 32], dv_acc[D / 32];
+  f32x4 dk_acc[2][D / 16], dv_acc[2][D / 16];
 #pragma unroll
-  for (int i = 0; i < D / 32; i++)
+  for (int cb = 0; cb < 2; cb++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) { dk_acc[i][r] = 0.f; dv_acc[i][r] = 0.f; }
+    for (int i = 0; i < D / 16; i++) dk_acc[cb][i] = dv_acc[cb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float c_log2 = p.scale_log2;
 
   const int n_qt = (t.q_rows + QT - 1) / QT;
@@ -730,45 +765,38 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   dkdv_lds_addr la;
   la.init(lane);
   {
-    zp_stager<D> vst;
+    zp_stager<D, 4, true> vst;
     vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
     vst.issue(Vs, 0, t.k_len);
     vst.issue(Vs + 64 * D * 2, 64, t.k_len);
   }
-  const char *Vt = Vs + (w >> 1) * (64 * D * 2);
-  const int vkb = w & 1;
+  const unsigned v0 = la.rows_base(Vs + kb[0] * 256), v1 = la.rows_base(Vs + kb[1] * 256);
+  const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
   // 32 floats of a row vector, one per lane of the lower half-wave (rows past the last valid one repeat it)
   auto stage_f32x32 = [&](float *dst, const float *src, int first, int last_valid) {
     int i = first + (lane & 31);
     if (i > last_valid) i = last_valid;
     if (lane < 32) zp_dma4(src + i, __builtin_amdgcn_readfirstlane(zp_lds_addr(dst)));
   };
-  int st_hh = 0, st_qt = n_qt - 1;
+  int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
+  auto staged = [&] { if (++st_hh == p.grp) { st_hh = 0; st_qt--; } };
   auto stage = [&](int buf) {
     const int hh = st_hh, i0 = st_qt * QT;
     const int h = g * p.grp + hh;
-    if (++st_hh == p.grp) { st_hh = 0; st_qt--; }
     qst.issue(Qs + buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
     ost.issue(Os + buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
     const int64_t base = (int64_t)h * p.T + t.q_tok0;
     stage_f32x32(Ls + buf * QT, p.lse2 + base, i0, t.q_rows - 1);
     stage_f32x32(Ds + buf * QT, p.dvec + base, i0, t.q_rows - 1);
   };
-  // the same copies for a tile of 32 valid rows, one per k-step of the S chain (piece 0: the scalar addresses)
-  const void *pc_q = nullptr, *pc_o = nullptr, *pc_l = nullptr, *pc_d = nullptr;
+  // the same copies for a tile of 32 valid rows, one per step of the S run but the first
+  const void *pc_q, *pc_o, *pc_l, *pc_d;
   unsigned pc_buf = 0;
   auto stage_piece = [&](auto n) {
     constexpr int N = decltype(n)::value;
     static_assert(2 * PW + 3 <= D / 16, "the copies of a tile fit the steps of one chain");
     if constexpr (N == 0) {
-      const int hh = st_hh, i0 = st_qt * QT;
-      const int h = g * p.grp + hh;
-      if (++st_hh == p.grp) { st_hh = 0; st_qt--; }
-      pc_q = zp_uniform_ptr(qst.base + (int64_t)i0 * qst.stride + (int64_t)hh * D);
-      pc_o = zp_uniform_ptr(ost.base + (int64_t)i0 * ost.stride + (int64_t)hh * D);
-      const int64_t base = (int64_t)h * p.T + t.q_tok0 + i0;
-      pc_l = zp_uniform_ptr(p.lse2 + base);
-      pc_d = zp_uniform_ptr(p.dvec + base);
+      return;
     } else if constexpr (N <= PW) {
       zp_dma16_so(pc_q, qst.off[N - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + pc_buf * TILEB + (qst.w * PW + N - 1) * 1024));
     } else if constexpr (N <= 2 * PW) {
@@ -782,14 +810,18 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   auto no_piece = [](auto) {};
 
   if (n_it > 0) stage(0);
+  staged();
   zp_wait_async();
 #pragma unroll
-  for (int b = 1; b < NBUF - 1; b++)
+  for (int b = 1; b < NBUF - 1; b++) {
     if (n_it > b) stage(b);
+    staged();
+  }
   __syncthreads();
 
-  const int kpos_w_min = t.k_pos0 + w * 32, kpos_w_max = t.k_pos0 + w * 32 + 31;
-  const int qpos_end = t.q_pos0 + t.q_rows;
+  const int k0_min = t.k_pos0 + kb[0], k1_min = t.k_pos0 + kb[1];  // first positions of the sub-blocks
+  const int qpos_end = t.q_pos0 + t.q_rows, qpos_end_l = qpos_end - q4;
+  constexpr int D_OFF = NBUF * QT * 4;
 
   int buf = 0, cur_qt = n_qt - 1, cur_hh = 0;
   for (int it = 0; it < n_it; it++) {
@@ -797,39 +829,53 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if (++cur_hh == p.grp) { cur_hh = 0; cur_qt--; }
     const int ahead = n_it - 1 - it;        // tiles after this one
     const int qpos0 = t.q_pos0 + i0;        // position of the tile's first query
-    const bool compute = qpos0 + QT - 1 >= kpos_w_min;  // otherwise every query of the tile precedes every key of this wave
-    const bool masked = qpos0 < kpos_w_max || qpos0 + QT > qpos_end;
+    // sub-blocks with a key that some query of the tile sees
+    const bool act0 = qpos0 + QT - 1 >= k0_min, act1 = qpos0 + QT - 1 >= k1_min && kb[1] < t.k_len;
+    const bool masked = qpos0 < (act1 ? k1_min : k0_min) + 15 || qpos0 + QT > qpos_end;
     // the tile NBUF - 1 iterations ahead is fetched inside this tile's S chain when it is a full tile and this wave
     // computes an unmasked one (the common case), else in front
     const bool fetch = ahead >= NBUF - 1;
-    const bool fused = fetch && compute && !masked && st_qt * QT + QT <= t.q_rows;
+    const bool fused = fetch && act1 && !masked && st_qt * QT + QT <= t.q_rows;
     pc_buf = buf == 0 ? NBUF - 1 : buf - 1;
+    // the sources of that tile are worked out unconditionally (and, past the end, in vain): values defined under a
+    // wave's branch would not stay in scalar registers
+    {
+      const int i0n = st_qt * QT;
+      pc_q = zp_uniform_ptr(qst.base + (int64_t)i0n * qst.stride + (int64_t)st_hh * D);
+      pc_o = zp_uniform_ptr(ost.base + (int64_t)i0n * ost.stride + (int64_t)st_hh * D);
+      const int64_t base = (int64_t)(g * p.grp + st_hh) * p.T + t.q_tok0 + i0n;
+      pc_l = zp_uniform_ptr(p.lse2 + base);
+      pc_d = zp_uniform_ptr(p.dvec + base);
+    }
     if (fetch && !fused) stage(pc_buf);
 
-    if (compute) {
-      const char *Qb = Qs + buf * TILEB;
-      const char *Ob = Os + buf * TILEB;
-      if (masked)
-        dkdv_block<D, true, false>(Qb, Ob, Ls + buf * QT, Ds + buf * QT, 0, kreg, Vt, vkb, dk_acc, dv_acc, qpos0, kpos, qpos_end, c_log2, hi, la, no_piece);
-      else if (fused)
-        dkdv_block<D, false, true>(Qb, Ob, Ls + buf * QT, Ds + buf * QT, 0, kreg, Vt, vkb, dk_acc, dv_acc, qpos0, kpos, qpos_end, c_log2, hi, la, stage_piece);
-      else
-        dkdv_block<D, false, false>(Qb, Ob, Ls + buf * QT, Ds + buf * QT, 0, kreg, Vt, vkb, dk_acc, dv_acc, qpos0, kpos, qpos_end, c_log2, hi, la, no_piece);
+    const char *Qb = Qs + buf * TILEB;
+    const char *Ob = Os + buf * TILEB;
+    if (act1) {
+      if (masked) dkdv_block<true, false, false>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      else if (fused) dkdv_block<false, false, true>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
+      else dkdv_block<false, false, false>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+    } else if (act0) {
+      dkdv_block<true, true, false>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     }
     // the next tile must have landed; the one behind it may stay in flight
     if (ahead >= NBUF - 1) zp_wait_async_upto<(NBUF - 2) * LOADS>();
     else zp_wait_async();
     __syncthreads();
+    staged();
     buf = buf + 1 == NBUF ? 0 : buf + 1;
   }
 
-  if (key_ok) {
+#pragma unroll
+  for (int cb = 0; cb < 2; cb++) {
+    if (krow[cb] >= t.k_len) continue;
+    const int64_t at = ((int64_t)t.k_tok0 + krow[cb]) * p.dkv_stride + (int64_t)g * D + q4;
     if (p.accumulate) {
-      add_acc_rows<D>((float *)p.dk + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dk_acc, p.scale);
-      add_acc_rows<D>((float *)p.dv + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dv_acc, 1.0f);
+      add_acc_rows16<D>((float *)p.dk + at, dk_acc[cb], p.scale);
+      add_acc_rows16<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
     } else {
-      store_acc_rows<D>(p.dk + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dk_acc, p.scale);
-      store_acc_rows<D>(p.dv + ktok * p.dkv_stride + (int64_t)g * D + 4 * hi, dv_acc, 1.0f);
+      store_acc_rows16<D>(p.dk + at, dk_acc[cb], p.scale);
+      store_acc_rows16<D>(p.dv + at, dv_acc[cb], 1.0f);
     }
   }
 }

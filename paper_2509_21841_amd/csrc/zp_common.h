@@ -30,6 +30,16 @@ struct zp_tile {
   int32_t aux;       // kernel specific
 };
 
+// The tile record of a workgroup in scalar registers (it is the same for all its lanes, which the compiler cannot know
+// where the item was claimed at run time: the tile copies' address arithmetic would run on the vector unit).
+__device__ __forceinline__ zp_tile zp_load_tile(const zp_tile *p) {
+  zp_tile t;
+#define ZP_U(f) t.f = __builtin_amdgcn_readfirstlane(p->f)
+  ZP_U(q_tok0); ZP_U(q_rows); ZP_U(q_pos0); ZP_U(k_tok0); ZP_U(k_len); ZP_U(k_pos0); ZP_U(out_row0); ZP_U(aux);
+#undef ZP_U
+  return t;
+}
+
 // How a launch hands its work items to workgroups. The XCDs of a chip do not run equally fast (on the boxes measured
 // the same four finish an equal share 4-8 % later than the other four), and the hardware deals workgroups to them
 // round-robin, so with one item per workgroup the fast ones idle at the end. Items 0 .. n_static-1 are therefore taken
@@ -372,6 +382,13 @@ struct zp_lds16 {
       tr_off[db] = b + tr * ROWB + (((2 * db + ((r16 >> 1) & 1)) ^ zp_swz16_mask<D>(tr)) << 4) + ((r16 & 1) << 3);
       asm volatile("" : "+v"(tr_off[db]));
     }
+  }
+  // moves all addresses by `bytes` (wave-uniform)
+  __device__ __forceinline__ void move(int bytes) {
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) row_off[kk] += bytes;
+#pragma unroll
+    for (int db = 0; db < D / 16; db++) tr_off[db] += bytes;
   }
   __device__ __forceinline__ bf16x8 rows_at(int tile_off, int kb, int kk) const {
     return *(const ZP_LDS bf16x8 *)(unsigned long long)(unsigned)(row_off[kk] + tile_off + kb * 16 * ROWB);
