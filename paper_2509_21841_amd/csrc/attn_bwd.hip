@@ -17,13 +17,12 @@ struct zp_bwd_params {
   float *lse2;        // [Hq][T] scratch: -LSE_i / scale
   const zp_tile *dq_tiles;
   const zp_tile *kv_tiles;
-  const zp_tile *kv_tiles_short;  // key blocks with few query tiles: run by the two-workgroups-per-CU kernel (d = 128)
-  int32_t n_dq_tiles, n_kv_tiles, n_kv_tiles_short, Hq, Hkv, grp, T;
+  int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;      // outputs (bf16, overwritten) ...
   int64_t dq_stride, dkv_stride;
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
-  zp_work_split work_dq, work_kv, work_kv_short;  // work hand-out of the three launches (counters set by the C ABI, the rest by the launcher)
+  zp_work_split work_dq, work_kv;  // work hand-out of the two launches (counters set by the C ABI, the rest by the launcher)
 };
 
 namespace {
@@ -31,43 +30,15 @@ namespace {
 constexpr int BWD_NT = 256;
 constexpr float LOG2E = 1.4426950408889634f;
 
+// writes (or adds, in float) the scaled accumulators of one row: 4 consecutive columns of every 16
 template <int D>
-__device__ __forceinline__ void store_acc_rows(__bf16 *dst, const f32x16 (&acc)[D / 32], float mul) {
-#pragma unroll
-  for (int db = 0; db < D / 32; db++)
-#pragma unroll
-    for (int b = 0; b < 4; b++) {
-      bf16x4 v4 = {(__bf16)(acc[db][4 * b] * mul), (__bf16)(acc[db][4 * b + 1] * mul),
-                   (__bf16)(acc[db][4 * b + 2] * mul), (__bf16)(acc[db][4 * b + 3] * mul)};
-      *(bf16x4 *)(dst + db * 32 + b * 8) = v4;
-    }
-}
-
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-
-// accumulate variant of store_acc_rows: dst is float, the scaled accumulator is added to what is there
-template <int D>
-__device__ __forceinline__ void add_acc_rows(float *dst, const f32x16 (&acc)[D / 32], float mul) {
-#pragma unroll
-  for (int db = 0; db < D / 32; db++)
-#pragma unroll
-    for (int b = 0; b < 4; b++) {
-      f32x4 cur = *(const f32x4 *)(dst + db * 32 + b * 8);
-      cur[0] += acc[db][4 * b] * mul; cur[1] += acc[db][4 * b + 1] * mul;
-      cur[2] += acc[db][4 * b + 2] * mul; cur[3] += acc[db][4 * b + 3] * mul;
-      *(f32x4 *)(dst + db * 32 + b * 8) = cur;
-    }
-}
-
-// the same for accumulators of the 16x16x32 MFMA: 4 consecutive columns per 16-column block
-template <int D>
-__device__ __forceinline__ void store_acc_rows16(__bf16 *dst, const f32x4 (&acc)[D / 16], float mul) {
+__device__ __forceinline__ void store_acc_rows(__bf16 *dst, const f32x4 (&acc)[D / 16], float mul) {
 #pragma unroll
   for (int db = 0; db < D / 16; db++)
     *(bf16x4 *)(dst + db * 16) = bf16x4{(__bf16)(acc[db][0] * mul), (__bf16)(acc[db][1] * mul), (__bf16)(acc[db][2] * mul), (__bf16)(acc[db][3] * mul)};
 }
 template <int D>
-__device__ __forceinline__ void add_acc_rows16(float *dst, const f32x4 (&acc)[D / 16], float mul) {
+__device__ __forceinline__ void add_acc_rows(float *dst, const f32x4 (&acc)[D / 16], float mul) {
 #pragma unroll
   for (int db = 0; db < D / 16; db++) {
     f32x4 cur = *(const f32x4 *)(dst + db * 16);
@@ -175,7 +146,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int nvis0_max = rb[0] < t.q_rows ? nvis_of(rb[0] + 15) : 0, nvis1_max = rb[1] < t.q_rows ? nvis_of(rb[1] + 15) : 0;
   const int n_kt = (nvis_of(t.q_rows - 1) + 63) / 64;
 
-  zp_stager<D, 4, true> kst, vst;
+  zp_stager<D> kst, vst;
   kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
   vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
   zp_lds16<D> lo;
@@ -240,7 +211,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   zp_wait_async();
   __syncthreads();
 
-  constexpr int PW = zp_stager<D, 4, true>::PER_WAVE;
+  constexpr int PW = zp_stager<D>::PER_WAVE;
   // one key tile out of LDS buffer BUF (compile-time, so that every LDS address is a register plus an immediate)
   auto key_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
@@ -296,8 +267,8 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   for (int qb = 0; qb < 2; qb++) {
     if (row[qb] >= t.q_rows) continue;
     const int64_t at = ((int64_t)t.q_tok0 + row[qb]) * p.dq_stride + (int64_t)h * D + q4;
-    if (p.accumulate) add_acc_rows16<D>((float *)p.dq + at, dq_acc[qb], p.scale);
-    else store_acc_rows16<D>(p.dq + at, dq_acc[qb], p.scale);
+    if (p.accumulate) add_acc_rows<D>((float *)p.dq + at, dq_acc[qb], p.scale);
+    else store_acc_rows<D>(p.dq + at, dq_acc[qb], p.scale);
   }
 }
 
@@ -305,10 +276,8 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // Tile fields: k_tok0/k_len/k_pos0 = this block of key rows; q_tok0/q_rows/q_pos0 = the query rows of the
 // same sequence from the first one that can see the block's first key to the end of the sequence.
 //
-// One wave per SIMD (the 128 accumulator registers of dK^T and dV^T plus the K/V operands leave no room for
-// two), so latency is hidden inside the wave: per 64-query tile the two 32-query blocks are software
-// pipelined -- LDS operands are fetched a phase ahead, the exp/scale arithmetic of one block is interleaved
-// with the MFMAs of the other.
+// Head dimension 64: K and V operands in registers, 64-query tiles whose two 32-query blocks are software pipelined
+// (dkdv_tile). Head dimension 128: the kernel further below.
 
 // Two neighbouring elements (registers r, r + 1 of an accumulator; the queries at positions qpos and qpos + 1) of P and
 // dS, packed as bf16. The accumulators were seeded with -LSE/scale and -D, so P = exp2(S c) and dS = P dP.
@@ -433,8 +402,8 @@ __device__ __forceinline__ void dkdv_tile(unsigned seed, const bf16x8 (&kreg)[2]
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int D>
-__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, D == 64 ? 2 : 1))) void attn_bwd_dkdv_kernel(zp_bwd_params p) {
+__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv64_kernel(zp_bwd_params p) {
+  constexpr int D = 64;
   constexpr int TILEB = 64 * D * 2;
   constexpr int NBUF = 4;                       // tiles are fetched three iterations ahead
   constexpr int LOADS = 2 * (TILEB / 4096) + 2; // async loads one wave issues per staged tile
@@ -484,7 +453,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
   const int n_qt = (t.q_rows + 63) / 64;
   const int n_it = n_qt * p.grp;  // iterations: query tiles outermost (last tile first), heads of the group innermost
 
-  zp_stager<D, 4, true> qst, ost;
+  zp_stager<D> qst, ost;
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
   ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, tid);
   zp_lds16<D> lo;  // of the tile in hand: moved on by a buffer after every tile
@@ -506,7 +475,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
   };
   // The same copies for a tile of 64 valid rows, cut into pieces that dkdv_tile issues between the MFMAs of its
   // last phase: every piece but the first one load (same order as `stage`).
-  constexpr int PW = zp_stager<D, 4, true>::PER_WAVE;
+  constexpr int PW = zp_stager<D>::PER_WAVE;
   const void *pc_q, *pc_o, *pc_l, *pc_d;
   unsigned pc_buf = 0;
   auto stage_piece = [&](auto n) {
@@ -591,37 +560,46 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
     if (krow[cb] >= t.k_len) continue;
     const int64_t at = ((int64_t)t.k_tok0 + krow[cb]) * p.dkv_stride + (int64_t)g * D + q4;
     if (p.accumulate) {
-      add_acc_rows16<D>((float *)p.dk + at, dk_acc[cb], p.scale);
-      add_acc_rows16<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
+      add_acc_rows<D>((float *)p.dk + at, dk_acc[cb], p.scale);
+      add_acc_rows<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
     } else {
-      store_acc_rows16<D>(p.dk + at, dk_acc[cb], p.scale);
-      store_acc_rows16<D>(p.dv + at, dv_acc[cb], 1.0f);
+      store_acc_rows<D>(p.dk + at, dk_acc[cb], p.scale);
+      store_acc_rows<D>(p.dv + at, dv_acc[cb], 1.0f);
     }
   }
 }
 
 // ---------------------------------------------------------------------------- dK, dV at head dimension 128
-// The LDS read addresses of zp_lds16 with two registers instead of twelve: the swizzle XORs the 16-byte chunk index with
-// a function of the row, so the offsets of the k-steps (row pattern) and of the 16-column blocks (transposed pattern)
-// differ from the first one by an XOR with a constant -- also after a multiple of 256 bytes (tile, row block) has been
-// added.
+// A lane's LDS read addresses in the zp_pad16 layout: of the Q and dO tiles (relative to the first buffer; everything
+// else is an immediate offset) and of the wave's V rows.
 struct dkdv_lds_addr {
-  unsigned row0, tr0;
-  __device__ __forceinline__ void init(int lane) {
-    const int r16 = lane & 15, q = lane >> 4, tr = 4 * q + (r16 >> 2);
-    row0 = r16 * 256 + ((q ^ zp_swz16_mask<128>(r16)) << 4);
-    tr0 = tr * 256 + ((((r16 >> 1) & 1) ^ zp_swz16_mask<128>(tr)) << 4) + ((r16 & 1) << 3);
+  unsigned row[2], tr[4], v[2][2];
+  __device__ __forceinline__ void init(int lane, const char *tiles, const char *v0, const char *v1) {
+#pragma unroll
+    for (int par = 0; par < 2; par++) {
+      const int r = zp_pad16::row_part(lane, par);
+      row[par] = zp_lds_addr(tiles) + r;
+      v[0][par] = zp_lds_addr(v0) + r;
+      v[1][par] = zp_lds_addr(v1) + r;
+      asm volatile("" : "+v"(row[par]), "+v"(v[0][par]), "+v"(v[1][par]));  // opaque: see zp_lds16
+    }
+#pragma unroll
+    for (int dq = 0; dq < 4; dq++) {
+      tr[dq] = zp_lds_addr(tiles) + zp_pad16::tr_part(lane, dq);
+      asm volatile("" : "+v"(tr[dq]));
+    }
   }
-  // base = LDS address of the tile + the lane's first offset
-  __device__ __forceinline__ unsigned rows_base(const char *tile) const { return zp_lds_addr(tile) + row0; }
-  static __device__ __forceinline__ bf16x8 rows(unsigned base, int blk16, int kk) {
-    return *(const ZP_LDS bf16x8 *)(unsigned long long)((base ^ (unsigned)(kk << 6)) + blk16 * 16 * 256);
+  // off: byte offset of the tile from the first buffer; rb: 16 rows; k: k-step; db: 16 columns
+  __device__ __forceinline__ bf16x8 rows(int off, int rb, int k) const {
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(row[k & 1] + off + rb * zp_pad16::R16 + (k >> 1) * 128);
   }
-  __device__ __forceinline__ unsigned tr_base(const char *tile) const { return zp_lds_addr(tile) + tr0; }
-  static __device__ __forceinline__ bf16x8 tr(unsigned base, int db) {
-    const unsigned o = base ^ (unsigned)(db << 5);
+  __device__ __forceinline__ bf16x8 vrows(int cb, int k) const {
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(v[cb][k & 1] + (k >> 1) * 128);
+  }
+  __device__ __forceinline__ bf16x8 cols(int off, int db) const {
+    const unsigned o = tr[db & 3] + off + (db >> 2) * 128;
     s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)o);
-    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + 16 * 256));
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + zp_pad16::R16));
     return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
   }
 };
@@ -629,37 +607,33 @@ struct dkdv_lds_addr {
 // One 32-query tile. Four runs of eight steps of one LDS operand (the dP run: one of dO, and both of V every second step)
 // and two MFMAs -- S, dP, dV^T, dK^T -- each a fenced pipeline with its operands two steps ahead; the last two steps of
 // a run request the first operands of the next one. One run at a time keeps the operands in flight within 28 registers
-// (all four streams two steps ahead would not fit beside the accumulators). The empty asm in every step keeps the
-// compiler from working out all the addresses of a run ahead of it. v0, v1: LDS addresses of the wave's V rows.
-// ONLY0: no query of the tile sees a key of sub-block 1.
-template <bool MASK, bool ONLY0, bool PIECES, class Piece>
-__device__ __forceinline__ void dkdv_block(const char *Qb, const char *Ob, unsigned seed, int d_off,
-                                           const bf16x8 (&kreg)[2][4], unsigned v0, unsigned v1,
-                                           f32x4 (&dk_acc)[2][8], f32x4 (&dv_acc)[2][8], int qpos0,
-                                           const int (&kpos)[2], int qpos_end, float c_log2, const dkdv_lds_addr &la,
-                                           Piece &&piece) {
+// (all four streams two steps ahead would not fit beside the accumulators). Q_OFF, O_OFF: byte offsets of the tile's Q and
+// dO rows; seed: LDS address of its -LSE/scale plus the lane's floats, -D is D_OFF bytes behind. ONLY0: no query of the
+// tile sees a key of sub-block 1.
+template <int Q_OFF, int O_OFF, int D_OFF, bool MASK, bool ONLY0, bool PIECES, class Piece>
+__device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2][4], f32x4 (&dk_acc)[2][8],
+                                           f32x4 (&dv_acc)[2][8], int qpos0, const int (&kpos)[2], int qpos_end,
+                                           float c_log2, const dkdv_lds_addr &la, Piece &&piece) {
   constexpr int N = 8, CB = ONLY0 ? 1 : 2;
   f32x4 s[2][2], dp[2][2], ls[2], ds[2];
 #pragma unroll
   for (int rb = 0; rb < 2; rb++) {  // -LSE/scale and -D of the 4 query rows this lane holds of each 16
     ls[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + rb * 64);
-    ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + d_off + rb * 64);
+    ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + rb * 64);
   }
-  unsigned xb = la.rows_base(Qb), yb = la.rows_base(Ob), xt = la.tr_base(Ob), yt = la.tr_base(Qb);
   bf16x8 x[N], y[N], v[4][2], xo[N], yo[N];  // step i: 16 rows i % 2, k-step i / 2 (S, dP); 16 columns i (dV^T, dK^T)
   auto load_v = [&](int k) {
-    v[k][0] = la.rows(v0, 0, k);
-    if (CB > 1) v[k][1] = la.rows(v1, 0, k);
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) v[k][cb] = la.vrows(cb, k);
   };
-  x[0] = la.rows(xb, 0, 0); x[1] = la.rows(xb, 1, 0);
+  x[0] = la.rows(Q_OFF, 0, 0); x[1] = la.rows(Q_OFF, 1, 0);
   zp_static_for<N>([&](auto ii) {
     constexpr int i = ii.value, rb = i % 2, k = i / 2;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) s[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], kreg[cb][k], k == 0 ? ls[rb] : s[rb][cb], 0, 0, 0);
-    asm volatile("" : "+v"(xb), "+v"(yb), "+v"(v0), "+v"(v1));
-    if constexpr (i + 2 < N) x[i + 2] = la.rows(xb, i % 2, k + 1);
-    else y[i + 2 - N] = la.rows(yb, i % 2, 0);
+    if constexpr (i + 2 < N) x[i + 2] = la.rows(Q_OFF, i % 2, k + 1);
+    else y[i + 2 - N] = la.rows(O_OFF, i % 2, 0);
     if constexpr (i == N - 2) load_v(0);
     if constexpr (PIECES) piece(ii);
   });
@@ -668,9 +642,8 @@ __device__ __forceinline__ void dkdv_block(const char *Qb, const char *Ob, unsig
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) dp[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[i], v[k][cb], k == 0 ? ds[rb] : dp[rb][cb], 0, 0, 0);
-    asm volatile("" : "+v"(yb), "+v"(v0), "+v"(v1), "+v"(xt));
-    if constexpr (i + 2 < N) y[i + 2] = la.rows(yb, i % 2, k + 1);
-    else xo[i + 2 - N] = la.tr(xt, i + 2 - N);
+    if constexpr (i + 2 < N) y[i + 2] = la.rows(O_OFF, i % 2, k + 1);
+    else xo[i + 2 - N] = la.cols(O_OFF, i + 2 - N);
     if constexpr (rb == 0 && k + 1 < 4) load_v(k + 1);
   });
   __builtin_amdgcn_sched_barrier(0);
@@ -685,53 +658,50 @@ __device__ __forceinline__ void dkdv_block(const char *Qb, const char *Ob, unsig
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) dv_acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[i], dkdv_operand(ppk[cb]), dv_acc[cb][i], 0, 0, 0);
-    asm volatile("" : "+v"(xt), "+v"(yt));
-    if constexpr (i + 2 < N) xo[i + 2] = la.tr(xt, i + 2);
-    else yo[i + 2 - N] = la.tr(yt, i + 2 - N);
+    if constexpr (i + 2 < N) xo[i + 2] = la.cols(O_OFF, i + 2);
+    else yo[i + 2 - N] = la.cols(Q_OFF, i + 2 - N);
   });
   zp_static_for<N>([&](auto ii) {
     constexpr int i = ii.value;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) dk_acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yo[i], dkdv_operand(dpk[cb]), dk_acc[cb][i], 0, 0, 0);
-    asm volatile("" : "+v"(yt));
-    if constexpr (i + 2 < N) yo[i + 2] = la.tr(yt, i + 2);
+    if constexpr (i + 2 < N) yo[i + 2] = la.cols(Q_OFF, i + 2);
   });
   __builtin_amdgcn_sched_barrier(0);
 }
 
-
-#ifndef ZP_DKDV_NBUF
-#define ZP_DKDV_NBUF 2
-#endif
-// Two waves per SIMD for head dimension 128 as well: two independent workgroups of four waves per CU (80 KB of LDS
+// Two waves per SIMD for head dimension 128 as well: two independent workgroups of four waves per CU (69 KB of LDS
 // each), a wave holding its K operands (32 registers) and its dK^T/dV^T accumulators (128) and working on 32-query
-// tiles, one block's S and dP at a time; the V operands do not fit beside them in 256 registers and are read from
-// LDS, where the workgroup's 128 V rows are staged once. An MFMA takes about 20 cycles of its wave's vector issue
-// time and the wave's LDS, scalar and wait instructions issue in line with it; a second wave on the SIMD, from a
-// workgroup that meets its own barriers, runs under all of that.
+// tiles, one product at a time; the V operands do not fit beside them in 256 registers and are read from LDS, where the
+// workgroup's 128 V rows are staged once. The wave's LDS, vector, scalar and wait instructions issue in line with its
+// MFMAs; a second wave on the SIMD, from a workgroup that meets its own barriers, runs under all of that.
+//
+// Bound: the power limit and vector issue. One box, this kernel against the two it replaces (32x32x16 MFMA; one wave per
+// SIMD with K and V in registers for long sequences, this split with an XOR per LDS read for short ones): 128K
+// long-tail GQA batch 25.17 -> 22.97 ms, four 16384-token sequences 15.49 -> 14.22, 64K lognormal MHA 2.70 -> 2.39,
+// 64 x 1K MHA 1.45 -> 1.29. The one-wave form on the 16x16x32 MFMA took 24.9 ms on the long-tail batch; with an XOR for
+// every LDS read (32 to the 64 vector operations a tile needs) this one took 24.7.
 __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv128_kernel(zp_bwd_params p) {
   constexpr int D = 128, QT = 32;
-  constexpr int TILEB = QT * D * 2;                // a staged tile: 32 query rows
-  constexpr int NBUF = ZP_DKDV_NBUF;               // staging buffers (three would not fit two workgroups per CU with the seeds)
-  typedef zp_stager<D, 8, true> stager;                  // 4 waves x 2 wave-loads = the first 32 rows of its 64-row pattern
+  constexpr int TILEB = 2 * zp_pad16::R16;         // a staged tile: 32 query rows
+  typedef zp_stager<D, 8, true> stager;               // 4 waves x 2 wave-loads = the first 32 rows of its 64-row pattern
   constexpr int PW = stager::PER_WAVE;
-  constexpr int LOADS = 2 * PW + 2;                // async loads one wave issues per staged tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char *Qs = smem;                                 // [NBUF][32][D]
-  char *Os = smem + NBUF * TILEB;                  // [NBUF][32][D]  (dO)
-  char *Vs = smem + 2 * NBUF * TILEB;              // [2][64][D]: the workgroup's V rows, staged once
-  float *Ls = (float *)(Vs + 2 * 64 * D * 2);      // [NBUF][32] -LSE / scale
-  float *Ds = Ls + NBUF * QT;                      // [NBUF][32] -D
+  char *Qs = smem;                                 // [2][2][32][D]: two buffers (three would not fit two workgroups per
+                                                   // CU) of a tile's Q rows and, behind them, its dO rows
+  char *Vs = smem + 4 * TILEB;                     // [128][D]: the workgroup's V rows, staged once
+  float *Ls = (float *)(Vs + 8 * zp_pad16::R16);   // [2][32] -LSE / scale
+  float *Ds = Ls + 2 * QT;                         // [2][32] -D
 
-  const int unit = zp_item_of_block(p.work_kv_short, (int *)(Ds + NBUF * QT));
-  if (unit < 0 || unit >= p.n_kv_tiles_short * p.Hkv) return;
+  const int unit = zp_item_of_block(p.work_kv, (int *)(Ds + 2 * QT));
+  if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
-  const zp_tile t = zp_load_tile(p.kv_tiles_short + tile_idx);
+  const zp_tile t = zp_load_tile(p.kv_tiles + tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
-  // the wave's two sub-blocks of 16 key rows: see attn_bwd_dkdv_kernel
+  // the wave's two sub-blocks of 16 key rows: see attn_bwd_dkdv64_kernel
   const int kb[2] = {16 * w, 16 * (7 - w)};
   const int krow[2] = {kb[0] + c16, kb[1] + c16};
   const int kpos[2] = {t.k_pos0 + krow[0] - q4, t.k_pos0 + krow[1] - q4};
@@ -763,14 +733,13 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
   ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, tid);
   dkdv_lds_addr la;
-  la.init(lane);
+  la.init(lane, smem, Vs + kb[0] / 16 * zp_pad16::R16, Vs + kb[1] / 16 * zp_pad16::R16);
   {
     zp_stager<D, 4, true> vst;
     vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
     vst.issue(Vs, 0, t.k_len);
-    vst.issue(Vs + 64 * D * 2, 64, t.k_len);
+    vst.issue(Vs + 4 * zp_pad16::R16, 64, t.k_len);
   }
-  const unsigned v0 = la.rows_base(Vs + kb[0] * 256), v1 = la.rows_base(Vs + kb[1] * 256);
   const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
   // 32 floats of a row vector, one per lane of the lower half-wave (rows past the last valid one repeat it)
   auto stage_f32x32 = [&](float *dst, const float *src, int first, int last_valid) {
@@ -783,8 +752,8 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   auto stage = [&](int buf) {
     const int hh = st_hh, i0 = st_qt * QT;
     const int h = g * p.grp + hh;
-    qst.issue(Qs + buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
-    ost.issue(Os + buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
+    qst.issue(Qs + 2 * buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
+    ost.issue(Qs + (2 * buf + 1) * TILEB, i0, t.q_rows, (int64_t)hh * D);
     const int64_t base = (int64_t)h * p.T + t.q_tok0;
     stage_f32x32(Ls + buf * QT, p.lse2 + base, i0, t.q_rows - 1);
     stage_f32x32(Ds + buf * QT, p.dvec + base, i0, t.q_rows - 1);
@@ -798,9 +767,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if constexpr (N == 0) {
       return;
     } else if constexpr (N <= PW) {
-      zp_dma16_so(pc_q, qst.off[N - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + pc_buf * TILEB + (qst.w * PW + N - 1) * 1024));
+      zp_dma16_so(pc_q, qst.off[N - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + 2 * pc_buf * TILEB + qst.dest(N - 1)));
     } else if constexpr (N <= 2 * PW) {
-      zp_dma16_so(pc_o, ost.off[N - PW - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Os) + pc_buf * TILEB + (ost.w * PW + N - PW - 1) * 1024));
+      zp_dma16_so(pc_o, ost.off[N - PW - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + (2 * pc_buf + 1) * TILEB + ost.dest(N - PW - 1)));
     } else if constexpr (N == 2 * PW + 1) {
       if (lane < 32) zp_dma4_so(pc_l, lane * 4, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + pc_buf * (QT * 4)));
     } else if constexpr (N == 2 * PW + 2) {
@@ -812,33 +781,28 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   if (n_it > 0) stage(0);
   staged();
   zp_wait_async();
-#pragma unroll
-  for (int b = 1; b < NBUF - 1; b++) {
-    if (n_it > b) stage(b);
-    staged();
-  }
   __syncthreads();
 
   const int k0_min = t.k_pos0 + kb[0], k1_min = t.k_pos0 + kb[1];  // first positions of the sub-blocks
   const int qpos_end = t.q_pos0 + t.q_rows, qpos_end_l = qpos_end - q4;
-  constexpr int D_OFF = NBUF * QT * 4;
+  constexpr int D_OFF = 2 * QT * 4;
 
-  int buf = 0, cur_qt = n_qt - 1, cur_hh = 0;
-  for (int it = 0; it < n_it; it++) {
+  int cur_qt = n_qt - 1, cur_hh = 0;
+  // one tile out of buffer BUF (compile-time, so that every LDS address is a register plus an immediate)
+  auto query_tile = [&](int it, auto BUF) {
+    constexpr int buf = decltype(BUF)::value;
     const int i0 = cur_qt * QT;
     if (++cur_hh == p.grp) { cur_hh = 0; cur_qt--; }
-    const int ahead = n_it - 1 - it;        // tiles after this one
     const int qpos0 = t.q_pos0 + i0;        // position of the tile's first query
     // sub-blocks with a key that some query of the tile sees
     const bool act0 = qpos0 + QT - 1 >= k0_min, act1 = qpos0 + QT - 1 >= k1_min && kb[1] < t.k_len;
     const bool masked = qpos0 < (act1 ? k1_min : k0_min) + 15 || qpos0 + QT > qpos_end;
-    // the tile NBUF - 1 iterations ahead is fetched inside this tile's S chain when it is a full tile and this wave
-    // computes an unmasked one (the common case), else in front
-    const bool fetch = ahead >= NBUF - 1;
+    // the next tile is fetched inside this tile's S run when it is a full tile and this wave computes an unmasked one
+    // (the common case), else in front; its sources are worked out unconditionally (and, past the end, in vain): values
+    // defined under a wave's branch would not stay in scalar registers
+    const bool fetch = it + 1 < n_it;
     const bool fused = fetch && act1 && !masked && st_qt * QT + QT <= t.q_rows;
-    pc_buf = buf == 0 ? NBUF - 1 : buf - 1;
-    // the sources of that tile are worked out unconditionally (and, past the end, in vain): values defined under a
-    // wave's branch would not stay in scalar registers
+    pc_buf = buf ^ 1;
     {
       const int i0n = st_qt * QT;
       pc_q = zp_uniform_ptr(qst.base + (int64_t)i0n * qst.stride + (int64_t)st_hh * D);
@@ -847,23 +811,21 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       pc_l = zp_uniform_ptr(p.lse2 + base);
       pc_d = zp_uniform_ptr(p.dvec + base);
     }
-    if (fetch && !fused) stage(pc_buf);
-
-    const char *Qb = Qs + buf * TILEB;
-    const char *Ob = Os + buf * TILEB;
+    if (fetch && !fused) stage(buf ^ 1);
     if (act1) {
-      if (masked) dkdv_block<true, false, false>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
-      else if (fused) dkdv_block<false, false, true>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
-      else dkdv_block<false, false, false>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      if (masked) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, false, false>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      else if (fused) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, true>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
+      else dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, false>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     } else if (act0) {
-      dkdv_block<true, true, false>(Qb, Ob, seed + buf * (QT * 4), D_OFF, kreg, v0, v1, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, true, false>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     }
-    // the next tile must have landed; the one behind it may stay in flight
-    if (ahead >= NBUF - 1) zp_wait_async_upto<(NBUF - 2) * LOADS>();
-    else zp_wait_async();
-    __syncthreads();
     staged();
-    buf = buf + 1 == NBUF ? 0 : buf + 1;
+    zp_wait_async();
+    __syncthreads();
+  };
+  for (int it = 0; it < n_it; it += 2) {
+    query_tile(it, std::integral_constant<int, 0>{});
+    if (it + 1 < n_it) query_tile(it + 1, std::integral_constant<int, 1>{});
   }
 
 #pragma unroll
@@ -871,11 +833,11 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if (krow[cb] >= t.k_len) continue;
     const int64_t at = ((int64_t)t.k_tok0 + krow[cb]) * p.dkv_stride + (int64_t)g * D + q4;
     if (p.accumulate) {
-      add_acc_rows16<D>((float *)p.dk + at, dk_acc[cb], p.scale);
-      add_acc_rows16<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
+      add_acc_rows<D>((float *)p.dk + at, dk_acc[cb], p.scale);
+      add_acc_rows<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
     } else {
-      store_acc_rows16<D>(p.dk + at, dk_acc[cb], p.scale);
-      store_acc_rows16<D>(p.dv + at, dv_acc[cb], 1.0f);
+      store_acc_rows<D>(p.dk + at, dk_acc[cb], p.scale);
+      store_acc_rows<D>(p.dv + at, dv_acc[cb], 1.0f);
     }
   }
 }
@@ -896,8 +858,6 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   int32_t *c = p->work_dq.counters;
   const int dq_grid = zp_plan_work_split(p->work_dq, c, ((dq_units + 7) / 8) * 8 * p->grp);
   const int kv_grid = zp_plan_work_split(p->work_kv, c ? c + ZP_COUNTER_BYTES / 4 : nullptr, ((kv_units + 7) / 8) * 8);
-  const int kv_units_short = p->n_kv_tiles_short * p->Hkv;   // only ever non-zero at d = 128
-  const int kv_short_grid = zp_plan_work_split(p->work_kv_short, c ? c + 2 * (ZP_COUNTER_BYTES / 4) : nullptr, ((kv_units_short + 7) / 8) * 8);
   if (dq_units > 0) {
     zp_prof_begin("attn_bwd_dq", stream);
     if (d == 128) hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 128 * 2 + 16, stream, *p);
@@ -908,16 +868,8 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   }
   if (kv_units > 0) {
     zp_prof_begin("attn_bwd_dkdv", stream);
-    if (d == 128) hipLaunchKernelGGL((attn_bwd_dkdv_kernel<128>), dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 128 * 2 + 2048 + 16, stream, *p);
-    else hipLaunchKernelGGL((attn_bwd_dkdv_kernel<64>), dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
-    zp_prof_end(stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
-  }
-  if (kv_units_short > 0) {
-    zp_prof_begin("attn_bwd_dkdv_short", stream);
-    hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_short_grid), dim3(BWD_NT),
-                       2 * ZP_DKDV_NBUF * 32 * 128 * 2 + 2 * 64 * 128 * 2 + 2 * ZP_DKDV_NBUF * 32 * 4 + 16, stream, *p);
+    if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16::R16 + 4 * 32 * 4 + 16, stream, *p);
+    else hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
     zp_prof_end(stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

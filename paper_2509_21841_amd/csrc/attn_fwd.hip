@@ -182,7 +182,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // prologue overlap; the explicit wait in front of the first barrier covers both (and tells the compiler that the
   // register operands have arrived: a wait of its own inside the key loop would drain the copies in flight).
 
-  zp_stager<D, 4, true> kst, vst;
+  zp_stager<D> kst, vst;
   kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
   vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
   zp_lds16<D> lo;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   zp_wait_async();
   __syncthreads();
 
-  constexpr int PW = zp_stager<D, 4, true>::PER_WAVE;
+  constexpr int PW = zp_stager<D>::PER_WAVE;
   // one key tile out of LDS buffer BUF (a compile-time constant, so every LDS address is register + immediate)
   auto key_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;

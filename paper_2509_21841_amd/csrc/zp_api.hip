@@ -31,13 +31,12 @@ struct zp_bwd_params {
   float *lse2;
   const zp_tile *dq_tiles;
   const zp_tile *kv_tiles;
-  const zp_tile *kv_tiles_short;  // key blocks with few query tiles: run by the two-workgroups-per-CU kernel (d = 128)
-  int32_t n_dq_tiles, n_kv_tiles, n_kv_tiles_short, Hq, Hkv, grp, T;
+  int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;
   int64_t dq_stride, dkv_stride;
   int32_t accumulate;
-  zp_work_split work_dq, work_kv, work_kv_short;
+  zp_work_split work_dq, work_kv;
 };
 int zp_launch_accum_to_bf16(const float *src, void *dst, int64_t n, hipStream_t stream);
 int zp_launch_attn_bwd(const zp_bwd_params *p, int d, hipStream_t stream);
@@ -185,9 +184,9 @@ int64_t count_pair_blocks(const zp_pair *pairs, int n, int bm) {
   return c;
 }
 
-// Every tile table in a workspace is preceded by WS_HEADER bytes of work counters (three sets: a call launches at most
-// three attention kernels), which travel with the table in the same copy and arrive as zeros.
-constexpr size_t WS_HEADER = 3 * ZP_COUNTER_BYTES;
+// Every tile table in a workspace is preceded by WS_HEADER bytes of work counters (two sets: a call launches at most
+// two attention kernels), which travel with the table in the same copy and arrive as zeros.
+constexpr size_t WS_HEADER = 2 * ZP_COUNTER_BYTES;
 inline int32_t *ws_counters(void *ws) { return (int32_t *)ws; }
 inline const zp_tile *ws_tiles(void *ws) { return (const zp_tile *)((char *)ws + WS_HEADER); }
 inline size_t tile_table_bytes(size_t n_tiles) { return WS_HEADER + align256(n_tiles * sizeof(zp_tile)); }
@@ -212,28 +211,6 @@ int upload_tiles(const std::vector<CostTile> &tiles, void *ws, hipStream_t strea
   zp_tile *h = (zp_tile *)((char *)host + WS_HEADER);
   for (size_t i = 0; i < tiles.size(); i++) h[i] = tiles[i].t;
   return pool_upload(slot, host, ws, bytes, stream);
-}
-
-// Sequences (or chunk pairs) whose key blocks loop over few (query tile, head) iterations go to the dK/dV kernel that
-// runs two workgroups per CU (head dimension 128 only): a workgroup's fixed cost -- launch, row operands, first tiles,
-// final stores -- is then covered by its neighbour, which is worth more than the other kernel's denser key loop below
-// about 256 iterations of 64 queries (measured crossover: 8K tokens with one query head per KV head, 2K-4K tokens with
-// 4-8). The choice is made per sequence, not per key block, so that the light last blocks of a long sequence stay in
-// the long kernel's launch and fill its tail.
-inline bool kv_rows_are_short(int64_t q_rows_max, int d, int grp) { return d == 128 && ((q_rows_max + 63) / 64) * grp < 256; }
-// Moves the tiles marked short (aux = 1) behind the others, keeping the order inside both parts; returns the number of
-// long tiles. When the short ones hold less than 30 % of the launch's work (query tiles to visit) they stay with the
-// long ones instead: two launches have two tails, and a few light sequences are worth more as the filler of the long
-// kernel's tail than they gain from the other kernel.
-size_t split_kv_tiles(std::vector<CostTile> &kt) {
-  int64_t work = 0, work_short = 0;
-  for (const CostTile &c : kt) {
-    work += c.cost;
-    if (c.t.aux) work_short += c.cost;
-  }
-  if (work_short * 10 < work * 3)
-    for (CostTile &c : kt) c.t.aux = 0;
-  return (size_t)(std::stable_partition(kt.begin(), kt.end(), [](const CostTile &c) { return c.t.aux == 0; }) - kt.begin());
 }
 
 }  // namespace
@@ -599,7 +576,6 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   for (int s : seq_order) {
     if (seq_skip && seq_skip[s]) continue;
     const int32_t L = cu[s + 1] - cu[s];
-    const int32_t short_rows = kv_rows_are_short(L, sh->d, sh->Hq / sh->Hkv) ? 1 : 0;
     for (int32_t j0 = 0; j0 < L; j0 += bnk) {
       CostTile c;
       c.t.k_tok0 = cu[s] + j0;
@@ -609,13 +585,12 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
       c.t.q_rows = L - j0;
       c.t.q_pos0 = j0;
       c.t.out_row0 = cu[s] + j0;
-      c.t.aux = short_rows;
+      c.t.aux = 0;
       c.cost = (c.t.q_rows + 63) / 64;
       kt.push_back(c);
     }
   }
   if (qt.empty() && kt.empty()) return ZP_OK;
-  const size_t n_kv_long = split_kv_tiles(kt);
   const size_t tile_bytes = tile_table_bytes(qt.size() + kt.size());
   const size_t dvec_bytes = align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float));
   if ((rc = check_ws(ws, ws_bytes, tile_bytes + 2 * dvec_bytes))) return rc;
@@ -633,10 +608,8 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.kv_tiles = ws_tiles(ws) + qt.size();
   p.work_dq.counters = ws_counters(ws);
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
-  p.work_kv.dyn_div = dyn_div_of(all, qt.size(), n_kv_long, sh->Hq / sh->Hkv);
-  p.work_kv_short.dyn_div = dyn_div_of(all, qt.size() + n_kv_long, kt.size() - n_kv_long, sh->Hq / sh->Hkv);
-  p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)n_kv_long;
-  p.kv_tiles_short = p.kv_tiles + n_kv_long; p.n_kv_tiles_short = (int32_t)(kt.size() - n_kv_long);
+  p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
+  p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv; p.T = sh->T;
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.dq = (__bf16 *)dq; p.dk = (__bf16 *)dk; p.dv = (__bf16 *)dv;
@@ -648,7 +621,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
 
 // Builds the dQ tiles (blocks of query rows of each pair's Q chunk against its KV chunk) and the dK/dV tiles (blocks
 // of key rows of each pair's KV chunk against the Q-chunk rows that can see them) of one ring round.
-static void plan_pairs_bwd(const zp_pair *pairs, int n_pairs, int bmq, int bnk, int d, int grp, std::vector<CostTile> &qt,
+static void plan_pairs_bwd(const zp_pair *pairs, int n_pairs, int bmq, int bnk, std::vector<CostTile> &qt,
                            std::vector<CostTile> &kt) {
   for (int i = 0; i < n_pairs; i++) {
     const zp_pair &pr = pairs[i];
@@ -667,7 +640,7 @@ static void plan_pairs_bwd(const zp_pair *pairs, int n_pairs, int bmq, int bnk, 
       CostTile c;
       c.t.k_tok0 = pr.k_tok0 + j0; c.t.k_len = std::min(bnk, pr.k_len - j0); c.t.k_pos0 = pr.k_pos0 + j0;
       c.t.q_tok0 = pr.q_tok0 + off; c.t.q_rows = pr.q_len - off; c.t.q_pos0 = pr.q_pos0 + off;
-      c.t.out_row0 = c.t.k_tok0; c.t.aux = kv_rows_are_short(pr.q_len, d, grp) ? 1 : 0;
+      c.t.out_row0 = c.t.k_tok0; c.t.aux = 0;
       c.cost = (c.t.q_rows + 63) / 64;
       kt.push_back(c);
     }
@@ -709,8 +682,7 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   }
   const int bmq = zp_attn_bwd_block_rows(sh->d, 0), bnk = zp_attn_bwd_block_rows(sh->d, 1);
   std::vector<CostTile> qt, kt;
-  plan_pairs_bwd(pairs, n_pairs, bmq, bnk, sh->d, sh->Hq / sh->Hkv, qt, kt);
-  const size_t n_kv_long = split_kv_tiles(kt);
+  plan_pairs_bwd(pairs, n_pairs, bmq, bnk, qt, kt);
   const size_t tile_bytes = tile_table_bytes(qt.size() + kt.size());
   const size_t dvec_bytes = align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float));
   if ((rc = check_ws(ws, ws_bytes, tile_bytes + 2 * dvec_bytes))) return rc;
@@ -728,10 +700,8 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.kv_tiles = ws_tiles(ws) + qt.size();
   p.work_dq.counters = ws_counters(ws);
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
-  p.work_kv.dyn_div = dyn_div_of(all, qt.size(), n_kv_long, sh->Hq / sh->Hkv);
-  p.work_kv_short.dyn_div = dyn_div_of(all, qt.size() + n_kv_long, kt.size() - n_kv_long, sh->Hq / sh->Hkv);
-  p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)n_kv_long;
-  p.kv_tiles_short = p.kv_tiles + n_kv_long; p.n_kv_tiles_short = (int32_t)(kt.size() - n_kv_long);
+  p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
+  p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv; p.T = sh->T;
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.dq = (__bf16 *)dq_acc; p.dk = (__bf16 *)dk_acc; p.dv = (__bf16 *)dv_acc;

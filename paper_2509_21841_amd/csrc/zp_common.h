@@ -11,7 +11,6 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
@@ -115,15 +114,6 @@ __device__ __forceinline__ void zp_block_to_unit(int bid, int grp, int &unit, in
 
 __device__ __forceinline__ float zp_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Three-operand maximum in one VALU operation (operands are finite or -inf here, never NaN). Inline assembly is
-// invisible to the compiler's hazard checks: never feed it a register an MFMA has just written unless an ordinary
-// instruction that reads the same accumulator comes first (data-dependently), which makes the compiler insert the
-// required wait states.
-__device__ __forceinline__ float zp_max3(float a, float b, float c) {
-  float d;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-  return d;
-}
 // max / sum across the two lanes l and l^32 that hold the two halves of one 32x32 MFMA column.
 __device__ __forceinline__ float zp_pair_max(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -144,34 +134,10 @@ __device__ __forceinline__ float zp_quad_sum(float x) {
   return zp_pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
-// 16-byte LDS read and the gfx950 transposing 8-byte LDS read.
-__device__ __forceinline__ bf16x8 zp_lds_read16(const char *smem, int off) {
-  return *(const ZP_LDS bf16x8 *)((const ZP_LDS char *)smem + off);
-}
-// Within each group of 16 lanes, lane i passes the address of 4 consecutive 16-bit elements of row i/4,
-// columns 4*(i%4)..+3 of a 4x16 block, and receives column i of rows 0..3.
-__device__ __forceinline__ bf16x4 zp_lds_read_tr(const char *smem, int off) {
-  s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)((ZP_LDS char *)smem + off));
-  return __builtin_bit_cast(bf16x4, v);
-}
-
+// The gfx950 transposing 8-byte LDS read (ds_read_b64_tr_b16): within each group of 16 lanes, lane i passes the address of
+// 4 consecutive 16-bit elements of row i/4, columns 4*(i%4)..+3 of a 4x16 block, and receives column i of rows 0..3.
 __device__ __forceinline__ bf16x8 zp_cat(bf16x4 a, bf16x4 b) {
   return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-// Swizzle for LDS tiles that are read BOTH row-wise (16 lanes: 16 consecutive rows, same 16-byte chunk) and
-// with the transposing read (32 lanes: 4 consecutive rows x 64 contiguous bytes): the 16-byte chunk index is
-// XORed with the row's low four bits with their two 2-bit fields swapped, which spreads both patterns over
-// all banks. `chunk` is the 16-byte chunk index in the row; returns the byte offset of that chunk.
-template <int D>
-__device__ __forceinline__ int zp_swz(int row, int chunk) {
-  if (D == 128) return row * 256 + ((chunk ^ (((row & 3) << 2) | ((row >> 2) & 3))) << 4);
-  return row * 128 + ((chunk ^ (((row & 1) << 2) | ((row >> 1) & 3))) << 4);
-}
-// Byte offset of element column `col` (multiple of 4) of row `row` under zp_swz.
-template <int D>
-__device__ __forceinline__ int zp_swz_col(int row, int col) {
-  return zp_swz<D>(row, col >> 3) + ((col & 7) << 1);
 }
 
 // The swizzle of tiles read as operands of the 16x16x32 MFMA: what the 16-byte chunk index of row `row` (r3 r2 r1 r0 in
@@ -188,6 +154,28 @@ __device__ __forceinline__ int zp_swz16_mask(int row) {
   if (D == 128) return (x << 3) | ((row & 3) << 1) | r3;
   return (x << 2) | (row & 2) | r3;
 }
+
+// The same bank pattern at D = 128 with the highest bit of the XOR turned into padding between groups of four rows
+// (asynchronous copies write 1 KB, four rows, at a time and can put each anywhere): the chunk index is XORed with r1 r0
+// r3 only, groups 1 and 2 of every four lie 128 bytes further. Read addresses of k-steps two apart and of 16-column
+// blocks four apart then differ by a constant instead of an XOR, so that two and four registers per lane
+// (zp_pad16::row_part, tr_part) and immediate offsets reach everything.
+struct zp_pad16 {
+  static constexpr int R16 = 4096 + 256;  // bytes of 16 rows
+  __device__ __forceinline__ static int mask(int row) { return ((row & 3) << 1) | ((row >> 3) & 1); }
+  // offset of the g-th group of four rows
+  __device__ __forceinline__ static int group(int g) { return (g >> 2) * R16 + (g & 3) * 1024 + (((g & 3) + 1) >> 1) * 128; }
+  // row operand of k-steps of parity `par` (k-step k: + k / 2 * 128), rows of the first 16
+  __device__ __forceinline__ static int row_part(int lane, int par) {
+    const int r = lane & 15, q = lane >> 4;
+    return group(r >> 2) + (r & 3) * 256 + (((4 * par + q) ^ mask(r)) << 4);
+  }
+  // transposed operand of 16-column blocks db with db % 4 == dq (db: + db / 4 * 128), first 16 rows (see zp_lds16::tr_at)
+  __device__ __forceinline__ static int tr_part(int lane, int dq) {
+    const int i = lane & 15, r = 4 * (lane >> 4) + (i >> 2);
+    return group(r >> 2) + (r & 3) * 256 + (((2 * dq + ((i >> 1) & 1)) ^ mask(r)) << 4) + ((i & 1) << 3);
+  }
+};
 
 // ---- asynchronous global -> LDS copies -------------------------------------------------------------
 // The direct-to-LDS loads are issued from inline assembly so that they stay truly asynchronous: the
@@ -245,7 +233,8 @@ __device__ __forceinline__ const void *zp_uniform_ptr(const void *p) {
 // out once (they carry the LDS swizzle); issuing a tile is then scalar address arithmetic plus the loads.
 // `init` takes the tensor base of the row run and the token stride (64 * stride * 2 bytes must fit 32 bits);
 // `issue` copies rows row0 .. row0+63 (rows past rows_total clamp to the last valid row).
-template <int D, int NW = 4, bool T16 = false>
+// PAD: LDS layout of the tile, zp_pad16 (D = 128 only) instead of zp_swz16.
+template <int D, int NW = 4, bool PAD = false>
 struct zp_stager {
   static constexpr int PER_WAVE = 64 * D * 2 / 1024 / NW;  // 1 KiB wave-loads per wave (NW = 4: the four waves share a 64-row tile; NW = 8: they cover its first 32 rows)
   static constexpr int LOADS = PER_WAVE;
@@ -254,16 +243,13 @@ struct zp_stager {
   const __bf16 *base;
   int w, lane;
   __device__ __forceinline__ static void row_chunk(int blk, int lane, int &r, int &c) {
-    if (T16) {
-      r = D == 128 ? blk * 4 + (lane >> 4) : blk * 8 + (lane >> 3);
-      c = (lane & (D / 8 - 1)) ^ zp_swz16_mask<D>(r);
-    } else if (D == 128) {
-      r = blk * 4 + (lane >> 4);
-      c = (lane & 15) ^ (((r & 3) << 2) | ((r >> 2) & 3));
-    } else {
-      r = blk * 8 + (lane >> 3);
-      c = (lane & 7) ^ (((r & 1) << 2) | ((r >> 1) & 3));
-    }
+    r = D == 128 ? blk * 4 + (lane >> 4) : blk * 8 + (lane >> 3);
+    c = (lane & (D / 8 - 1)) ^ (PAD ? zp_pad16::mask(r) : zp_swz16_mask<D>(r));
+  }
+  // where in the LDS tile this wave's n-th load goes
+  __device__ __forceinline__ int dest(int n) const {
+    static_assert(!PAD || D == 128, "");
+    return PAD ? zp_pad16::group(w * PER_WAVE + n) : (w * PER_WAVE + n) * 1024;
   }
   __device__ __forceinline__ void init(const __bf16 *gbase, int64_t tok_stride, int tid) {
     lane = tid & 63;
@@ -283,7 +269,7 @@ struct zp_stager {
     if (row0 + 64 <= rows_total) {
       const void *sb = zp_uniform_ptr(base + (int64_t)row0 * stride + extra);
 #pragma unroll
-      for (int n = 0; n < PER_WAVE; n++) zp_dma16_so(sb, off[n], lds0 + (w * PER_WAVE + n) * 1024);
+      for (int n = 0; n < PER_WAVE; n++) zp_dma16_so(sb, off[n], lds0 + dest(n));
     } else {
       int ln = lane;
       asm volatile("" : "+v"(ln));  // keeps the rare path's addresses out of the registers of the loop around it
@@ -293,67 +279,9 @@ struct zp_stager {
         row_chunk(w * PER_WAVE + n, ln, r, c);
         int gr = row0 + r;
         if (gr > rows_total - 1) gr = rows_total - 1;
-        zp_dma16(base + (int64_t)gr * stride + c * 8 + extra, lds0 + (w * PER_WAVE + n) * 1024);
+        zp_dma16(base + (int64_t)gr * stride + c * 8 + extra, lds0 + dest(n));
       }
     }
-  }
-};
-
-// LDS read offsets of one lane for the two MFMA operand patterns of a [64][D] zp_swz tile, worked out once.
-// rows(kb, kk): 16 bytes of row 32*kb + (lane%32), head-dim elements 16*kk + 8*(lane/32) ..+7  (row-major operand)
-// tr(kb, m, j, db): transposed 4-row piece for k-slots 4j..4j+3 of MFMA m of 32-row block kb, columns 32*db + lane%32
-template <int D>
-struct zp_lds_offsets {
-  int row_off[D / 16];      // + kb * 32 * ROWB
-  int tr_off[2][D / 32];    // [j][db], + (kb * 32 + m * 16) * ROWB
-  static constexpr int ROWB = D * 2;
-  __device__ __forceinline__ void init(int lane) {
-    const int r32 = lane & 31, hi = lane >> 5;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; kk++) row_off[kk] = zp_swz<D>(r32, 2 * kk + hi);
-    const int g16 = lane >> 4, i16 = lane & 15;
-    const int trow = 4 * (g16 >> 1) + (i16 >> 2);
-    const int tcol = 16 * (g16 & 1) + 4 * (i16 & 3);
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int db = 0; db < D / 32; db++) tr_off[j][db] = zp_swz_col<D>(8 * j + trow, db * 32 + tcol);
-  }
-  // Absolute form: the lane's offsets include the LDS address of `base` from then on, and the *_at readers take a
-  // tile's byte offset from `base` -- with a compile-time offset every read is a register plus an immediate (the
-  // pointer form costs one vector add per read for the base, which the compiler only knows as a relocation).
-  __device__ __forceinline__ void init_abs(int lane, const char *base) {
-    init(lane);
-    const int b = (int)(unsigned)(unsigned long long)(const ZP_LDS char *)base;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; kk++) {
-      row_off[kk] += b;
-      asm volatile("" : "+v"(row_off[kk]));  // opaque from here on: the compiler would otherwise split the sum again and redo the add at every read
-    }
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int db = 0; db < D / 32; db++) {
-        tr_off[j][db] += b;
-        asm volatile("" : "+v"(tr_off[j][db]));
-      }
-  }
-  __device__ __forceinline__ bf16x8 rows_at(int tile_off, int kb, int kk) const {
-    return *(const ZP_LDS bf16x8 *)(unsigned long long)(unsigned)(row_off[kk] + tile_off + kb * 32 * ROWB);
-  }
-  __device__ __forceinline__ bf16x8 tr_at(int tile_off, int kb, int m, int db) const {
-    const int o = tile_off + (kb * 32 + m * 16) * ROWB;
-    s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(unsigned)(tr_off[0][db] + o));
-    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(unsigned)(tr_off[1][db] + o));
-    return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
-  }
-  // the swizzle depends on row % 16 only (D = 128) / row % 8 (D = 64), so blocks of 32 and 16 rows shift by a constant
-  __device__ __forceinline__ bf16x8 rows(const char *tile, int kb, int kk) const {
-    return zp_lds_read16(tile, row_off[kk] + kb * 32 * ROWB);
-  }
-  __device__ __forceinline__ bf16x8 tr(const char *tile, int kb, int m, int db) const {
-    const int o = (kb * 32 + m * 16) * ROWB;
-    return zp_cat(zp_lds_read_tr(tile, tr_off[0][db] + o), zp_lds_read_tr(tile, tr_off[1][db] + o));
   }
 };
 
@@ -374,7 +302,8 @@ struct zp_lds16 {
 #pragma unroll
     for (int kk = 0; kk < D / 32; kk++) {
       row_off[kk] = b + r16 * ROWB + (((4 * kk + q) ^ zp_swz16_mask<D>(r16)) << 4);
-      asm volatile("" : "+v"(row_off[kk]));  // opaque from here on: see zp_lds_offsets
+      // opaque from here on: the compiler would otherwise split the sum again and redo the add at every read
+      asm volatile("" : "+v"(row_off[kk]));
     }
     const int tr = 4 * q + (r16 >> 2);
 #pragma unroll
