@@ -91,7 +91,7 @@ int varlen_attn_fwd(const void *q, const void *k, const void *v, int64_t q_strid
  * counters = 257 KiB, one copy
  * per GPU, held until the process ends) and is built on the device from the sequence boundaries, which travel by value
  * in the launch arguments. The call allocates nothing on host or device, reads no host memory from the device and
- * uploads nothing; it enqueues two kernels on `stream`. Limits: S <= ZP_NOALLOC_MAX_SEQS sequences and at most
+ * uploads nothing; it enqueues one kernel or (long tables) two on `stream`. Limits: S <= ZP_NOALLOC_MAX_SEQS sequences and at most
  * ZP_NOALLOC_MAX_TILES blocks of 128 query rows (sum over unflagged sequences of ceil(len / 128)); beyond them the
  * call returns ZP_ETOOLARGE and enqueues nothing. Every call on a GPU uses that GPU's one table: calls on the same GPU
  * must be ordered on one stream (or otherwise not overlap), else they race. Keep zp_profile_enable off around it

@@ -23,6 +23,7 @@ struct zp_bwd_params {
   int64_t dq_stride, dkv_stride;
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
   zp_work_split work_dq, work_kv;  // work hand-out of the two launches (counters set by the C ABI, the rest by the launcher)
+  zp_inline_tiles inl;  // the dQ tiles and, behind them, the dK/dV tiles if dq_tiles and kv_tiles are null
 };
 
 namespace {
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   if (unit >= p.n_dq_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = zp_load_tile(p.dq_tiles + tile_idx);
+  const zp_tile t = ZP_TILE(p.dq_tiles, p.inl, 0, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int unit = zp_item_of_block(p.work_kv, (int *)(Ds + NBUF * 64));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
-  const zp_tile t = zp_load_tile(p.kv_tiles + tile_idx);
+  const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
@@ -697,7 +698,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int unit = zp_item_of_block(p.work_kv, (int *)(Ds + 2 * QT));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
-  const zp_tile t = zp_load_tile(p.kv_tiles + tile_idx);
+  const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);

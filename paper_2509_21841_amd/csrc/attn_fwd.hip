@@ -147,7 +147,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   if (unit >= p.n_tiles * p.Hkv) return;
   const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = zp_load_tile(p.tiles + tile_idx);
+  const zp_tile t = ZP_TILE(p.tiles, p.inl, 0, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);

@@ -38,6 +38,15 @@ __device__ __forceinline__ zp_tile zp_load_tile(const zp_tile *p) {
 #undef ZP_U
   return t;
 }
+// `idx` of the table in device memory, or of the launch arguments (from `first` on) if there is none
+#define ZP_TILE(tiles, inl, first, idx) ((tiles) ? zp_load_tile((tiles) + (idx)) : zp_load_tile((inl).t + (first) + (idx)))
+
+// A launch's tile table where it is short: in the launch arguments themselves (4 KB at most in all), so that nothing is
+// uploaded in front of the launch.
+#define ZP_INLINE_TILES 112
+struct zp_inline_tiles {
+  zp_tile t[ZP_INLINE_TILES];
+};
 
 // How a launch hands its work items to workgroups. The XCDs of a chip do not run equally fast (on the boxes measured
 // the same four finish an equal share 4-8 % later than the other four), and the hardware deals workgroups to them
@@ -55,11 +64,12 @@ struct zp_work_split {
   int32_t n_items, n_static;
   int32_t dyn_div;  // 1 / dyn_div of the items are claimed at run time (0: the default, 8)
 };
+#define ZP_CLAIM_MIN_ITEMS (8 * 128)  // smaller launches take every item by number
 // Host side: the split and the grid of a launch of n_items (a multiple of 8) items.
 inline int zp_plan_work_split(zp_work_split &ws, int32_t *counters, int n_items) {
   ws.counters = counters;
   ws.n_items = n_items;
-  if (n_items < 8 * 128 || counters == nullptr) {  // small launches: every item by number
+  if (n_items < ZP_CLAIM_MIN_ITEMS || counters == nullptr) {
     ws.n_static = n_items;
     return n_items;
   }
@@ -101,6 +111,7 @@ struct zp_attn_params {
   int64_t lse_stride;
   int32_t update;    // partial kernel only: merge the result into the running (o, lse) found at the output rows
   zp_work_split work;  // which workgroups take their item by number and which claim one (set by the launcher)
+  zp_inline_tiles inl; // the tile table if `tiles` is null
 };
 
 // blockIdx -> (unit, head-in-group). Workgroups are dealt to the 8 XCDs round-robin by blockIdx, so

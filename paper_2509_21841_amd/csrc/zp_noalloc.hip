@@ -86,6 +86,24 @@ __global__ __launch_bounds__(256) void plan_fwd_tiles_kernel(PlanArgs a, int32_t
   tiles[slot] = t;
 }
 
+// The same order on the host, for a table of at most ZP_INLINE_TILES records.
+void fill_inline(const PlanArgs &a, zp_inline_tiles &inl) {
+  int order[ZP_INLINE_TILES], n = 0;  // sequences with blocks, longest first; equal lengths in ascending index
+  auto len = [&](int s) { return a.cu[s + 1] - a.cu[s]; };
+  for (int s = 0; s < a.S; s++) {
+    if (((a.skip_bits[s >> 5] >> (s & 31)) & 1u) || len(s) == 0) continue;
+    int i = n++;
+    for (; i > 0 && len(order[i - 1]) < len(s); i--) order[i] = order[i - 1];
+    order[i] = s;
+  }
+  int slot = 0;
+  for (int i = 0; i < n; i++) {
+    const int s = order[i], L = len(s);
+    for (int r0 = (L - 1) / BM * BM; r0 >= 0; r0 -= BM)
+      inl.t[slot++] = zp_tile{a.cu[s] + r0, L - r0 < BM ? L - r0 : BM, r0, a.cu[s], L, 0, a.cu[s] + r0, 0};
+  }
+}
+
 std::mutex g_mu;
 constexpr int MAX_DEVICES = 64;
 void *g_scratch_ptr[MAX_DEVICES] = {};
@@ -146,25 +164,32 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
   if (n_tiles == 0) return ZP_OK;
   a.n_tiles = (int32_t)n_tiles;
 
-  void *tiles = nullptr;
-  int rc = scratch_for_current_device(&tiles);
-  if (rc) return rc;
-  // Every slot the attention kernel reads is rewritten by the planning kernel of the same call, on the same stream,
-  // and so are the work counters in front of the table: nothing of an earlier call survives into this one.
-  hipLaunchKernelGGL(plan_fwd_tiles_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, (hipStream_t)stream, a,
-                     (int32_t *)tiles, (zp_tile *)((char *)tiles + ZP_COUNTER_BYTES));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return zp_report_hip_error((int)e, "plan_fwd_tiles launch");
-
   zp_attn_params p{};
+  p.n_tiles = a.n_tiles;
+  const int64_t items = (n_tiles * sh->Hkv + 7) / 8 * 8 * (sh->Hq / sh->Hkv);
+  if (n_tiles <= ZP_INLINE_TILES && items < ZP_CLAIM_MIN_ITEMS) {
+    // a short table goes into the launch arguments (and the shared array is not touched)
+    fill_inline(a, p.inl);
+  } else {
+    void *tiles = nullptr;
+    const int rc = scratch_for_current_device(&tiles);
+    if (rc) return rc;
+    // Every slot the attention kernel reads is rewritten by the planning kernel of the same call, on the same stream,
+    // and so are the work counters in front of the table: nothing of an earlier call survives into this one.
+    hipLaunchKernelGGL(plan_fwd_tiles_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, (hipStream_t)stream, a,
+                       (int32_t *)tiles, (zp_tile *)((char *)tiles + ZP_COUNTER_BYTES));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return zp_report_hip_error((int)e, "plan_fwd_tiles launch");
+    p.tiles = (const zp_tile *)((char *)tiles + ZP_COUNTER_BYTES);
+    p.work.counters = (int32_t *)tiles;
+  }
   p.q = (const __bf16 *)q; p.k = (const __bf16 *)k; p.v = (const __bf16 *)v;
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
-  p.tiles = (const zp_tile *)((char *)tiles + ZP_COUNTER_BYTES); p.n_tiles = (int32_t)n_tiles; p.work.counters = (int32_t *)tiles;
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
   p.scale = sh->scale > 0.f ? sh->scale : 1.0f / std::sqrt((float)sh->d);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o; p.o_stride = o_stride; p.lse = lse; p.lse_stride = sh->T;
-  e = (hipError_t)zp_launch_attn_fwd(&p, sh->d, 0, BM, (hipStream_t)stream);
+  const hipError_t e = (hipError_t)zp_launch_attn_fwd(&p, sh->d, 0, BM, (hipStream_t)stream);
   if (e != hipSuccess) return zp_report_hip_error((int)e, "attn_fwd launch");
   return ZP_OK;
 }

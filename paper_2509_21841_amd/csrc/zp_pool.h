@@ -48,6 +48,11 @@ class zp_staging_pool {
     *host_out = s.host;
     return 0;
   }
+  // The slot's event, for a backend whose copy marks it by itself.
+  typename Backend::event_t event(int slot) {
+    std::lock_guard<std::mutex> lk(mu_);
+    return slots_[slot].ev;
+  }
   // The caller has enqueued the copy out of the slot: records the slot's event behind it on `stream`; the slot stays
   // busy until the event completes. On a backend error the slot is freed (nothing reads it).
   int submitted(int slot, typename Backend::stream_t stream) {

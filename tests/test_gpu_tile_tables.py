@@ -1,0 +1,101 @@
+"""Where a call's tile table travels: in the launch arguments (up to 112 tiles and under 1024 work items) or through the
+workspace. The kernels are deterministic, so a batch gives the same bits whichever way its table took; the table's length
+and the number of items are taken to both sides of their limits. Calls that upload a table are also recorded into a HIP
+graph and replayed between other calls that use the staging buffers."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_21841_amd import binding as B
+from paper_2509_21841_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def bits(t):
+    return t.contiguous().view(torch.int16 if t.dtype == torch.bfloat16 else torch.int32)
+
+
+def run(lengths, q, k, v, do, n):
+    """Forward and backward of the first n tokens, cut into `lengths`."""
+    cu = synth.cu_seqlens(lengths)
+    q, k, v, do = q[:n], k[:n], v[:n], do[:n]
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    o2, lse2 = torch.zeros_like(o), torch.zeros_like(lse)
+    B.varlen_attn_fwd_noalloc(q, k, v, cu, o2, lse2)
+    assert torch.equal(bits(o), bits(o2)) and torch.equal(bits(lse), bits(lse2))
+    return (o, lse.t()) + tuple(B.varlen_attn_bwd(do, q, k, v, o, lse, cu))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tiles,Hq,Hkv", [(1, 1, 1), (55, 2, 1), (56, 2, 2), (57, 2, 1), (111, 4, 2), (112, 1, 1), (112, 2, 2),
+                                          (113, 1, 1), (50, 20, 4), (52, 20, 4), (31, 33, 11)])
+def test_short_tables_equal_long_ones(tiles, Hq, Hkv, d):
+    # forward: `tiles` tiles; backward: twice that in one table (56 is its limit)
+    lengths = [129 + i % 100 for i in range(tiles // 2)] + ([40] if tiles % 2 else [])
+    extra = [1000] * 15   # 120 more tiles: the other route
+    n = sum(lengths)
+    q, k, v, do = synth.make_qkv(n + sum(extra), Hq, Hkv, d, 83, DEV, with_dout=True)
+    got = run(lengths, q, k, v, do, n)
+    want = run(lengths + extra, q, k, v, do, n + sum(extra))
+    for a, b in zip(got, want):
+        assert torch.equal(bits(a), bits(b[:n]))
+
+
+def test_uploaded_tables_in_a_captured_graph():
+    """The staging buffer of a captured upload is read at every replay: calls in between must not get it."""
+    lengths = [130] * 64
+    Hq, Hkv, d, T = 8, 2, 128, 130 * 64
+    cu = synth.cu_seqlens(lengths)
+    q, k, v, do = synth.make_qkv(T, Hq, Hkv, d, 91, DEV, with_dout=True)
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    grads = [torch.empty_like(x) for x in (q, k, v)]
+    call = lambda: (B.varlen_attn_fwd(q, k, v, cu, o=o, lse=lse),
+                    B.varlen_attn_bwd(do, q, k, v, o, lse, cu, dq=grads[0], dk=grads[1], dv=grads[2]))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for _ in range(4):
+            call()                               # the workspaces of the capture stream, and staging buffers to spare
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    other = [300, 1, 77] * 40
+    oq, ok, ov = synth.make_qkv(sum(other), Hq, Hkv, d, 92, DEV)
+    for rep in range(4):
+        fresh = synth.make_qkv(T, Hq, Hkv, d, 930 + rep, DEV, with_dout=True)
+        for dst, src in zip((q, k, v, do), fresh):
+            dst.copy_(src)
+        B.varlen_attn_fwd(oq, ok, ov, synth.cu_seqlens(other))       # takes free staging buffers in between
+        wo, wl = B.varlen_attn_fwd(q, k, v, cu)
+        want = [wo, wl] + list(B.varlen_attn_bwd(do, q, k, v, wo, wl, cu))
+        for t in (o, lse, *grads):
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip((o, lse, *grads), want):
+            assert torch.equal(bits(a), bits(b)), f"replay {rep}"
+
+
+def test_noalloc_with_a_long_table_replays_from_a_captured_graph():
+    lengths = [900, 129, 0, 1, 2049] * 8
+    Hq, Hkv, d, T = 8, 2, 128, sum(lengths)
+    cu = synth.cu_seqlens(lengths)
+    q, k, v = synth.make_qkv(T, Hq, Hkv, d, 95, DEV)
+    o, lse = torch.zeros_like(q), torch.zeros((Hq, T), dtype=torch.float32, device=DEV)
+    B.varlen_attn_fwd_noalloc(q, k, v, cu, o, lse)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.varlen_attn_fwd_noalloc(q, k, v, cu, o, lse)
+    for rep in range(3):
+        for dst, src in zip((q, k, v), synth.make_qkv(T, Hq, Hkv, d, 960 + rep, DEV)):
+            dst.copy_(src)
+        wo, wl = B.varlen_attn_fwd(q, k, v, cu)
+        o.zero_(); lse.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(bits(o), bits(wo)) and torch.equal(bits(lse), bits(wl)), f"replay {rep}"
