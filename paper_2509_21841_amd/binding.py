@@ -7,6 +7,7 @@ library or a failing call raises.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 
 import numpy as np
@@ -119,9 +120,12 @@ def _check(rc: int):
         raise ZpError(rc, lib().zp_strerror(rc).decode())
 
 
-def _stream_ptr(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream_ptr(stream=None) -> int:
+    """The hipStream_t of `stream`, or of the current device's current stream (without building a Stream object for it:
+    that takes longer than the launch)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _cu_host(cu_seqlens) -> np.ndarray:
@@ -130,9 +134,23 @@ def _cu_host(cu_seqlens) -> np.ndarray:
     return np.ascontiguousarray(cu_seqlens, dtype=np.int32)
 
 
+def _cu_ptr(cu: np.ndarray) -> int:
+    return cu.__array_interface__["data"][0]
+
+
+def _skip_ptr(seq_skip, cu):
+    """(flags kept alive, their address or None)."""
+    if seq_skip is None:
+        return None, None
+    skip = np.ascontiguousarray(seq_skip, dtype=np.uint8)
+    assert len(skip) == len(cu) - 1
+    return skip, _cu_ptr(skip)
+
+
 def _tok_stride(t: torch.Tensor) -> int:
-    assert t.dim() == 3 and t.stride(2) == 1 and t.stride(1) == t.shape[2], "need [T,H,d] with contiguous heads"
-    return t.stride(0) if t.shape[0] > 1 else t.shape[1] * t.shape[2]
+    st, sz = t.stride(), t.shape
+    assert len(st) == 3 and st[2] == 1 and st[1] == sz[2], "need [T,H,d] with contiguous heads"
+    return st[0] if sz[0] > 1 else sz[1] * sz[2]
 
 
 _ws_cache: dict = {}
@@ -141,7 +159,7 @@ _ws_cache: dict = {}
 def workspace(nbytes: int, device, tag: str = "default", stream=None) -> torch.Tensor:
     """A cached device scratch tensor of at least nbytes (256-byte aligned by the torch allocator), one per device,
     entry point and stream: calls on one stream are ordered and may share it, calls on different streams may not."""
-    key = (str(device), tag, _stream_ptr(stream).value or 0)
+    key = (device, tag, _stream_ptr(stream))
     t = _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
         t = torch.empty(max(int(nbytes), 4096), dtype=torch.uint8, device=device)
@@ -150,7 +168,7 @@ def workspace(nbytes: int, device, tag: str = "default", stream=None) -> torch.T
 
 
 def workspace_bytes(which: int, shape: ZpShape, cu_host=None, n_desc: int = 0) -> int:
-    cup = cu_host.ctypes.data_as(ctypes.c_void_p) if cu_host is not None else None
+    cup = _cu_ptr(cu_host) if cu_host is not None else None
     return int(lib().zp_workspace_bytes(which, ctypes.byref(shape), cup, n_desc))
 
 
@@ -172,11 +190,9 @@ def varlen_attn_fwd(q, k, v, cu_seqlens, o=None, lse=None, scale=0.0, ws=None, s
     need = workspace_bytes(FN_FWD, sh, cu)
     if ws is None:
         ws = workspace(need, q.device, "fwd", stream)
-    skip = None if seq_skip is None else np.ascontiguousarray(seq_skip, dtype=np.uint8)
-    assert skip is None or len(skip) == len(cu) - 1
-    skp = None if skip is None else skip.ctypes.data_as(ctypes.c_void_p)
+    skip, skp = _skip_ptr(seq_skip, cu)
     _check(lib().varlen_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), _tok_stride(q), _tok_stride(k), _tok_stride(v),
-                                 cu.ctypes.data_as(ctypes.c_void_p), skp, o.data_ptr(), _tok_stride(o), lse.data_ptr(),
+                                 _cu_ptr(cu), skp, o.data_ptr(), _tok_stride(o), lse.data_ptr(),
                                  ctypes.byref(sh), ws.data_ptr(), ws.numel(), _stream_ptr(stream)))
     return o, lse
 
@@ -191,11 +207,9 @@ def varlen_attn_fwd_noalloc(q, k, v, cu_seqlens, o, lse, scale=0.0, stream=None,
     T, Hq, d = q.shape
     Hkv = k.shape[1]
     sh = make_shape(T, len(cu) - 1, Hq, Hkv, d, scale)
-    skip = None if seq_skip is None else np.ascontiguousarray(seq_skip, dtype=np.uint8)
-    assert skip is None or len(skip) == len(cu) - 1
-    skp = None if skip is None else skip.ctypes.data_as(ctypes.c_void_p)
+    skip, skp = _skip_ptr(seq_skip, cu)
     _check(lib().varlen_attn_fwd_noalloc(q.data_ptr(), k.data_ptr(), v.data_ptr(), _tok_stride(q), _tok_stride(k),
-                                         _tok_stride(v), cu.ctypes.data_as(ctypes.c_void_p), skp, o.data_ptr(),
+                                         _tok_stride(v), _cu_ptr(cu), skp, o.data_ptr(),
                                          _tok_stride(o), lse.data_ptr(), ctypes.byref(sh), _stream_ptr(stream)))
     return o, lse
 
@@ -214,12 +228,11 @@ def varlen_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, dq=None, dk=None, dv=None
     if ws is None:
         ws = workspace(need, q.device, "bwd", stream)
     assert _tok_stride(dk) == _tok_stride(dv)
-    skip = None if seq_skip is None else np.ascontiguousarray(seq_skip, dtype=np.uint8)
-    assert skip is None or len(skip) == len(cu) - 1
+    skip, skp = _skip_ptr(seq_skip, cu)
     _check(lib().varlen_attn_bwd(dout.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                                  _tok_stride(dout), _tok_stride(q), _tok_stride(k), _tok_stride(v), _tok_stride(o),
-                                 cu.ctypes.data_as(ctypes.c_void_p),
-                                 None if skip is None else skip.ctypes.data_as(ctypes.c_void_p),
+                                 _cu_ptr(cu),
+                                 skp,
                                  dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
                                  _tok_stride(dq), _tok_stride(dk), ctypes.byref(sh), ws.data_ptr(), ws.numel(),
                                  _stream_ptr(stream)))
@@ -416,7 +429,7 @@ def remap_tokens(src, idx, mode: int = 0, dst=None, stream=None):
     """Row gather (mode 0: dst[i] = src[idx[i]]) or scatter (mode 1: dst[idx[i]] = src[i]); idx int32 on device."""
     assert src.is_contiguous()
     n = src.shape[0]
-    row_bytes = int(np.prod(src.shape[1:])) * src.element_size()
+    row_bytes = math.prod(src.shape[1:]) * src.element_size()
     if dst is None:
         dst = torch.empty_like(src)
     _check(lib().remap_tokens(src.data_ptr(), dst.data_ptr(), int(row_bytes), idx.data_ptr(), int(n), int(mode),
