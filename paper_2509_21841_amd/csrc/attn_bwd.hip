@@ -31,13 +31,7 @@ namespace {
 constexpr int BWD_NT = 256;
 constexpr float LOG2E = 1.4426950408889634f;
 
-// writes (or adds, in float) the scaled accumulators of one row: 4 consecutive columns of every 16
-template <int D>
-__device__ __forceinline__ void store_acc_rows(__bf16 *dst, const f32x4 (&acc)[D / 16], float mul) {
-#pragma unroll
-  for (int db = 0; db < D / 16; db++)
-    *(bf16x4 *)(dst + db * 16) = bf16x4{(__bf16)(acc[db][0] * mul), (__bf16)(acc[db][1] * mul), (__bf16)(acc[db][2] * mul), (__bf16)(acc[db][3] * mul)};
-}
+// adds the scaled accumulators of one row to float values: 4 consecutive columns of every 16
 template <int D>
 __device__ __forceinline__ void add_acc_rows(float *dst, const f32x4 (&acc)[D / 16], float mul) {
 #pragma unroll
@@ -266,10 +260,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 #pragma unroll
   for (int qb = 0; qb < 2; qb++) {
-    if (row[qb] >= t.q_rows) continue;
-    const int64_t at = ((int64_t)t.q_tok0 + row[qb]) * p.dq_stride + (int64_t)h * D + q4;
-    if (p.accumulate) add_acc_rows<D>((float *)p.dq + at, dq_acc[qb], p.scale);
-    else store_acc_rows<D>(p.dq + at, dq_acc[qb], p.scale);
+    const int64_t at = ((int64_t)t.q_tok0 + rb[qb]) * p.dq_stride + (int64_t)h * D;
+    if (!p.accumulate) zp_store_rows<D>(smem + w * ZP_ROWS_LDS, dq_acc[qb], p.scale, p.dq + at, p.dq_stride, t.q_rows - rb[qb], lane);
+    else if (row[qb] < t.q_rows) add_acc_rows<D>((float *)p.dq + at + c16 * p.dq_stride + q4, dq_acc[qb], p.scale);
   }
 }
 
@@ -558,14 +551,14 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 #pragma unroll
   for (int cb = 0; cb < 2; cb++) {
-    if (krow[cb] >= t.k_len) continue;
-    const int64_t at = ((int64_t)t.k_tok0 + krow[cb]) * p.dkv_stride + (int64_t)g * D + q4;
-    if (p.accumulate) {
-      add_acc_rows<D>((float *)p.dk + at, dk_acc[cb], p.scale);
-      add_acc_rows<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
-    } else {
-      store_acc_rows<D>(p.dk + at, dk_acc[cb], p.scale);
-      store_acc_rows<D>(p.dv + at, dv_acc[cb], 1.0f);
+    const int64_t at = ((int64_t)t.k_tok0 + kb[cb]) * p.dkv_stride + (int64_t)g * D;
+    if (!p.accumulate) {
+      char *own = smem + w * ZP_ROWS_LDS;
+      zp_store_rows<D>(own, dk_acc[cb], p.scale, p.dk + at, p.dkv_stride, t.k_len - kb[cb], lane);
+      zp_store_rows<D>(own, dv_acc[cb], 1.0f, p.dv + at, p.dkv_stride, t.k_len - kb[cb], lane);
+    } else if (krow[cb] < t.k_len) {
+      add_acc_rows<D>((float *)p.dk + at + c16 * p.dkv_stride + q4, dk_acc[cb], p.scale);
+      add_acc_rows<D>((float *)p.dv + at + c16 * p.dkv_stride + q4, dv_acc[cb], 1.0f);
     }
   }
 }
@@ -831,14 +824,14 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 #pragma unroll
   for (int cb = 0; cb < 2; cb++) {
-    if (krow[cb] >= t.k_len) continue;
-    const int64_t at = ((int64_t)t.k_tok0 + krow[cb]) * p.dkv_stride + (int64_t)g * D + q4;
-    if (p.accumulate) {
-      add_acc_rows<D>((float *)p.dk + at, dk_acc[cb], p.scale);
-      add_acc_rows<D>((float *)p.dv + at, dv_acc[cb], 1.0f);
-    } else {
-      store_acc_rows<D>(p.dk + at, dk_acc[cb], p.scale);
-      store_acc_rows<D>(p.dv + at, dv_acc[cb], 1.0f);
+    const int64_t at = ((int64_t)t.k_tok0 + kb[cb]) * p.dkv_stride + (int64_t)g * D;
+    if (!p.accumulate) {
+      char *own = smem + w * ZP_ROWS_LDS;
+      zp_store_rows<D>(own, dk_acc[cb], p.scale, p.dk + at, p.dkv_stride, t.k_len - kb[cb], lane);
+      zp_store_rows<D>(own, dv_acc[cb], 1.0f, p.dv + at, p.dkv_stride, t.k_len - kb[cb], lane);
+    } else if (krow[cb] < t.k_len) {
+      add_acc_rows<D>((float *)p.dk + at + c16 * p.dkv_stride + q4, dk_acc[cb], p.scale);
+      add_acc_rows<D>((float *)p.dv + at + c16 * p.dkv_stride + q4, dv_acc[cb], 1.0f);
     }
   }
 }

@@ -254,9 +254,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const float l_tot = zp_quad_sum(l_sum[qb]);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     const float lse = l_tot > 0.f ? (__logf(l_tot) - nm[qb] * 0.6931471805599453f) : -INFINITY;
-    if (row[qb] >= t.q_rows) continue;
     const int64_t orow = (int64_t)t.out_row0 + row[qb];
     if (PARTIAL) {
+      if (row[qb] >= t.q_rows) continue;
       // weights of the running row (w_old) and of this partial (w_new, its 1/l folded in); without update: 0 and 1/l
       float w_old = 0.f, w_new = inv, lse_out = lse;
       if (p.update) {
@@ -284,14 +284,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         *(f32x4 *)(op + db * 16) = v4;
       }
     } else {
-      if (q4 == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse;
-      __bf16 *op = (__bf16 *)p.o + orow * p.o_stride + (int64_t)h * D + q4;
-#pragma unroll
-      for (int db = 0; db < D / 16; db++) {
-        bf16x4 v4 = {(__bf16)(o_acc[qb][db][0] * inv), (__bf16)(o_acc[qb][db][1] * inv),
-                     (__bf16)(o_acc[qb][db][2] * inv), (__bf16)(o_acc[qb][db][3] * inv)};
-        *(bf16x4 *)(op + db * 16) = v4;
-      }
+      if (q4 == 0 && row[qb] < t.q_rows) p.lse[(int64_t)h * p.lse_stride + orow] = lse;
+      zp_store_rows<D>(smem + w * ZP_ROWS_LDS, o_acc[qb], inv, (__bf16 *)p.o + ((int64_t)t.out_row0 + rb[qb]) * p.o_stride + (int64_t)h * D,
+                       p.o_stride, t.q_rows - rb[qb], lane);
     }
   }
 }

@@ -341,6 +341,29 @@ struct zp_lds16 {
   }
 };
 
+// Writes 16 rows of bf16 results held as 16x16x32 MFMA accumulators (lane l: row l%16, columns 16 db + 4 (l/16) ..+3),
+// scaled by mul, to dst, dst + stride, ... (n_valid rows of them). They pass through ZP_ROWS_LDS bytes of LDS of this wave's
+// own, so that a store instruction covers whole rows (16 bytes per lane) instead of 16 rows' pieces of 32 bytes each: a
+// quarter of the cache line accesses. (The pieces kept a workgroup's end busy for about 3 us on short sequences.)
+#define ZP_ROWS_LDS (16 * (256 + 32))
+template <int D>
+__device__ __forceinline__ void zp_store_rows(char *lds, const f32x4 (&acc)[D / 16], float mul, __bf16 *dst, int64_t stride,
+                                              int n_valid, int lane) {
+  constexpr int ROWB = D * 2 + 32, CPR = D / 8, RPI = 64 / CPR;  // 16-byte chunks per row, rows per store instruction
+  ZP_LDS char *w = (ZP_LDS char *)lds + (lane & 15) * ROWB + (lane >> 4) * 8;
+#pragma unroll
+  for (int db = 0; db < D / 16; db++)
+    *(ZP_LDS bf16x4 *)(w + db * 32) = bf16x4{(__bf16)(acc[db][0] * mul), (__bf16)(acc[db][1] * mul), (__bf16)(acc[db][2] * mul),
+                                             (__bf16)(acc[db][3] * mul)};
+  const int r0 = lane / CPR, c = lane % CPR;
+#pragma unroll
+  for (int i = 0; i < 16 / RPI; i++) {
+    const int r = r0 + i * RPI;
+    const bf16x8 v = *(const ZP_LDS bf16x8 *)((const ZP_LDS char *)lds + r * ROWB + c * 16);
+    if (r < n_valid) *(bf16x8 *)(dst + (int64_t)r * stride + c * 8) = v;
+  }
+}
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
 template <class F, int... I>
 __device__ __forceinline__ void zp_static_for_impl(F &&f, std::integer_sequence<int, I...>) {
