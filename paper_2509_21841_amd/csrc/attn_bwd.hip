@@ -18,6 +18,7 @@ struct zp_bwd_params {
   const zp_tile *dq_tiles;
   const zp_tile *kv_tiles;
   int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
+  uint32_t m_hkv, m_grp;  // zp_div_magic of Hkv and grp (set by the launcher)
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;      // outputs (bf16, overwritten) ...
   int64_t dq_stride, dkv_stride;
@@ -116,12 +117,12 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   char *Ks = smem;               // [2][64][D]
   char *Vs = smem + 2 * TILEB;   // [2][64][D]
 
-  const int item = zp_item_of_block(p.work_dq, (int *)(smem + 4 * TILEB));
+  const int item = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_dq, (int *)(smem + 4 * TILEB)));
   if (item < 0) return;
   int unit, hh;
-  zp_block_to_unit(item, p.grp, unit, hh);
+  zp_block_to_unit(item, p.grp, p.m_grp, unit, hh);
   if (unit >= p.n_dq_tiles * p.Hkv) return;
-  const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
   const zp_tile t = ZP_TILE(p.dq_tiles, p.inl, 0, tile_idx);
 
@@ -136,7 +137,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     int n = t.q_pos0 + r - t.k_pos0 + 1;
     return n < 0 ? 0 : (n > t.k_len ? t.k_len : n);
   };
-  const int nvis_lane[2] = {nvis_of(row[0]), nvis_of(row[1])};
+  // rows behind the block's last one repeat it (and are not stored)
+  const int rowc[2] = {min(row[0], t.q_rows - 1), min(row[1], t.q_rows - 1)};
+  const int nvis_lane[2] = {nvis_of(rowc[0]), nvis_of(rowc[1])};
   const int nvis0_min = nvis_of(rb[0]), nvis1_min = nvis_of(rb[1]);
   const int nvis0_max = rb[0] < t.q_rows ? nvis_of(rb[0] + 15) : 0, nvis1_max = rb[1] < t.q_rows ? nvis_of(rb[1] + 15) : 0;
   const int n_kt = (nvis_of(t.q_rows - 1) + 63) / 64;
@@ -151,26 +154,20 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   // after that. The explicit wait before the first barrier covers all of it and tells the compiler that the register
   // operands have arrived (a wait of its own inside the key loop would drain the copies in flight every iteration).
   bf16x8 qreg[2][D / 32], doreg[2][D / 32], oreg[2][D / 32];
-  float lse_nat[2] = {0.f, 0.f};
+  float lse_nat[2];
 #pragma unroll
   for (int qb = 0; qb < 2; qb++) {
-    const int64_t tok = (int64_t)t.q_tok0 + row[qb];
+    const int64_t tok = (int64_t)t.q_tok0 + rowc[qb];
     const __bf16 *qp = p.q + tok * p.q_stride + (int64_t)h * D + 2 * q4;
     const __bf16 *dop = p.dout + tok * p.do_stride + (int64_t)h * D + 2 * q4;
     const __bf16 *op = p.o + tok * p.o_stride + (int64_t)h * D + 2 * q4;
 #pragma unroll
     for (int kk = 0; kk < D / 32; kk++) {
-      if (row[qb] < t.q_rows) {
-        qreg[qb][kk] = *(const bf16x8 *)(qp + 32 * kk);
-        doreg[qb][kk] = *(const bf16x8 *)(dop + 32 * kk);
-        oreg[qb][kk] = *(const bf16x8 *)(op + 32 * kk);
-      } else {
-        qreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        doreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        oreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      }
+      qreg[qb][kk] = *(const bf16x8 *)(qp + 32 * kk);
+      doreg[qb][kk] = *(const bf16x8 *)(dop + 32 * kk);
+      oreg[qb][kk] = *(const bf16x8 *)(op + 32 * kk);
     }
-    if (row[qb] < t.q_rows) lse_nat[qb] = p.lse[(int64_t)h * p.T + tok];
+    lse_nat[qb] = p.lse[(int64_t)h * p.T + tok];
   }
   if (n_kt > 0) {
     kst.issue(Ks, 0, t.k_len);
@@ -406,9 +403,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   float *Ls = (float *)(smem + 2 * NBUF * TILEB);  // [NBUF][64] -LSE / scale
   float *Ds = Ls + NBUF * 64;                   // [NBUF][64] -D
 
-  const int unit = zp_item_of_block(p.work_kv, (int *)(Ds + NBUF * 64));
+  const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ds + NBUF * 64)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
-  const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -422,18 +419,14 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   bf16x8 kreg[2][D / 32], vreg[2][D / 32];
 #pragma unroll
   for (int cb = 0; cb < 2; cb++) {
-    const int64_t ktok = (int64_t)t.k_tok0 + krow[cb];
+    // rows behind the block's last key repeat it: a key column never mixes with another, and those are not stored
+    const int64_t ktok = (int64_t)t.k_tok0 + min(krow[cb], t.k_len - 1);
     const __bf16 *kp = p.k + ktok * p.k_stride + (int64_t)g * D + 2 * q4;
     const __bf16 *vp = p.v + ktok * p.v_stride + (int64_t)g * D + 2 * q4;
 #pragma unroll
     for (int kk = 0; kk < D / 32; kk++) {
-      if (krow[cb] < t.k_len) {
-        kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
-        vreg[cb][kk] = *(const bf16x8 *)(vp + 32 * kk);
-      } else {
-        kreg[cb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        vreg[cb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      }
+      kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
+      vreg[cb][kk] = *(const bf16x8 *)(vp + 32 * kk);
     }
   }
 
@@ -688,9 +681,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   float *Ls = (float *)(Vs + 8 * zp_pad16::R16);   // [2][32] -LSE / scale
   float *Ds = Ls + 2 * QT;                         // [2][32] -D
 
-  const int unit = zp_item_of_block(p.work_kv, (int *)(Ds + 2 * QT));
+  const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ds + 2 * QT)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
-  const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -705,12 +698,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   bf16x8 kreg[2][D / 32];
 #pragma unroll
   for (int cb = 0; cb < 2; cb++) {
-    const __bf16 *kp = p.k + ((int64_t)t.k_tok0 + krow[cb]) * p.k_stride + (int64_t)g * D + 2 * q4;
+    const __bf16 *kp = p.k + ((int64_t)t.k_tok0 + min(krow[cb], t.k_len - 1)) * p.k_stride + (int64_t)g * D + 2 * q4;
 #pragma unroll
-    for (int kk = 0; kk < D / 32; kk++) {
-      if (krow[cb] < t.k_len) kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
-      else kreg[cb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
+    for (int kk = 0; kk < D / 32; kk++) kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
   }
 
   f32x4 dk_acc[2][D / 16], dv_acc[2][D / 16];
@@ -846,6 +836,8 @@ extern "C" int zp_attn_bwd_block_rows(int d, int which) { (void)d; (void)which; 
 extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t stream) {
   zp_bwd_params params = *p_in;
   zp_bwd_params *p = &params;
+  p->m_hkv = zp_div_magic(p->Hkv);
+  p->m_grp = zp_div_magic(p->grp);
   const int dq_units = p->n_dq_tiles * p->Hkv;
   const int kv_units = p->n_kv_tiles * p->Hkv;
   // item numbering padded to a multiple of 8 (one residue per XCD); the kernels drop the padding

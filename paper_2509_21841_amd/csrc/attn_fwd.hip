@@ -140,12 +140,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   char *Ks = smem;                  // [2][BN][D] bf16
   char *Vs = smem + 2 * C::TILEB;   // [2][BN][D] bf16
 
-  const int item = zp_item_of_block(p.work, (int *)(smem + 4 * C::TILEB));
+  const int item = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work, (int *)(smem + 4 * C::TILEB)));
   if (item < 0) return;
   int unit, hh;
-  zp_block_to_unit(item, p.grp, unit, hh);
+  zp_block_to_unit(item, p.grp, p.m_grp, unit, hh);
   if (unit >= p.n_tiles * p.Hkv) return;
-  const int tile_idx = unit / p.Hkv, g = unit - tile_idx * p.Hkv;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
   const zp_tile t = ZP_TILE(p.tiles, p.inl, 0, tile_idx);
 
@@ -161,7 +161,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int n = t.q_pos0 + r - t.k_pos0 + 1;
     return n < 0 ? 0 : (n > t.k_len ? t.k_len : n);
   };
-  const int nvis_lane[2] = {nvis_of(row[0]), nvis_of(row[1])};
+  // rows behind the block's last one repeat it (and are not stored)
+  const int rowc[2] = {min(row[0], t.q_rows - 1), min(row[1], t.q_rows - 1)};
+  const int nvis_lane[2] = {nvis_of(rowc[0]), nvis_of(rowc[1])};
   // fewest and most keys a sub-block's rows see (none if the block ends before it)
   const int nvis0_min = nvis_of(rb[0]), nvis1_min = nvis_of(rb[1]);
   const int nvis0_max = rb[0] < t.q_rows ? nvis_of(rb[0] + 15) : 0, nvis1_max = rb[1] < t.q_rows ? nvis_of(rb[1] + 15) : 0;
@@ -171,12 +173,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   bf16x8 qreg[2][D / 32];
 #pragma unroll
   for (int qb = 0; qb < 2; qb++) {
-    const __bf16 *qp = p.q + (int64_t)(t.q_tok0 + row[qb]) * p.q_stride + (int64_t)h * D + 2 * q4;
+    const __bf16 *qp = p.q + (int64_t)(t.q_tok0 + rowc[qb]) * p.q_stride + (int64_t)h * D + 2 * q4;
 #pragma unroll
-    for (int kk = 0; kk < D / 32; kk++) {
-      if (row[qb] < t.q_rows) qreg[qb][kk] = *(const bf16x8 *)(qp + 32 * kk);
-      else qreg[qb][kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
+    for (int kk = 0; kk < D / 32; kk++) qreg[qb][kk] = *(const bf16x8 *)(qp + 32 * kk);
   }
   // No wait here: the first tile copy is issued right behind these loads so that the two memory latencies of the
   // prologue overlap; the explicit wait in front of the first barrier covers both (and tells the compiler that the
@@ -301,6 +300,7 @@ extern "C" int zp_launch_attn_fwd(const zp_attn_params *p, int d, int partial, i
   const int units = p->n_tiles * p->Hkv;
   if (units == 0) return 0;
   zp_attn_params q = *p;
+  q.m_hkv = zp_div_magic(p->Hkv); q.m_grp = zp_div_magic(p->grp);
   const int grid = zp_plan_work_split(q.work, p->work.counters, ((units + 7) / 8) * 8 * p->grp);
   p = &q;
   (void)block_rows;

@@ -32,6 +32,7 @@ struct zp_bwd_params {
   const zp_tile *dq_tiles;
   const zp_tile *kv_tiles;
   int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
+  uint32_t m_hkv, m_grp;
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;
   int64_t dq_stride, dkv_stride;

@@ -29,17 +29,30 @@ struct zp_tile {
   int32_t aux;       // kernel specific
 };
 
+// n / d for a wave-uniform n (any 32-bit value) on the scalar unit; m = zp_div_magic(d). The estimate falls short by one at
+// most. (The compiler's division runs on the vector unit: some 30 dependent instructions in front of the tile record.)
+inline uint32_t zp_div_magic(uint32_t d) { return 0xffffffffu / d; }
+__device__ __forceinline__ int zp_udiv(int n, int d, uint32_t m) {
+  const uint32_t q = __umulhi((uint32_t)n, m);
+  return (int)((uint32_t)n - q * (uint32_t)d >= (uint32_t)d ? q + 1 : q);
+}
+
 // The tile record of a workgroup in scalar registers (it is the same for all its lanes, which the compiler cannot know
-// where the item was claimed at run time: the tile copies' address arithmetic would run on the vector unit).
-__device__ __forceinline__ zp_tile zp_load_tile(const zp_tile *p) {
+// where the item was claimed at run time: the record would come through the vector memory path and the tile copies'
+// address arithmetic run on the vector unit). Tables are written before the kernel starts.
+template <class P>
+__device__ __forceinline__ zp_tile zp_load_tile(P p) {
   zp_tile t;
 #define ZP_U(f) t.f = __builtin_amdgcn_readfirstlane(p->f)
   ZP_U(q_tok0); ZP_U(q_rows); ZP_U(q_pos0); ZP_U(k_tok0); ZP_U(k_len); ZP_U(k_pos0); ZP_U(out_row0); ZP_U(aux);
 #undef ZP_U
   return t;
 }
-// `idx` of the table in device memory, or of the launch arguments (from `first` on) if there is none
-#define ZP_TILE(tiles, inl, first, idx) ((tiles) ? zp_load_tile((tiles) + (idx)) : zp_load_tile((inl).t + (first) + (idx)))
+// `idx` of the table in device memory (read through the scalar cache), or of the launch arguments (from `first` on) if
+// there is none
+#define ZP_TILE(tiles, inl, first, idx)                                                                            \
+  ((tiles) ? zp_load_tile((const __attribute__((address_space(4))) zp_tile *)(uintptr_t)(tiles) + (idx))           \
+           : zp_load_tile((inl).t + (first) + (idx)))
 
 // A launch's tile table where it is short: in the launch arguments themselves (4 KB at most in all), so that nothing is
 // uploaded in front of the launch.
@@ -82,7 +95,7 @@ inline int zp_plan_work_split(zp_work_split &ws, int32_t *counters, int n_items)
 // of the workgroup must call it (it holds a barrier for the workgroups that claim).
 __device__ __forceinline__ int zp_item_of_block(const zp_work_split &ws, int *slot) {
   const int b = blockIdx.x;
-  if (b < ws.n_static) return b;
+  if (b < ws.n_static) return __builtin_amdgcn_readfirstlane(b);
   if (threadIdx.x == 0) {
     const int per = (ws.n_items - ws.n_static) >> 3, x = b & 7;
     int item = -1;
@@ -103,6 +116,7 @@ struct zp_attn_params {
   int64_t q_stride, k_stride, v_stride;
   const zp_tile *tiles;
   int32_t n_tiles, Hq, Hkv, grp;
+  uint32_t m_hkv, m_grp;  // zp_div_magic of Hkv and grp (set by the launcher)
   float scale_log2;  // scale * log2(e)
   float scale;
   void *o;           // bf16 [.][Hq][d] (whole) or float [part_rows][Hq][d] (partial)
@@ -117,10 +131,10 @@ struct zp_attn_params {
 // blockIdx -> (unit, head-in-group). Workgroups are dealt to the 8 XCDs round-robin by blockIdx, so
 // units (tile, kv head) are dealt round-robin too -- the cost-sorted list stays balanced across XCDs --
 // while the grp query heads of one unit get consecutive slots on the SAME XCD and share K/V in its L2.
-__device__ __forceinline__ void zp_block_to_unit(int bid, int grp, int &unit, int &hh) {
-  int x = bid & 7, y = bid >> 3;
-  hh = y % grp;
-  unit = (y / grp) * 8 + x;
+__device__ __forceinline__ void zp_block_to_unit(int bid, int grp, uint32_t m_grp, int &unit, int &hh) {
+  const int x = bid & 7, y = bid >> 3, yq = zp_udiv(y, grp, m_grp);
+  hh = y - yq * grp;
+  unit = yq * 8 + x;
 }
 
 __device__ __forceinline__ float zp_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
