@@ -678,10 +678,11 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   char *Qs = smem;                                 // [2][2][32][D]: two buffers (three would not fit two workgroups per
                                                    // CU) of a tile's Q rows and, behind them, its dO rows
   char *Vs = smem + 4 * TILEB;                     // [128][D]: the workgroup's V rows, staged once
-  float *Ls = (float *)(Vs + 8 * zp_pad16::R16);   // [2][32] -LSE / scale
-  float *Ds = Ls + 2 * QT;                         // [2][32] -D
+  // [2][2][64]: a tile's 32 values of -LSE / scale and, behind them, of -D (the copies write 64 floats, the upper half
+  // of no use: no lane mask to set up)
+  float *Ls = (float *)(Vs + 8 * zp_pad16::R16);
 
-  const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ds + 2 * QT)));
+  const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ls + 4 * 64)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
@@ -725,12 +726,6 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     vst.issue(Vs + 4 * zp_pad16::R16, 64, t.k_len);
   }
   const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
-  // 32 floats of a row vector, one per lane of the lower half-wave (rows past the last valid one repeat it)
-  auto stage_f32x32 = [&](float *dst, const float *src, int first, int last_valid) {
-    int i = first + (lane & 31);
-    if (i > last_valid) i = last_valid;
-    if (lane < 32) zp_dma4(src + i, __builtin_amdgcn_readfirstlane(zp_lds_addr(dst)));
-  };
   int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
   auto staged = [&] { if (++st_hh == p.grp) { st_hh = 0; st_qt--; } };
   auto stage = [&](int buf) {
@@ -738,16 +733,18 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int h = g * p.grp + hh;
     qst.issue(Qs + 2 * buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
     ost.issue(Qs + (2 * buf + 1) * TILEB, i0, t.q_rows, (int64_t)hh * D);
-    const int64_t base = (int64_t)h * p.T + t.q_tok0;
-    stage_f32x32(Ls + buf * QT, p.lse2 + base, i0, t.q_rows - 1);
-    stage_f32x32(Ds + buf * QT, p.dvec + base, i0, t.q_rows - 1);
+    // waves 0 and 2 fetch the one row vector, 1 and 3 the other
+    int r = i0 + (lane & 31);
+    if (r > t.q_rows - 1) r = t.q_rows - 1;
+    zp_dma4((qst.w & 1 ? p.dvec : p.lse2) + (int64_t)h * p.T + t.q_tok0 + r,
+            __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + buf * 512 + (qst.w & 1) * 256));
   };
   // the same copies for a tile of 32 valid rows, one per step of the S run but the first
-  const void *pc_q, *pc_o, *pc_l, *pc_d;
+  const void *pc_q, *pc_o, *pc_s;
   unsigned pc_buf = 0;
   auto stage_piece = [&](auto n) {
     constexpr int N = decltype(n)::value;
-    static_assert(2 * PW + 3 <= D / 16, "the copies of a tile fit the steps of one chain");
+    static_assert(2 * PW + 2 <= D / 16, "the copies of a tile fit the steps of one chain");
     if constexpr (N == 0) {
       return;
     } else if constexpr (N <= PW) {
@@ -755,9 +752,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     } else if constexpr (N <= 2 * PW) {
       zp_dma16_so(pc_o, ost.off[N - PW - 1], __builtin_amdgcn_readfirstlane(zp_lds_addr(Qs) + (2 * pc_buf + 1) * TILEB + ost.dest(N - PW - 1)));
     } else if constexpr (N == 2 * PW + 1) {
-      if (lane < 32) zp_dma4_so(pc_l, lane * 4, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + pc_buf * (QT * 4)));
-    } else if constexpr (N == 2 * PW + 2) {
-      if (lane < 32) zp_dma4_so(pc_d, lane * 4, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ds) + pc_buf * (QT * 4)));
+      zp_dma4_so(pc_s, (lane & 31) * 4, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + pc_buf * 512 + (qst.w & 1) * 256));
     }
   };
   auto no_piece = [](auto) {};
@@ -769,7 +764,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
   const int k0_min = t.k_pos0 + kb[0], k1_min = t.k_pos0 + kb[1];  // first positions of the sub-blocks
   const int qpos_end = t.q_pos0 + t.q_rows, qpos_end_l = qpos_end - q4;
-  constexpr int D_OFF = 2 * QT * 4;
+  constexpr int D_OFF = 256;
 
   int cur_qt = n_qt - 1, cur_hh = 0;
   // one tile out of buffer BUF (compile-time, so that every LDS address is a register plus an immediate)
@@ -792,16 +787,15 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       pc_q = zp_uniform_ptr(qst.base + (int64_t)i0n * qst.stride + (int64_t)st_hh * D);
       pc_o = zp_uniform_ptr(ost.base + (int64_t)i0n * ost.stride + (int64_t)st_hh * D);
       const int64_t base = (int64_t)(g * p.grp + st_hh) * p.T + t.q_tok0 + i0n;
-      pc_l = zp_uniform_ptr(p.lse2 + base);
-      pc_d = zp_uniform_ptr(p.dvec + base);
+      pc_s = zp_uniform_ptr((qst.w & 1 ? p.dvec : p.lse2) + base);
     }
     if (fetch && !fused) stage(buf ^ 1);
     if (act1) {
-      if (masked) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, false, false>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
-      else if (fused) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, true>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
-      else dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, false>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      if (masked) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      else if (fused) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, true>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
+      else dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     } else if (act0) {
-      dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, true, false>(seed + buf * (QT * 4), kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, true, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     }
     staged();
     zp_wait_async();
@@ -854,7 +848,7 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   }
   if (kv_units > 0) {
     zp_prof_begin("attn_bwd_dkdv", stream);
-    if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16::R16 + 4 * 32 * 4 + 16, stream, *p);
+    if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16::R16 + 4 * 64 * 4 + 16, stream, *p);
     else hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
     zp_prof_end(stream);
     hipError_t e = hipGetLastError();
