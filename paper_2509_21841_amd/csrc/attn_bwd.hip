@@ -109,9 +109,10 @@ __device__ __forceinline__ void dq_half(int Kb, int Vb, int half, const bf16x8 (
 // Two waves per SIMD (two workgroups of four waves per CU, 64 KB of LDS each). An MFMA takes about 20 cycles of the
 // issuing wave's vector issue time, and a wave issues its LDS, scalar and wait instructions one after the other as
 // well; with a second wave on the SIMD all of that runs under the other wave's MFMAs. Working through a tile in two
-// 32-key halves keeps the wave within the 256 registers this needs.
+// 32-key halves keeps the wave within the 256 registers this needs. Three at head dimension 64 (168 registers, 32 KB of
+// LDS): 8 sequences of 4096 tokens, GQA 32/8, 761 us with two and 713 with three; 64 x 1K MHA 561 and 481.
 template <int D>
-__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(zp_bwd_params p) {
+__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2))) void attn_bwd_dq_kernel(zp_bwd_params p) {
   constexpr int TILEB = 64 * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char *Ks = smem;               // [2][64][D]
@@ -564,7 +565,7 @@ struct dkdv_lds_addr {
   __device__ __forceinline__ void init(int lane, const char *tiles, const char *v0, const char *v1) {
 #pragma unroll
     for (int par = 0; par < 2; par++) {
-      const int r = zp_pad16::row_part(lane, par);
+      const int r = zp_pad16<128>::row_part(lane, par);
       row[par] = zp_lds_addr(tiles) + r;
       v[0][par] = zp_lds_addr(v0) + r;
       v[1][par] = zp_lds_addr(v1) + r;
@@ -572,13 +573,13 @@ struct dkdv_lds_addr {
     }
 #pragma unroll
     for (int dq = 0; dq < 4; dq++) {
-      tr[dq] = zp_lds_addr(tiles) + zp_pad16::tr_part(lane, dq);
+      tr[dq] = zp_lds_addr(tiles) + zp_pad16<128>::tr_part(lane, dq);
       asm volatile("" : "+v"(tr[dq]));
     }
   }
   // off: byte offset of the tile from the first buffer; rb: 16 rows; k: k-step; db: 16 columns
   __device__ __forceinline__ bf16x8 rows(int off, int rb, int k) const {
-    return *(const ZP_LDS bf16x8 *)(unsigned long long)(row[k & 1] + off + rb * zp_pad16::R16 + (k >> 1) * 128);
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(row[k & 1] + off + rb * zp_pad16<128>::R16 + (k >> 1) * 128);
   }
   __device__ __forceinline__ bf16x8 vrows(int cb, int k) const {
     return *(const ZP_LDS bf16x8 *)(unsigned long long)(v[cb][k & 1] + (k >> 1) * 128);
@@ -586,7 +587,7 @@ struct dkdv_lds_addr {
   __device__ __forceinline__ bf16x8 cols(int off, int db) const {
     const unsigned o = tr[db & 3] + off + (db >> 2) * 128;
     s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)o);
-    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + zp_pad16::R16));
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + zp_pad16<128>::R16));
     return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
   }
 };
@@ -671,7 +672,7 @@ __device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2
 // every LDS read (32 to the 64 vector operations a tile needs) this one took 24.7.
 __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv128_kernel(zp_bwd_params p) {
   constexpr int D = 128, QT = 32;
-  constexpr int TILEB = 2 * zp_pad16::R16;         // a staged tile: 32 query rows
+  constexpr int TILEB = 2 * zp_pad16<128>::R16;         // a staged tile: 32 query rows
   typedef zp_stager<D, 8, true> stager;               // 4 waves x 2 wave-loads = the first 32 rows of its 64-row pattern
   constexpr int PW = stager::PER_WAVE;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -680,7 +681,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   char *Vs = smem + 4 * TILEB;                     // [128][D]: the workgroup's V rows, staged once
   // [2][2][64]: a tile's 32 values of -LSE / scale and, behind them, of -D (the copies write 64 floats, the upper half
   // of no use: no lane mask to set up)
-  float *Ls = (float *)(Vs + 8 * zp_pad16::R16);
+  float *Ls = (float *)(Vs + 8 * zp_pad16<128>::R16);
 
   const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ls + 4 * 64)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
@@ -718,12 +719,12 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
   ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, tid);
   dkdv_lds_addr la;
-  la.init(lane, smem, Vs + kb[0] / 16 * zp_pad16::R16, Vs + kb[1] / 16 * zp_pad16::R16);
+  la.init(lane, smem, Vs + kb[0] / 16 * zp_pad16<128>::R16, Vs + kb[1] / 16 * zp_pad16<128>::R16);
   {
     zp_stager<D, 4, true> vst;
     vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
     vst.issue(Vs, 0, t.k_len);
-    vst.issue(Vs + 4 * zp_pad16::R16, 64, t.k_len);
+    vst.issue(Vs + 4 * zp_pad16<128>::R16, 64, t.k_len);
   }
   const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
   int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
@@ -848,7 +849,7 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   }
   if (kv_units > 0) {
     zp_prof_begin("attn_bwd_dkdv", stream);
-    if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16::R16 + 4 * 64 * 4 + 16, stream, *p);
+    if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16<128>::R16 + 4 * 64 * 4 + 16, stream, *p);
     else hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
     zp_prof_end(stream);
     hipError_t e = hipGetLastError();

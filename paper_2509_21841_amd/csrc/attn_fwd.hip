@@ -132,8 +132,10 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Two workgroups per CU at head dimension 128 (64 KB of LDS, up to 256 registers), three at 64 (32 KB, up to 168: 8
+// sequences of 4096 tokens, GQA 32/8: 631 us with two, 568 with three; a fourth does not fit the registers).
 template <int D, int NW, bool PARTIAL>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(zp_attn_params p) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2))) void attn_fwd_kernel(zp_attn_params p) {
   using C = FwdCfg<D, NW>;
   static_assert(NW == 4, "the tile stager is laid out for four waves");
   extern __shared__ __attribute__((aligned(16))) char smem[];

@@ -180,25 +180,31 @@ __device__ __forceinline__ int zp_swz16_mask(int row) {
   return (x << 2) | (row & 2) | r3;
 }
 
-// The same bank pattern at D = 128 with the highest bit of the XOR turned into padding between groups of four rows
-// (asynchronous copies write 1 KB, four rows, at a time and can put each anywhere): the chunk index is XORed with r1 r0
-// r3 only, groups 1 and 2 of every four lie 128 bytes further. Read addresses of k-steps two apart and of 16-column
-// blocks four apart then differ by a constant instead of an XOR, so that two and four registers per lane
-// (zp_pad16::row_part, tr_part) and immediate offsets reach everything.
+// The same bank pattern with the highest bit of the XOR turned into padding at D = 128: the chunk index is XORed with
+// r1 r0 r3 only, and groups 1 and 2 of every four groups of four rows lie 128 bytes further (asynchronous copies write
+// 1 KB, four rows, at a time and can put each anywhere). Read addresses of k-steps two apart and of 16-column blocks
+// four apart then differ by a constant instead of an XOR, so that two and four registers per lane (row_part, tr_part)
+// and immediate offsets reach everything. At D = 64 that many k-steps and blocks is all there are: zp_swz16 as it is.
+template <int D>
 struct zp_pad16 {
-  static constexpr int R16 = 4096 + 256;  // bytes of 16 rows
-  __device__ __forceinline__ static int mask(int row) { return ((row & 3) << 1) | ((row >> 3) & 1); }
-  // offset of the g-th group of four rows
-  __device__ __forceinline__ static int group(int g) { return (g >> 2) * R16 + (g & 3) * 1024 + (((g & 3) + 1) >> 1) * 128; }
+  static constexpr int ROWB = 2 * D, R16 = D == 128 ? 4096 + 256 : 2048;  // bytes of a row and of 16 rows
+  __device__ __forceinline__ static int mask(int row) {
+    return D == 128 ? ((row & 3) << 1) | ((row >> 3) & 1) : zp_swz16_mask<64>(row);
+  }
+  // offset of the g-th KB of rows (D = 128: four, 64: eight)
+  __device__ __forceinline__ static int group(int g) {
+    return D == 128 ? (g >> 2) * R16 + (g & 3) * 1024 + (((g & 3) + 1) >> 1) * 128 : g * 1024;
+  }
+  __device__ __forceinline__ static int row(int r) { return D == 128 ? group(r >> 2) + (r & 3) * 256 : r * ROWB; }
   // row operand of k-steps of parity `par` (k-step k: + k / 2 * 128), rows of the first 16
   __device__ __forceinline__ static int row_part(int lane, int par) {
     const int r = lane & 15, q = lane >> 4;
-    return group(r >> 2) + (r & 3) * 256 + (((4 * par + q) ^ mask(r)) << 4);
+    return row(r) + (((4 * par + q) ^ mask(r)) << 4);
   }
   // transposed operand of 16-column blocks db with db % 4 == dq (db: + db / 4 * 128), first 16 rows (see zp_lds16::tr_at)
   __device__ __forceinline__ static int tr_part(int lane, int dq) {
     const int i = lane & 15, r = 4 * (lane >> 4) + (i >> 2);
-    return group(r >> 2) + (r & 3) * 256 + (((2 * dq + ((i >> 1) & 1)) ^ mask(r)) << 4) + ((i & 1) << 3);
+    return row(r) + (((2 * dq + ((i >> 1) & 1)) ^ mask(r)) << 4) + ((i & 1) << 3);
   }
 };
 
@@ -258,7 +264,7 @@ __device__ __forceinline__ const void *zp_uniform_ptr(const void *p) {
 // out once (they carry the LDS swizzle); issuing a tile is then scalar address arithmetic plus the loads.
 // `init` takes the tensor base of the row run and the token stride (64 * stride * 2 bytes must fit 32 bits);
 // `issue` copies rows row0 .. row0+63 (rows past rows_total clamp to the last valid row).
-// PAD: LDS layout of the tile, zp_pad16 (D = 128 only) instead of zp_swz16.
+// PAD: LDS layout of the tile, zp_pad16 instead of zp_swz16.
 template <int D, int NW = 4, bool PAD = false>
 struct zp_stager {
   static constexpr int PER_WAVE = 64 * D * 2 / 1024 / NW;  // 1 KiB wave-loads per wave (NW = 4: the four waves share a 64-row tile; NW = 8: they cover its first 32 rows)
@@ -269,12 +275,11 @@ struct zp_stager {
   int w, lane;
   __device__ __forceinline__ static void row_chunk(int blk, int lane, int &r, int &c) {
     r = D == 128 ? blk * 4 + (lane >> 4) : blk * 8 + (lane >> 3);
-    c = (lane & (D / 8 - 1)) ^ (PAD ? zp_pad16::mask(r) : zp_swz16_mask<D>(r));
+    c = (lane & (D / 8 - 1)) ^ (PAD ? zp_pad16<D>::mask(r) : zp_swz16_mask<D>(r));
   }
   // where in the LDS tile this wave's n-th load goes
   __device__ __forceinline__ int dest(int n) const {
-    static_assert(!PAD || D == 128, "");
-    return PAD ? zp_pad16::group(w * PER_WAVE + n) : (w * PER_WAVE + n) * 1024;
+    return PAD ? zp_pad16<D>::group(w * PER_WAVE + n) : (w * PER_WAVE + n) * 1024;
   }
   __device__ __forceinline__ void init(const __bf16 *gbase, int64_t tok_stride, int tid) {
     lane = tid & 63;
