@@ -22,6 +22,7 @@ struct zp_bwd_params {
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;      // outputs (bf16, overwritten) ...
   int64_t dq_stride, dkv_stride;
+  int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
   zp_work_split work_dq, work_kv;  // work hand-out of the two launches (counters set by the C ABI, the rest by the launcher)
   zp_inline_tiles inl;  // the dQ tiles and, behind them, the dK/dV tiles if dq_tiles and kv_tiles are null
@@ -560,12 +561,14 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // ---------------------------------------------------------------------------- dK, dV at head dimension 128
 // A lane's LDS read addresses in the zp_pad16 layout: of the Q and dO tiles (relative to the first buffer; everything
 // else is an immediate offset) and of the wave's V rows.
+template <int D>
 struct dkdv_lds_addr {
+  typedef zp_pad16<D> L;
   unsigned row[2], tr[4], v[2][2];
   __device__ __forceinline__ void init(int lane, const char *tiles, const char *v0, const char *v1) {
 #pragma unroll
     for (int par = 0; par < 2; par++) {
-      const int r = zp_pad16<128>::row_part(lane, par);
+      const int r = L::row_part(lane, par);
       row[par] = zp_lds_addr(tiles) + r;
       v[0][par] = zp_lds_addr(v0) + r;
       v[1][par] = zp_lds_addr(v1) + r;
@@ -573,13 +576,13 @@ struct dkdv_lds_addr {
     }
 #pragma unroll
     for (int dq = 0; dq < 4; dq++) {
-      tr[dq] = zp_lds_addr(tiles) + zp_pad16<128>::tr_part(lane, dq);
+      tr[dq] = zp_lds_addr(tiles) + L::tr_part(lane, dq);
       asm volatile("" : "+v"(tr[dq]));
     }
   }
   // off: byte offset of the tile from the first buffer; rb: 16 rows; k: k-step; db: 16 columns
   __device__ __forceinline__ bf16x8 rows(int off, int rb, int k) const {
-    return *(const ZP_LDS bf16x8 *)(unsigned long long)(row[k & 1] + off + rb * zp_pad16<128>::R16 + (k >> 1) * 128);
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(row[k & 1] + off + rb * L::R16 + (k >> 1) * 128);
   }
   __device__ __forceinline__ bf16x8 vrows(int cb, int k) const {
     return *(const ZP_LDS bf16x8 *)(unsigned long long)(v[cb][k & 1] + (k >> 1) * 128);
@@ -587,29 +590,29 @@ struct dkdv_lds_addr {
   __device__ __forceinline__ bf16x8 cols(int off, int db) const {
     const unsigned o = tr[db & 3] + off + (db >> 2) * 128;
     s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)o);
-    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + zp_pad16<128>::R16));
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + L::R16));
     return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
   }
 };
 
-// One 32-query tile. Four runs of eight steps of one LDS operand (the dP run: one of dO, and both of V every second step)
+// One 32-query tile. Four runs of D / 16 steps of one LDS operand (the dP run: one of dO, and both of V every second step)
 // and two MFMAs -- S, dP, dV^T, dK^T -- each a fenced pipeline with its operands two steps ahead; the last two steps of
 // a run request the first operands of the next one. One run at a time keeps the operands in flight within 28 registers
 // (all four streams two steps ahead would not fit beside the accumulators). Q_OFF, O_OFF: byte offsets of the tile's Q and
 // dO rows; seed: LDS address of its -LSE/scale plus the lane's floats, -D is D_OFF bytes behind. ONLY0: no query of the
 // tile sees a key of sub-block 1.
-template <int Q_OFF, int O_OFF, int D_OFF, bool MASK, bool ONLY0, bool PIECES, class Piece>
-__device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2][4], f32x4 (&dk_acc)[2][8],
-                                           f32x4 (&dv_acc)[2][8], int qpos0, const int (&kpos)[2], int qpos_end,
-                                           float c_log2, const dkdv_lds_addr &la, Piece &&piece) {
-  constexpr int N = 8, CB = ONLY0 ? 1 : 2;
+template <int D, int Q_OFF, int O_OFF, int D_OFF, bool MASK, bool ONLY0, bool PIECES, class Piece>
+__device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2][D / 32], f32x4 (&dk_acc)[2][D / 16],
+                                           f32x4 (&dv_acc)[2][D / 16], int qpos0, const int (&kpos)[2], int qpos_end,
+                                           float c_log2, const dkdv_lds_addr<D> &la, Piece &&piece) {
+  constexpr int N = D / 16, KK = D / 32, CB = ONLY0 ? 1 : 2;
   f32x4 s[2][2], dp[2][2], ls[2], ds[2];
 #pragma unroll
   for (int rb = 0; rb < 2; rb++) {  // -LSE/scale and -D of the 4 query rows this lane holds of each 16
     ls[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + rb * 64);
     ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + rb * 64);
   }
-  bf16x8 x[N], y[N], v[4][2], xo[N], yo[N];  // step i: 16 rows i % 2, k-step i / 2 (S, dP); 16 columns i (dV^T, dK^T)
+  bf16x8 x[N], y[N], v[KK][2], xo[N], yo[N];  // step i: 16 rows i % 2, k-step i / 2 (S, dP); 16 columns i (dV^T, dK^T)
   auto load_v = [&](int k) {
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) v[k][cb] = la.vrows(cb, k);
@@ -632,7 +635,7 @@ __device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2
     for (int cb = 0; cb < CB; cb++) dp[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[i], v[k][cb], k == 0 ? ds[rb] : dp[rb][cb], 0, 0, 0);
     if constexpr (i + 2 < N) y[i + 2] = la.rows(O_OFF, i % 2, k + 1);
     else xo[i + 2 - N] = la.cols(O_OFF, i + 2 - N);
-    if constexpr (rb == 0 && k + 1 < 4) load_v(k + 1);
+    if constexpr (rb == 0 && k + 1 < KK) load_v(k + 1);
   });
   __builtin_amdgcn_sched_barrier(0);
   unsigned ppk[2][4], dpk[2][4];
@@ -718,7 +721,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   stager qst, ost;
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
   ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, tid);
-  dkdv_lds_addr la;
+  dkdv_lds_addr<D> la;
   la.init(lane, smem, Vs + kb[0] / 16 * zp_pad16<128>::R16, Vs + kb[1] / 16 * zp_pad16<128>::R16);
   {
     zp_stager<D, 4, true> vst;
@@ -792,11 +795,11 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     if (fetch && !fused) stage(buf ^ 1);
     if (act1) {
-      if (masked) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
-      else if (fused) dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, true>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
-      else dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      if (masked) dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      else if (fused) dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, true>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
+      else dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, false, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     } else if (act0) {
-      dkdv_block<2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, true, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, D_OFF, true, true, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     }
     staged();
     zp_wait_async();
@@ -819,6 +822,148 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       add_acc_rows<D>((float *)p.dv + at + c16 * p.dkv_stride + q4, dv_acc[cb], 1.0f);
     }
   }
+}
+
+// dK, dV of a launch that leaves most of the chip idle: a workgroup owns 32 key rows instead of 128 and its four waves go
+// through the (query tile, head) iterations by turns, each with staging buffers of its own (145 KB of LDS in all at
+// D = 128) and no barrier in the loop; their accumulators are added up at the end, through LDS, in wave order. Four times
+// the workgroups, a quarter of the serial chain. 1218 tokens, GQA 4/2, d = 128: 32 us with 128 key rows per workgroup
+// (22 iterations one after the other on 32 of 256 CUs), 17 us with 32. See dkdv_is_chain_bound for when it is used.
+template <int D>
+__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
+  constexpr int QT = 32;
+  typedef zp_pad16<D> L;
+  constexpr int TILEB = 2 * L::R16;                // a staged tile: 32 query rows
+  constexpr int OWN = 4 * TILEB + 1024;            // a wave's LDS: two buffers of Q and dO rows, two of row vectors
+  constexpr int LOADS = 2 * (64 * D / 1024) + 2;   // copies of one tile
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  char *own = smem + w * OWN;
+  char *Vs = smem + 4 * OWN;                       // [32][D]: the workgroup's V rows
+  float *Ls = (float *)(own + 4 * TILEB);          // [2][2][64]: see attn_bwd_dkdv128_kernel
+
+  // the four workgroups of a key block on one XCD
+  const int x = blockIdx.x & 7, y = blockIdx.x >> 3, part = y & 3, unit = (y >> 2) * 8 + x;
+  if (unit >= p.n_kv_tiles * p.Hkv) return;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
+  const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
+  const int kb[2] = {32 * part, 32 * part + 16};
+  if (kb[0] >= t.k_len) return;
+
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  const int krow[2] = {kb[0] + c16, kb[1] + c16};
+  const int kpos[2] = {t.k_pos0 + krow[0] - q4, t.k_pos0 + krow[1] - q4};
+
+  // K operands in registers, V operands from LDS (rows behind the last key repeat it, see attn_bwd_dkdv128_kernel)
+  bf16x8 kreg[2][D / 32];
+#pragma unroll
+  for (int cb = 0; cb < 2; cb++) {
+    const __bf16 *kp = p.k + ((int64_t)t.k_tok0 + min(krow[cb], t.k_len - 1)) * p.k_stride + (int64_t)g * D + 2 * q4;
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
+  }
+  f32x4 acc[4][D / 16];  // dK of the two sub-blocks, dV of the two
+#pragma unroll
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) acc[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4(&dk_acc)[2][D / 16] = *(f32x4(*)[2][D / 16]) & acc[0];
+  f32x4(&dv_acc)[2][D / 16] = *(f32x4(*)[2][D / 16]) & acc[2];
+
+  // iterations: query tiles outermost (last tile first), heads of the group innermost; this wave's are w, w + 4, ...
+  const int n_qt = (t.q_rows + QT - 1) / QT, n_it = n_qt * p.grp;
+  {
+    zp_stager<D, 8, true> vst;  // 4 waves x its loads = the first 32 rows of its 64-row pattern
+    vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
+    vst.issue(Vs, kb[0], t.k_len);
+  }
+  zp_stager<D, 2, true> qst, ost;  // one wave copies a tile by itself: the first of the two waves of a 64-row pattern
+  qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, lane);
+  ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, lane);
+  dkdv_lds_addr<D> la;
+  la.init(lane, own, Vs, Vs + L::R16);
+  auto stage = [&](int it, int buf) {
+    const int qi = zp_udiv(it, p.grp, p.m_grp), hh = it - qi * p.grp, i0 = (n_qt - 1 - qi) * QT;
+    qst.issue(own + 2 * buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
+    ost.issue(own + (2 * buf + 1) * TILEB, i0, t.q_rows, (int64_t)hh * D);
+    int r = i0 + (lane & 31);
+    if (r > t.q_rows - 1) r = t.q_rows - 1;
+    const int64_t at = (int64_t)(g * p.grp + hh) * p.T + t.q_tok0 + r;
+    const unsigned l0 = __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + buf * 512);
+    zp_dma4(p.lse2 + at, l0);
+    zp_dma4(p.dvec + at, l0 + 256);
+  };
+  const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
+  const int k0_min = t.k_pos0 + kb[0], k1_min = t.k_pos0 + kb[1];
+  const int qpos_end = t.q_pos0 + t.q_rows, qpos_end_l = qpos_end - q4;
+  const float c_log2 = p.scale_log2;
+  auto no_piece = [](auto) {};
+
+  if (w < n_it) stage(w, 0);
+  zp_wait_async();
+  __syncthreads();  // the V rows are there
+
+  auto query_tile = [&](int it, auto BUF) {
+    constexpr int buf = decltype(BUF)::value;
+    const int qpos0 = t.q_pos0 + (n_qt - 1 - zp_udiv(it, p.grp, p.m_grp)) * QT;
+    if (it + 4 < n_it) {
+      stage(it + 4, buf ^ 1);
+      zp_wait_async_upto<LOADS>();  // this tile's copies, issued before those
+    } else {
+      zp_wait_async();
+    }
+    asm volatile("" ::: "memory");  // no read of the tile moves up here
+    __builtin_amdgcn_sched_barrier(0);
+    const bool act0 = qpos0 + QT - 1 >= k0_min, act1 = qpos0 + QT - 1 >= k1_min && kb[1] < t.k_len;
+    const bool masked = qpos0 < (act1 ? k1_min : k0_min) + 15 || qpos0 + QT > qpos_end;
+    if (act1) {
+      if (masked) dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      else dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+    } else if (act0) {
+      dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true, true, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+    }
+    // the buffer is written again behind this point: every read of it has to have returned
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int it = w; it < n_it; it += 8) {
+    query_tile(it, std::integral_constant<int, 0>{});
+    if (it + 4 < n_it) query_tile(it + 4, std::integral_constant<int, 1>{});
+  }
+
+  // add up the four waves' accumulators: wave a does accumulator a (dK, dK, dV, dV of sub-blocks 0, 1, 0, 1)
+  constexpr int ACCB = (D / 16) * 64 * 16;  // bytes of one accumulator of one wave
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) *(ZP_LDS f32x4 *)((ZP_LDS char *)smem + (w * 4 + a) * ACCB + (i * 64 + lane) * 16) = acc[a][i];
+  __syncthreads();
+  f32x4 sum[D / 16];
+#pragma unroll
+  for (int i = 0; i < D / 16; i++) {
+    sum[i] = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)smem + w * ACCB + (i * 64 + lane) * 16);
+#pragma unroll
+    for (int o = 1; o < 4; o++) {
+      const f32x4 v = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)smem + (o * 4 + w) * ACCB + (i * 64 + lane) * 16);
+      sum[i][0] += v[0]; sum[i][1] += v[1]; sum[i][2] += v[2]; sum[i][3] += v[3];
+    }
+  }
+  __syncthreads();  // the rows pass through LDS on their way out
+  const int cb = w & 1;
+  const float mul = w < 2 ? p.scale : 1.0f;
+  __bf16 *out = w < 2 ? p.dk : p.dv;
+  const int64_t at = ((int64_t)t.k_tok0 + kb[cb]) * p.dkv_stride + (int64_t)g * D;
+  if (!p.accumulate) zp_store_rows<D>(smem + w * ZP_ROWS_LDS, sum, mul, out + at, p.dkv_stride, t.k_len - kb[cb], lane);
+  else if (kb[cb] + c16 < t.k_len) add_acc_rows<D>((float *)out + at + c16 * p.dkv_stride + q4, sum, mul);
+}
+
+template <int D>
+constexpr size_t split_lds() {
+  constexpr size_t R16 = zp_pad16<D>::R16, loop = 4 * (8 * R16 + 1024) + 2 * R16, end = 16 * (D / 16) * 64 * 16;
+  return loop > end ? loop : end;
 }
 
 }  // namespace
@@ -849,7 +994,11 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   }
   if (kv_units > 0) {
     zp_prof_begin("attn_bwd_dkdv", stream);
-    if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16<128>::R16 + 4 * 64 * 4 + 16, stream, *p);
+    if (p->kv_split) {
+      const dim3 grid(((kv_units + 7) / 8) * 8 * 4);
+      if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(BWD_NT), split_lds<128>(), stream, *p);
+      else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, grid, dim3(BWD_NT), split_lds<64>(), stream, *p);
+    } else if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16<128>::R16 + 4 * 64 * 4 + 16, stream, *p);
     else hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
     zp_prof_end(stream);
     hipError_t e = hipGetLastError();

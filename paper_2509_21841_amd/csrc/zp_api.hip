@@ -36,6 +36,7 @@ struct zp_bwd_params {
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;
   int64_t dq_stride, dkv_stride;
+  int32_t kv_split;
   int32_t accumulate;
   zp_work_split work_dq, work_kv;
   zp_inline_tiles inl;
@@ -258,6 +259,20 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   *dev = ws_tiles(ws);
   *counters = ws_counters(ws);
   return upload_tiles(tiles, ws, stream);
+}
+// Whether the dK/dV launch ends when its longest workgroup does, with most CUs idle by then: the kernel that spreads a
+// key block's iterations over 16 waves then takes a quarter of the chain's time, at 1.3 / 0.7 of the other's cost per
+// iteration (one workgroup per CU in place of two). An iteration is a (32-query tile, head); about 1.05 us in a
+// workgroup that has its CU to itself. Chain: max * 1.05 against max / 4 * 1.3 and total / 256 CUs * 1.3; the line lies
+// where the last is a little under the first.
+bool dkdv_is_chain_bound(const std::vector<CostTile> &kt, int Hkv, int grp) {
+  int64_t total = 0, longest = 0;
+  for (const CostTile &c : kt) {
+    const int64_t n = (int64_t)((c.t.q_rows + 31) / 32) * grp;
+    total += n * Hkv;
+    longest = std::max(longest, n);
+  }
+  return total * 10 < longest * 256 * 6;
 }
 // work items of a launch over n tiles: (tile, KV head) units padded to one per XCD, times the heads in a group
 int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7) / 8 * 8 * grp; }
@@ -662,6 +677,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
+  p.kv_split = dkdv_is_chain_bound(kt, sh->Hkv, sh->Hq / sh->Hkv);
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
@@ -754,6 +770,7 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
+  p.kv_split = dkdv_is_chain_bound(kt, sh->Hkv, sh->Hq / sh->Hkv);
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();

@@ -1,0 +1,58 @@
+"""dK/dV of launches that leave most of the chip idle (four waves of a workgroup share a 32-row key block's query tiles by
+turns): block and tile edges, fewer iterations than waves, one to eight heads per KV head, both head dimensions, written
+and accumulated, against the fp64 oracle, and the batch sizes around which the other kernel takes over."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2509_21841_amd import binding as B
+from paper_2509_21841_amd import synth
+from util import Checks, assert_close, widen
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# The first keys of a short sequence have a handful of terms dS_ij q_i, the largest about 8, whose bf16 operand carries
+# 2^-9 of it (1.6e-2): two of them and the output's half-spacing (7.8e-3 below 4) make 4e-2. Small tensors have little to
+# average over, so the relative-L2 bound is three times the stated one (a wrong mask or index is of order one in both).
+MAXABS, RELL2 = 4e-2, 1.5e-2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lengths,Hq,Hkv", [([1], 1, 1), ([15, 16, 17, 31, 32, 33], 2, 1), ([127, 128, 129], 3, 1), ([65, 1, 0, 300], 8, 1),
+                                            ([500], 4, 4), ([97, 161], 4, 2), ([1100], 5, 1)])
+def test_small_batches(lengths, Hq, Hkv, d):
+    T = sum(lengths)
+    q, k, v, do = synth.make_qkv(T, Hq, Hkv, d, 101, DEV, with_dout=True)
+    cu = synth.cu_seqlens(lengths)
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    got = B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
+    ref = oracle.varlen_attn_bwd(widen(do), widen(q), widen(k), widen(v), cu)
+    checks = Checks()
+    for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+        checks.close(name, widen(a), b, maxabs=MAXABS, rell2=RELL2)
+    checks.finish()
+    again = B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
+    for a, b in zip(got, again):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    # accumulated in float, one pair per sequence: the written results are these, rounded once
+    acc = [torch.zeros(x.shape, dtype=torch.float32, device=DEV) for x in (q, k, v)]
+    pairs = [dict(q_tok0=int(cu[i]), q_len=n, k_tok0=int(cu[i]), k_len=n, q_pos0=0, k_pos0=0, out_row0=0) for i, n in enumerate(lengths) if n]
+    B.chunk_attn_partial_bwd(do, q, k, v, o, lse, pairs, *acc)
+    for a, b in zip(acc, got):
+        assert torch.equal(a.to(torch.bfloat16).view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 8, 24, 40, 48, 64, 96])
+def test_both_sides_of_the_rule(n, d):
+    """n sequences of 300 tokens under 2 KV heads: the first one's gradients do not depend on which kernel the batch
+    takes beyond the order of the float sums."""
+    L, Hq, Hkv = 300, 4, 2
+    q, k, v, do = synth.make_qkv(L * n, Hq, Hkv, d, 103, DEV, with_dout=True)
+    cu = synth.cu_seqlens([L] * n)
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    got = B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
+    ref = oracle.varlen_attn_bwd(widen(do[:L]), widen(q[:L]), widen(k[:L]), widen(v[:L]), synth.cu_seqlens([L]))
+    for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+        assert_close(name, widen(a[:L]), b, maxabs=MAXABS, rell2=RELL2)
