@@ -1,6 +1,7 @@
 """Where a call's tile table travels: in the launch arguments (up to 112 tiles and under 1024 work items) or through the
-workspace. The kernels are deterministic, so a batch gives the same bits whichever way its table took; the table's length
-and the number of items are taken to both sides of their limits. Calls that upload a table are also recorded into a HIP
+workspace. O, LSE and dQ of a sequence are the same bits whichever way its table took and whatever else is in the batch
+(dK and dV up to the order of their float sums, which depends on how full the launch is); the table's length and the
+number of items are taken to both sides of their limits. Calls that upload a table are also recorded into a HIP
 graph and replayed between other calls that use the staging buffers."""
 import numpy as np
 import pytest
@@ -39,8 +40,13 @@ def test_short_tables_equal_long_ones(tiles, Hq, Hkv, d):
     q, k, v, do = synth.make_qkv(n + sum(extra), Hq, Hkv, d, 83, DEV, with_dout=True)
     got = run(lengths, q, k, v, do, n)
     want = run(lengths + extra, q, k, v, do, n + sum(extra))
-    for a, b in zip(got, want):
+    for a, b in zip(got[:3], want[:3]):
         assert torch.equal(bits(a), bits(b[:n]))
+    for a, b in zip(got[3:], want[3:]):
+        # the same products added up in float in two orders (under 1e-5 apart: a thousand terms of order one at 2^-24 each),
+        # then rounded to bfloat16: neighbouring values at most, 2^-7 of the larger one
+        a, b = a.float(), b[:n].float()
+        assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-4).all())
 
 
 def test_uploaded_tables_in_a_captured_graph():
