@@ -39,10 +39,11 @@ constexpr float P_SUM_MAX = 4096.0f;
 // The probabilities are taken against the reference the rows already have, nm = -(reference) in scaled log2 units, and
 // only their sum is looked at: a maximum per tile costs 20 of 136 vector operations and puts a cross-lane exchange in
 // front of the first exp2, while all that it protects against is a reference so far below the scores that the
-// probabilities grow out of range. When a lane's 16 probabilities add up to more than P_SUM_MAX (or to NaN), the rows'
-// maxima are worked out and the tile's probabilities taken again. A row without a reference has nm = +inf, which makes
-// its first tile end there. Probabilities, sums and O are floating point throughout, so the reference's distance
-// from the row maximum costs no precision.
+// probabilities grow out of range. When the 16 probabilities of one of a row's four lanes add up to more than P_SUM_MAX
+// (or to NaN), the row's maximum is worked out and its probabilities of the tile taken again. A row without a reference
+// has nm = +inf, which makes its first tile end there. The other rows of the wave keep their reference, so that no bit of
+// a row depends on the tokens behind it. Probabilities, sums and O are floating point throughout, so the reference's
+// distance from the row maximum costs no precision.
 template <int D, bool MASK, bool ONLY1, bool PIECES, class Piece>
 __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2][D / 32], f32x4 (&o_acc)[2][D / 16],
                                          float (&nm)[2], float (&l_sum)[2], float c_log2, int j0, int q4,
@@ -106,7 +107,8 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
 #pragma unroll
         for (int r = 0; r < 4; r++) m = fmaxf(m, s[qb][kb][r]);
       m = zp_quad_max(m) * c_log2;
-      const float mc_old = -nm[qb], mc = fmaxf(mc_old, m);
+      const bool moves = zp_quad_max(t[qb] <= P_SUM_MAX ? 0.f : 1.f) > 0.f;
+      const float mc_old = -nm[qb], mc = moves ? fmaxf(mc_old, m) : mc_old;
       const bool none = mc == -INFINITY;  // no key seen yet: keep waiting, every probability of this tile is zero
       const float alpha = none ? 1.0f : zp_exp2(mc_old - mc);
       nm[qb] = -mc;

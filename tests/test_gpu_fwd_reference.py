@@ -67,3 +67,21 @@ def test_partials_on_every_side_of_the_diagonal(q_pos0, k_pos0, q_len, k_len, d)
     rop, rlp = oracle.chunk_attn_partial(widen(q), widen(k), widen(v), [pair], q_len)
     assert_close("O_part", widen(op), rop, bf16_out=False)
     assert_lse_close("LSE_part", widen(lp), rlp)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("c", [1, 72, 200, 300])
+def test_rows_do_not_depend_on_later_tokens(c, d):
+    """O and LSE of the first c tokens are the same bits whatever follows them: the rows behind, which share a wave with
+    them, get queries and keys that move their own reference in every tile."""
+    L, Hq, Hkv = 333, 4, 2
+    q, k, v = synth.make_qkv(L, Hq, Hkv, d, 77, DEV)
+    cu = synth.cu_seqlens([L])
+    want = B.varlen_attn_fwd(q, k, v, cu)
+    for scale in (0.0, 8.0, 64.0):
+        q2, k2, v2 = (x.clone() for x in (q, k, v))
+        for x in (q2, k2, v2):
+            x[c:] *= scale
+        got = B.varlen_attn_fwd(q2, k2, v2, cu)
+        assert torch.equal(got[0][:c].view(torch.int16), want[0][:c].view(torch.int16)), scale
+        assert torch.equal(got[1][:, :c].contiguous().view(torch.int32), want[1][:, :c].contiguous().view(torch.int32)), scale
