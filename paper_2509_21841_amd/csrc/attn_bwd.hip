@@ -828,7 +828,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // through the (query tile, head) iterations by turns, each with staging buffers of its own (145 KB of LDS in all at
 // D = 128) and no barrier in the loop; their accumulators are added up at the end, through LDS, in wave order. Four times
 // the workgroups, a quarter of the serial chain. 1218 tokens, GQA 4/2, d = 128: 32 us with 128 key rows per workgroup
-// (22 iterations one after the other on 32 of 256 CUs), 17 us with 32. See dkdv_is_chain_bound for when it is used.
+// (22 iterations one after the other on 32 of 256 CUs), 17 us with 32. See dkdv_split_is_faster for when it is used.
 template <int D>
 __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
   constexpr int QT = 32;
@@ -993,7 +993,7 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
     if (e != hipSuccess) return (int)e;
   }
   if (kv_units > 0) {
-    zp_prof_begin("attn_bwd_dkdv", stream);
+    zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : "attn_bwd_dkdv", stream);
     if (p->kv_split) {
       const dim3 grid(((kv_units + 7) / 8) * 8 * 4);
       if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(BWD_NT), split_lds<128>(), stream, *p);

@@ -260,19 +260,66 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   *counters = ws_counters(ws);
   return upload_tiles(tiles, ws, stream);
 }
-// Whether the dK/dV launch ends when its longest workgroup does, with most CUs idle by then: the kernel that spreads a
-// key block's iterations over 16 waves then takes a quarter of the chain's time, at 1.3 / 0.7 of the other's cost per
-// iteration (one workgroup per CU in place of two). An iteration is a (32-query tile, head); about 1.05 us in a
-// workgroup that has its CU to itself. Chain: max * 1.05 against max / 4 * 1.3 and total / 256 CUs * 1.3; the line lies
-// where the last is a little under the first.
-bool dkdv_is_chain_bound(const std::vector<CostTile> &kt, int Hkv, int grp) {
-  int64_t total = 0, longest = 0;
-  for (const CostTile &c : kt) {
-    const int64_t n = (int64_t)((c.t.q_rows + 31) / 32) * grp;
-    total += n * Hkv;
-    longest = std::max(longest, n);
+// Whether the split dK/dV kernel, which spreads a key block's iterations over 16 waves, is the faster one. It takes a
+// quarter of the longest chain, but a CU holds one of its workgroups and each pays for a prologue and for adding up its
+// waves' sums, so it gains on launches that leave most CUs idle and loses (up to 2.5 times) on all others. Both times are
+// estimated in microseconds; an iteration is a (32-query tile, head). Both kernels deal the units (tile, KV head) to the
+// XCDs by turns, and the XCD that ends last decides.
+//  - One workgroup per key block: the first 32 units of an XCD get a CU each, the next 32 share those in the same order; an
+//    iteration beside another workgroup takes 1.44 times as long. The longest chain with its companion's share, and the
+//    masked tiles at its end. With more than two workgroups per CU the split is not looked at.
+//  - Split: four workgroups per unit (those without keys cost a prologue as well). The longest one while 32 CUs hold all of
+//    an XCD's, else their time over 32 CUs and a part of those that start last, no more than the longest per round of 32.
+// The constants are fitted to 1014 launches (d = 64 and 128, 4/4 to 32/8 and 8/1 heads, equal sequences of 100 to 16000
+// tokens and random ones, 925 of them within 512 units); the estimates are 5 % off in the mean, and the first is taken 6 %
+// lower. Of the 654 launches that take the split none is more than 6 % faster without it; six of the others would be 6 to
+// 13 % faster with it. n sequences of L tokens, us, one workgroup per key block / split:
+//    d   heads    L    taken: split              not taken
+//   128   4/4    300   n =  3:   18.9 /   12.6   n = 16:   19.9 /   28.9
+//   128   8/1   1000   n =  6:  269.8 /  106.1   n = 28:  269.2 /  396.0
+//   128  32/8   4000   n =  1:  505.8 /  401.0   n =  2:  728.3 /  786.7
+//    64  16/4    300   n = 10:   34.1 /   26.2   n = 19:   34.2 /   40.8
+//    64   8/1  16000   n =  2: 2170.9 / 1726.3   n =  4: 3235.0 / 3426.4
+bool dkdv_split_is_faster(const std::vector<CostTile> &kt, int d, int Hkv, int grp) {
+  struct Cost {
+    float whole, whole_it, whole_head;     // one workgroup per key block: fixed, per iteration, per head
+    float launch, split, split_it, tail;   // split: per launch; per workgroup: fixed, per iteration of a wave; share of the last
+  };
+  const Cost c = d == 64 ? Cost{7.05f, 0.519f, 0.910f, 3.83f, 3.16f, 0.855f, 0.517f}
+                         : Cost{8.33f, 0.943f, 0.630f, 3.79f, 4.50f, 1.504f, 0.542f};
+  if ((int64_t)kt.size() * Hkv > 512) return false;
+  // per XCD: units and their chains; iterations per wave of the split's workgroups, and of the (up to 8) units that start last
+  float chain[8][64];
+  int n[8] = {}, n_last[8] = {};
+  int64_t it[8] = {}, it_last[8] = {}, longest = 0;
+  int u = (int)kt.size() * Hkv;
+  for (size_t i = kt.size(); i-- > 0;) {
+    const int64_t its = (int64_t)((kt[i].t.q_rows + 31) / 32) * grp, per_wave = (its + 3) / 4;
+    const int parts = (kt[i].t.k_len + 31) / 32;
+    longest = std::max(longest, its);
+    for (int g = 0; g < Hkv; g++) {
+      const int x = --u & 7;
+      chain[x][u >> 3] = (float)its;
+      if (n_last[x] < 32) {
+        n_last[x] += parts;
+        it_last[x] += parts * per_wave;
+      }
+      n[x]++;
+      it[x] += parts * per_wave;
+    }
   }
-  return total * 10 < longest * 256 * 6;
+  float its_whole = 0.f;
+  const float wg = c.split + c.split_it * (float)((longest + 3) / 4);
+  float split = wg;
+  for (int x = 0; x < 8; x++) {
+    for (int i = 0; i < std::min(32, n[x]); i++)
+      its_whole = std::max(its_whole, chain[x][i] + (i + 32 < n[x] ? 0.44f * chain[x][i + 32] : 0.f));
+    if (n[x] <= 8) continue;
+    const float last = c.split + c.split_it * (float)it_last[x] / (float)n_last[x];
+    const float fill = (c.split * 4.f * (float)n[x] + c.split_it * (float)it[x]) / 32.f + c.tail * last;
+    split = std::max(split, std::min(fill, wg * (float)((n[x] + 7) / 8)));
+  }
+  return c.launch + split < c.whole + c.whole_it * its_whole + c.whole_head * (float)grp;
 }
 // work items of a launch over n tiles: (tile, KV head) units padded to one per XCD, times the heads in a group
 int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7) / 8 * 8 * grp; }
@@ -677,7 +724,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
-  p.kv_split = dkdv_is_chain_bound(kt, sh->Hkv, sh->Hq / sh->Hkv);
+  p.kv_split = dkdv_split_is_faster(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
@@ -770,7 +817,7 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
-  p.kv_split = dkdv_is_chain_bound(kt, sh->Hkv, sh->Hq / sh->Hkv);
+  p.kv_split = dkdv_split_is_faster(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();

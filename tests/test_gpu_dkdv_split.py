@@ -56,3 +56,26 @@ def test_both_sides_of_the_rule(n, d):
     ref = oracle.varlen_attn_bwd(widen(do[:L]), widen(q[:L]), widen(k[:L]), widen(v[:L]), synth.cu_seqlens([L]))
     for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
         assert_close(name, widen(a[:L]), b, maxabs=MAXABS, rell2=RELL2)
+
+
+def dkdv_labels(*call):
+    B.profile_enable(True)
+    B.varlen_attn_bwd(*call)
+    torch.cuda.synchronize()
+    labels = {name for name, _ in B.profile_records() if name.startswith("attn_bwd_dkdv")}
+    B.profile_enable(False)
+    return labels
+
+
+# Which of the two kernels is faster was measured for each of these launches; all are at least 10 % apart.
+@pytest.mark.parametrize("d,Hq,Hkv,L,n,split", [
+    (128, 4, 4, 300, 3, True), (128, 4, 4, 300, 10, False), (128, 4, 4, 300, 19, False), (128, 4, 4, 1000, 7, False),
+    (128, 8, 1, 1000, 6, True), (128, 8, 1, 1000, 17, False), (128, 8, 1, 1000, 28, False), (128, 8, 1, 4000, 2, True),
+    (128, 32, 8, 300, 10, False), (128, 32, 8, 1000, 2, True), (128, 32, 8, 1000, 9, False), (128, 4, 4, 100, 32, False),
+    (64, 4, 4, 300, 3, True), (64, 4, 4, 300, 16, False), (64, 16, 4, 300, 10, True), (64, 16, 4, 300, 19, False),
+    (64, 8, 1, 1000, 6, True), (64, 8, 1, 1000, 34, False), (64, 4, 2, 100, 13, True), (64, 4, 2, 300, 38, False)])
+def test_the_faster_kernel_is_taken(d, Hq, Hkv, L, n, split):
+    q, k, v, do = synth.make_qkv(L * n, Hq, Hkv, d, 107, DEV, with_dout=True)
+    cu = synth.cu_seqlens([L] * n)
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    assert dkdv_labels(do, q, k, v, o, lse, cu) == {"attn_bwd_dkdv_split" if split else "attn_bwd_dkdv"}
