@@ -10,6 +10,10 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream). Calls only enqueue work:
  *    no device synchronisation, no device memory allocation. The library keeps a small pool of pinned
  *    host staging buffers (grown on demand) for its descriptor uploads.
+ *  - Calls can be captured into a HIP graph: descriptors become part of the graph (no staging buffer is taken or
+ *    allocated while `stream` is capturing). Every replay uses the device pointers of the call, `ws` among them: they
+ *    must stay valid, and `ws` must not be used by calls that may run at the same time, for as long as the graph is
+ *    replayed.
  *  - `ws` is caller-provided device scratch of at least zp_workspace_bytes(...) bytes, 256-byte aligned.
  *    Its contents are undefined afterwards. Two calls that share one `ws` must be ordered on one stream.
  *  - Layouts: token-major packed tensors. Q, O, dO, dQ are [T][Hq][d]; K, V, dK, dV are [T][Hkv][d],

@@ -80,7 +80,7 @@ struct HipPoolBackend {
 zp_staging_pool<HipPoolBackend> g_pool;
 
 constexpr int UPLOAD_NT = 1024, UPLOAD_UNROLL = 4;
-// One workgroup: 64 KB of host reads in flight at a time. n16: 16-byte pieces. flag: null if the slot is never given back.
+// One workgroup: 64 KB of host reads in flight at a time. n16: 16-byte pieces.
 __global__ __launch_bounds__(UPLOAD_NT) void upload_kernel(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int64_t n16,
                                                            uint32_t *flag) {
   for (int64_t base = threadIdx.x; base < n16; base += UPLOAD_NT * UPLOAD_UNROLL) {
@@ -93,29 +93,63 @@ __global__ __launch_bounds__(UPLOAD_NT) void upload_kernel(const u32x4 *__restri
       if (base + u * UPLOAD_NT < n16) dst[base + u * UPLOAD_NT] = v[u];
   }
   __syncthreads();  // every piece has been read: it has been written
-  if (threadIdx.x == 0 && flag) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-int pool_acquire(size_t bytes, int *slot_out, void **host_out) {
-  const int e = g_pool.acquire((bytes + 15) & ~(size_t)15, slot_out, host_out);
-  return e ? hip_fail((hipError_t)e, "staging buffer") : ZP_OK;
+// The same for a table that travels in the launch arguments, one launch per UPLOAD_ARGS pieces.
+constexpr int UPLOAD_ARGS = 248;
+struct UploadArgs {
+  u32x4 v[UPLOAD_ARGS];
+};
+static_assert(sizeof(UploadArgs) + 16 <= 4096, "kernel arguments are limited to 4 KB");
+__global__ __launch_bounds__(256) void upload_args_kernel(UploadArgs a, u32x4 *__restrict__ dst, int n16) {
+  if ((int)threadIdx.x < n16) dst[threadIdx.x] = a.v[threadIdx.x];
 }
-// Copies `bytes` from the slot to device memory on `stream`; the slot stays busy until that has happened. `dev` is 16-byte
-// aligned and has room for `bytes` rounded up to 16.
-int pool_upload(int slot, const void *host, void *dev, size_t bytes, hipStream_t stream) {
-  uint32_t *flag = g_pool.event(slot);
-  __atomic_store_n(flag, 0u, __ATOMIC_RELEASE);
-  // A captured copy reads the slot again at every replay: it is never given back.
+
+// A table on its way to the device: upload_begin says where to write it (`host`), upload_send copies it. While the stream
+// is capturing, the table goes by value into the launches that write it, so that it lives as long as the graph does: a
+// staging slot would be read by every replay, could never be given back, and a new one cannot be allocated during a
+// capture. Replays pay one small launch per 4 KB for that.
+struct Upload {
+  void *host = nullptr;
+  int slot = -1;           // of the staging pool; -1: `own`
+  std::vector<u32x4> own;
+};
+int upload_begin(size_t bytes, hipStream_t stream, Upload &u) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
-  hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(UPLOAD_NT), 0, stream, (const u32x4 *)host, (u32x4 *)dev, (int64_t)((bytes + 15) / 16),
-                     cap == hipStreamCaptureStatusNone ? flag : nullptr);
+  if (cap != hipStreamCaptureStatusNone) {
+    u.own.resize((bytes + 15) / 16);
+    u.host = u.own.data();
+    return ZP_OK;
+  }
+  const int e = g_pool.acquire((bytes + 15) & ~(size_t)15, &u.slot, &u.host);
+  return e ? hip_fail((hipError_t)e, "staging buffer") : ZP_OK;
+}
+// Copies `bytes` to device memory on `stream`; a slot stays busy until that has happened. `dev` is 16-byte aligned and has
+// room for `bytes` rounded up to 16.
+int upload_send(Upload &u, void *dev, size_t bytes, hipStream_t stream) {
+  const int64_t n16 = (int64_t)((bytes + 15) / 16);
+  if (u.slot < 0) {
+    for (int64_t at = 0; at < n16; at += UPLOAD_ARGS) {
+      UploadArgs a;
+      const int n = (int)std::min<int64_t>(UPLOAD_ARGS, n16 - at);
+      std::memcpy(a.v, u.own.data() + at, (size_t)n * 16);
+      std::memset((void *)(a.v + n), 0, (size_t)(UPLOAD_ARGS - n) * 16);
+      hipLaunchKernelGGL(upload_args_kernel, dim3(1), dim3(256), 0, stream, a, (u32x4 *)dev + at, n);
+    }
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? hip_fail(e, "descriptor upload") : ZP_OK;
+  }
+  uint32_t *flag = g_pool.event(u.slot);
+  __atomic_store_n(flag, 0u, __ATOMIC_RELEASE);
+  hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(UPLOAD_NT), 0, stream, (const u32x4 *)u.host, (u32x4 *)dev, n16, flag);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
-    g_pool.abandon(slot);
+    g_pool.abandon(u.slot);
     return hip_fail(e, "descriptor upload");
   }
-  const int r = g_pool.submitted(slot, stream);
+  const int r = g_pool.submitted(u.slot, stream);
   return r ? hip_fail((hipError_t)r, "descriptor upload") : ZP_OK;
 }
 
@@ -233,14 +267,13 @@ int dyn_div_of(const std::vector<CostTile> &tiles, size_t first, size_t n, int w
 int upload_tiles(const std::vector<CostTile> &tiles, void *ws, hipStream_t stream) {
   if (tiles.empty()) return ZP_OK;
   const size_t bytes = WS_HEADER + tiles.size() * sizeof(zp_tile);
-  int slot;
-  void *host;
-  int rc = pool_acquire(bytes, &slot, &host);
+  Upload u;
+  int rc = upload_begin(bytes, stream, u);
   if (rc) return rc;
-  std::memset(host, 0, WS_HEADER);
-  zp_tile *h = (zp_tile *)((char *)host + WS_HEADER);
+  std::memset(u.host, 0, WS_HEADER);
+  zp_tile *h = (zp_tile *)((char *)u.host + WS_HEADER);
   for (size_t i = 0; i < tiles.size(); i++) h[i] = tiles[i].t;
-  return pool_upload(slot, host, ws, bytes, stream);
+  return upload_send(u, ws, bytes, stream);
 }
 
 // Puts the tile table where the kernels find it. A table that fits the launch arguments goes there when none of its
@@ -587,10 +620,9 @@ int lse_merge(const float *o_part, const float *lse_part, int64_t part_rows, con
   const size_t item_bytes = n_items * 8;
   if ((rc = check_ws(ws, ws_bytes, desc_bytes + align256(item_bytes)))) return rc;
   if (n_items == 0) return ZP_OK;
-  int slot;
-  void *host;
-  if ((rc = pool_acquire(desc_bytes + item_bytes, &slot, &host))) return rc;
-  char *h = (char *)host;
+  Upload u;
+  if ((rc = upload_begin(desc_bytes + item_bytes, (hipStream_t)stream, u))) return rc;
+  char *h = (char *)u.host;
   std::memcpy(h, merges, (size_t)n_merges * sizeof(zp_merge));
   int32_t *items = (int32_t *)(h + desc_bytes);
   size_t n = 0;
@@ -600,7 +632,7 @@ int lse_merge(const float *o_part, const float *lse_part, int64_t part_rows, con
       items[2 * n + 1] = r0;
       n++;
     }
-  if ((rc = pool_upload(slot, host, ws, desc_bytes + item_bytes, (hipStream_t)stream))) return rc;
+  if ((rc = upload_send(u, ws, desc_bytes + item_bytes, (hipStream_t)stream))) return rc;
   int max_parts = 1;
   for (int i = 0; i < n_merges; i++) max_parts = std::max(max_parts, (int)merges[i].n_parts);
   hipError_t e = (hipError_t)zp_launch_lse_merge(o_part, lse_part, part_rows, ws, (char *)ws + desc_bytes, (int)n_items,

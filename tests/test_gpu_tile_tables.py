@@ -50,7 +50,7 @@ def test_short_tables_equal_long_ones(tiles, Hq, Hkv, d):
 
 
 def test_uploaded_tables_in_a_captured_graph():
-    """The staging buffer of a captured upload is read at every replay: calls in between must not get it."""
+    """Replays of a graph that uploads tables, between other calls that use the staging buffers."""
     lengths = [130] * 64
     Hq, Hkv, d, T = 8, 2, 128, 130 * 64
     cu = synth.cu_seqlens(lengths)
@@ -62,7 +62,7 @@ def test_uploaded_tables_in_a_captured_graph():
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
         for _ in range(4):
-            call()                               # the workspaces of the capture stream, and staging buffers to spare
+            call()                               # the workspaces of the capture stream
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=side):
@@ -105,3 +105,57 @@ def test_noalloc_with_a_long_table_replays_from_a_captured_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(bits(o), bits(wo)) and torch.equal(bits(lse), bits(wl)), f"replay {rep}"
+
+
+def uploading_calls(lengths, Hq, Hkv, d, seed):
+    """Inputs, outputs and a call (inputs, outputs) that uploads long tables: forward, chunk pairs and merge of a first
+    sequence over 4000 tokens, backward, all with one workspace of their own."""
+    T, cu = sum(lengths), synth.cu_seqlens(lengths)
+    x = synth.make_qkv(T, Hq, Hkv, d, seed, DEV, with_dout=True)
+    outs = [torch.zeros_like(x[0]), torch.zeros((Hq, T), dtype=torch.float32, device=DEV)] + [torch.zeros_like(t) for t in x[:3]]
+    pairs, merges, rows = B.chunk_pairs(0, lengths[0], 4) if lengths[0] > 4000 else (None, None, 0)
+    parts = (torch.empty((rows, Hq, d), dtype=torch.float32, device=DEV), torch.empty((Hq, rows), dtype=torch.float32, device=DEV))
+    sh = B.make_shape(T, len(lengths), Hq, Hkv, d)
+    ws = torch.empty(max(B.workspace_bytes(B.FN_FWD, sh, cu), B.workspace_bytes(B.FN_BWD, sh, cu), B.workspace_bytes(B.FN_PARTIAL, sh, None, 10),
+                         B.workspace_bytes(B.FN_MERGE, sh, None, 4)), dtype=torch.uint8, device=DEV)
+    skip = np.asarray([rows > 0] + [False] * (len(lengths) - 1), np.uint8)
+
+    def call(x, outs):
+        q, k, v, do = x
+        o, lse, dq, dk, dv = outs
+        B.varlen_attn_fwd(q, k, v, cu, o=o, lse=lse, seq_skip=skip, ws=ws)
+        if rows:
+            B.chunk_attn_partial(q, k, v, pairs, rows, o_part=parts[0], lse_part=parts[1], ws=ws)
+            B.lse_merge(*parts, merges, o, lse, ws=ws)
+        B.varlen_attn_bwd(do, q, k, v, o, lse, cu, dq=dq, dk=dk, dv=dv, ws=ws)
+    return x, outs, call
+
+
+def test_captures_need_no_staging_buffers():
+    """Two graphs with more uploading calls each than the process has ever had under way at once, captured without a call
+    before them on their stream: the tables of a captured call belong to its graph (there is nothing to allocate for them
+    while the stream is capturing, and nothing to give back)."""
+    Hq, Hkv, d = 8, 2, 128
+    side = torch.cuda.Stream()
+    graphs = []
+    for seed, lengths in ((97, [130] * 64), (98, [8192, 40, 1, 3000])):
+        x, outs, call = uploading_calls(lengths, Hq, Hkv, d, seed)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            for _ in range(30):
+                call(x, outs)
+        graphs.append((graph, x, outs, call))
+    for rep in range(3):
+        for n, (graph, x, outs, call) in enumerate(graphs):
+            for dst, src in zip(x, synth.make_qkv(x[0].shape[0], Hq, Hkv, d, 980 + 2 * rep + n, DEV, with_dout=True)):
+                dst.copy_(src)
+            want = [torch.zeros_like(t) for t in outs]
+            call(x, want)
+            for t in outs:
+                t.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(outs, want):
+                assert torch.equal(bits(a), bits(b)), (rep, n)
