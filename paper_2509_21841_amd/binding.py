@@ -156,13 +156,36 @@ def _tok_stride(t: torch.Tensor) -> int:
 _ws_cache: dict = {}
 
 
+def _on(stream):
+    """Context in which torch allocates for `stream` (None: the current stream as it is)."""
+    if stream is None or isinstance(stream, torch.cuda.Stream):
+        return torch.cuda.stream(stream)
+    return torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream))
+
+
+def _is_capturing(stream=None) -> bool:
+    if stream is None or stream.cuda_stream == _stream_ptr():
+        return torch.cuda.is_current_stream_capturing()
+    with _on(stream):
+        return torch.cuda.is_current_stream_capturing()
+
+
 def workspace(nbytes: int, device, tag: str = "default", stream=None) -> torch.Tensor:
-    """A cached device scratch tensor of at least nbytes (256-byte aligned by the torch allocator), one per device,
-    entry point and stream: calls on one stream are ordered and may share it, calls on different streams may not."""
+    """A device scratch tensor of at least nbytes (256-byte aligned by the torch allocator) for one call on `stream`: a
+    cached one per device, entry point and stream (calls on one stream are ordered and may share it, calls on different
+    streams may not; one that is outgrown is given back in the order of its stream). A call that is being captured gets a
+    new one from the memory pool of its graph, which keeps it as long as the graph can be replayed: a cached one may be
+    outgrown and given away before that, and replays on another stream would share it with the calls of this one. (That
+    is torch.cuda.graph's pool; calls captured by other means have to bring their own ws.)"""
+    size = max(int(nbytes), 4096)
+    if _is_capturing(stream):
+        with _on(stream):
+            return torch.empty(size, dtype=torch.uint8, device=device)
     key = (device, tag, _stream_ptr(stream))
     t = _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
-        t = torch.empty(max(int(nbytes), 4096), dtype=torch.uint8, device=device)
+        with _on(stream):
+            t = torch.empty(size, dtype=torch.uint8, device=device)
         _ws_cache[key] = t
     return t
 

@@ -159,3 +159,54 @@ def test_captures_need_no_staging_buffers():
             torch.cuda.synchronize()
             for a, b in zip(outs, want):
                 assert torch.equal(bits(a), bits(b)), (rep, n)
+
+
+def test_a_graph_outlives_the_scratch_of_its_stream():
+    """Calls captured without a workspace of the caller's, then a larger eager call on the capture stream (which replaces
+    that stream's cached scratch) and new tensors: replays give the right results and write to nobody else's memory."""
+    Hq, Hkv, d = 8, 2, 128
+    side = torch.cuda.Stream()
+    small, large = [130] * 64, [700] * 64
+
+    def call(x, outs, cu):
+        q, k, v, do = x
+        o, lse, dq, dk, dv = outs
+        B.varlen_attn_fwd(q, k, v, cu, o=o, lse=lse)
+        B.varlen_attn_bwd(do, q, k, v, o, lse, cu, dq=dq, dk=dk, dv=dv)
+
+    def buffers(lengths, seed):
+        x = synth.make_qkv(sum(lengths), Hq, Hkv, d, seed, DEV, with_dout=True)
+        return x, [torch.zeros_like(x[0]), torch.zeros((Hq, sum(lengths)), dtype=torch.float32, device=DEV)] + [torch.zeros_like(t) for t in x[:3]]
+
+    x, outs = buffers(small, 99)
+    bx, bouts = buffers(large, 100)
+    graphs = []
+    for _ in range(2):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            call(x, outs, synth.cu_seqlens(small))
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call(x, outs, synth.cu_seqlens(small))
+        with torch.cuda.stream(side):
+            call(bx, bouts, synth.cu_seqlens(large))
+        torch.cuda.synchronize()
+        graphs.append(graph)
+    need = B.workspace_bytes(B.FN_BWD, B.make_shape(sum(small), len(small), Hq, Hkv, d), synth.cu_seqlens(small))
+    others = [torch.full((n,), 0x5A, dtype=torch.uint8, device=DEV) for n in (4096, 4096, need, need, need)]
+    for rep in range(3):
+        for dst, src in zip(x, synth.make_qkv(sum(small), Hq, Hkv, d, 990 + rep, DEV, with_dout=True)):
+            dst.copy_(src)
+        want = [torch.zeros_like(t) for t in outs]
+        call(x, want, synth.cu_seqlens(small))
+        for graph in graphs:
+            for t in outs:
+                t.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(outs, want):
+                assert torch.equal(bits(a), bits(b)), rep
+    for t in others:
+        assert bool((t == 0x5A).all())

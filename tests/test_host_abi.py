@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2509_21841_amd import binding as B
@@ -233,3 +234,21 @@ def test_ring_round_pairs_over_scattered_runs_and_bad_input():
     assert np.array_equal(orig, want) and sorted(orig.tolist()) == list(range(116))
     with pytest.raises(B.ZpError):
         B.segment_positions(lengths, segs[:-1], 116)    # the runs do not tile the layout
+
+
+def test_scratch_of_captured_calls_is_not_shared(monkeypatch):
+    """The cached scratch tensor of a stream is replaced when a larger batch comes, a graph's must stay: a call that is
+    being captured neither takes the cached one nor leaves its own in the cache."""
+    capturing = [False]
+    monkeypatch.setattr(B, "_ws_cache", {})
+    monkeypatch.setattr(B, "_stream_ptr", lambda stream=None: 7)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
+    eager = B.workspace(5000, "cpu", "fwd")
+    assert B.workspace(4000, "cpu", "fwd") is eager
+    capturing[0] = True
+    first, second = B.workspace(4000, "cpu", "fwd"), B.workspace(9000, "cpu", "fwd")
+    assert len({t.data_ptr() for t in (eager, first, second)}) == 3 and second.numel() >= 9000
+    fresh = B.workspace(100, "cpu", "bwd")           # nothing cached yet for this entry point
+    capturing[0] = False
+    assert B.workspace(5000, "cpu", "fwd") is eager
+    assert B.workspace(100, "cpu", "bwd") is not fresh
