@@ -98,7 +98,11 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
   };
 #pragma unroll
   for (int qb = QB0; qb < 2; qb++) take(qb, nm[qb]);
-  if (__builtin_amdgcn_ballot_w64(!(t[QB0] <= P_SUM_MAX && t[1] <= P_SUM_MAX)) != 0) {
+  uint64_t far[2];  // lanes of out-of-range sums
+#pragma unroll
+  for (int qb = QB0; qb < 2; qb++) far[qb] = __builtin_amdgcn_ballot_w64(!(t[qb] <= P_SUM_MAX));
+  // (unlikely: behind the loop's own code, which a short sequence's few tiles have to fetch as well)
+  if (__builtin_expect((far[QB0] | far[1]) != 0, 0)) {
 #pragma unroll
     for (int qb = QB0; qb < 2; qb++) {
       float m = s[qb][0][0];
@@ -107,7 +111,9 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
 #pragma unroll
         for (int r = 0; r < 4; r++) m = fmaxf(m, s[qb][kb][r]);
       m = zp_quad_max(m) * c_log2;
-      const bool moves = zp_quad_max(t[qb] <= P_SUM_MAX ? 0.f : 1.f) > 0.f;
+      uint32_t rows = (uint32_t)far[qb] | (uint32_t)(far[qb] >> 32);  // the four lanes of a row are 16 apart
+      rows = ((rows | rows >> 16) & 0xffff) * 0x10001u;
+      const bool moves = __builtin_amdgcn_inverse_ballot_w64((uint64_t)rows << 32 | rows);
       const float mc_old = -nm[qb], mc = moves ? fmaxf(mc_old, m) : mc_old;
       const bool none = mc == -INFINITY;  // no key seen yet: keep waiting, every probability of this tile is zero
       const float alpha = none ? 1.0f : zp_exp2(mc_old - mc);
