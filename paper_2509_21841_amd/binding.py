@@ -163,8 +163,11 @@ def _on(stream):
     return torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream))
 
 
-def _is_capturing(stream=None) -> bool:
-    if stream is None or stream.cuda_stream == _stream_ptr():
+def _is_capturing(stream, ptr: int) -> bool:
+    """Whether `stream`, whose hipStream_t is ptr, is capturing (the default stream never is)."""
+    if ptr == 0:
+        return False
+    if stream is None:
         return torch.cuda.is_current_stream_capturing()
     with _on(stream):
         return torch.cuda.is_current_stream_capturing()
@@ -177,16 +180,15 @@ def workspace(nbytes: int, device, tag: str = "default", stream=None) -> torch.T
     new one from the memory pool of its graph, which keeps it as long as the graph can be replayed: a cached one may be
     outgrown and given away before that, and replays on another stream would share it with the calls of this one. (That
     is torch.cuda.graph's pool; calls captured by other means have to bring their own ws.)"""
-    size = max(int(nbytes), 4096)
-    if _is_capturing(stream):
-        with _on(stream):
-            return torch.empty(size, dtype=torch.uint8, device=device)
-    key = (device, tag, _stream_ptr(stream))
-    t = _ws_cache.get(key)
+    ptr = _stream_ptr(stream)
+    key = (device, tag, ptr)
+    capturing = _is_capturing(stream, ptr)
+    t = None if capturing else _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
         with _on(stream):
-            t = torch.empty(size, dtype=torch.uint8, device=device)
-        _ws_cache[key] = t
+            t = torch.empty(max(int(nbytes), 4096), dtype=torch.uint8, device=device)
+        if not capturing:
+            _ws_cache[key] = t
     return t
 
 
