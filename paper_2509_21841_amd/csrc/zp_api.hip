@@ -23,24 +23,6 @@ int zp_merge_rows_per_item(void);
 int zp_launch_lse_merge(const float *o_part, const float *lse_part, int64_t part_rows, const void *merges_dev,
                         const void *items_dev, int n_items, int Hq, int d, void *o, int64_t o_stride, float *lse,
                         int64_t T, int max_parts, hipStream_t stream);
-struct zp_bwd_params {
-  const __bf16 *q, *k, *v, *o, *dout;
-  int64_t q_stride, k_stride, v_stride, o_stride, do_stride;
-  const float *lse;
-  float *dvec;
-  float *lse2;
-  const zp_tile *dq_tiles;
-  const zp_tile *kv_tiles;
-  int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
-  uint32_t m_hkv, m_grp;
-  float scale_log2, scale;
-  __bf16 *dq, *dk, *dv;
-  int64_t dq_stride, dkv_stride;
-  int32_t kv_split;
-  int32_t accumulate;
-  zp_work_split work_dq, work_kv;
-  zp_inline_tiles inl;
-};
 int zp_launch_accum_to_bf16(const float *src, void *dst, int64_t n, hipStream_t stream);
 int zp_launch_attn_bwd(const zp_bwd_params *p, int d, hipStream_t stream);
 int zp_attn_bwd_block_rows(int d, int which);

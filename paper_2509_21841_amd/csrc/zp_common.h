@@ -127,6 +127,28 @@ struct zp_attn_params {
   zp_work_split work;  // which workgroups take their item by number and which claim one (set by the launcher)
   zp_inline_tiles inl; // the tile table if `tiles` is null
 };
+static_assert(sizeof(zp_attn_params) <= 4096, "kernel arguments are limited to 4 KB");
+
+// Parameters of the two backward kernels. Strides as above.
+struct zp_bwd_params {
+  const __bf16 *q, *k, *v, *o, *dout;
+  int64_t q_stride, k_stride, v_stride, o_stride, do_stride;
+  const float *lse;   // [Hq][T]
+  float *dvec;        // [Hq][T] scratch: -D_i = -(dO_i . O_i)
+  float *lse2;        // [Hq][T] scratch: -LSE_i / scale
+  const zp_tile *dq_tiles;
+  const zp_tile *kv_tiles;
+  int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
+  uint32_t m_hkv, m_grp;  // zp_div_magic of Hkv and grp (set by the launcher)
+  float scale_log2, scale;
+  __bf16 *dq, *dk, *dv;      // outputs (bf16, overwritten) ...
+  int64_t dq_stride, dkv_stride;
+  int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
+  int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
+  zp_work_split work_dq, work_kv;  // work hand-out of the two launches (counters set by the C ABI, the rest by the launcher)
+  zp_inline_tiles inl;  // the dQ tiles and, behind them, the dK/dV tiles if dq_tiles and kv_tiles are null
+};
+static_assert(sizeof(zp_bwd_params) <= 4096, "kernel arguments are limited to 4 KB");
 
 // blockIdx -> (unit, head-in-group). Workgroups are dealt to the 8 XCDs round-robin by blockIdx, so
 // units (tile, kv head) are dealt round-robin too -- the cost-sorted list stays balanced across XCDs --
