@@ -15,8 +15,6 @@ constexpr int BN = 64;  // keys per LDS tile
 
 template <int D, int NW>
 struct FwdCfg {
-  static constexpr int NT = NW * 64;
-  static constexpr int BM = NW * 32;
   static constexpr int TILEB = BN * D * 2;  // bytes per K (or V) tile
 };
 

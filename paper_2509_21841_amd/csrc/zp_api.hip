@@ -210,7 +210,7 @@ void plan_whole(const int32_t *cu, int S, int bm, std::vector<CostTile> &out, co
     if (skip && skip[s]) continue;
     const int32_t L = cu[s + 1] - cu[s];
     for (int32_t r0 = ((L - 1) / bm) * bm; L > 0 && r0 >= 0; r0 -= bm) {
-      CostTile c;
+      CostTile c{};
       c.t.q_tok0 = cu[s] + r0;
       c.t.q_rows = std::min(bm, L - r0);
       c.t.q_pos0 = r0;
@@ -218,7 +218,6 @@ void plan_whole(const int32_t *cu, int S, int bm, std::vector<CostTile> &out, co
       c.t.k_len = L;
       c.t.k_pos0 = 0;
       c.t.out_row0 = cu[s] + r0;
-      c.t.aux = 0;
       c.cost = tile_cost(c.t);
       out.push_back(c);
     }
@@ -487,7 +486,7 @@ int chunk_attn_partial(const void *q, const void *k, const void *v, int64_t q_st
   for (int i = 0; i < n_pairs; i++) {
     const zp_pair &pr = pairs[i];
     for (int32_t r0 = 0; r0 < pr.q_len; r0 += bm) {
-      CostTile c;
+      CostTile c{};
       c.t.q_tok0 = pr.q_tok0 + r0;
       c.t.q_rows = std::min(bm, pr.q_len - r0);
       c.t.q_pos0 = pr.q_pos0 + r0;
@@ -495,7 +494,6 @@ int chunk_attn_partial(const void *q, const void *k, const void *v, int64_t q_st
       c.t.k_len = pr.k_len;
       c.t.k_pos0 = pr.k_pos0;
       c.t.out_row0 = pr.out_row0 + r0;
-      c.t.aux = 0;
       c.cost = tile_cost(c.t);
       tiles.push_back(c);
     }
@@ -546,7 +544,7 @@ int chunk_attn_update(const void *q, const void *k, const void *v, int64_t q_str
   for (int i = 0; i < n_pairs; i++) {
     const zp_pair &pr = pairs[i];
     for (int32_t r0 = 0; r0 < pr.q_len; r0 += bm) {
-      CostTile c;
+      CostTile c{};
       c.t.q_tok0 = pr.q_tok0 + r0;
       c.t.q_rows = std::min(bm, pr.q_len - r0);
       c.t.q_pos0 = pr.q_pos0 + r0;
@@ -554,7 +552,6 @@ int chunk_attn_update(const void *q, const void *k, const void *v, int64_t q_str
       c.t.k_len = pr.k_len;
       c.t.k_pos0 = pr.k_pos0;
       c.t.out_row0 = c.t.q_tok0;  // the running rows are the query's own token rows
-      c.t.aux = 0;
       c.cost = tile_cost(c.t);
       if (c.cost > 0) tiles.push_back(c);  // a block that sees no key leaves its rows as they are
     }
@@ -708,7 +705,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
     if (seq_skip && seq_skip[s]) continue;
     const int32_t L = cu[s + 1] - cu[s];
     for (int32_t j0 = 0; j0 < L; j0 += bnk) {
-      CostTile c;
+      CostTile c{};
       c.t.k_tok0 = cu[s] + j0;
       c.t.k_len = std::min(bnk, L - j0);
       c.t.k_pos0 = j0;
@@ -716,7 +713,6 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
       c.t.q_rows = L - j0;
       c.t.q_pos0 = j0;
       c.t.out_row0 = cu[s] + j0;
-      c.t.aux = 0;
       c.cost = (c.t.q_rows + 63) / 64;
       kt.push_back(c);
     }
@@ -758,10 +754,10 @@ static void plan_pairs_bwd(const zp_pair *pairs, int n_pairs, int bmq, int bnk, 
   for (int i = 0; i < n_pairs; i++) {
     const zp_pair &pr = pairs[i];
     for (int32_t r0 = 0; r0 < pr.q_len; r0 += bmq) {
-      CostTile c;
+      CostTile c{};
       c.t.q_tok0 = pr.q_tok0 + r0; c.t.q_rows = std::min(bmq, pr.q_len - r0); c.t.q_pos0 = pr.q_pos0 + r0;
       c.t.k_tok0 = pr.k_tok0; c.t.k_len = pr.k_len; c.t.k_pos0 = pr.k_pos0;
-      c.t.out_row0 = c.t.q_tok0; c.t.aux = 0;
+      c.t.out_row0 = c.t.q_tok0;
       c.cost = tile_cost(c.t);
       if (c.cost > 0) qt.push_back(c);
     }
@@ -769,10 +765,10 @@ static void plan_pairs_bwd(const zp_pair *pairs, int n_pairs, int bmq, int bnk, 
       // first query row of the chunk that sees the block's first key
       const int32_t off = std::max(0, pr.k_pos0 + j0 - pr.q_pos0);
       if (off >= pr.q_len) continue;
-      CostTile c;
+      CostTile c{};
       c.t.k_tok0 = pr.k_tok0 + j0; c.t.k_len = std::min(bnk, pr.k_len - j0); c.t.k_pos0 = pr.k_pos0 + j0;
       c.t.q_tok0 = pr.q_tok0 + off; c.t.q_rows = pr.q_len - off; c.t.q_pos0 = pr.q_pos0 + off;
-      c.t.out_row0 = c.t.k_tok0; c.t.aux = 0;
+      c.t.out_row0 = c.t.k_tok0;
       c.cost = (c.t.q_rows + 63) / 64;
       kt.push_back(c);
     }

@@ -26,7 +26,7 @@ struct zp_tile {
   int32_t k_len;     // keys in the run
   int32_t k_pos0;    // position of the first key inside the sequence
   int32_t out_row0;  // first output row (packed token, or partial-result row)
-  int32_t aux;       // kernel specific
+  int32_t unused;    // a record is 32 bytes
 };
 
 // n / d for a wave-uniform n (any 32-bit value) on the scalar unit; m = zp_div_magic(d). The estimate falls short by one at
@@ -44,7 +44,7 @@ template <class P>
 __device__ __forceinline__ zp_tile zp_load_tile(P p) {
   zp_tile t;
 #define ZP_U(f) t.f = __builtin_amdgcn_readfirstlane(p->f)
-  ZP_U(q_tok0); ZP_U(q_rows); ZP_U(q_pos0); ZP_U(k_tok0); ZP_U(k_len); ZP_U(k_pos0); ZP_U(out_row0); ZP_U(aux);
+  ZP_U(q_tok0); ZP_U(q_rows); ZP_U(q_pos0); ZP_U(k_tok0); ZP_U(k_len); ZP_U(k_pos0); ZP_U(out_row0);
 #undef ZP_U
   return t;
 }
