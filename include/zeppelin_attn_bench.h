@@ -13,14 +13,14 @@
 extern "C" {
 #endif
 
-/* Measurement aid: enqueues a register-only loop of bf16 MFMAs (256 workgroups x 4 waves, iters * 32 instructions of
- * 32x32x16 per wave = 256 * 4 * iters * 32 * 32768 flop in total) with all-zero (random_operands = 0) or random
+/* Measurement aid: enqueues a register-only loop of the bf16 MFMA the attention kernels use (256 workgroups x 4 waves,
+ * iters * 64 instructions of 16x16x32 per wave = 256 * 4 * iters * 64 * 16384 flop in total) with all-zero (random_operands = 0) or random
  * operand values, so a caller that times the launch learns the MFMA rate the chip sustains on such data: the clock
  * held under random operands is lower than under zeros. out: device, ZP_MFMA_PROBE_OUT_BYTES bytes, overwritten.
  * iters in [1, 2^22]. Returns -1 on a null or misaligned pointer or iters out of range,
  * else the hipError_t of the launch (0 = success). */
 #define ZP_MFMA_PROBE_OUT_BYTES 262144
-#define ZP_MFMA_PROBE_FLOP_PER_ITER 1073741824.0 /* 256 * 4 * 32 * 32768 */
+#define ZP_MFMA_PROBE_FLOP_PER_ITER 1073741824.0 /* 256 * 4 * 64 * 16384 */
 int zp_mfma_probe(float *out, int32_t iters, int32_t random_operands, void *stream);
 
 /* Measurement aid: per-kernel durations from hipEvents recorded on the launch stream.

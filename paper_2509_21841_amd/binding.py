@@ -356,7 +356,7 @@ def accum_to_bf16(src, dst=None, stream=None):
     return dst
 
 
-MFMA_PROBE_FLOP_PER_ITER = 256.0 * 4 * 32 * 32768.0
+MFMA_PROBE_FLOP_PER_ITER = 256.0 * 4 * 64 * 16384.0
 
 
 BENCH_LIB_PATH = os.path.join(_HERE, "libzeppelin_bench.so")

@@ -1,5 +1,5 @@
-// Device probe: the bf16 MFMA rate this chip sustains on register-resident operands, with all-zero or with
-// random (sign, exponent, mantissa) operand values. The clock the chip holds depends on the switching power of
+// Device probe: the rate this chip sustains on register-resident operands with the instruction of the attention kernels,
+// the 16x16x32 bf16 MFMA, with all-zero or with random (sign, exponent, mantissa) operand values. The clock the chip holds depends on the switching power of
 // the data, so the second figure, not the nominal peak, is what a kernel working on N(0,1) inputs can approach.
 // Built into its own small library (libzeppelin_bench.so): a measurement aid, not part of the engine.
 #include "zp_common.h"
@@ -27,28 +27,26 @@ __global__ __launch_bounds__(256) void mfma_probe_kernel(float *out, int iters, 
     a[j] = __builtin_bit_cast(bf16x8, ua);
     b[j] = __builtin_bit_cast(bf16x8, ub);
   }
-  f32x16 acc[4];
+  f32x4 acc[8];
 #pragma unroll
-  for (int c = 0; c < 4; c++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) acc[c][r] = 0.f;
+  for (int c = 0; c < 8; c++) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int it = 0; it < iters; it++) {
 #pragma unroll
     for (int u = 0; u < 8; u++)
 #pragma unroll
-      for (int c = 0; c < 4; c++)
-        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[(u + c) & 3], b[u & 3], acc[c], 0, 0, 0);
+      for (int c = 0; c < 8; c++)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[(u + c) & 3], b[u & 3], acc[c], 0, 0, 0);
   }
   float s = 0.f;
 #pragma unroll
-  for (int c = 0; c < 4; c++)
+  for (int c = 0; c < 8; c++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) s += acc[c][r];
+    for (int r = 0; r < 4; r++) s += acc[c][r];
   out[blockIdx.x * 256 + threadIdx.x] = s;
 }
 }  // namespace
 
-// 256 workgroups of 4 waves; each wave issues iters * 32 MFMAs of 32x32x16 (32768 flop each).
+// 256 workgroups of 4 waves; each wave issues iters * 64 MFMAs of 16x16x32 (16384 flop each).
 extern "C" int zp_mfma_probe(float *out, int32_t iters, int32_t random_operands, void *stream) {
   if (!out || ((uintptr_t)out & 15) || iters < 1 || iters > (1 << 22)) return -1;
   hipLaunchKernelGGL(mfma_probe_kernel, dim3(256), dim3(256), 0, (hipStream_t)stream, out, iters, random_operands ? 1 : 0);
