@@ -12,10 +12,11 @@ from util import Checks, assert_close, widen
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-# The first keys of a short sequence have a handful of terms dS_ij q_i, the largest about 8, whose bf16 operand carries
-# 2^-9 of it (1.6e-2): two of them and the output's half-spacing (7.8e-3 below 4) make 4e-2. Small tensors have little to
-# average over, so the relative-L2 bound is three times the stated one (a wrong mask or index is of order one in both).
-MAXABS, RELL2 = 4e-2, 1.5e-2
+# The first keys of a sequence have a handful of terms dS_ij q_i, the largest about 8, whose bf16 operand carries 2^-9 of it
+# (1.6e-2): two of them and the output's half-spacing (7.8e-3 below 4) make 4e-2. The relative-L2 bound is the stated one;
+# batches of sequences under 200 tokens have little to average over and get three times that (a wrong mask or index is of
+# order one in both).
+MAXABS, RELL2 = 4e-2, 5e-3
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -30,7 +31,7 @@ def test_small_batches(lengths, Hq, Hkv, d):
     ref = oracle.varlen_attn_bwd(widen(do), widen(q), widen(k), widen(v), cu)
     checks = Checks()
     for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
-        checks.close(name, widen(a), b, maxabs=MAXABS, rell2=RELL2)
+        checks.close(name, widen(a), b, maxabs=MAXABS, rell2=RELL2 if min(lengths) >= 200 else 3 * RELL2)
     checks.finish()
     again = B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
     for a, b in zip(got, again):
@@ -46,16 +47,19 @@ def test_small_batches(lengths, Hq, Hkv, d):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [1, 8, 24, 40, 48, 64, 96])
 def test_both_sides_of_the_rule(n, d):
-    """n sequences of 300 tokens under 2 KV heads: the first one's gradients do not depend on which kernel the batch
-    takes beyond the order of the float sums."""
+    """n sequences of 300 tokens under 2 KV heads: the first and the last one's gradients do not depend on which kernel the
+    batch takes beyond the order of the float sums."""
     L, Hq, Hkv = 300, 4, 2
     q, k, v, do = synth.make_qkv(L * n, Hq, Hkv, d, 103, DEV, with_dout=True)
     cu = synth.cu_seqlens([L] * n)
     o, lse = B.varlen_attn_fwd(q, k, v, cu)
     got = B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
-    ref = oracle.varlen_attn_bwd(widen(do[:L]), widen(q[:L]), widen(k[:L]), widen(v[:L]), synth.cu_seqlens([L]))
-    for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
-        assert_close(name, widen(a[:L]), b, maxabs=MAXABS, rell2=RELL2)
+    for sl in [slice(0, L)] + [slice(L * n - L, L * n)] * (n > 1):
+        ref = oracle.varlen_attn_bwd(widen(do[sl]), widen(q[sl]), widen(k[sl]), widen(v[sl]), synth.cu_seqlens([L]))
+        for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+            assert_close(name, widen(a[sl]), b, maxabs=MAXABS, rell2=RELL2)
+    if n <= 8 or n >= 40:
+        assert dkdv_labels(do, q, k, v, o, lse, cu) == {"attn_bwd_dkdv_split" if n <= 8 else "attn_bwd_dkdv"}
 
 
 def dkdv_labels(*call):

@@ -30,8 +30,30 @@ PROFILES = {
     "steps": lambda i: 40.0 * (i // 32 % 3) - 60.0,                 # up and down by 40 within and between tiles
     "falling": lambda i: -0.3 * i,
     "one-peak": lambda i: np.where(i == 70, 80.0, -80.0),
-    "just-over": lambda i: np.where(i % 64 < 32, 0.0, 8.4),         # around the sum that moves the reference (4096)
+    # a lane's 16 probabilities of every tile behind the first near the sum that moves the reference (16 e^5.545 = 4096):
+    # the row's own level is 2.5 % of the score wide, so that all rows stay under it, or all pass it
+    "just-under": lambda i: np.where(i < 64, 0.0, 5.0),
+    "just-over": lambda i: np.where(i < 64, 0.0, 6.2),
 }
+
+
+def second_tile_sums(q, k):
+    """[Hq, rows from 128 on, 4]: sums of a row's four lanes over their keys of the second tile (keys 4 l .. 4 l + 3 of every
+    16), against the row's maximum over the first tile."""
+    L, Hq, d = q.shape
+    grp = Hq // k.shape[1]
+    qq, kk = widen(q)[128:], widen(k)[:128]
+    s = np.stack([qq[:, h] @ kk[:, h // grp].T for h in range(Hq)]) * d ** -0.5
+    p = np.exp(s[:, :, 64:] - s[:, :, :64].max(-1, keepdims=True))
+    return p.reshape(Hq, L - 128, 4, 4, 4).sum((2, 4))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_profiles_around_the_limit(d):
+    for profile, inside in (("just-under", True), ("just-over", False)):
+        q, k, _ = inputs(333, 4, 2, d, 71, PROFILES[profile])
+        sums = second_tile_sums(q, k)
+        assert (sums < 4050).all() and sums.max() > 3000 if inside else (sums > 4150).all() and sums.min() < 5500
 
 
 @pytest.mark.parametrize("d", [64, 128])
