@@ -299,7 +299,7 @@ def measure(job, steps: int, warmup: int):
     B.profile_enable(False)
     by = {}
     for label, ms in recs:
-        # the dK/dV of launches that leave most of the chip idle is the same work as the others'
+        # the same work by the kernel for launches that leave most of the chip idle
         by.setdefault("attn_bwd_dkdv" if label == "attn_bwd_dkdv_split" else label, []).append(ms)
     kern = {k: {"launches_per_step": len(v) // steps, "avg_ms": float(np.mean(v)), "ms_per_step": float(np.sum(v)) / steps}
             for k, v in by.items()}

@@ -649,7 +649,7 @@ __device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2
 // workgroup's 128 V rows are staged once. The wave's LDS, vector, scalar and wait instructions issue in line with its
 // MFMAs; a second wave on the SIMD, from a workgroup that meets its own barriers, runs under all of that.
 //
-// Bound: the power limit and vector issue. One box, this kernel against the two it replaces (32x32x16 MFMA; one wave per
+// Bound: the power limit and vector issue. On one card, this kernel against the two it replaces (32x32x16 MFMA; one wave per
 // SIMD with K and V in registers for long sequences, this split with an XOR per LDS read for short ones): 128K
 // long-tail GQA batch 25.17 -> 22.97 ms, four 16384-token sequences 15.49 -> 14.22, 64K lognormal MHA 2.70 -> 2.39,
 // 64 x 1K MHA 1.45 -> 1.29. The one-wave form on the 16x16x32 MFMA took 24.9 ms on the long-tail batch; with an XOR for
@@ -806,10 +806,10 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 }
 
 // dK, dV of a launch that leaves most of the chip idle: a workgroup owns 32 key rows instead of 128 and its four waves go
-// through the (query tile, head) iterations by turns, each with staging buffers of its own (145 KB of LDS in all at
+// through the (query tile, head) iterations by turns, each with staging buffers of its own (148.5 KB of LDS in all at
 // D = 128) and no barrier in the loop; their accumulators are added up at the end, through LDS, in wave order. Four times
 // the workgroups, a quarter of the serial chain. 1218 tokens, GQA 4/2, d = 128: 32 us with 128 key rows per workgroup
-// (22 iterations one after the other on 32 of 256 CUs), 17 us with 32. See dkdv_split_is_faster for when it is used.
+// (22 iterations one after the other in 24 workgroups), 17 us with 32. See dkdv_split_is_faster for when it is used.
 template <int D>
 __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
   constexpr int QT = 32;

@@ -30,7 +30,7 @@ constexpr float P_SUM_MAX = 4096.0f;
 // address unit behind the copies of the other waves.
 //
 // Bound: the power limit. The 16x16x32 MFMA accumulates twice as many products per accumulator access as the 32x32x16;
-// a register-only loop on random operands holds 1920-2000 TFLOP/s with it against 1520-1800, at the price of twice the
+// a register-only loop on random operands holds 1885-1956 TFLOP/s with it (zp_mfma_probe) against 1520-1800, at the price of twice the
 // issue slots. On four 16384-token sequences (GQA 32/8, d = 128) the 32x32x16 form of this kernel took 7.66 ms and
 // this one takes 7.11 (on zeros, where power does not bind, 5.72 and 5.91: it issues more and waits more).
 //

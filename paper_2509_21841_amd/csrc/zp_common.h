@@ -61,7 +61,7 @@ struct zp_inline_tiles {
   zp_tile t[ZP_INLINE_TILES];
 };
 
-// How a launch hands its work items to workgroups. The XCDs of a chip do not run equally fast (on the boxes measured
+// How a launch hands its work items to workgroups. The XCDs of a chip do not run equally fast (on the cards measured
 // the same four finish an equal share 4-8 % later than the other four), and the hardware deals workgroups to them
 // round-robin, so with one item per workgroup the fast ones idle at the end. Items 0 .. n_static-1 are therefore taken
 // by number (workgroup b runs item b, on XCD b % 8, no cost), and the last ones -- the cheapest of the launch -- are

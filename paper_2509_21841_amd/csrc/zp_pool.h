@@ -1,9 +1,9 @@
 // Pool of host staging buffers for descriptor uploads, written against a small backend interface so that the slot
-// state machine can be exercised on the CPU with several threads (the library plugs in pinned memory and hipEvents).
+// state machine can be exercised on the CPU with several threads (the library plugs in pinned memory and flags in it).
 //
-// A slot is FREE, RESERVED (handed to one caller, who is filling it; its event has not been recorded for this use and
-// must not be queried) or IN_FLIGHT (the copy that reads it has been enqueued and its event recorded; the slot becomes
-// free again once that event has completed). Only FREE slots, and IN_FLIGHT slots whose event has completed, are handed
+// A slot is FREE, RESERVED (handed to one caller, who is filling it; its event says nothing about this use and must not be
+// queried) or IN_FLIGHT (the copy that reads it has been enqueued; the slot becomes free again once its event is done: an
+// event recorded behind the copy, or a flag that the copy sets itself). Only FREE slots, and IN_FLIGHT slots whose event has completed, are handed
 // out, so two threads never fill the same buffer.
 #pragma once
 #include <cstddef>
