@@ -163,10 +163,7 @@ def _on(stream):
     return torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream))
 
 
-def _is_capturing(stream, ptr: int) -> bool:
-    """Whether `stream`, whose hipStream_t is ptr, is capturing (the default stream never is)."""
-    if ptr == 0:
-        return False
+def _is_capturing(stream) -> bool:
     if stream is None:
         return torch.cuda.is_current_stream_capturing()
     with _on(stream):
@@ -182,7 +179,7 @@ def workspace(nbytes: int, device, tag: str = "default", stream=None) -> torch.T
     is torch.cuda.graph's pool; calls captured by other means have to bring their own ws.)"""
     ptr = _stream_ptr(stream)
     key = (device, tag, ptr)
-    capturing = _is_capturing(stream, ptr)
+    capturing = ptr != 0 and _is_capturing(stream)   # the default stream cannot be captured
     t = None if capturing else _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
         with _on(stream):
