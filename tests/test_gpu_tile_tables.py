@@ -210,3 +210,19 @@ def test_a_graph_outlives_the_scratch_of_its_stream():
                 assert torch.equal(bits(a), bits(b)), rep
     for t in others:
         assert bool((t == 0x5A).all())
+
+
+def test_scratch_of_a_given_stream_is_allocated_for_it():
+    """stream= other than the current one: the cached scratch belongs to that stream for the allocator too, so that one which
+    is outgrown is handed out again only behind the calls that still use it."""
+    side = torch.cuda.Stream()
+    lengths = [130] * 64
+    q, k, v = synth.make_qkv(sum(lengths), 4, 2, 64, 111, DEV)
+    want = B.varlen_attn_fwd(q, k, v, synth.cu_seqlens(lengths))
+    side.wait_stream(torch.cuda.current_stream())
+    got = B.varlen_attn_fwd(q, k, v, synth.cu_seqlens(lengths), stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(got[0]), bits(want[0])) and torch.equal(bits(got[1]), bits(want[1]))
+    at = B.workspace(1, q.device, "fwd", side).data_ptr()
+    owner = [s["stream"] for s in torch.cuda.memory_snapshot() if s["address"] <= at < s["address"] + s["total_size"]]
+    assert owner == [side.cuda_stream]
