@@ -21,6 +21,19 @@ struct FwdCfg {
 // The partial sum of a lane's probabilities of a tile above which the reference maximum of its rows has to move.
 constexpr float P_SUM_MAX = 4096.0f;
 
+// A row's reference is worked out anew where `far` has one of its four lanes; m: this lane's largest score of the tile.
+// Returns what the row's sums are multiplied by. A row that has seen no key yet keeps waiting (nm = +inf).
+__device__ __forceinline__ float fwd_move_reference(uint64_t far, float m, float c_log2, float &nm) {
+  m = zp_quad_max(m) * c_log2;
+  uint32_t rows = (uint32_t)far | (uint32_t)(far >> 32);  // the four lanes of a row are 16 apart
+  rows = ((rows | rows >> 16) & 0xffff) * 0x10001u;
+  const bool moves = __builtin_amdgcn_inverse_ballot_w64((uint64_t)rows << 32 | rows);
+  const float mc_old = -nm, mc = moves ? fmaxf(mc_old, m) : mc_old;
+  const float alpha = mc == -INFINITY ? 1.0f : zp_exp2(mc_old - mc);
+  nm = -mc;
+  return alpha;
+}
+
 // One 64-key tile for one wave of two 16-query sub-blocks. Kb, Vb: byte offsets of the K and V tile from the LDS base
 // that the lane offsets in `lo` carry (compile-time at the call sites, so every read is a register plus an immediate).
 // ONLY1: no query of sub-block 0 sees a key of this tile. Both products run as fenced steps of one LDS operand and the
@@ -108,20 +121,13 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
       for (int kb = 0; kb < 4; kb++)
 #pragma unroll
         for (int r = 0; r < 4; r++) m = fmaxf(m, s[qb][kb][r]);
-      m = zp_quad_max(m) * c_log2;
-      uint32_t rows = (uint32_t)far[qb] | (uint32_t)(far[qb] >> 32);  // the four lanes of a row are 16 apart
-      rows = ((rows | rows >> 16) & 0xffff) * 0x10001u;
-      const bool moves = __builtin_amdgcn_inverse_ballot_w64((uint64_t)rows << 32 | rows);
-      const float mc_old = -nm[qb], mc = moves ? fmaxf(mc_old, m) : mc_old;
-      const bool none = mc == -INFINITY;  // no key seen yet: keep waiting, every probability of this tile is zero
-      const float alpha = none ? 1.0f : zp_exp2(mc_old - mc);
-      nm[qb] = -mc;
+      const float alpha = fwd_move_reference(far[qb], m, c_log2, nm[qb]);
       l_sum[qb] *= alpha;
 #pragma unroll
       for (int i = 0; i < DB; i++)
 #pragma unroll
         for (int r = 0; r < 4; r++) o_acc[qb][i][r] *= alpha;
-      take(qb, none ? 0.f : -mc);
+      take(qb, nm[qb] == INFINITY ? 0.f : nm[qb]);  // no key seen yet: every probability of this tile is zero
     }
   }
 #pragma unroll
@@ -136,6 +142,59 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
     if constexpr (n + 3 < 2 * DB) va[n + 3] = lo.tr_at(Vb, (n + 3) / DB, (n + 3) % DB);
   });
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// Normalises and writes O and LSE of a wave's QB sub-blocks of 16 rows (rb: their first rows in the block). own: LDS of the
+// wave's own for zp_store_rows.
+template <int D, bool PARTIAL, int QB>
+__device__ __forceinline__ void fwd_finish(const zp_attn_params &p, const zp_tile &t, int h, int lane, const int (&rb)[QB],
+                                           const f32x4 (&o_acc)[QB][D / 16], const float (&nm)[QB], const float (&l_sum)[QB], char *own) {
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+#pragma unroll
+  for (int qb = 0; qb < QB; qb++) {
+    const int row = rb[qb] + c16;
+    const float l_tot = zp_quad_sum(l_sum[qb]);
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    float lse = -INFINITY;
+    {
+#pragma clang fp contract(off)  // one rounding more or less from kernel to kernel otherwise
+      if (l_tot > 0.f) lse = __logf(l_tot) - nm[qb] * 0.6931471805599453f;
+    }
+    const int64_t orow = (int64_t)t.out_row0 + row;
+    if (PARTIAL) {
+      if (row >= t.q_rows) continue;
+      // weights of the running row (w_old) and of this partial (w_new, its 1/l folded in); without update: 0 and 1/l
+      float w_old = 0.f, w_new = inv, lse_out = lse;
+      if (p.update) {
+        const float lse_old = p.lse[(int64_t)h * p.lse_stride + orow];
+        const float mx = fmaxf(lse_old, lse);
+        if (mx == -INFINITY) {
+          w_new = 0.f;
+        } else {
+          const float e_old = __expf(lse_old - mx), e_new = __expf(lse - mx);
+          const float tot = e_old + e_new;
+          lse_out = mx + __logf(tot);
+          w_old = e_old / tot;
+          w_new = e_new / tot * inv;
+        }
+      }
+      if (q4 == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse_out;
+      float *op = (float *)p.o + orow * p.o_stride + (int64_t)h * D + q4;
+#pragma unroll
+      for (int db = 0; db < D / 16; db++) {
+        f32x4 v4 = {o_acc[qb][db][0] * w_new, o_acc[qb][db][1] * w_new, o_acc[qb][db][2] * w_new, o_acc[qb][db][3] * w_new};
+        if (w_old > 0.f) {  // a row that has seen no key yet may hold anything
+          const f32x4 old = *(const f32x4 *)(op + db * 16);
+          v4[0] += w_old * old[0]; v4[1] += w_old * old[1]; v4[2] += w_old * old[2]; v4[3] += w_old * old[3];
+        }
+        *(f32x4 *)(op + db * 16) = v4;
+      }
+    } else {
+      if (q4 == 0 && row < t.q_rows) p.lse[(int64_t)h * p.lse_stride + orow] = lse;
+      zp_store_rows<D>(own, o_acc[qb], inv, (__bf16 *)p.o + ((int64_t)t.out_row0 + rb[qb]) * p.o_stride + (int64_t)h * D,
+                       p.o_stride, t.q_rows - rb[qb], lane);
+    }
+  }
 }
 
 // Two workgroups per CU at head dimension 128 (64 KB of LDS, up to 256 registers), three at 64 (32 KB, up to 168: 8
@@ -255,46 +314,276 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
     if (it + 1 < n_kt) key_tile(it + 1, std::integral_constant<int, 1>{});
   }
 
-  // epilogue: normalise, write O and LSE
-#pragma unroll
-  for (int qb = 0; qb < 2; qb++) {
-    const float l_tot = zp_quad_sum(l_sum[qb]);
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    const float lse = l_tot > 0.f ? (__logf(l_tot) - nm[qb] * 0.6931471805599453f) : -INFINITY;
-    const int64_t orow = (int64_t)t.out_row0 + row[qb];
-    if (PARTIAL) {
-      if (row[qb] >= t.q_rows) continue;
-      // weights of the running row (w_old) and of this partial (w_new, its 1/l folded in); without update: 0 and 1/l
-      float w_old = 0.f, w_new = inv, lse_out = lse;
-      if (p.update) {
-        const float lse_old = p.lse[(int64_t)h * p.lse_stride + orow];
-        const float mx = fmaxf(lse_old, lse);
-        if (mx == -INFINITY) {
-          w_new = 0.f;
-        } else {
-          const float e_old = __expf(lse_old - mx), e_new = __expf(lse - mx);
-          const float tot = e_old + e_new;
-          lse_out = mx + __logf(tot);
-          w_old = e_old / tot;
-          w_new = e_new / tot * inv;
-        }
-      }
-      if (q4 == 0) p.lse[(int64_t)h * p.lse_stride + orow] = lse_out;
-      float *op = (float *)p.o + orow * p.o_stride + (int64_t)h * D + q4;
-#pragma unroll
-      for (int db = 0; db < D / 16; db++) {
-        f32x4 v4 = {o_acc[qb][db][0] * w_new, o_acc[qb][db][1] * w_new, o_acc[qb][db][2] * w_new, o_acc[qb][db][3] * w_new};
-        if (w_old > 0.f) {  // a row that has seen no key yet may hold anything
-          const f32x4 old = *(const f32x4 *)(op + db * 16);
-          v4[0] += w_old * old[0]; v4[1] += w_old * old[1]; v4[2] += w_old * old[2]; v4[3] += w_old * old[3];
-        }
-        *(f32x4 *)(op + db * 16) = v4;
-      }
+  fwd_finish<D, PARTIAL, 2>(p, t, h, lane, rb, o_acc, nm, l_sum, smem + w * ZP_ROWS_LDS);
+}
+
+// ---- launches that leave much of the chip idle: two waves per 16 query rows ---------------------------------------
+// The score wave of a pair: softmax arithmetic of a tile (SM, s -> pn; 2: masked) with the score product of the next one (SC:
+// K at lk, into sn) spread over it. Returns the lanes whose rows' reference moved; their O is then to be multiplied by alpha.
+// What a row computes, and in which order, is what fwd_tile computes: the results are the same bits.
+// ahead: the first K operands, requested by the step before; on return those of the tile behind (lk moves there by `step`).
+constexpr int PAIR_KA = 4;
+template <int D, int SM, bool SC>
+__device__ __forceinline__ uint64_t fwd_pair_scores(const bf16x8 (&qreg)[D / 32], bf16x8 (&pn)[2], f32x4 (&s)[4], f32x4 (&sn)[4], float &nm,
+                                                    float &l_sum, float &alpha, float c_log2, int j0, int q4, int nvis_lane,
+                                                    zp_pad16_addr<D> &lk, bf16x8 (&ahead)[PAIR_KA], int step) {
+  constexpr int N = SC ? 4 * (D / 32) : 0, KA = PAIR_KA, EP = N ? N : 1;
+  constexpr int LEAD = SC ? 0 : 18;  // steps of the softmax arithmetic in front of the first MFMA
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[N + KA];
+  if constexpr (SC)
+    for (int n = 0; n < KA; n++) a[n] = ahead[n];
+  float ta = 0.f, tb = 0.f, x[16];
+  // step e: element e's fma, e - 1's exp2, e - 2's sum and conversion
+  auto stage = [&](auto ee, auto st) {
+    constexpr int e = decltype(ee)::value, kb = e / 4, r = e % 4;
+    if constexpr (SM == 0 || e < 0 || e >= 16) return;
+    else if constexpr (decltype(st)::value == 0) {
+      if (SM == 2 && j0 + 16 * kb + q4 + r >= nvis_lane) s[kb][r] = -INFINITY;
+      x[e] = __builtin_fmaf(s[kb][r], c_log2, nm);
+    } else if constexpr (decltype(st)::value == 1) {
+      x[e] = zp_exp2(x[e]);
     } else {
-      if (q4 == 0 && row[qb] < t.q_rows) p.lse[(int64_t)h * p.lse_stride + orow] = lse;
-      zp_store_rows<D>(smem + w * ZP_ROWS_LDS, o_acc[qb], inv, (__bf16 *)p.o + ((int64_t)t.out_row0 + rb[qb]) * p.o_stride + (int64_t)h * D,
-                       p.o_stride, t.q_rows - rb[qb], lane);
+      if (kb & 1) tb += x[e]; else ta += x[e];
+      pn[kb >> 1][(kb & 1) * 4 + r] = (__bf16)x[e];
     }
+  };
+  auto arith = [&](auto from, auto to) {
+    zp_static_for<decltype(to)::value - decltype(from)::value>([&](auto i) {
+      constexpr int e = decltype(from)::value + decltype(i)::value;
+      stage(std::integral_constant<int, e>{}, std::integral_constant<int, 0>{});
+      stage(std::integral_constant<int, e - 1>{}, std::integral_constant<int, 1>{});
+      stage(std::integral_constant<int, e - 2>{}, std::integral_constant<int, 2>{});
+    });
+  };
+  __builtin_amdgcn_sched_barrier(0);
+  arith(std::integral_constant<int, 0>{}, std::integral_constant<int, LEAD>{});
+  zp_static_for<N>([&](auto nn) {
+    constexpr int n = nn.value;
+    __builtin_amdgcn_sched_barrier(0);
+    sn[n % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], qreg[n / 4], n / 4 == 0 ? zero : sn[n % 4], 0, 0, 0);
+    if constexpr (n + KA < N) a[n + KA] = lk.rows(0, (n + KA) % 4, (n + KA) / 4);
+    else {
+      if constexpr (n + KA == N) lk.move_rows(step);
+      ahead[n + KA - N] = lk.rows(0, (n + KA - N) % 4, (n + KA - N) / 4);
+    }
+    arith(std::integral_constant<int, LEAD + n * (18 - LEAD) / EP>{}, std::integral_constant<int, LEAD + (n + 1) * (18 - LEAD) / EP>{});
+  });
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (SM == 0) return 0;
+  float t = ta + tb;
+  const uint64_t far = __builtin_amdgcn_ballot_w64(!(t <= P_SUM_MAX));
+  if (__builtin_expect(far != 0, 0)) {
+    float m = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 4; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) m = fmaxf(m, s[kb][r]);
+    alpha = fwd_move_reference(far, m, c_log2, nm);
+    l_sum *= alpha;
+    const float ref = nm == INFINITY ? 0.f : nm;
+    ta = tb = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 4; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const float p = zp_exp2(__builtin_fmaf(s[kb][r], c_log2, ref));
+        if (kb & 1) tb += p; else ta += p;
+        pn[kb >> 1][(kb & 1) * 4 + r] = (__bf16)p;
+      }
+    t = ta + tb;
+  }
+  l_sum += t;
+  return far;
+}
+
+// The value wave: the second product of a tile (V at lv), the probabilities p of its rows, and whether (and by what) O is
+// multiplied first. ahead, step: as above.
+template <int D>
+constexpr int PAIR_VA = D / 16;
+template <int D>
+__device__ __forceinline__ void fwd_pair_values(f32x4 (&o_acc)[D / 16], const bf16x8 (&p)[2], int moved, unsigned al, zp_pad16_addr<D> &lv,
+                                                bf16x8 (&ahead)[PAIR_VA<D>], int step) {
+  constexpr int DB = D / 16, N = 2 * DB, VA = PAIR_VA<D>;
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(moved) != 0, 0)) {
+    const float alpha = *(const ZP_LDS float *)(unsigned long long)al;
+#pragma unroll
+    for (int i = 0; i < DB; i++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) o_acc[i][r] *= alpha;
+  }
+  bf16x8 va[N];
+  for (int n = 0; n < VA; n++) va[n] = ahead[n];
+  zp_static_for<N>([&](auto nn) {
+    constexpr int n = nn.value;
+    __builtin_amdgcn_sched_barrier(0);
+    o_acc[n % DB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[n], p[n / DB], o_acc[n % DB], 0, 0, 0);
+    constexpr int v = n + VA;
+    if constexpr (v < N) va[v] = lv.cols(2 * (v / DB) * zp_pad16<D>::R16, v % DB);
+    else {
+      if constexpr (v == N) lv.move_cols(step);
+      ahead[v - N] = lv.cols(2 * ((v - N) / DB) * zp_pad16<D>::R16, (v - N) % DB);
+    }
+  });
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+constexpr int PAIR_BUFS = 4;  // staged K and V tiles: 158 KB of LDS at d = 128
+template <int D>
+constexpr size_t pair_lds() { return 2 * PAIR_BUFS * 4 * (size_t)zp_pad16<D>::R16 + 2 * 4 * 2048 + 4 * 4 * 256 + 2 * 4 * 16; }
+
+// 64 query rows per workgroup of eight waves: waves 0-3 work out the scores and probabilities of 16 rows each, waves 4-7, on
+// the same SIMDs, the second product of the same rows one tile behind them, and issue the copies. Probabilities pass through
+// LDS, two tiles' worth; one barrier per tile.
+//
+// Bound: the serial chain of a workgroup's key tiles. A wave's MFMAs, LDS reads, copies and vector operations issue one after
+// the other, so a wave alone on its SIMD takes their sum: 2450 cycles per tile with attn_fwd_kernel (32 rows per wave, d =
+// 128), 1850 with 16 rows per wave and one wave per SIMD, also when its products and arithmetic are pipelined across
+// tiles, and 1450 with two waves that share the work (1750, 1350 and 1120 at d = 64). Of these 1450 the score wave's own
+// operations are about 1200: sixteen exp2 and what goes with them 450, MFMAs and K operands 450, the rest hand-over and
+// barrier. One sequence of 4000 tokens, 4 heads: 71.4 -> 43.3 us at d = 128, 51.9 -> 33.5 at 64; 300 tokens: 10.1 -> 7.3
+// and 8.0 -> 6.1. It works on half as many rows per CU as attn_fwd_kernel at twice the LDS reads per MFMA, so that launches
+// that fill the chip are faster there: zp_plan_fwd_pair has the rule.
+template <int D, bool PARTIAL>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))) void attn_fwd_pair_kernel(zp_attn_params p) {
+  constexpr int TILEB = 4 * zp_pad16<D>::R16, NB = PAIR_BUFS;
+  typedef zp_stager<D, 4, true> stager;
+  constexpr int PW = stager::PER_WAVE;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  char *Ks = smem;                  // [NB][BN][D]: tile j in buffer j % NB
+  char *Vs = smem + NB * TILEB;     // [NB][BN][D]
+  char *Ps = smem + 2 * NB * TILEB; // [2][4][2][64 x 16 bytes]: a tile's probabilities, pair by pair
+  char *As = Ps + 2 * 4 * 2048;     // [2][4][64]: what O is multiplied by; behind them the rows' sums and references
+  char *Fs = As + 4 * 4 * 256;      // [2][4]: whether it is
+
+  int unit, hh;
+  zp_block_to_unit(blockIdx.x, p.grp, p.m_grp, unit, hh);
+  if (unit >= p.n_tiles * p.Hkv) return;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
+  const int h = g * p.grp + hh;
+  const zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+  const bool values = __builtin_amdgcn_readfirstlane(tid >> 8) != 0;
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  const int rb = 16 * w;
+  auto nvis_of = [&](int r) {
+    int n = t.q_pos0 + r - t.k_pos0 + 1;
+    return n < 0 ? 0 : (n > t.k_len ? t.k_len : n);
+  };
+  // rows behind the block's last one repeat it (and are not stored)
+  const int nvis_lane = nvis_of(min(rb + c16, t.q_rows - 1)), nvis_min = nvis_of(rb);
+  const int n_kt = (nvis_of(t.q_rows - 1) + BN - 1) / BN;              // tiles the workgroup stages
+  const int n_w = rb < t.q_rows ? (nvis_of(min(rb + 15, t.q_rows - 1)) + BN - 1) / BN : 0;  // tiles this pair's rows see
+
+  stager kst, vst;
+  kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid & 255);
+  vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid & 255);
+  static_assert(NB == 4, "the counts of copies in flight below");
+  const int n4 = min(n_kt, NB);
+  const unsigned own_p = zp_lds_addr(Ps) + w * 2048 + lane * 16, own_a = zp_lds_addr(As) + w * 256 + lane * 4, own_f = zp_lds_addr(Fs) + w * 16;
+
+  if (!values) {
+    // the block's query rows (to the buffer of V that is filled last) and K of the first NB tiles
+    {
+      stager qst;
+      qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)h * D, p.q_stride, tid);
+      qst.issue(Vs + (NB - 1) * TILEB, 0, t.q_rows);
+    }
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+      if (j < n_kt) kst.issue(Ks + j * TILEB, j * BN, t.k_len);
+    zp_pad16_addr<D> lk;  // of the K tile in hand
+    lk.init(lane, Ks);
+    float nm = INFINITY, l_sum = 0.f, alpha = 1.f;
+    const float c_log2 = p.scale_log2;
+    f32x4 s[2][4];  // scores of tile j in s[j % 2]
+    bf16x8 pb[2];
+    // the query rows and K of tile 0; behind them K of the others
+    if (n4 == 4) zp_wait_async_upto<3 * PW>();
+    else if (n4 == 3) zp_wait_async_upto<2 * PW>();
+    else if (n4 == 2) zp_wait_async_upto<PW>();
+    else zp_wait_async();
+    __syncthreads();
+    bf16x8 qreg[D / 32], ahead[PAIR_KA];
+#pragma unroll
+    for (int kk = 0; kk < D / 32; kk++) {
+      const unsigned at = lk.row[kk & 1] + (unsigned)((2 * NB - 1) * TILEB + w * zp_pad16<D>::R16 + (kk >> 1) * 128);
+      qreg[kk] = *(const ZP_LDS bf16x8 *)(unsigned long long)at;
+    }
+#pragma unroll
+    for (int n = 0; n < PAIR_KA; n++) ahead[n] = lk.rows(0, n % 4, n / 4);
+    if (n_w > 0) {
+      int no_step = 0;
+      fwd_pair_scores<D, 0, true>(qreg, pb, s[0], s[0], nm, l_sum, alpha, c_log2, 0, q4, nvis_lane, lk, ahead, no_step);
+    }
+    lk.move_rows(TILEB);
+    zp_wait_async();
+    auto key_tile = [&](int it, auto PAR) {
+      constexpr int par = decltype(PAR)::value;
+      // K of tile it + 2 and what the value wave needs next have landed; the value wave is done with the probabilities two
+      // tiles back
+      __syncthreads();
+      if (it == 0) {
+#pragma unroll
+        for (int n = 0; n < PAIR_KA; n++) ahead[n] = lk.rows(0, n % 4, n / 4);
+      }
+      if (it < n_w) {
+        uint64_t far;
+        const int j0 = it * BN, step = ((it + 1) & (NB - 1)) == NB - 1 ? -(NB - 1) * TILEB : TILEB;
+        if (it + 1 >= n_w) far = fwd_pair_scores<D, 2, false>(qreg, pb, s[par], s[par ^ 1], nm, l_sum, alpha, c_log2, j0, q4, nvis_lane, lk, ahead, step);
+        else if (j0 + BN > nvis_min) far = fwd_pair_scores<D, 2, true>(qreg, pb, s[par], s[par ^ 1], nm, l_sum, alpha, c_log2, j0, q4, nvis_lane, lk, ahead, step);
+        else far = fwd_pair_scores<D, 1, true>(qreg, pb, s[par], s[par ^ 1], nm, l_sum, alpha, c_log2, j0, q4, nvis_lane, lk, ahead, step);
+        *(ZP_LDS bf16x8 *)(unsigned long long)(own_p + par * 4 * 2048) = pb[0];
+        *(ZP_LDS bf16x8 *)(unsigned long long)(own_p + par * 4 * 2048 + 1024) = pb[1];
+        *(ZP_LDS int *)(unsigned long long)(own_f + par * 64) = far != 0;
+        if (far != 0) *(ZP_LDS float *)(unsigned long long)(own_a + par * 1024) = alpha;
+      }
+    };
+    for (int it = 0; it < n_kt; it += 2) {
+      key_tile(it, std::integral_constant<int, 0>{});
+      if (it + 1 < n_kt) key_tile(it + 1, std::integral_constant<int, 1>{});
+    }
+    *(ZP_LDS float *)(unsigned long long)(own_a + 2048) = l_sum;
+    *(ZP_LDS float *)(unsigned long long)(own_a + 3072) = nm;
+    __syncthreads();  // the last tile's probabilities, the rows' sums and references
+  } else {
+#pragma unroll
+    for (int j = 0; j < NB - 1; j++)
+      if (j < n_kt) vst.issue(Vs + j * TILEB, j * BN, t.k_len);
+    zp_pad16_addr<D> lv;  // of the V tile in hand
+    lv.init(lane, Vs);
+    f32x4 o_acc[1][D / 16];
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) o_acc[0][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();  // (the score waves' first product)
+    bf16x8 ahead[PAIR_VA<D>];
+    for (int it = 0; it <= n_kt; it++) {
+      // V of tile it and K of it + 2 have landed (behind them V of it + 1 and K of it + 3), the probabilities of tile it - 1
+      // are there; everybody is done with K of tile it and V of it - 2
+      if (it + 3 < n_kt) zp_wait_async_upto<2 * PW>();
+      else if (it + 1 < n_kt) zp_wait_async_upto<PW>();
+      else zp_wait_async();
+      __syncthreads();
+      const unsigned par = (it - 1) & 1;
+      bf16x8 pr[2];
+      int moved;
+      if (it > 0) {
+        moved = *(const ZP_LDS int *)(unsigned long long)(own_f + par * 64);
+        pr[0] = *(const ZP_LDS bf16x8 *)(unsigned long long)(own_p + par * 4 * 2048);
+        pr[1] = *(const ZP_LDS bf16x8 *)(unsigned long long)(own_p + par * 4 * 2048 + 1024);
+      } else {
+#pragma unroll
+        for (int n = 0; n < PAIR_VA<D>; n++) ahead[n] = lv.cols(2 * (n / (D / 16)) * zp_pad16<D>::R16, n % (D / 16));
+      }
+      if (it + NB < n_kt) kst.issue(Ks + (it & (NB - 1)) * TILEB, (it + NB) * BN, t.k_len);
+      if (it > 0 && it - 2 + NB < n_kt) vst.issue(Vs + ((it - 2) & (NB - 1)) * TILEB, (it - 2 + NB) * BN, t.k_len);
+      if (it > 0 && it <= n_w)
+        fwd_pair_values<D>(o_acc[0], pr, moved, own_a + par * 1024, lv, ahead, ((it - 1) & (NB - 1)) == NB - 1 ? -(NB - 1) * TILEB : TILEB);
+    }
+    const float l_sum[1] = {*(const ZP_LDS float *)(unsigned long long)(own_a + 2048)}, nm[1] = {*(const ZP_LDS float *)(unsigned long long)(own_a + 3072)};
+    // K's buffers are free: the rows go out through them
+    fwd_finish<D, PARTIAL, 1>(p, t, h, lane, {rb}, o_acc, nm, l_sum, Ks + w * ZP_ROWS_LDS_OF(D));
   }
 }
 
@@ -312,6 +601,19 @@ extern "C" int zp_launch_attn_fwd(const zp_attn_params *p, int d, int partial, i
   const int grid = zp_plan_work_split(q.work, p->work.counters, ((units + 7) / 8) * 8 * p->grp);
   p = &q;
   (void)block_rows;
+  if (q.pair) {
+    const int pair_grid = ((units + 7) / 8) * 8 * p->grp;
+    zp_prof_begin(partial ? "attn_fwd_partial_pair" : "attn_fwd_pair", stream);
+#define ZP_FWD_PAIR(D, PART) hipLaunchKernelGGL((attn_fwd_pair_kernel<D, PART>), dim3(pair_grid), dim3(512), pair_lds<D>(), stream, q)
+    if (d == 128) {
+      if (partial) ZP_FWD_PAIR(128, true); else ZP_FWD_PAIR(128, false);
+    } else {
+      if (partial) ZP_FWD_PAIR(64, true); else ZP_FWD_PAIR(64, false);
+    }
+#undef ZP_FWD_PAIR
+    zp_prof_end(stream);
+    return (int)hipGetLastError();
+  }
 #define ZP_FWD_LAUNCH(D, NW, PART)                                                                      \
   do {                                                                                                  \
     size_t lds = 4 * (size_t)FwdCfg<D, NW>::TILEB + 16;                                                    \

@@ -12,6 +12,7 @@
 
 #include "../../include/zeppelin_attn.h"
 #include "zp_common.h"
+#include "zp_pair.h"
 #include "zp_pool.h"
 
 extern "C" {
@@ -453,6 +454,7 @@ int varlen_attn_fwd(const void *q, const void *k, const void *v, int64_t q_strid
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
   p.n_tiles = (int32_t)tiles.size(); p.work.dyn_div = dyn_div_of(tiles, 0, tiles.size(), 1);
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
+  zp_plan_fwd_pair(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o; p.o_stride = o_stride; p.lse = lse; p.lse_stride = sh->T;
   hipError_t e = (hipError_t)zp_launch_attn_fwd(&p, sh->d, 0, bm, (hipStream_t)stream);
@@ -508,6 +510,7 @@ int chunk_attn_partial(const void *q, const void *k, const void *v, int64_t q_st
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
   p.n_tiles = (int32_t)tiles.size(); p.work.dyn_div = dyn_div_of(tiles, 0, tiles.size(), 1);
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
+  zp_plan_fwd_pair(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o_part; p.o_stride = (int64_t)sh->Hq * sh->d; p.lse = lse_part; p.lse_stride = part_rows;
   hipError_t e = (hipError_t)zp_launch_attn_fwd(&p, sh->d, 1, bm, (hipStream_t)stream);
@@ -567,6 +570,7 @@ int chunk_attn_update(const void *q, const void *k, const void *v, int64_t q_str
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
   p.n_tiles = (int32_t)tiles.size(); p.work.dyn_div = dyn_div_of(tiles, 0, tiles.size(), 1);
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
+  zp_plan_fwd_pair(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o_run; p.o_stride = (int64_t)sh->Hq * sh->d; p.lse = lse_run; p.lse_stride = sh->T;
   p.update = 1;

@@ -124,6 +124,7 @@ struct zp_attn_params {
   float *lse;        // [Hq][lse_stride]
   int64_t lse_stride;
   int32_t update;    // partial kernel only: merge the result into the running (o, lse) found at the output rows
+  int32_t pair;      // by the kernel for launches that leave much of the chip idle: tiles of 64 rows, in the launch arguments
   zp_work_split work;  // which workgroups take their item by number and which claim one (set by the launcher)
   zp_inline_tiles inl; // the tile table if `tiles` is null
 };
@@ -382,11 +383,49 @@ struct zp_lds16 {
   }
 };
 
+// A lane's read addresses in a tile of the zp_pad16 layout; everything but these six is an immediate offset.
+template <int D>
+struct zp_pad16_addr {
+  typedef zp_pad16<D> L;
+  unsigned row[2], tr[4];
+  __device__ __forceinline__ void init(int lane, const char *tile) {
+#pragma unroll
+    for (int par = 0; par < 2; par++) {
+      row[par] = zp_lds_addr(tile) + L::row_part(lane, par);
+      asm volatile("" : "+v"(row[par]));  // opaque: see zp_lds16
+    }
+#pragma unroll
+    for (int dq = 0; dq < 4; dq++) {
+      tr[dq] = zp_lds_addr(tile) + L::tr_part(lane, dq);
+      asm volatile("" : "+v"(tr[dq]));
+    }
+  }
+  __device__ __forceinline__ void move_rows(int bytes) {
+#pragma unroll
+    for (int par = 0; par < 2; par++) row[par] += bytes;
+  }
+  __device__ __forceinline__ void move_cols(int bytes) {
+#pragma unroll
+    for (int dq = 0; dq < 4; dq++) tr[dq] += bytes;
+  }
+  // off: byte offset of the tile; rb: 16 rows; k: k-step; db: 16 columns (of 32 rows)
+  __device__ __forceinline__ bf16x8 rows(int off, int rb, int k) const {
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(row[k & 1] + off + rb * L::R16 + (k >> 1) * 128);
+  }
+  __device__ __forceinline__ bf16x8 cols(int off, int db) const {
+    const unsigned o = tr[db & 3] + off + (db >> 2) * 128;
+    s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)o);
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + L::R16));
+    return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
+  }
+};
+
 // Writes 16 rows of bf16 results held as 16x16x32 MFMA accumulators (lane l: row l%16, columns 16 db + 4 (l/16) ..+3),
 // scaled by mul, to dst, dst + stride, ... (n_valid rows of them). They pass through ZP_ROWS_LDS bytes of LDS of this wave's
 // own, so that a store instruction covers whole rows (16 bytes per lane) instead of 16 rows' pieces of 32 bytes each: a
 // quarter of the cache line accesses. (The pieces kept a workgroup's end busy for about 3 us on short sequences.)
-#define ZP_ROWS_LDS (16 * (256 + 32))
+#define ZP_ROWS_LDS_OF(D) (16 * (2 * (D) + 32))
+#define ZP_ROWS_LDS ZP_ROWS_LDS_OF(128)
 template <int D>
 __device__ __forceinline__ void zp_store_rows(char *lds, const f32x4 (&acc)[D / 16], float mul, __bf16 *dst, int64_t stride,
                                               int n_valid, int lane) {

@@ -9,6 +9,7 @@
 
 #include "../../include/zeppelin_attn.h"
 #include "zp_common.h"
+#include "zp_pair.h"
 
 extern "C" int zp_launch_attn_fwd(const zp_attn_params *p, int d, int partial, int block_rows, hipStream_t stream);
 extern "C" int zp_attn_fwd_block_rows(int d);
@@ -186,6 +187,7 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
   p.q = (const __bf16 *)q; p.k = (const __bf16 *)k; p.v = (const __bf16 *)v;
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
+  zp_plan_fwd_pair(p, sh->d);
   p.scale = sh->scale > 0.f ? sh->scale : 1.0f / std::sqrt((float)sh->d);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o; p.o_stride = o_stride; p.lse = lse; p.lse_stride = sh->T;

@@ -1,0 +1,85 @@
+// Launches that leave much of the chip idle: which of two kernels they take, and the tile table of the one that puts two
+// waves on every 16 query rows (host side).
+#pragma once
+#include <algorithm>
+
+#include "zp_common.h"
+
+// key tiles of 64 that a tile's last row sees
+inline int zp_key_tiles(const zp_tile &t) {
+  int64_t n = (int64_t)t.q_pos0 + t.q_rows - t.k_pos0;
+  n = n < 0 ? 0 : n > t.k_len ? t.k_len : n;
+  return (int)((n + 63) / 64);
+}
+
+// Cuts the 128-row tiles of a table in the launch arguments into tiles of 64 rows, heaviest first; returns their number, or 0
+// if they do not fit.
+inline int zp_halve_tiles(const zp_tile *in, int n, zp_inline_tiles &out, int (&cost)[ZP_INLINE_TILES]) {
+  int m = 0;
+  for (int i = 0; i < n; i++)
+    for (int r0 = (in[i].q_rows - 1) / 64 * 64; r0 >= 0; r0 -= 64) {
+      if (m == ZP_INLINE_TILES) return 0;
+      zp_tile t = in[i];
+      t.q_tok0 += r0; t.q_pos0 += r0; t.out_row0 += r0;
+      t.q_rows = std::min(64, t.q_rows - r0);
+      const int c = zp_key_tiles(t);
+      int at = m++;
+      for (; at > 0 && cost[at - 1] < c; at--) { out.t[at] = out.t[at - 1]; cost[at] = cost[at - 1]; }
+      out.t[at] = t;
+      cost[at] = c;
+    }
+  return m;
+}
+
+// Estimated time of a launch in microseconds, from its tiles' costs (descending, each `heads` times): one workgroup per CU up to
+// 256 items; beyond, the lightest of the first 256 are followed by the heaviest of the rest.
+struct zp_pair_cost {
+  float wg, tile, launch, item;  // per workgroup, per key tile, per launch, per item of the launch
+  float share;                   // whole items: what a second workgroup on the CU adds of its own time (pairs: 1)
+};
+inline float zp_pair_estimate(const zp_pair_cost &c, const int *cost, int n, int heads, bool pairs) {
+  const int items = n * heads;
+  const float head = c.launch + c.item * (float)items;
+  auto dur = [&](int i) { return c.wg + c.tile * (float)cost[i / heads]; };
+  float most = dur(0);
+  if (items <= 256) return head + most;
+  if (items <= 512) {
+    for (int k = 0; k < items - 256; k++) most = std::max(most, pairs ? dur(255 - k) + dur(256 + k) : dur(k) + c.share * dur(256 + k));
+    return head + most;
+  }
+  float sum = 0.f;
+  for (int i = 0; i < n; i++) sum += c.wg + c.tile * (float)cost[i];
+  sum *= (float)heads / 256.f;
+  return head + (pairs ? std::max(most, 1.03f * sum + 0.5f * dur(items - 1)) : std::max(most + c.share * dur(256), sum * 0.5f * (1.f + c.share)));
+}
+
+// Turns the table of a launch (n tiles of 128 rows, in the launch arguments) into the one of the kernel with two waves per 16
+// rows where the estimates say that it is faster; false: the table stays as it is.
+inline bool zp_take_pairs(zp_tile *tiles, int &n, int heads, const zp_pair_cost &whole, const zp_pair_cost &pair) {
+  if ((int64_t)n * heads > 1024 || n > ZP_INLINE_TILES) return false;
+  zp_inline_tiles half;
+  int cost64[ZP_INLINE_TILES], cost128[ZP_INLINE_TILES];
+  const int m = zp_halve_tiles(tiles, n, half, cost64);
+  if (m == 0 || m * heads > 1024) return false;
+  for (int i = 0; i < n; i++) cost128[i] = zp_key_tiles(tiles[i]);
+  std::sort(cost128, cost128 + n, [](int a, int b) { return a > b; });
+  if (!(zp_pair_estimate(pair, cost64, m, heads, true) < 0.93f * zp_pair_estimate(whole, cost128, n, heads, false))) return false;
+  for (int i = 0; i < m; i++) tiles[i] = half.t[i];
+  n = m;
+  return true;
+}
+
+// The forward's two kernels. Constants fitted to 850 launches whose tables fit (4/2 to 64/8 and 8/1 heads; equal, ragged and
+// lognormal lengths of 64 to 16000 tokens in all): the estimates are 4 and 5 % off in the mean. Of the 669 launches that take
+// the pairs none is more than 1.1 % slower with them, and all 850 together take 0.79 of the time (geometric mean). n
+// sequences of L tokens, us, whole / pairs:
+//    d   heads    L    taken: pairs            not taken
+//    64   4/4    300   n =  1:   8.0 /  6.1
+//    64   4/4   4000   n =  1:  51.9 / 33.5    64/8, L =  762, n = 2:  17.7 / 24.2
+//   128   4/4   1000   n =  4:  23.2 / 15.4    64/8, L =  894, n = 2:  27.8 / 35.1
+//   128   8/2   2085   n =  1:  41.4 / 27.1    16/4, L =  200, n = 20: 21.9 / 26.2
+inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
+  static const zp_pair_cost whole[2] = {{2.95f, 0.769f, 1.74f, 0.0023f, 0.345f}, {2.20f, 1.074f, 3.19f, 0.0032f, 0.536f}};
+  static const zp_pair_cost pair[2] = {{2.03f, 0.471f, 1.95f, 0.0022f, 1.f}, {2.63f, 0.660f, 1.64f, 0.0027f, 1.f}};
+  if (p.tiles == nullptr) p.pair = zp_take_pairs(p.inl.t, p.n_tiles, p.Hq, whole[d == 128], pair[d == 128]);
+}

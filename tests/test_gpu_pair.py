@@ -1,0 +1,95 @@
+"""Launches that leave much of the chip idle take kernels that put two waves on every 16 query rows. What a row computes there
+is what it computes in a full launch, in the same order: the results of a small batch are the same bits as those of the same
+sequences in front of enough others to fill the chip. Edges of 16-row sub-blocks, 64-row blocks and 64-key tiles, one to many
+heads per KV head, strided inputs, chunk pairs on every side of the diagonal, running updates, rows whose reference moves."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_21841_amd import binding as B
+from paper_2509_21841_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+BATCHES = [([1], 1, 1), ([15, 16, 17, 0, 31, 32, 33], 2, 1), ([63, 64, 65], 3, 3), ([127, 128, 129, 1, 191, 192, 193], 4, 2),
+           ([255, 257, 320], 8, 1), ([449, 2], 6, 3), ([1100], 5, 1), ([2000], 4, 4)]
+
+
+def bits(t):
+    return t.contiguous().view(torch.int16 if t.dtype == torch.bfloat16 else torch.int32)
+
+
+def labels(call):
+    B.profile_enable(True)
+    out = call()
+    torch.cuda.synchronize()
+    names = [name for name, _ in B.profile_records()]
+    B.profile_enable(False)
+    return out, names
+
+
+def filler(Hq):
+    return [700] * (4096 // Hq // 6 + 12)   # over 1024 items by themselves, and more tiles than the launch arguments hold
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("steep", [False, True])
+@pytest.mark.parametrize("lengths,Hq,Hkv", BATCHES)
+def test_forward_is_the_same_bits(lengths, Hq, Hkv, steep, d):
+    n, all_lengths = sum(lengths), lengths + filler(Hq)
+    T = sum(all_lengths)
+    qkv = torch.cat(synth.make_qkv(T, Hq, Hkv, d, 121, DEV), 1)   # slices of one buffer
+    if steep:   # scores that rise along the sequence: references move in later tiles
+        qkv[:, Hq:Hq + Hkv] += (torch.arange(T, device=DEV) % 997 * 0.02)[:, None, None].to(torch.bfloat16)
+        qkv[:, :Hq] += 0.5
+    cut = lambda x: (x[:, :Hq], x[:, Hq:Hq + Hkv], x[:, Hq + Hkv:])
+    (o, lse), names = labels(lambda: B.varlen_attn_fwd(*cut(qkv[:n]), synth.cu_seqlens(lengths), scale=0.13))
+    assert names == ["attn_fwd_pair"]
+    (wo, wlse), names = labels(lambda: B.varlen_attn_fwd(*cut(qkv), synth.cu_seqlens(all_lengths), scale=0.13))
+    assert names == ["attn_fwd"]
+    assert torch.equal(bits(o), bits(wo[:n])) and torch.equal(bits(lse), bits(wlse[:, :n]))
+    o2, lse2 = torch.zeros_like(o), torch.zeros_like(lse)
+    _, names = labels(lambda: B.varlen_attn_fwd_noalloc(*cut(qkv[:n]), synth.cu_seqlens(lengths), o2, lse2, scale=0.13))
+    assert names == ["attn_fwd_pair"] and torch.equal(bits(o2), bits(o)) and torch.equal(bits(lse2), bits(lse))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("q_pos0,k_pos0,q_len,k_len", [(0, 0, 128, 128), (40, 70, 128, 130), (0, 100, 200, 90), (64, 1, 17, 127), (5, 64, 113, 65),
+                                                       (0, 127, 128, 1), (0, 128, 128, 64), (300, 0, 65, 299), (33, 0, 15, 512)])
+def test_chunk_pairs_are_the_same_bits(q_pos0, k_pos0, q_len, k_len, d):
+    T, Hq, Hkv = 1024, 4, 2
+    q, k, v = synth.make_qkv(T, Hq, Hkv, d, 123, DEV)
+    pair = dict(q_tok0=3, q_len=q_len, k_tok0=511, k_len=k_len, q_pos0=q_pos0, k_pos0=k_pos0, out_row0=0)
+    more = [dict(q_tok0=0, q_len=1000, k_tok0=0, k_len=1000, q_pos0=0, k_pos0=0, out_row0=q_len + 1000 * i) for i in range(40)]
+    part, names = labels(lambda: B.chunk_attn_partial(q, k, v, [pair], q_len))
+    assert names == ["attn_fwd_partial_pair"]
+    want, names = labels(lambda: B.chunk_attn_partial(q, k, v, [pair] + more, q_len + 1000 * len(more)))
+    assert names == ["attn_fwd_partial"]
+    assert torch.equal(bits(part[0]), bits(want[0][:q_len])) and torch.equal(bits(part[1]), bits(want[1][:, :q_len]))
+    # folded into running rows that have seen keys already, and into rows that have not
+    first = dict(q_tok0=3, q_len=q_len // 2, k_tok0=100, k_len=77, q_pos0=500, k_pos0=0, out_row0=0)
+    runs = []
+    for others in ([], [dict(q_tok0=1024 + 1000 * i, q_len=1000, k_tok0=1024, k_len=1000, q_pos0=0, k_pos0=0, out_row0=0) for i in range(40)]):
+        X = [torch.cat([x, x[:1000].repeat(40, 1, 1)]) for x in (q, k, v)]
+        o_run = torch.full((X[0].shape[0], Hq, d), 7.0, device=DEV)
+        lse_run = torch.full((Hq, X[0].shape[0]), float("-inf"), device=DEV)
+        B.chunk_attn_update(*X, [first], o_run, lse_run)
+        _, names = labels(lambda: B.chunk_attn_update(*X, [pair] + others, o_run, lse_run))
+        if q_pos0 + q_len > k_pos0:
+            assert names == ["attn_fwd_partial" if others else "attn_fwd_partial_pair"]
+        runs.append((o_run[3:3 + q_len], lse_run[:, 3:3 + q_len]))
+    for a, b in zip(*runs):
+        assert torch.equal(bits(a), bits(b))
+
+
+def test_nothing_visible_is_not_poisoned():
+    """Infinities and NaN in later tokens of the sequence leave earlier 64-row blocks alone, and stay where they belong."""
+    L, Hq, Hkv = 256, 4, 2
+    for d in (64, 128):
+        q, k, v = synth.make_qkv(L, Hq, Hkv, d, 125, DEV)
+        want = B.varlen_attn_fwd(q, k, v, synth.cu_seqlens([L]))
+        k2, v2 = k.clone(), v.clone()
+        k2[192:], v2[192:] = float("nan"), float("inf")
+        got = B.varlen_attn_fwd(q, k2, v2, synth.cu_seqlens([L]))
+        assert torch.equal(bits(got[0][:192]), bits(want[0][:192])) and torch.equal(bits(got[1][:, :192]), bits(want[1][:, :192]))
+        assert not torch.isfinite(got[0][200:]).any()
