@@ -25,6 +25,17 @@ __device__ __forceinline__ void add_acc_rows(float *dst, const f32x4 (&acc)[D / 
   }
 }
 
+// D = dO . O of a lane's row, whose four lanes hold 8 consecutive head-dim elements of every 32 each
+template <int D>
+__device__ __forceinline__ float row_d(const bf16x8 (&doreg)[D / 32], const bf16x8 (&oreg)[D / 32]) {
+  float sum = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < D / 32; kk++)
+#pragma unroll
+    for (int e = 0; e < 8; e++) sum = __builtin_fmaf((float)doreg[kk][e], (float)oreg[kk][e], sum);
+  return zp_quad_sum(sum);
+}
+
 // ------------------------------------------------------------------------------------------- dQ
 // 32 of a tile's 64 keys (half `half`) for one wave of two 16-query sub-blocks: S^T and dP^T, dS^T, dQ^T += K^T dS^T, all on the
 // 16x16x32 MFMA (attn_fwd.hip has the orientation and the layouts; zp_lds16 the LDS side). Steps of one LDS operand
@@ -160,12 +171,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
   f32x4 negD[2];
 #pragma unroll
   for (int qb = 0; qb < 2; qb++) {
-    float dsum = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < D / 32; kk++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) dsum += (float)doreg[qb][kk][e] * (float)oreg[qb][kk][e];
-    const float Dq = zp_quad_sum(dsum);
+    const float Dq = row_d<D>(doreg[qb], oreg[qb]);
     lse2[qb] = lse_nat[qb] * LOG2E;
     negD[qb] = f32x4{-Dq, -Dq, -Dq, -Dq};
     if (row[qb] < t.q_rows && q4 == 0) {
@@ -244,6 +250,217 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
     if (!p.accumulate) zp_store_rows<D>(smem + w * ZP_ROWS_LDS, dq_acc[qb], p.scale, p.dq + at, p.dq_stride, t.q_rows - rb[qb], lane);
     else if (row[qb] < t.q_rows) add_acc_rows<D>((float *)p.dq + at + c16 * p.dq_stride + q4, dq_acc[qb], p.scale);
   }
+}
+
+// ---- dQ of launches that leave much of the chip idle: two waves per 16 query rows
+// A wave's LDS read addresses: K and V rows of its 32 keys of the tile in hand, and the transposed K operands of its half of
+// the columns of the tile before.
+template <int D>
+struct dq_pair_addr {
+  typedef zp_pad16<D> L;
+  static constexpr int NC = D / 32;  // 16-column blocks of a wave
+  unsigned k[2], v[2], t[NC];
+  __device__ __forceinline__ void init(int lane, int half, const char *ks, const char *vs) {
+#pragma unroll
+    for (int par = 0; par < 2; par++) {
+      const int at = L::row_part(lane, par) + half * 2 * L::R16;
+      k[par] = zp_lds_addr(ks) + at;
+      v[par] = zp_lds_addr(vs) + at;
+      asm volatile("" : "+v"(k[par]), "+v"(v[par]));  // opaque: see zp_lds16
+    }
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      t[c] = zp_lds_addr(ks) + (D == 128 ? L::tr_part(lane, c) + half * 128 : L::tr_part(lane, 2 * half + c));
+      asm volatile("" : "+v"(t[c]));
+    }
+  }
+  __device__ __forceinline__ bf16x8 rows(const unsigned (&a)[2], int rb, int kk) const {
+    return *(const ZP_LDS bf16x8 *)(unsigned long long)(a[kk & 1] + rb * L::R16 + (kk >> 1) * 128);
+  }
+  __device__ __forceinline__ bf16x8 cols(int h, int c) const {
+    const unsigned o = t[c] + h * 2 * L::R16;
+    s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)o);
+    s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ZP_LDS s16x4 *)(unsigned long long)(o + L::R16));
+    return zp_cat(__builtin_bit_cast(bf16x4, u0), __builtin_bit_cast(bf16x4, u1));
+  }
+};
+
+// A step of one wave of a pair: S^T, dP^T and dS^T of its 32 keys of a tile (SP; dS to LDS address out), and dQ^T += K^T dS^T of
+// the tile before for its columns (DQ: dS of that tile's two halves at in; the second one only if `both`).
+template <int D, bool SP, bool MASK, bool DQ, class Copies>
+__device__ __forceinline__ void dq_pair_step(const bf16x8 (&qreg)[D / 32], const bf16x8 (&doreg)[D / 32], f32x4 (&dq_acc)[D / 32], float c_log2,
+                                             float lse2, const f32x4 &negD, int key0, int q4, int nvis_lane, const dq_pair_addr<D> &la,
+                                             unsigned in, unsigned out, bool both, Copies &&copies) {
+  constexpr int KK = D / 32, NC = D / 32, N1 = SP ? 4 * KK : 0, N2 = DQ ? 2 * NC : 0, XA = 6;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  bf16x8 x[N1 + 1], xt[N2 + 1], dsb[2];
+  f32x4 s[2], dp[2];
+  auto load = [&](auto nn) {  // operand n: K and V alternating, 16 keys n / 2 % 2, k-step n / 4
+    constexpr int n = decltype(nn)::value;
+    if constexpr (n < N1) x[n] = la.rows(n % 2 ? la.v : la.k, n / 2 % 2, n / 4);
+  };
+  zp_static_for<XA>(load);
+  if constexpr (DQ) {
+    dsb[0] = *(const ZP_LDS bf16x8 *)(unsigned long long)in;
+    dsb[1] = *(const ZP_LDS bf16x8 *)(unsigned long long)(in + 1024);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  copies();  // while the first operands arrive
+  zp_static_for<N1>([&](auto nn) {
+    constexpr int n = nn.value, kb = n / 2 % 2, k = n / 4;
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (n % 2 == 0) s[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], qreg[k], k == 0 ? zero : s[kb], 0, 0, 0);
+    else dp[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], doreg[k], k == 0 ? negD : dp[kb], 0, 0, 0);
+    load(std::integral_constant<int, n + XA>{});
+    if constexpr (N2 != 0 && n % 2 == 1) xt[n / 2] = la.cols(n / 2 / NC, n / 2 % NC);
+  });
+  __builtin_amdgcn_sched_barrier(0);
+  // dS element e: its fma, exp2, product and conversion one step apart, over the MFMAs of the second product
+  float e0[8];
+  bf16x8 dsn;
+  auto stage = [&](auto ee, auto st) {
+    constexpr int e = decltype(ee)::value, kb = e / 4, r = e % 4;
+    if constexpr (!SP || e < 0 || e >= 8) return;
+    else if constexpr (decltype(st)::value == 0) e0[e] = __builtin_fmaf(s[kb][r], c_log2, -lse2);
+    else if constexpr (decltype(st)::value == 1) {
+      e0[e] = zp_exp2(e0[e]);
+      if (MASK && key0 + 16 * kb + q4 + r >= nvis_lane) e0[e] = 0.f;
+    } else dsn[e] = (__bf16)(e0[e] * dp[kb][r]);
+  };
+  auto arith = [&](auto ee) {
+    constexpr int e = decltype(ee)::value;
+    stage(std::integral_constant<int, e>{}, std::integral_constant<int, 0>{});
+    stage(std::integral_constant<int, e - 1>{}, std::integral_constant<int, 1>{});
+    stage(std::integral_constant<int, e - 2>{}, std::integral_constant<int, 2>{});
+  };
+  if constexpr (DQ) {
+    if constexpr (!SP) zp_static_for<N2>([&](auto nn) { xt[nn.value] = la.cols(nn.value / NC, nn.value % NC); });
+    zp_static_for<N2>([&](auto nn) {
+      constexpr int n = nn.value, h = n / NC, c = n % NC;
+      __builtin_amdgcn_sched_barrier(0);
+      if (SP || h == 0 || both) dq_acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[n], dsb[h], dq_acc[c], 0, 0, 0);
+      zp_static_for<10 / N2>([&](auto u) { arith(std::integral_constant<int, n * (10 / N2) + decltype(u)::value>{}); });
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    zp_static_for<10 - 10 / N2 * N2>([&](auto u) { arith(std::integral_constant<int, 10 / N2 * N2 + decltype(u)::value>{}); });
+  } else {
+    zp_static_for<10>([&](auto u) { arith(u); });
+  }
+  if constexpr (SP) *(ZP_LDS bf16x8 *)(unsigned long long)out = dsn;
+}
+
+constexpr int PAIR_BUFS = 4;
+template <int D>
+constexpr size_t dq_pair_lds() { return 2 * PAIR_BUFS * 4 * (size_t)zp_pad16<D>::R16 + 2 * 4 * 2048; }
+
+// 64 query rows per workgroup of eight waves. Waves w and w + 4 share 16 rows: each works out dS for 32 of a tile's 64 keys,
+// hands it over through LDS, and adds the tile before to dQ for half of the columns. One barrier per tile. What a row
+// computes, and in which order, is what attn_bwd_dq_kernel computes.
+//
+// Bound: the serial chain of a workgroup's key tiles (see attn_fwd_pair_kernel). Per tile 2850 cycles with
+// attn_bwd_dq_kernel alone on a CU and 2250 here at d = 128, 1930 and 1550 at d = 64; MFMAs alone take 1070 of the 2250, the
+// arithmetic between them 800, operand reads and copies the rest. Forward and backward of 1218 tokens, GQA 4/2, d = 128:
+// dQ 14.0 -> 11.6 us; zp_plan_dq_pair has more figures and the rule.
+template <int D>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_pair_kernel(zp_bwd_params p) {
+  constexpr int TILEB = 4 * zp_pad16<D>::R16, NB = PAIR_BUFS;
+  typedef zp_stager<D, 8, true> stager;
+  constexpr int PW = stager::PER_WAVE;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  char *Ks = smem;                   // [NB][64][D]: tile j in buffer j % NB
+  char *Vs = smem + NB * TILEB;      // [NB][64][D]
+  char *Ss = smem + 2 * NB * TILEB;  // [2][4][2][64 x 16 bytes]: a tile's dS, pair by pair, half by half
+
+  int unit, hh;
+  zp_block_to_unit(blockIdx.x, p.grp, p.m_grp, unit, hh);
+  if (unit >= p.n_dq_tiles * p.Hkv) return;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
+  const int h = g * p.grp + hh;
+  const zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
+  const int half = __builtin_amdgcn_readfirstlane(tid >> 8);
+  const int c16 = lane & 15, q4 = 4 * (lane >> 4);
+  const int rb = 16 * w, row = rb + c16;
+  auto nvis_of = [&](int r) {
+    int n = t.q_pos0 + r - t.k_pos0 + 1;
+    return n < 0 ? 0 : (n > t.k_len ? t.k_len : n);
+  };
+  const int rowc = min(row, t.q_rows - 1);  // rows behind the block's last one repeat it (and are not stored)
+  const int nvis_lane = nvis_of(rowc), nvis_min = nvis_of(rb), nvis_max = rb < t.q_rows ? nvis_of(rb + 15) : 0;
+  const int n_kt = (nvis_of(t.q_rows - 1) + 63) / 64;
+
+  stager kst, vst;
+  kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
+  vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
+  // row operands first, the first two tiles' copies right behind them (see attn_bwd_dq_kernel)
+  bf16x8 qreg[D / 32], doreg[D / 32], oreg[D / 32];
+  const int64_t tok = (int64_t)t.q_tok0 + rowc;
+#pragma unroll
+  for (int kk = 0; kk < D / 32; kk++) {
+    qreg[kk] = *(const bf16x8 *)(p.q + tok * p.q_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
+    doreg[kk] = *(const bf16x8 *)(p.dout + tok * p.do_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
+    oreg[kk] = *(const bf16x8 *)(p.o + tok * p.o_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
+  }
+  const float lse_nat = p.lse[(int64_t)h * p.T + tok];
+#pragma unroll
+  for (int j = 0; j < 2; j++)
+    if (j < n_kt) {
+      kst.issue(Ks + j * TILEB, 64 * j, t.k_len);
+      vst.issue(Vs + j * TILEB, 64 * j, t.k_len);
+    }
+  dq_pair_addr<D> la;
+  la.init(lane, half, Ks, Vs);
+  const unsigned own = zp_lds_addr(Ss) + w * 2048 + lane * 16;
+  const float Dq = row_d<D>(doreg, oreg), lse2 = lse_nat * LOG2E;
+  const f32x4 negD = {-Dq, -Dq, -Dq, -Dq};
+  f32x4 dq_acc[D / 32];
+#pragma unroll
+  for (int i = 0; i < D / 32; i++) dq_acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float c_log2 = p.scale_log2;
+  zp_wait_async();
+
+  for (int it = 0; it <= n_kt; it++) {
+    // tile `it` has landed (the one behind it may be in flight), dS of the tile before is there; everybody is done with V of
+    // tile it - 1, K of it - 2 and dS of it - 2
+    if (it > 1) {
+      if (it + 1 < n_kt) zp_wait_async_upto<2 * PW>();
+      else zp_wait_async();
+    }
+    __syncthreads();
+    auto copies = [&] {
+      if (it + 2 < n_kt) {
+        kst.issue(Ks + ((it + 2) & (NB - 1)) * TILEB, (it + 2) * 64, t.k_len);
+        vst.issue(Vs + ((it + 2) & (NB - 1)) * TILEB, (it + 2) * 64, t.k_len);
+      }
+    };
+    const int key0 = 64 * it + 32 * half;
+    const unsigned out = own + (it & 1) * 4 * 2048 + half * 1024, in = own + ((it - 1) & 1) * 4 * 2048;
+    if (it < n_kt && key0 < nvis_max) {
+      if (it == 0) dq_pair_step<D, true, true, false>(qreg, doreg, dq_acc, c_log2, lse2, negD, key0, q4, nvis_lane, la, in, out, true, copies);
+      else if (key0 + 32 > nvis_min) dq_pair_step<D, true, true, true>(qreg, doreg, dq_acc, c_log2, lse2, negD, key0, q4, nvis_lane, la, in, out, true, copies);
+      else dq_pair_step<D, true, false, true>(qreg, doreg, dq_acc, c_log2, lse2, negD, key0, q4, nvis_lane, la, in, out, true, copies);
+    } else if (it > 0 && 64 * (it - 1) < nvis_max) {
+      dq_pair_step<D, false, false, true>(qreg, doreg, dq_acc, c_log2, lse2, negD, key0, q4, nvis_lane, la, in, out, 64 * (it - 1) + 32 < nvis_max, copies);
+    } else {
+      copies();
+    }
+    const int step = (it & (NB - 1)) == NB - 1 ? -(NB - 1) * TILEB : TILEB, step_t = it == 0 ? 0 : ((it - 1) & (NB - 1)) == NB - 1 ? -(NB - 1) * TILEB : TILEB;
+#pragma unroll
+    for (int i = 0; i < 2; i++) { la.k[i] += step; la.v[i] += step; }
+#pragma unroll
+    for (int i = 0; i < D / 32; i++) la.t[i] += step_t;
+  }
+
+  if (half == 0 && row < t.q_rows && q4 == 0) {
+    const int64_t r = (int64_t)h * p.T + t.q_tok0 + row;
+    p.dvec[r] = -Dq;
+    p.lse2[r] = -lse_nat / p.scale;
+  }
+  // V's buffers are free: everybody has passed the barrier behind the last product that reads them
+  const int64_t at = ((int64_t)t.q_tok0 + rb) * p.dq_stride + (int64_t)h * D + half * (D / 2);
+  if (!p.accumulate) zp_store_rows<D / 2>(Vs + (half * 4 + w) * ZP_ROWS_LDS_OF(D / 2), dq_acc, p.scale, p.dq + at, p.dq_stride, t.q_rows - rb, lane);
+  else if (row < t.q_rows) add_acc_rows<D / 2>((float *)p.dq + at + c16 * p.dq_stride + q4, dq_acc, p.scale);
 }
 
 // ------------------------------------------------------------------------------------------- dK, dV
@@ -966,8 +1183,12 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   const int dq_grid = zp_plan_work_split(p->work_dq, c, ((dq_units + 7) / 8) * 8 * p->grp);
   const int kv_grid = zp_plan_work_split(p->work_kv, c ? c + ZP_COUNTER_BYTES / 4 : nullptr, ((kv_units + 7) / 8) * 8);
   if (dq_units > 0) {
-    zp_prof_begin("attn_bwd_dq", stream);
-    if (d == 128) hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 128 * 2 + 16, stream, *p);
+    zp_prof_begin(p->dq_pair ? "attn_bwd_dq_pair" : "attn_bwd_dq", stream);
+    if (p->dq_pair) {
+      const dim3 grid(((dq_units + 7) / 8) * 8 * p->grp);
+      if (d == 128) hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<128>, grid, dim3(512), dq_pair_lds<128>(), stream, *p);
+      else hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<64>, grid, dim3(512), dq_pair_lds<64>(), stream, *p);
+    } else if (d == 128) hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 128 * 2 + 16, stream, *p);
     else hipLaunchKernelGGL((attn_bwd_dq_kernel<64>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 64 * 2 + 16, stream, *p);
     zp_prof_end(stream);
     hipError_t e = hipGetLastError();

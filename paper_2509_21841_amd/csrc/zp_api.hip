@@ -743,6 +743,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv; p.T = sh->T;
+  zp_plan_dq_pair(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.dq = (__bf16 *)dq; p.dk = (__bf16 *)dk; p.dv = (__bf16 *)dv;
   p.dq_stride = dq_stride; p.dkv_stride = dkv_stride;
@@ -836,6 +837,7 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv; p.T = sh->T;
+  zp_plan_dq_pair(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.dq = (__bf16 *)dq_acc; p.dk = (__bf16 *)dk_acc; p.dv = (__bf16 *)dv_acc;
   p.dq_stride = (int64_t)sh->Hq * sh->d; p.dkv_stride = (int64_t)sh->Hkv * sh->d;

@@ -2,6 +2,7 @@
 // waves on every 16 query rows (host side).
 #pragma once
 #include <algorithm>
+#include <cstring>
 
 #include "zp_common.h"
 
@@ -12,23 +13,23 @@ inline int zp_key_tiles(const zp_tile &t) {
   return (int)((n + 63) / 64);
 }
 
-// Cuts the 128-row tiles of a table in the launch arguments into tiles of 64 rows, heaviest first; returns their number, or 0
-// if they do not fit.
-inline int zp_halve_tiles(const zp_tile *in, int n, zp_inline_tiles &out, int (&cost)[ZP_INLINE_TILES]) {
+// Cuts the 128-row tiles of a table in the launch arguments into tiles of 64 rows (they fit), the later rows of a block first;
+// with `cost`, all of them heaviest first.
+inline void zp_halve_tiles(const zp_tile *in, int n, zp_inline_tiles &out, int *cost) {
   int m = 0;
   for (int i = 0; i < n; i++)
     for (int r0 = (in[i].q_rows - 1) / 64 * 64; r0 >= 0; r0 -= 64) {
-      if (m == ZP_INLINE_TILES) return 0;
       zp_tile t = in[i];
       t.q_tok0 += r0; t.q_pos0 += r0; t.out_row0 += r0;
       t.q_rows = std::min(64, t.q_rows - r0);
-      const int c = zp_key_tiles(t);
       int at = m++;
-      for (; at > 0 && cost[at - 1] < c; at--) { out.t[at] = out.t[at - 1]; cost[at] = cost[at - 1]; }
+      if (cost) {
+        const int c = zp_key_tiles(t);
+        for (; at > 0 && cost[at - 1] < c; at--) { out.t[at] = out.t[at - 1]; cost[at] = cost[at - 1]; }
+        cost[at] = c;
+      }
       out.t[at] = t;
-      cost[at] = c;
     }
-  return m;
 }
 
 // Estimated time of a launch in microseconds, from its tiles' costs (descending, each `heads` times): one workgroup per CU up to
@@ -53,18 +54,30 @@ inline float zp_pair_estimate(const zp_pair_cost &c, const int *cost, int n, int
   return head + (pairs ? std::max(most, 1.03f * sum + 0.5f * dur(items - 1)) : std::max(most + c.share * dur(256), sum * 0.5f * (1.f + c.share)));
 }
 
-// Turns the table of a launch (n tiles of 128 rows, in the launch arguments) into the one of the kernel with two waves per 16
-// rows where the estimates say that it is faster; false: the table stays as it is.
-inline bool zp_take_pairs(zp_tile *tiles, int &n, int heads, const zp_pair_cost &whole, const zp_pair_cost &pair) {
-  if ((int64_t)n * heads > 1024 || n > ZP_INLINE_TILES) return false;
+// Turns the table of a launch (n tiles of 128 rows in the launch arguments, `behind` tiles of another launch behind them) into
+// the one of the kernel with two waves per 16 rows where that is the faster one; false: the table stays as it is. With a CU
+// for every workgroup it always is, the launch being its longest chain; beyond, its estimate has to be below `margin` of the
+// other kernel's.
+inline bool zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int Hkv, int grp, const zp_pair_cost &whole, const zp_pair_cost &pair,
+                          float margin) {
+  const int heads = Hkv * grp;
+  zp_tile *tiles = inl.t;
+  if (n > ZP_INLINE_TILES || (int64_t)n * heads > 1024) return false;
+  int m = 0;
+  for (int i = 0; i < n; i++) m += tiles[i].q_rows > 64 ? 2 : 1;
+  if (m + behind > ZP_INLINE_TILES || m * heads > 1024) return false;
   zp_inline_tiles half;
-  int cost64[ZP_INLINE_TILES], cost128[ZP_INLINE_TILES];
-  const int m = zp_halve_tiles(tiles, n, half, cost64);
-  if (m == 0 || m * heads > 1024) return false;
-  for (int i = 0; i < n; i++) cost128[i] = zp_key_tiles(tiles[i]);
-  std::sort(cost128, cost128 + n, [](int a, int b) { return a > b; });
-  if (!(zp_pair_estimate(pair, cost64, m, heads, true) < 0.93f * zp_pair_estimate(whole, cost128, n, heads, false))) return false;
-  for (int i = 0; i < m; i++) tiles[i] = half.t[i];
+  if ((m * Hkv + 7) / 8 * grp <= 32) {
+    zp_halve_tiles(tiles, n, half, nullptr);
+  } else {
+    int cost64[ZP_INLINE_TILES], cost128[ZP_INLINE_TILES];
+    zp_halve_tiles(tiles, n, half, cost64);
+    for (int i = 0; i < n; i++) cost128[i] = zp_key_tiles(tiles[i]);
+    std::sort(cost128, cost128 + n, [](int a, int b) { return a > b; });
+    if (!(zp_pair_estimate(pair, cost64, m, heads, true) < margin * zp_pair_estimate(whole, cost128, n, heads, false))) return false;
+  }
+  std::memmove(tiles + m, tiles + n, (size_t)behind * sizeof(zp_tile));
+  std::memcpy(tiles, half.t, (size_t)m * sizeof(zp_tile));
   n = m;
   return true;
 }
@@ -81,5 +94,16 @@ inline bool zp_take_pairs(zp_tile *tiles, int &n, int heads, const zp_pair_cost 
 inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
   static const zp_pair_cost whole[2] = {{2.95f, 0.769f, 1.74f, 0.0023f, 0.345f}, {2.20f, 1.074f, 3.19f, 0.0032f, 0.536f}};
   static const zp_pair_cost pair[2] = {{2.03f, 0.471f, 1.95f, 0.0022f, 1.f}, {2.63f, 0.660f, 1.64f, 0.0027f, 1.f}};
-  if (p.tiles == nullptr) p.pair = zp_take_pairs(p.inl.t, p.n_tiles, p.Hq, whole[d == 128], pair[d == 128]);
+  if (p.tiles == nullptr) p.pair = zp_take_pairs(p.inl, p.n_tiles, 0, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.93f);
+}
+
+// The dQ kernels, whose tiles have the dK/dV tiles behind them. Of 610 such launches the 429 that take the pairs are at most 4 %
+// slower with them (eight 11-token sequences, 64/8 heads); the whole backward takes 0.94 of the time in the mean of all. One
+// sequence of L tokens, 4 heads, dQ alone, us, whole / pairs: L = 1000, d = 128: 25.0 / 18.1, d = 64: 17.2 / 12.6; L = 4000: 81.4 / 62.2
+// and 55.6 / 43.4.
+inline void zp_plan_dq_pair(zp_bwd_params &p, int d) {
+  static const zp_pair_cost whole[2] = {{2.5f, 0.817f, 1.4f, 0.0023f, 0.345f}, {2.8f, 1.20f, 2.8f, 0.0032f, 0.536f}};
+  static const zp_pair_cost pair[2] = {{2.5f, 0.655f, -0.6f, 0.0022f, 1.f}, {3.2f, 0.945f, -0.2f, 0.0027f, 1.f}};
+  if (p.dq_tiles == nullptr)
+    p.dq_pair = p.n_dq_tiles > 0 && zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.85f);
 }

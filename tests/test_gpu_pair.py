@@ -93,3 +93,43 @@ def test_nothing_visible_is_not_poisoned():
         got = B.varlen_attn_fwd(q, k2, v2, synth.cu_seqlens([L]))
         assert torch.equal(bits(got[0][:192]), bits(want[0][:192])) and torch.equal(bits(got[1][:, :192]), bits(want[1][:, :192]))
         assert not torch.isfinite(got[0][200:]).any()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lengths,Hq,Hkv", BATCHES)
+def test_dq_is_the_same_bits(lengths, Hq, Hkv, d):
+    n, all_lengths = sum(lengths), lengths + filler(Hq)
+    T = sum(all_lengths)
+    qkv = torch.cat(synth.make_qkv(T, Hq, Hkv, d, 127, DEV), 1)
+    do = synth.make_qkv(T, Hq, Hkv, d, 129, DEV)[0]
+    cut = lambda x: (x[:, :Hq], x[:, Hq:Hq + Hkv], x[:, Hq + Hkv:])
+    o, lse = B.varlen_attn_fwd(*cut(qkv), synth.cu_seqlens(all_lengths), scale=0.13)
+    call = lambda: B.varlen_attn_bwd(do[:n], *cut(qkv[:n]), o[:n], lse[:, :n].contiguous(), synth.cu_seqlens(lengths), scale=0.13)
+    got, names = labels(call)
+    assert names[0] == "attn_bwd_dq_pair"
+    want, names = labels(lambda: B.varlen_attn_bwd(do, *cut(qkv), o, lse, synth.cu_seqlens(all_lengths), scale=0.13))
+    assert names[0] == "attn_bwd_dq"
+    assert torch.equal(bits(got[0]), bits(want[0][:n]))
+    for a, b in zip(got[1:], want[1:]):   # sums of the same products in two orders, rounded to bfloat16
+        a, b = a.float(), b[:n].float()
+        assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-4).all())
+    for a, b in zip(got, call()):
+        assert torch.equal(bits(a), bits(b))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("q_pos0,k_pos0,q_len,k_len", [(0, 0, 128, 128), (40, 70, 128, 130), (64, 1, 17, 127), (5, 64, 113, 65), (0, 127, 128, 1),
+                                                       (300, 0, 65, 299), (33, 0, 15, 512)])
+def test_accumulated_dq_is_the_same_bits(q_pos0, k_pos0, q_len, k_len, d):
+    Hq, Hkv, T = 4, 2, 1024 + 40 * 1000
+    q, k, v, do = synth.make_qkv(T, Hq, Hkv, d, 131, DEV, with_dout=True)
+    pair = dict(q_tok0=3, q_len=q_len, k_tok0=511, k_len=k_len, q_pos0=q_pos0, k_pos0=k_pos0, out_row0=0)
+    more = [dict(q_tok0=1024 + 1000 * i, q_len=1000, k_tok0=1024 + 1000 * i, k_len=1000, q_pos0=0, k_pos0=0, out_row0=0) for i in range(40)]
+    lse = torch.randn((Hq, T), device=DEV) + 8.0
+    runs = []
+    for pairs, label in (([pair], "attn_bwd_dq_pair"), ([pair] + more, "attn_bwd_dq")):
+        acc = [torch.ones(x.shape, dtype=torch.float32, device=DEV) for x in (q, k, v)]
+        _, names = labels(lambda: B.chunk_attn_partial_bwd(do, q, k, v, q, lse, pairs, *acc))
+        assert names[0] == label
+        runs.append(acc)
+    assert torch.equal(bits(runs[0][0][:1024]), bits(runs[1][0][:1024]))
