@@ -1022,22 +1022,81 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   }
 }
 
-// dK, dV of a launch that leaves most of the chip idle: a workgroup owns 32 key rows instead of 128 and its four waves go
-// through the (query tile, head) iterations by turns, each with staging buffers of its own (148.5 KB of LDS in all at
-// D = 128) and no barrier in the loop; their accumulators are added up at the end, through LDS, in wave order. Four times
-// the workgroups, a quarter of the serial chain. 1218 tokens, GQA 4/2, d = 128: 32 us with 128 key rows per workgroup
-// (22 iterations one after the other in 24 workgroups), 17 us with 32. See dkdv_split_is_faster for when it is used.
+// A 32-query tile for one wave of 16 key rows: the four products S, dP, dV^T, dK^T as one pipeline of 4 D / 16 steps of one LDS
+// operand and its MFMA, operands requested AHEAD steps ahead. exp2 runs under the dP product, dS = P dP under the dV product.
+// Q_OFF, O_OFF, seed, D_OFF: as for dkdv_block. V fits the registers here. `piece(integral_constant<int, n>)`, n = 0 .. D / 16, is
+// called every third step: the caller's copies of a later tile go there one by one.
+template <int D, int Q_OFF, int O_OFF, int D_OFF, bool MASK, class Piece>
+__device__ __forceinline__ void dkdv_half_block(unsigned seed, const bf16x8 (&kreg)[D / 32], const bf16x8 (&vreg)[D / 32], f32x4 (&dk_acc)[D / 16],
+                                                f32x4 (&dv_acc)[D / 16], int qpos0, int kpos, int qpos_end, float c_log2,
+                                                const zp_pad16_addr<D> &la, Piece &&piece) {
+  constexpr int N = D / 16, EPS = 8 / N, AHEAD = 6;  // steps of a product; elements of P or dS per step
+  f32x4 s[2], dp[2], ls[2], ds[2];
+#pragma unroll
+  for (int rb = 0; rb < 2; rb++) {  // -LSE/scale and -D of the 4 query rows this lane holds of each 16
+    ls[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + rb * 64);
+    ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + rb * 64);
+  }
+  bf16x8 x[4 * N];  // step i of a product: 16 rows i % 2, k-step i / 2 (S, dP); 16 columns i (dV^T, dK^T)
+  auto load = [&](auto nn) {
+    constexpr int n = decltype(nn)::value, ph = n / N, i = n % N;
+    if constexpr (ph < 2) x[n] = la.rows(ph ? O_OFF : Q_OFF, i % 2, i / 2);
+    else if constexpr (ph < 4) x[n] = la.cols(ph == 2 ? O_OFF : Q_OFF, i);
+  };
+  zp_static_for<AHEAD>(load);
+  float pe[8], de[8];
+  unsigned ppk[4], dpk[4];  // elements 2j, 2j + 1: 16 rows j / 2, registers 2 (j % 2) and + 1
+  zp_static_for<4 * N>([&](auto nn) {
+    constexpr int n = nn.value, ph = n / N, i = n % N, rb = i % 2, k = i / 2;
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (ph == 0) s[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], kreg[k], k == 0 ? ls[rb] : s[rb], 0, 0, 0);
+    else if constexpr (ph == 1) dp[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], vreg[k], k == 0 ? ds[rb] : dp[rb], 0, 0, 0);
+    else if constexpr (ph == 2) dv_acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], dkdv_operand(ppk), dv_acc[i], 0, 0, 0);
+    else dk_acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], dkdv_operand(dpk), dk_acc[i], 0, 0, 0);
+    load(std::integral_constant<int, n + AHEAD>{});
+    if constexpr (n % 3 == 1 && n / 3 <= N) piece(std::integral_constant<int, n / 3>{});
+    if constexpr (ph == 1 || ph == 2) {
+#pragma unroll
+      for (int e = i * EPS; e < i * EPS + EPS; e++) {
+        const int er = e / 4, r = e % 4, qpos = qpos0 + 16 * er + r;
+        if (ph == 1) {
+          pe[e] = zp_exp2(s[er][r] * c_log2);
+          if (MASK && (qpos < kpos || qpos >= qpos_end)) pe[e] = 0.f;
+          if (e % 2) ppk[e / 2] = __builtin_bit_cast(unsigned, (bf16x2){(__bf16)pe[e - 1], (__bf16)pe[e]});
+        } else {
+          de[e] = pe[e] * dp[er][r];
+          if (e % 2) dpk[e / 2] = __builtin_bit_cast(unsigned, (bf16x2){(__bf16)de[e - 1], (__bf16)de[e]});
+        }
+      }
+    }
+  });
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// A group's LDS in the kernel below: two buffers of 32 Q and dO rows, two of row vectors.
 template <int D>
-__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
+constexpr int split_own() { return 8 * zp_pad16<D>::R16 + 1024; }
+
+// dK, dV of launches that whole key blocks do not spread over the chip: a workgroup owns 32 key rows instead of 128. Its eight
+// waves are four groups of two; the groups go through the (query tile, head) iterations by turns, each with staging buffers of
+// its own (140 KB of LDS in all at D = 128), and the two waves of a group, on one SIMD, share the tile and do 16 key rows
+// each. The groups' accumulators are added up at the end, through LDS, in their order.
+//
+// Bound: a group's chain of iterations: 1.21 us each at d = 128, 0.81 at 64 (2850 and 1900 cycles, of which the MFMAs of a SIMD's
+// two waves are 1024 and 512, their arithmetic under MFMAs about as much, hand-over and addresses 600); with one wave per
+// group and 32 key rows per wave, whose operations issue one after the other, 1.50 and 0.86. 1000 tokens, 4/2 heads, d = 128:
+// one workgroup per 128 keys 76 us, one wave per group 32, two 26; 1218 tokens 32.1, 14.6 and 12.8. See dkdv_split_is_faster for when
+// it is used.
+template <int D>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
   constexpr int QT = 32;
   typedef zp_pad16<D> L;
   constexpr int TILEB = 2 * L::R16;                // a staged tile: 32 query rows
-  constexpr int OWN = 4 * TILEB + 1024;            // a wave's LDS: two buffers of Q and dO rows, two of row vectors
-  constexpr int LOADS = 2 * (64 * D / 1024) + 2;   // copies of one tile
+  constexpr int OWN = split_own<D>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  char *own = smem + w * OWN;
-  char *Vs = smem + 4 * OWN;                       // [32][D]: the workgroup's V rows
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave & 3, half = wave >> 2;
+  char *own = smem + group * OWN;
   float *Ls = (float *)(own + 4 * TILEB);          // [2][2][64]: see attn_bwd_dkdv128_kernel
 
   // the four workgroups of a key block on one XCD
@@ -1045,122 +1104,127 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) 
   if (unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
-  const int kb[2] = {32 * part, 32 * part + 16};
-  if (kb[0] >= t.k_len) return;
+  if (32 * part >= t.k_len) return;
 
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
-  const int krow[2] = {kb[0] + c16, kb[1] + c16};
-  const int kpos[2] = {t.k_pos0 + krow[0] - q4, t.k_pos0 + krow[1] - q4};
+  const int kb = 32 * part + 16 * half, krow = kb + c16;  // the wave's key rows, the lane's
+  const int kpos = t.k_pos0 + krow - q4;                  // less the lane's first query row, as qpos_end below
 
-  // K operands in registers, V operands from LDS (rows behind the last key repeat it, see attn_bwd_dkdv128_kernel)
-  bf16x8 kreg[2][D / 32];
+  // K and V operands in registers (rows behind the last key repeat it: a key column never mixes with another, and those are
+  // not stored)
+  bf16x8 kreg[D / 32], vreg[D / 32];
+  const int64_t ktok = (int64_t)t.k_tok0 + min(krow, t.k_len - 1);
+  const __bf16 *kp = p.k + ktok * p.k_stride + (int64_t)g * D + 2 * q4, *vp = p.v + ktok * p.v_stride + (int64_t)g * D + 2 * q4;
 #pragma unroll
-  for (int cb = 0; cb < 2; cb++) {
-    const __bf16 *kp = p.k + ((int64_t)t.k_tok0 + min(krow[cb], t.k_len - 1)) * p.k_stride + (int64_t)g * D + 2 * q4;
-#pragma unroll
-    for (int kk = 0; kk < D / 32; kk++) kreg[cb][kk] = *(const bf16x8 *)(kp + 32 * kk);
+  for (int kk = 0; kk < D / 32; kk++) {
+    kreg[kk] = *(const bf16x8 *)(kp + 32 * kk);
+    vreg[kk] = *(const bf16x8 *)(vp + 32 * kk);
   }
-  f32x4 acc[4][D / 16];  // dK of the two sub-blocks, dV of the two
+  f32x4 dk_acc[D / 16], dv_acc[D / 16];
 #pragma unroll
-  for (int a = 0; a < 4; a++)
-#pragma unroll
-    for (int i = 0; i < D / 16; i++) acc[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4(&dk_acc)[2][D / 16] = *(f32x4(*)[2][D / 16]) & acc[0];
-  f32x4(&dv_acc)[2][D / 16] = *(f32x4(*)[2][D / 16]) & acc[2];
+  for (int i = 0; i < D / 16; i++) dk_acc[i] = dv_acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // iterations: query tiles outermost (last tile first), heads of the group innermost; this wave's are w, w + 4, ...
+  // iterations: query tiles outermost (last tile first), heads of the group innermost; this group's are group, group + 4, ...
   const int n_qt = (t.q_rows + QT - 1) / QT, n_it = n_qt * p.grp;
-  {
-    zp_stager<D, 8, true> vst;  // 4 waves x its loads = the first 32 rows of its 64-row pattern
-    vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
-    vst.issue(Vs, kb[0], t.k_len);
-  }
-  zp_stager<D, 2, true> qst, ost;  // one wave copies a tile by itself: the first of the two waves of a 64-row pattern
-  qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, lane);
-  ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, lane);
-  dkdv_lds_addr<D> la;
-  la.init(lane, own, Vs, Vs + L::R16);
-  auto stage = [&](int it, int buf) {
-    const int qi = zp_udiv(it, p.grp, p.m_grp), hh = it - qi * p.grp, i0 = (n_qt - 1 - qi) * QT;
-    qst.issue(own + 2 * buf * TILEB, i0, t.q_rows, (int64_t)hh * D);
-    ost.issue(own + (2 * buf + 1) * TILEB, i0, t.q_rows, (int64_t)hh * D);
+  // of a tile the first wave copies the Q rows and -LSE / scale, the second one the dO rows and -D (a wave copies 32 rows by
+  // itself: the first of the two waves of a 64-row pattern)
+  zp_stager<D, 2, true> st;
+  st.init((half ? p.dout : p.q) + (int64_t)t.q_tok0 * (half ? p.do_stride : p.q_stride) + (int64_t)g * p.grp * D, half ? p.do_stride : p.q_stride, lane);
+  const float *rowvec = (half ? p.dvec : p.lse2) + (int64_t)g * p.grp * p.T + t.q_tok0;
+  zp_pad16_addr<D> la;
+  la.init(lane, own);
+  // the query tile and head of an iteration four behind
+  const int dq = zp_udiv(4, p.grp, p.m_grp), dh = 4 - dq * p.grp;
+  auto on = [&](int &i0, int &hh) {
+    const bool wrap = hh + dh >= p.grp;
+    i0 -= QT * (wrap ? dq + 1 : dq);
+    hh += wrap ? dh - p.grp : dh;
+  };
+  auto stage = [&](int i0, int hh, int buf) {
+    st.issue(own + (2 * buf + half) * TILEB, i0, t.q_rows, (int64_t)hh * D);
     int r = i0 + (lane & 31);
     if (r > t.q_rows - 1) r = t.q_rows - 1;
-    const int64_t at = (int64_t)(g * p.grp + hh) * p.T + t.q_tok0 + r;
-    const unsigned l0 = __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + buf * 512);
-    zp_dma4(p.lse2 + at, l0);
-    zp_dma4(p.dvec + at, l0 + 256);
+    zp_dma4(rowvec + (int64_t)hh * p.T + r, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + buf * 512 + half * 256));
   };
   const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
-  const int k0_min = t.k_pos0 + kb[0], k1_min = t.k_pos0 + kb[1];
+  const int k_min = t.k_pos0 + kb;
   const int qpos_end = t.q_pos0 + t.q_rows, qpos_end_l = qpos_end - q4;
   const float c_log2 = p.scale_log2;
-  auto no_piece = [](auto) {};
 
-  if (w < n_it) stage(w, 0);
-  zp_wait_async();
-  __syncthreads();  // the V rows are there
-
+  const int q0 = zp_udiv(group, p.grp, p.m_grp);
+  int i0 = (n_qt - 1 - q0) * QT, next_i0 = i0, next_hh = group - q0 * p.grp;  // this iteration's first query row; the next one's
+  if (group < n_it) stage(next_i0, next_hh, 0);
+  on(next_i0, next_hh);
   auto query_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
-    const int qpos0 = t.q_pos0 + (n_qt - 1 - zp_udiv(it, p.grp, p.m_grp)) * QT;
-    if (it + 4 < n_it) {
-      stage(it + 4, buf ^ 1);
-      zp_wait_async_upto<LOADS>();  // this tile's copies, issued before those
-    } else {
-      zp_wait_async();
+    // the tile has landed; both waves of the group are done with the one before
+    zp_wait_async();
+    __syncthreads();
+    const int qpos0 = t.q_pos0 + i0;
+    const bool compute = it < n_it && qpos0 + QT - 1 >= k_min && kb < t.k_len, masked = qpos0 < k_min + 15 || qpos0 + QT > qpos_end;
+    // at D = 128 the next tile is fetched inside this one's products when it is a full one (the common case): eight waves'
+    // copies issued at once wait up to 140 cycles each for the address unit (4000 tokens, 4/2 heads: 91 us in front, 86 inside;
+    // at D = 64, where the products have half as many steps for them, 58 and 65)
+    const bool fused = D == 128 && compute && !masked && it + 4 < n_it && next_i0 + QT <= t.q_rows;
+    if (it + 4 < n_it && !fused) stage(next_i0, next_hh, buf ^ 1);
+    const void *pc_t = zp_uniform_ptr(st.base + (int64_t)next_i0 * st.stride + (int64_t)next_hh * D), *pc_r = zp_uniform_ptr(rowvec + (int64_t)next_hh * p.T + next_i0);
+    auto stage_piece = [&](auto nn) {
+      constexpr int n = decltype(nn)::value;
+      if constexpr (n < decltype(st)::PER_WAVE)
+        zp_dma16_so(pc_t, st.off[n], __builtin_amdgcn_readfirstlane(zp_lds_addr(own) + (2 * (buf ^ 1) + half) * TILEB + st.dest(n)));
+      else
+        zp_dma4_so(pc_r, (lane & 31) * 4, __builtin_amdgcn_readfirstlane(zp_lds_addr(Ls) + (buf ^ 1) * 512 + half * 256));
+    };
+    auto no_piece = [](auto) {};
+    if (compute) {
+      if (masked)
+        dkdv_half_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+      else if (D == 128 && fused)
+        dkdv_half_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
+      else
+        dkdv_half_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     }
-    asm volatile("" ::: "memory");  // no read of the tile moves up here
-    __builtin_amdgcn_sched_barrier(0);
-    const bool act0 = qpos0 + QT - 1 >= k0_min, act1 = qpos0 + QT - 1 >= k1_min && kb[1] < t.k_len;
-    const bool masked = qpos0 < (act1 ? k1_min : k0_min) + 15 || qpos0 + QT > qpos_end;
-    if (act1) {
-      if (masked) dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
-      else dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false, false, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
-    } else if (act0) {
-      dkdv_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true, true, false>(seed + buf * 512, kreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
-    }
-    // the buffer is written again behind this point: every read of it has to have returned
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
+    i0 = next_i0;
+    on(next_i0, next_hh);
   };
-  for (int it = w; it < n_it; it += 8) {
+  for (int it = group; it - group < n_it; it += 8) {
     query_tile(it, std::integral_constant<int, 0>{});
-    if (it + 4 < n_it) query_tile(it + 4, std::integral_constant<int, 1>{});
+    if (it - group + 4 < n_it) query_tile(it + 4, std::integral_constant<int, 1>{});
   }
 
-  // add up the four waves' accumulators: wave a does accumulator a (dK, dK, dV, dV of sub-blocks 0, 1, 0, 1)
+  // add up the four groups' accumulators: of the four results (dK and dV of the two sub-blocks) a wave does half of the
+  // columns of one
   constexpr int ACCB = (D / 16) * 64 * 16;  // bytes of one accumulator of one wave
   __syncthreads();
 #pragma unroll
-  for (int a = 0; a < 4; a++)
-#pragma unroll
-    for (int i = 0; i < D / 16; i++) *(ZP_LDS f32x4 *)((ZP_LDS char *)smem + (w * 4 + a) * ACCB + (i * 64 + lane) * 16) = acc[a][i];
-  __syncthreads();
-  f32x4 sum[D / 16];
-#pragma unroll
   for (int i = 0; i < D / 16; i++) {
-    sum[i] = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)smem + w * ACCB + (i * 64 + lane) * 16);
+    *(ZP_LDS f32x4 *)((ZP_LDS char *)smem + ((group * 2 + half) * 2) * ACCB + (i * 64 + lane) * 16) = dk_acc[i];
+    *(ZP_LDS f32x4 *)((ZP_LDS char *)smem + ((group * 2 + half) * 2 + 1) * ACCB + (i * 64 + lane) * 16) = dv_acc[i];
+  }
+  __syncthreads();
+  const int which = group & 1, ch = group >> 1;
+  f32x4 sum[D / 32];
+#pragma unroll
+  for (int i = 0; i < D / 32; i++) {
+    const ZP_LDS char *at = (const ZP_LDS char *)smem + (half * 2 + which) * ACCB + ((ch * (D / 32) + i) * 64 + lane) * 16;
+    sum[i] = *(const ZP_LDS f32x4 *)at;
 #pragma unroll
     for (int o = 1; o < 4; o++) {
-      const f32x4 v = *(const ZP_LDS f32x4 *)((const ZP_LDS char *)smem + (o * 4 + w) * ACCB + (i * 64 + lane) * 16);
+      const f32x4 v = *(const ZP_LDS f32x4 *)(at + o * 4 * ACCB);
       sum[i][0] += v[0]; sum[i][1] += v[1]; sum[i][2] += v[2]; sum[i][3] += v[3];
     }
   }
   __syncthreads();  // the rows pass through LDS on their way out
-  const int cb = w & 1;
-  const float mul = w < 2 ? p.scale : 1.0f;
-  __bf16 *out = w < 2 ? p.dk : p.dv;
-  const int64_t at = ((int64_t)t.k_tok0 + kb[cb]) * p.dkv_stride + (int64_t)g * D;
-  if (!p.accumulate) zp_store_rows<D>(smem + w * ZP_ROWS_LDS, sum, mul, out + at, p.dkv_stride, t.k_len - kb[cb], lane);
-  else if (kb[cb] + c16 < t.k_len) add_acc_rows<D>((float *)out + at + c16 * p.dkv_stride + q4, sum, mul);
+  const float mul = which ? 1.0f : p.scale;
+  __bf16 *out = which ? p.dv : p.dk;
+  const int64_t at = ((int64_t)t.k_tok0 + kb) * p.dkv_stride + (int64_t)g * D + ch * (D / 2);
+  if (!p.accumulate) zp_store_rows<D / 2>(smem + wave * ZP_ROWS_LDS_OF(D / 2), sum, mul, out + at, p.dkv_stride, t.k_len - kb, lane);
+  else if (krow < t.k_len) add_acc_rows<D / 2>((float *)out + at + c16 * p.dkv_stride + q4, sum, mul);
 }
 
 template <int D>
 constexpr size_t split_lds() {
-  constexpr size_t R16 = zp_pad16<D>::R16, loop = 4 * (8 * R16 + 1024) + 2 * R16, end = 16 * (D / 16) * 64 * 16;
+  constexpr size_t loop = 4 * (size_t)split_own<D>(), end = 16 * (D / 16) * 64 * 16;
   return loop > end ? loop : end;
 }
 
@@ -1198,8 +1262,8 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
     zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : "attn_bwd_dkdv", stream);
     if (p->kv_split) {
       const dim3 grid(((kv_units + 7) / 8) * 8 * 4);
-      if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(BWD_NT), split_lds<128>(), stream, *p);
-      else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, grid, dim3(BWD_NT), split_lds<64>(), stream, *p);
+      if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(512), split_lds<128>(), stream, *p);
+      else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, grid, dim3(512), split_lds<64>(), stream, *p);
     } else if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16<128>::R16 + 4 * 64 * 4 + 16, stream, *p);
     else hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
     zp_prof_end(stream);

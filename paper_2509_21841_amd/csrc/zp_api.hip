@@ -275,41 +275,43 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   *counters = ws_counters(ws);
   return upload_tiles(tiles, ws, stream);
 }
-// Whether the split dK/dV kernel, which spreads a key block's iterations over 16 waves, is the faster one. It takes a
+// Whether the split dK/dV kernel, which spreads a key block's iterations over 32 waves, is the faster one. It takes a
 // quarter of the longest chain, but a CU holds one of its workgroups and each pays for a prologue and for adding up its
-// waves' sums, so it gains on launches that leave most CUs idle and loses (up to 2.5 times) on all others. Both times are
-// estimated in microseconds; an iteration is a (32-query tile, head). Both kernels deal the units (tile, KV head) to the
-// XCDs by turns, and the XCD that ends last decides.
+// groups' sums, so it gains on launches that do not fill the CUs or fill them unevenly and loses (up to 2.1 times) on all
+// others. Both times are estimated in microseconds; an iteration is a (32-query tile, head). Both kernels deal the units (tile,
+// KV head) to the XCDs by turns, and the XCD that ends last decides.
 //  - One workgroup per key block: the first 32 units of an XCD get a CU each, the next 32 share those in the same order; an
-//    iteration beside another workgroup takes 1.44 times as long. The longest chain with its companion's share, and the
-//    masked tiles at its end. With more than two workgroups per CU the split is not looked at.
+//    iteration beside another workgroup takes 1.33 times as long. The longest chain with its companion's share, and the
+//    masked tiles at its end; behind two workgroups per CU, no less than all iterations at that rate. With more than 80 units
+//    per XCD the split is not looked at.
 //  - Split: four workgroups per unit (those without keys cost a prologue as well). The longest one while 32 CUs hold all of
 //    an XCD's, else their time over 32 CUs and a part of those that start last, no more than the longest per round of 32.
-// The constants are fitted to 1014 launches (d = 64 and 128, 4/4 to 32/8 and 8/1 heads, equal sequences of 100 to 16000
-// tokens and random ones, 925 of them within 512 units); the estimates are 5 % off in the mean, and the first is taken 6 %
-// lower. Of the 654 launches that take the split none is more than 6 % faster without it; six of the others would be 6 to
-// 13 % faster with it. n sequences of L tokens, us, one workgroup per key block / split:
+// The constants are fitted to 1080 launches within 640 units (4/4 to 64/8 and 8/1 heads, equal, ragged and lognormal lengths
+// of 100 to 60000 tokens in all); the estimates are 4 to 8 % off in the mean. At d = 128 the split's is up to a fifth low behind
+// two rounds of the chip, so that it has to win by more there. Of the 920 launches that take the split three are more than 6 % faster
+// without it (13 to 20 sequences under 40 tokens, 10 to 16 %); together the 1080 take 0.54 of the time without any split.
+// n sequences of L tokens, us, one workgroup per key block / split:
 //    d   heads    L    taken: split              not taken
-//   128   4/4    300   n =  3:   18.9 /   12.6   n = 16:   19.9 /   28.9
-//   128   8/1   1000   n =  6:  269.8 /  106.1   n = 28:  269.2 /  396.0
-//   128  32/8   4000   n =  1:  505.8 /  401.0   n =  2:  728.3 /  786.7
-//    64  16/4    300   n = 10:   34.1 /   26.2   n = 19:   34.2 /   40.8
-//    64   8/1  16000   n =  2: 2170.9 / 1726.3   n =  4: 3235.0 / 3426.4
+//   128   4/4    300   n =  3:   18.9 /   11.3   n = 16:   19.9 /   26.0
+//   128  32/8    846   n =  2:  122.2 /   45.7   64/8, 3038, n = 9: 859.9 / 922.3
+//    64   8/1   1000   n =  6:  155.2 /   57.9   n = 34:  204.1 /  262.0
+//    64   4/2  40130 in 22:    393.4 /  366.5    4/2, 63227 in 50: 315.5 /  441.2
 bool dkdv_split_is_faster(const std::vector<CostTile> &kt, int d, int Hkv, int grp) {
   struct Cost {
-    float whole, whole_it, whole_head;     // one workgroup per key block: fixed, per iteration, per head
-    float launch, split, split_it, tail;   // split: per launch; per workgroup: fixed, per iteration of a wave; share of the last
+    float whole, whole_it, whole_head, share;  // one workgroup per key block: fixed, per iteration, per head; of the companion's
+    float launch, split, split_it, tail, empty;  // split: per launch; per workgroup: fixed, per iteration of a group; share of the last
   };
-  const Cost c = d == 64 ? Cost{7.05f, 0.519f, 0.910f, 3.83f, 3.16f, 0.855f, 0.517f}
-                         : Cost{8.33f, 0.943f, 0.630f, 3.79f, 4.50f, 1.504f, 0.542f};
-  if ((int64_t)kt.size() * Hkv > 512) return false;
-  // per XCD: units and their chains; iterations per wave of the split's workgroups, and of the (up to 8) units that start last
-  float chain[8][64];
-  int n[8] = {}, n_last[8] = {};
+  const Cost c = d == 64 ? Cost{6.96f, 0.544f, 1.12f, 0.351f, 3.82f, 2.46f, 0.807f, 0.521f, 3.82f}
+                         : Cost{8.25f, 1.009f, 0.386f, 0.325f, 3.48f, 4.42f, 1.209f, 0.523f, 3.71f};
+  const int64_t units = (int64_t)kt.size() * Hkv;
+  if (units > 640) return false;
+  // per XCD: units and their chains; workgroups with keys, their iterations per group, and of the (up to 8) units that start last
+  float chain[8][80];
+  int n[8] = {}, n_wg[8] = {}, n_last[8] = {};
   int64_t it[8] = {}, it_last[8] = {}, longest = 0;
-  int u = (int)kt.size() * Hkv;
+  int u = (int)units;
   for (size_t i = kt.size(); i-- > 0;) {
-    const int64_t its = (int64_t)((kt[i].t.q_rows + 31) / 32) * grp, per_wave = (its + 3) / 4;
+    const int64_t its = (int64_t)((kt[i].t.q_rows + 31) / 32) * grp, per_group = (its + 3) / 4;
     const int parts = (kt[i].t.k_len + 31) / 32;
     longest = std::max(longest, its);
     for (int g = 0; g < Hkv; g++) {
@@ -317,24 +319,29 @@ bool dkdv_split_is_faster(const std::vector<CostTile> &kt, int d, int Hkv, int g
       chain[x][u >> 3] = (float)its;
       if (n_last[x] < 32) {
         n_last[x] += parts;
-        it_last[x] += parts * per_wave;
+        it_last[x] += parts * per_group;
       }
       n[x]++;
-      it[x] += parts * per_wave;
+      n_wg[x] += parts;
+      it[x] += parts * per_group;
     }
   }
   float its_whole = 0.f;
   const float wg = c.split + c.split_it * (float)((longest + 3) / 4);
   float split = wg;
   for (int x = 0; x < 8; x++) {
+    float sum = 0.f;
+    for (int i = 0; i < n[x]; i++) sum += chain[x][i];
     for (int i = 0; i < std::min(32, n[x]); i++)
-      its_whole = std::max(its_whole, chain[x][i] + (i + 32 < n[x] ? 0.44f * chain[x][i + 32] : 0.f));
+      its_whole = std::max(its_whole, chain[x][i] + (i + 32 < n[x] ? c.share * chain[x][i + 32] : 0.f));
+    if (n[x] > 64) its_whole = std::max(its_whole, sum * (1.f + c.share) / 64.f);
     if (n[x] <= 8) continue;
     const float last = c.split + c.split_it * (float)it_last[x] / (float)n_last[x];
-    const float fill = (c.split * 4.f * (float)n[x] + c.split_it * (float)it[x]) / 32.f + c.tail * last;
+    const float fill = (c.split * (float)n_wg[x] + c.empty * (float)(4 * n[x] - n_wg[x]) + c.split_it * (float)it[x]) / 32.f + c.tail * last;
     split = std::max(split, std::min(fill, wg * (float)((n[x] + 7) / 8)));
   }
-  return c.launch + split < c.whole + c.whole_it * its_whole + c.whole_head * (float)grp;
+  const float margin = d == 64 || units <= 128 ? 0.96f : 0.81f;
+  return c.launch + split < margin * (c.whole + c.whole_it * its_whole + c.whole_head * (float)grp);
 }
 // work items of a launch over n tiles: (tile, KV head) units padded to one per XCD, times the heads in a group
 int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7) / 8 * 8 * grp; }
