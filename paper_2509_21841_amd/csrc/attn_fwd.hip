@@ -22,15 +22,18 @@ struct FwdCfg {
 constexpr float P_SUM_MAX = 4096.0f;
 
 // A row's reference is worked out anew where `far` has one of its four lanes; m: this lane's largest score of the tile.
-// Returns what the row's sums are multiplied by. A row that has seen no key yet keeps waiting (nm = +inf).
-__device__ __forceinline__ float fwd_move_reference(uint64_t far, float m, float c_log2, float &nm) {
+// Returns what the row's sums are multiplied by; its probabilities of the tile are taken again with ref. A row that has seen no
+// key yet keeps waiting (nm = +inf), and every one of them is zero.
+__device__ __forceinline__ float fwd_move_reference(uint64_t far, float m, float c_log2, float &nm, float &ref) {
   m = zp_quad_max(m) * c_log2;
   uint32_t rows = (uint32_t)far | (uint32_t)(far >> 32);  // the four lanes of a row are 16 apart
   rows = ((rows | rows >> 16) & 0xffff) * 0x10001u;
   const bool moves = __builtin_amdgcn_inverse_ballot_w64((uint64_t)rows << 32 | rows);
   const float mc_old = -nm, mc = moves ? fmaxf(mc_old, m) : mc_old;
-  const float alpha = mc == -INFINITY ? 1.0f : zp_exp2(mc_old - mc);
+  const bool none = mc == -INFINITY;
+  const float alpha = none ? 1.0f : zp_exp2(mc_old - mc);
   nm = -mc;
+  ref = none ? 0.f : -mc;
   return alpha;
 }
 
@@ -121,13 +124,14 @@ __device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2]
       for (int kb = 0; kb < 4; kb++)
 #pragma unroll
         for (int r = 0; r < 4; r++) m = fmaxf(m, s[qb][kb][r]);
-      const float alpha = fwd_move_reference(far[qb], m, c_log2, nm[qb]);
+      float ref;
+      const float alpha = fwd_move_reference(far[qb], m, c_log2, nm[qb], ref);
       l_sum[qb] *= alpha;
 #pragma unroll
       for (int i = 0; i < DB; i++)
 #pragma unroll
         for (int r = 0; r < 4; r++) o_acc[qb][i][r] *= alpha;
-      take(qb, nm[qb] == INFINITY ? 0.f : nm[qb]);  // no key seen yet: every probability of this tile is zero
+      take(qb, ref);
     }
   }
 #pragma unroll
@@ -379,9 +383,9 @@ __device__ __forceinline__ uint64_t fwd_pair_scores(const bf16x8 (&qreg)[D / 32]
     for (int kb = 0; kb < 4; kb++)
 #pragma unroll
       for (int r = 0; r < 4; r++) m = fmaxf(m, s[kb][r]);
-    alpha = fwd_move_reference(far, m, c_log2, nm);
+    float ref;
+    alpha = fwd_move_reference(far, m, c_log2, nm, ref);
     l_sum *= alpha;
-    const float ref = nm == INFINITY ? 0.f : nm;
     ta = tb = 0.f;
 #pragma unroll
     for (int kb = 0; kb < 4; kb++)
