@@ -6,6 +6,7 @@
 // Both recompute P from the forward's LSE. In each kernel the accumulator of the first two products already
 // has the register layout the third/fourth product needs as its B operand; the transposed A operands
 // (K^T, Q^T, dO^T) come from the row-major LDS tiles through the transposing LDS read.
+#include <algorithm>
 #include <type_traits>
 #include "zp_common.h"
 
@@ -860,6 +861,44 @@ __device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The end of a dK/dV workgroup of two groups of four waves, which have gone through the iterations by turns: the first group
+// adds up and writes dK, the second one dV, each with what the other hands over through LDS (D KB).
+template <int D>
+__device__ __forceinline__ void dkdv_add_groups(const zp_bwd_params &p, const zp_tile &t, int g, int group, int w, int lane, const int (&kb)[2],
+                                                f32x4 (&dk_acc)[2][D / 16], f32x4 (&dv_acc)[2][D / 16], char *smem) {
+  constexpr int ACCB = (D / 16) * 1024;  // bytes of one accumulator of one wave
+  __syncthreads();  // (the tiles have been read)
+  ZP_LDS char *give = (ZP_LDS char *)smem + ((group * 4 + w) * 2) * ACCB + lane * 16;
+  const ZP_LDS char *take = (const ZP_LDS char *)smem + (((group ^ 1) * 4 + w) * 2) * ACCB + lane * 16;
+  auto hand_over = [&](const f32x4 (&acc)[2][D / 16]) {
+#pragma unroll
+    for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+      for (int i = 0; i < D / 16; i++) *(ZP_LDS f32x4 *)(give + cb * ACCB + i * 1024) = acc[cb][i];
+  };
+  auto finish = [&](f32x4 (&acc)[2][D / 16], __bf16 *out, float mul) {
+#pragma unroll
+    for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+      for (int i = 0; i < D / 16; i++) {
+        const f32x4 v = *(const ZP_LDS f32x4 *)(take + cb * ACCB + i * 1024);
+        acc[cb][i][0] += v[0]; acc[cb][i][1] += v[1]; acc[cb][i][2] += v[2]; acc[cb][i][3] += v[3];
+      }
+    __syncthreads();  // the rows pass through LDS on their way out
+#pragma unroll
+    for (int cb = 0; cb < 2; cb++) {
+      const int64_t at = ((int64_t)t.k_tok0 + kb[cb]) * p.dkv_stride + (int64_t)g * D;
+      if (!p.accumulate) zp_store_rows<D>(smem + (group * 4 + w) * ZP_ROWS_LDS, acc[cb], mul, out + at, p.dkv_stride, t.k_len - kb[cb], lane);
+      else if (kb[cb] + (lane & 15) < t.k_len) add_acc_rows<D>((float *)out + at + (lane & 15) * p.dkv_stride + 4 * (lane >> 4), acc[cb], mul);
+    }
+  };
+  if (group == 0) hand_over(dv_acc);
+  else hand_over(dk_acc);
+  __syncthreads();
+  if (group == 0) finish(dk_acc, p.dk, p.scale);
+  else finish(dv_acc, p.dv, 1.0f);
+}
+
 // Two waves per SIMD for head dimension 128 as well: two independent workgroups of four waves per CU (69 KB of LDS
 // each), a wave holding its K operands (32 registers) and its dK^T/dV^T accumulators (128) and working on 32-query
 // tiles, one product at a time; the V operands do not fit beside them in 256 registers and are read from LDS, where the
@@ -871,25 +910,33 @@ __device__ __forceinline__ void dkdv_block(unsigned seed, const bf16x8 (&kreg)[2
 // long-tail GQA batch 25.17 -> 22.97 ms, four 16384-token sequences 15.49 -> 14.22, 64K lognormal MHA 2.70 -> 2.39,
 // 64 x 1K MHA 1.45 -> 1.29. The one-wave form on the 16x16x32 MFMA took 24.9 ms on the long-tail batch; with an XOR for
 // every LDS read (32 to the 64 vector operations a tile needs) this one took 24.7.
-__global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv128_kernel(zp_bwd_params p) {
+//
+// G = 2: both of a CU's workgroups become groups of one, which go through the iterations of ONE key block by turns and add up
+// their accumulators at the end. The same work per CU and half the chain, at the price of a prologue and an end that
+// nothing else runs beside (9.3 us per workgroup) and of meeting at one barrier: for launches of a few waves of workgroups, in which the
+// longest chains and the last wave decide. 8000 ragged tokens, 32/8 heads: 500 -> 360 us, 10709 tokens, 8/8: 121 -> 88; 64K lognormal MHA
+// 2315 -> 2818.
+template <int G>
+__global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv128_kernel(zp_bwd_params p) {
   constexpr int D = 128, QT = 32;
   constexpr int TILEB = 2 * zp_pad16<128>::R16;         // a staged tile: 32 query rows
   typedef zp_stager<D, 8, true> stager;               // 4 waves x 2 wave-loads = the first 32 rows of its 64-row pattern
   constexpr int PW = stager::PER_WAVE;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char *Qs = smem;                                 // [2][2][32][D]: two buffers (three would not fit two workgroups per
-                                                   // CU) of a tile's Q rows and, behind them, its dO rows
-  char *Vs = smem + 4 * TILEB;                     // [128][D]: the workgroup's V rows, staged once
+  const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  char *Qs = smem + group * 4 * TILEB;             // [2][2][32][D] of the group: two buffers (three would not fit two workgroups
+                                                   // per CU) of a tile's Q rows and, behind them, its dO rows
+  char *Vs = smem + G * 4 * TILEB;                 // [128][D]: the workgroup's V rows, staged once
   // [2][2][64]: a tile's 32 values of -LSE / scale and, behind them, of -D (the copies write 64 floats, the upper half
   // of no use: no lane mask to set up)
-  float *Ls = (float *)(Vs + 8 * zp_pad16<128>::R16);
+  float *Ls = (float *)(Vs + 8 * zp_pad16<128>::R16) + group * 4 * 64;
 
-  const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ls + 4 * 64)));
+  const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Vs + 8 * zp_pad16<128>::R16 + G * 4 * 64 * 4)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = G == 1 ? threadIdx.x : threadIdx.x & 255, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
   // the wave's two sub-blocks of 16 key rows: see attn_bwd_dkdv64_kernel
   const int kb[2] = {16 * w, 16 * (7 - w)};
@@ -920,16 +967,22 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
   ost.init(p.dout + (int64_t)t.q_tok0 * p.do_stride + (int64_t)g * p.grp * D, p.do_stride, tid);
   dkdv_lds_addr<D> la;
-  la.init(lane, smem, Vs + kb[0] / 16 * zp_pad16<128>::R16, Vs + kb[1] / 16 * zp_pad16<128>::R16);
+  la.init(lane, Qs, Vs + kb[0] / 16 * zp_pad16<128>::R16, Vs + kb[1] / 16 * zp_pad16<128>::R16);
   {
     zp_stager<D, 4, true> vst;
     vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
-    vst.issue(Vs, 0, t.k_len);
-    vst.issue(Vs + 4 * zp_pad16<128>::R16, 64, t.k_len);
+    for (int half = G == 1 ? 0 : group; half < (G == 1 ? 2 : group + 1); half++) vst.issue(Vs + half * 4 * zp_pad16<128>::R16, 64 * half, t.k_len);
   }
   const unsigned seed = zp_lds_addr(Ls) + q4 * 4;
+  // a group's iterations are group, group + G, ...
+  auto on = [&](int &hh, int &qt, int by) {
+    for (int i = 0; i < by; i++)
+      if (++hh == p.grp) { hh = 0; qt--; }
+  };
   int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
-  auto staged = [&] { if (++st_hh == p.grp) { st_hh = 0; st_qt--; } };
+  on(st_hh, st_qt, group);
+  int cur_qt = st_qt, cur_hh = st_hh;
+  auto staged = [&] { on(st_hh, st_qt, G); };
   auto stage = [&](int buf) {
     const int hh = st_hh, i0 = st_qt * QT;
     const int h = g * p.grp + hh;
@@ -959,7 +1012,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   };
   auto no_piece = [](auto) {};
 
-  if (n_it > 0) stage(0);
+  if (group < n_it) stage(0);
   staged();
   zp_wait_async();
   __syncthreads();
@@ -968,20 +1021,20 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int qpos_end = t.q_pos0 + t.q_rows, qpos_end_l = qpos_end - q4;
   constexpr int D_OFF = 256;
 
-  int cur_qt = n_qt - 1, cur_hh = 0;
   // one tile out of buffer BUF (compile-time, so that every LDS address is a register plus an immediate)
   auto query_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
     const int i0 = cur_qt * QT;
-    if (++cur_hh == p.grp) { cur_hh = 0; cur_qt--; }
+    on(cur_hh, cur_qt, G);
     const int qpos0 = t.q_pos0 + i0;        // position of the tile's first query
     // sub-blocks with a key that some query of the tile sees
-    const bool act0 = qpos0 + QT - 1 >= k0_min, act1 = qpos0 + QT - 1 >= k1_min && kb[1] < t.k_len;
+    const bool here = G == 1 || it < n_it;
+    const bool act0 = here && qpos0 + QT - 1 >= k0_min, act1 = here && qpos0 + QT - 1 >= k1_min && kb[1] < t.k_len;
     const bool masked = qpos0 < (act1 ? k1_min : k0_min) + 15 || qpos0 + QT > qpos_end;
     // the next tile is fetched inside this tile's S run when it is a full tile and this wave computes an unmasked one
     // (the common case), else in front; its sources are worked out unconditionally (and, past the end, in vain): values
     // defined under a wave's branch would not stay in scalar registers
-    const bool fetch = it + 1 < n_it;
+    const bool fetch = it + G < n_it;
     const bool fused = fetch && act1 && !masked && st_qt * QT + QT <= t.q_rows;
     pc_buf = buf ^ 1;
     {
@@ -1003,9 +1056,13 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     zp_wait_async();
     __syncthreads();
   };
-  for (int it = 0; it < n_it; it += 2) {
-    query_tile(it, std::integral_constant<int, 0>{});
-    if (it + 1 < n_it) query_tile(it + 1, std::integral_constant<int, 1>{});
+  for (int it = 0; it < n_it; it += 2 * G) {
+    query_tile(it + group, std::integral_constant<int, 0>{});
+    if (it + G < n_it) query_tile(it + G + group, std::integral_constant<int, 1>{});
+  }
+  if constexpr (G == 2) {
+    dkdv_add_groups<D>(p, t, g, group, w, lane, kb, dk_acc, dv_acc, smem);
+    return;
   }
 
 #pragma unroll
@@ -1030,12 +1087,12 @@ template <int D, int Q_OFF, int O_OFF, int D_OFF, bool MASK, class Piece>
 __device__ __forceinline__ void dkdv_half_block(unsigned seed, const bf16x8 (&kreg)[D / 32], const bf16x8 (&vreg)[D / 32], f32x4 (&dk_acc)[D / 16],
                                                 f32x4 (&dv_acc)[D / 16], int qpos0, int kpos, int qpos_end, float c_log2,
                                                 const zp_pad16_addr<D> &la, Piece &&piece) {
-  constexpr int N = D / 16, EPS = 8 / N, AHEAD = 6;  // steps of a product; elements of P or dS per step
+  constexpr int N = D / 16, EPS = 8 / N, AHEAD = D == 64 ? 3 : 6;  // steps of a product; elements of P or dS per step
   f32x4 s[2], dp[2], ls[2], ds[2];
 #pragma unroll
   for (int rb = 0; rb < 2; rb++) {  // -LSE/scale and -D of the 4 query rows this lane holds of each 16
     ls[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + rb * 64);
-    ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + rb * 64);
+    if (D == 128) ds[rb] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + rb * 64);
   }
   bf16x8 x[4 * N];  // step i of a product: 16 rows i % 2, k-step i / 2 (S, dP); 16 columns i (dV^T, dK^T)
   auto load = [&](auto nn) {
@@ -1054,6 +1111,7 @@ __device__ __forceinline__ void dkdv_half_block(unsigned seed, const bf16x8 (&kr
     else if constexpr (ph == 2) dv_acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], dkdv_operand(ppk), dv_acc[i], 0, 0, 0);
     else dk_acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[n], dkdv_operand(dpk), dk_acc[i], 0, 0, 0);
     load(std::integral_constant<int, n + AHEAD>{});
+    if constexpr (D == 64 && (n == 0 || n == 1)) ds[n] = *(const ZP_LDS f32x4 *)(unsigned long long)(seed + D_OFF + n * 64);
     if constexpr (n % 3 == 1 && n / 3 <= N) piece(std::integral_constant<int, n / 3>{});
     if constexpr (ph == 1 || ph == 2) {
 #pragma unroll
@@ -1082,13 +1140,13 @@ constexpr int split_own() { return 8 * zp_pad16<D>::R16 + 1024; }
 // its own (140 KB of LDS in all at D = 128), and the two waves of a group, on one SIMD, share the tile and do 16 key rows
 // each. The groups' accumulators are added up at the end, through LDS, in their order.
 //
+// One workgroup per CU at d = 128, two at 64 (70 KB of LDS, 128 registers: what a second one adds is worth a third).
 // Bound: a group's chain of iterations: 1.21 us each at d = 128, 0.81 at 64 (2850 and 1900 cycles, of which the MFMAs of a SIMD's
 // two waves are 1024 and 512, their arithmetic under MFMAs about as much, hand-over and addresses 600); with one wave per
 // group and 32 key rows per wave, whose operations issue one after the other, 1.50 and 0.86. 1000 tokens, 4/2 heads, d = 128:
-// one workgroup per 128 keys 76 us, one wave per group 32, two 26; 1218 tokens 32.1, 14.6 and 12.8. See dkdv_split_is_faster for when
-// it is used.
+// one wave per group 31.7 us, two 27.1; 4000 tokens 105.6 and 85.5 (61.8 and 58.6 at d = 64). See dkdv_kernel_for for when it is used.
 template <int D>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2, D == 64 ? 4 : 2))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
   constexpr int QT = 32;
   typedef zp_pad16<D> L;
   constexpr int TILEB = 2 * L::R16;                // a staged tile: 32 query rows
@@ -1264,8 +1322,13 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
       const dim3 grid(((kv_units + 7) / 8) * 8 * 4);
       if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(512), split_lds<128>(), stream, *p);
       else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, grid, dim3(512), split_lds<64>(), stream, *p);
-    } else if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel, dim3(kv_grid), dim3(BWD_NT), 16 * zp_pad16<128>::R16 + 4 * 64 * 4 + 16, stream, *p);
-    else hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
+    } else if (d == 128) {
+      constexpr size_t R16 = zp_pad16<128>::R16;
+      if (p->kv_pair) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel<2>, dim3(kv_grid), dim3(2 * BWD_NT), std::max(24 * R16 + 2 * 1024 + 16, (size_t)131072), stream, *p);
+      else hipLaunchKernelGGL(attn_bwd_dkdv128_kernel<1>, dim3(kv_grid), dim3(BWD_NT), 16 * R16 + 1024 + 16, stream, *p);
+    } else {
+      hipLaunchKernelGGL(attn_bwd_dkdv64_kernel, dim3(kv_grid), dim3(BWD_NT), 8 * 64 * 64 * 2 + 2048 + 16, stream, *p);
+    }
     zp_prof_end(stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

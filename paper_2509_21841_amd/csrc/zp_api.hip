@@ -275,73 +275,92 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   *counters = ws_counters(ws);
   return upload_tiles(tiles, ws, stream);
 }
-// Whether the split dK/dV kernel, which spreads a key block's iterations over 32 waves, is the faster one. It takes a
-// quarter of the longest chain, but a CU holds one of its workgroups and each pays for a prologue and for adding up its
-// groups' sums, so it gains on launches that do not fill the CUs or fill them unevenly and loses (up to 2.1 times) on all
-// others. Both times are estimated in microseconds; an iteration is a (32-query tile, head). Both kernels deal the units (tile,
-// KV head) to the XCDs by turns, and the XCD that ends last decides.
-//  - One workgroup per key block: the first 32 units of an XCD get a CU each, the next 32 share those in the same order; an
-//    iteration beside another workgroup takes 1.33 times as long. The longest chain with its companion's share, and the
-//    masked tiles at its end; behind two workgroups per CU, no less than all iterations at that rate. With more than 80 units
-//    per XCD the split is not looked at.
-//  - Split: four workgroups per unit (those without keys cost a prologue as well). The longest one while 32 CUs hold all of
-//    an XCD's, else their time over 32 CUs and a part of those that start last, no more than the longest per round of 32.
-// The constants are fitted to 1080 launches within 640 units (4/4 to 64/8 and 8/1 heads, equal, ragged and lognormal lengths
-// of 100 to 60000 tokens in all); the estimates are 4 to 8 % off in the mean. At d = 128 the split's is up to a fifth low behind
-// two rounds of the chip, so that it has to win by more there. Of the 920 launches that take the split three are more than 6 % faster
-// without it (13 to 20 sequences under 40 tokens, 10 to 16 %); together the 1080 take 0.54 of the time without any split.
-// n sequences of L tokens, us, one workgroup per key block / split:
-//    d   heads    L    taken: split              not taken
-//   128   4/4    300   n =  3:   18.9 /   11.3   n = 16:   19.9 /   26.0
-//   128  32/8    846   n =  2:  122.2 /   45.7   64/8, 3038, n = 9: 859.9 / 922.3
-//    64   8/1   1000   n =  6:  155.2 /   57.9   n = 34:  204.1 /  262.0
-//    64   4/2  40130 in 22:    393.4 /  366.5    4/2, 63227 in 50: 315.5 /  441.2
-bool dkdv_split_is_faster(const std::vector<CostTile> &kt, int d, int Hkv, int grp) {
-  struct Cost {
-    float whole, whole_it, whole_head, share;  // one workgroup per key block: fixed, per iteration, per head; of the companion's
-    float launch, split, split_it, tail, empty;  // split: per launch; per workgroup: fixed, per iteration of a group; share of the last
-  };
-  const Cost c = d == 64 ? Cost{6.96f, 0.544f, 1.12f, 0.351f, 3.82f, 2.46f, 0.807f, 0.521f, 3.82f}
-                         : Cost{8.25f, 1.009f, 0.386f, 0.325f, 3.48f, 4.42f, 1.209f, 0.523f, 3.71f};
+// Which dK/dV kernel a launch takes, by estimates of their times in microseconds; an iteration is a (32-query tile, head). All deal
+// the units (tile, KV head) to the XCDs by turns, and the XCD that ends last decides.
+//  - whole: one workgroup of four waves per key block. The first 32 units of an XCD get a CU each, the next 32 share those in
+//    the same order; an iteration beside another workgroup takes 1.35 to 1.39 times as long. The longest chain with its
+//    companion's share; behind two workgroups per CU, no less than all iterations and a part of those that start last.
+//  - pair (d = 128): one workgroup of two groups of four waves per key block and CU, half the chain. The longest one, or all of
+//    them over 32 CUs and a part of those that start last.
+//  - split: four workgroups of four groups of two waves per key block (those without keys cost a prologue as well), a quarter
+//    of the chain. One per CU at d = 128, two at 64. The longest one while 32 CUs hold all of an XCD's, else their time over
+//    the CUs and a part of those that start last, no more than the longest per round.
+// More than 1024 units always take the first: their number evens out what the others gain. The constants are fitted to some 875
+// launches of 4/4 to 64/8 and 8/1 heads (equal, ragged and lognormal lengths of 100 to 100000 tokens in all); the
+// estimates are 5 to 8 % off in the mean, so the split is taken when its is 5 % below (at d = 64 18 % behind
+// 128 units, where two of its workgroups share a CU) and the pair when its is 3 % below. On 870 other launches the kernel taken
+// is 1 % behind the fastest in the mean; none is more than 12 % behind the first one. n sequences,
+// us, whole / pair / split:
+//    d   heads   tokens                              taken
+//    64   8/1    3722, longest 2315, n =  3:  329.8 /     - /  119.2   split
+//    64   8/8   26831, longest 3762, n = 20:  149.9 /     - /  210.6   whole
+//   128   4/4    6434, longest 2665, n =  5:   92.3 /  71.4 /   57.7   split
+//   128   8/8    6813, longest 2453, n =  9:   91.1 /  69.0 /   96.3   pair
+//   128  32/8    8547, longest 5430, n =  2:  779.0 / 632.6 /  878.4   pair
+//   128  32/32  12000, longest 3074, n = 11:  384.9 / 424.7 /  766.3   whole
+struct KvCost {
+  float whole, whole_it, whole_head, share, rate, whole_tail;  // fixed, per iteration, per head; of the companion's; all of them, of the last
+  float pair, pair_wg, pair_it, pair_tail;                     // per launch; per workgroup: fixed, per iteration of a group; share of the last
+  float split, split_wg, split_it, split_tail, empty, beside;  // the same; a workgroup without keys; what a second one on the CU adds
+};
+enum KvKernel { KV_WHOLE, KV_PAIR, KV_SPLIT };
+KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int grp) {
+  static const KvCost cost[2] = {{7.07f, 0.541f, 1.142f, 0.393f, 0.951f, 0.991f, 0.f, 0.f, 0.f, 0.f, 4.13f, 2.0f, 0.809f, 0.703f, 2.18f, 0.549f},
+                                 {8.19f, 1.011f, 0.370f, 0.346f, 0.968f, 0.509f, 2.77f, 6.50f, 1.51f, 0.917f, 2.58f, 5.03f, 1.267f, 0.444f, 4.22f, 1.f}};
+  const KvCost &c = cost[d == 128];
   const int64_t units = (int64_t)kt.size() * Hkv;
-  if (units > 640) return false;
-  // per XCD: units and their chains; workgroups with keys, their iterations per group, and of the (up to 8) units that start last
-  float chain[8][80];
-  int n[8] = {}, n_wg[8] = {}, n_last[8] = {};
-  int64_t it[8] = {}, it_last[8] = {}, longest = 0;
+  if (units > 1024) return KV_WHOLE;
+  struct Xcd {
+    int n = 0, wg = 0, last_wg = 0;      // units; workgroups of the split with keys, those of them that start last (about 32)
+    float it = 0.f, split_it = 0.f, last_it = 0.f, last32 = 0.f;  // iterations; of the split's workgroups' groups; of its last; of the last 32 units
+    float chain[128];
+  } xcd[8];
+  int64_t longest = 0;
   int u = (int)units;
   for (size_t i = kt.size(); i-- > 0;) {
     const int64_t its = (int64_t)((kt[i].t.q_rows + 31) / 32) * grp, per_group = (its + 3) / 4;
     const int parts = (kt[i].t.k_len + 31) / 32;
     longest = std::max(longest, its);
     for (int g = 0; g < Hkv; g++) {
-      const int x = --u & 7;
-      chain[x][u >> 3] = (float)its;
-      if (n_last[x] < 32) {
-        n_last[x] += parts;
-        it_last[x] += parts * per_group;
+      Xcd &x = xcd[--u & 7];
+      x.chain[u >> 3] = (float)its;
+      if (x.n < 32) x.last32 += (float)its / 32.f;
+      if (x.last_wg < 32) {
+        x.last_wg += parts;
+        x.last_it += (float)(parts * per_group);
       }
-      n[x]++;
-      n_wg[x] += parts;
-      it[x] += parts * per_group;
+      x.n++;
+      x.wg += parts;
+      x.it += (float)its;
+      x.split_it += (float)(parts * per_group);
     }
   }
-  float its_whole = 0.f;
-  const float wg = c.split + c.split_it * (float)((longest + 3) / 4);
-  float split = wg;
-  for (int x = 0; x < 8; x++) {
-    float sum = 0.f;
-    for (int i = 0; i < n[x]; i++) sum += chain[x][i];
-    for (int i = 0; i < std::min(32, n[x]); i++)
-      its_whole = std::max(its_whole, chain[x][i] + (i + 32 < n[x] ? c.share * chain[x][i + 32] : 0.f));
-    if (n[x] > 64) its_whole = std::max(its_whole, sum * (1.f + c.share) / 64.f);
-    if (n[x] <= 8) continue;
-    const float last = c.split + c.split_it * (float)it_last[x] / (float)n_last[x];
-    const float fill = (c.split * (float)n_wg[x] + c.empty * (float)(4 * n[x] - n_wg[x]) + c.split_it * (float)it[x]) / 32.f + c.tail * last;
-    split = std::max(split, std::min(fill, wg * (float)((n[x] + 7) / 8)));
+  const bool two = d == 64;  // workgroups of the split on a CU
+  const float top = c.split_wg + c.split_it * (float)((longest + 3) / 4), slow = two ? 1.f + c.beside : 1.f;
+  const int places = two ? 64 : 32;
+  int64_t split_wgs = 0;
+  float whole_its = 0.f, pair = c.pair_wg + c.pair_it * (float)((longest + 1) / 2), split = top;
+  for (const Xcd &x : xcd) {
+    split_wgs += x.wg;
+    for (int i = 0; i < std::min(32, x.n); i++)
+      whole_its = std::max(whole_its, x.chain[i] + (i + 32 < x.n ? c.share * x.chain[i + 32] : 0.f));
+    if (x.n > 64) whole_its = std::max(whole_its, x.it / 32.f * c.rate + c.whole_tail * x.last32);
+    if (x.n > 32)
+      pair = std::max(pair, (c.pair_wg * (float)x.n + c.pair_it * 0.5f * x.it) / 32.f + c.pair_tail * (c.pair_wg + c.pair_it * 0.5f * x.last32));
+    if (x.n > 8) {
+      const float all = c.split_wg * (float)x.wg + c.empty * (float)(4 * x.n - x.wg) + c.split_it * x.split_it;
+      const float fill = all * slow / (float)places + c.split_tail * (c.split_wg + c.split_it * x.last_it / (float)x.last_wg);
+      split = std::max(split, std::min(fill, top * slow * (float)((4 * x.n + places - 1) / places)));
+    }
   }
-  const float margin = d == 64 || units <= 128 ? 0.96f : 0.81f;
-  return c.launch + split < margin * (c.whole + c.whole_it * its_whole + c.whole_head * (float)grp);
+  const float t_whole = c.whole + c.whole_it * whole_its + c.whole_head * (float)grp;
+  const float t_pair = d == 128 ? c.pair + pair : t_whole, t_split = c.split + split;
+  // sequences under 64 keys leave most of the split's workgroups without any; behind one per CU it then loses up to a fifth, but
+  // for heads that share a short chain at d = 64 (thirteen sequences of 10 tokens, 64/8: 16.8 us whole, 9.3 split)
+  const bool empty = units > 64 && split_wgs < 2 * units && (d == 128 || grp == 1);
+  const float margin = d == 64 && units > 128 ? 0.82f : 0.95f;
+  if (t_split < margin * std::min(t_whole, t_pair) && !empty) return KV_SPLIT;
+  return t_pair < 0.97f * t_whole ? KV_PAIR : KV_WHOLE;
 }
 // work items of a launch over n tiles: (tile, KV head) units padded to one per XCD, times the heads in a group
 int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7) / 8 * 8 * grp; }
@@ -745,7 +764,9 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
-  p.kv_split = dkdv_split_is_faster(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
+  const KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
+  p.kv_pair = kv == KV_PAIR;
+  p.kv_split = kv == KV_SPLIT;
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
@@ -839,7 +860,9 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
-  p.kv_split = dkdv_split_is_faster(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
+  const KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
+  p.kv_pair = kv == KV_PAIR;
+  p.kv_split = kv == KV_SPLIT;
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
   p.work_kv.dyn_div = dyn_div_of(all, qt.size(), kt.size(), sh->Hq / sh->Hkv);
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();

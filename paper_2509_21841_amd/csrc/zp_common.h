@@ -145,6 +145,7 @@ struct zp_bwd_params {
   __bf16 *dq, *dk, *dv;      // outputs (bf16, overwritten) ...
   int64_t dq_stride, dkv_stride;
   int32_t dq_pair;           // dQ by the kernel for launches that leave much of the chip idle: tiles of 64 rows, in the launch arguments
+  int32_t kv_pair;           // dK/dV at head dimension 128 by workgroups of two groups of four waves
   int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
   zp_work_split work_dq, work_kv;  // work hand-out of the two launches (counters set by the C ABI, the rest by the launcher)
