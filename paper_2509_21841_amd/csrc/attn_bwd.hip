@@ -373,11 +373,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   char *Ss = smem + 2 * NB * TILEB;  // [2][4][2][64 x 16 bytes]: a tile's dS, pair by pair, half by half
 
   int unit, hh;
-  zp_block_to_unit(blockIdx.x, p.grp, p.m_grp, unit, hh);
+  int part;
+  zp_block_to_unit(zp_pair_item(p.dq_pair, part), p.grp, p.m_grp, unit, hh);
   if (unit >= p.n_dq_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+  zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+  if (!zp_pair_rows(t, part)) return;
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
   const int half = __builtin_amdgcn_readfirstlane(tid >> 8);
@@ -1307,7 +1309,7 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   if (dq_units > 0) {
     zp_prof_begin(p->dq_pair ? "attn_bwd_dq_pair" : "attn_bwd_dq", stream);
     if (p->dq_pair) {
-      const dim3 grid(((dq_units + 7) / 8) * 8 * p->grp);
+      const dim3 grid(((dq_units + 7) / 8) * 8 * p->grp * (p->dq_pair == ZP_PAIR_HALVES ? 2 : 1));
       if (d == 128) hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<128>, grid, dim3(512), dq_pair_lds<128>(), stream, *p);
       else hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<64>, grid, dim3(512), dq_pair_lds<64>(), stream, *p);
     } else if (d == 128) hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 128 * 2 + 16, stream, *p);

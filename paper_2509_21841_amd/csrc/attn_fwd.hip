@@ -287,7 +287,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
     // unmasked tile (the common case), else in front of it
     const bool fetch = it + 1 < n_kt;
     const bool fused = fetch && act0 && !masked && j0 + 2 * BN <= t.k_len;
-    if (fetch && !fused) {
+    if (__builtin_expect(fetch && !fused, 0)) {  // (behind the loop's own code: 2.5 % of a launch with one workgroup per CU)
       kst.issue(Ks + (buf ^ 1) * C::TILEB, j0 + BN, t.k_len);
       vst.issue(Vs + (buf ^ 1) * C::TILEB, j0 + BN, t.k_len);
     }
@@ -461,11 +461,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
   char *Fs = As + 4 * 4 * 256;      // [2][4]: whether it is
 
   int unit, hh;
-  zp_block_to_unit(blockIdx.x, p.grp, p.m_grp, unit, hh);
+  int half;
+  zp_block_to_unit(zp_pair_item(p.pair, half), p.grp, p.m_grp, unit, hh);
   if (unit >= p.n_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+  zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+  if (!zp_pair_rows(t, half)) return;
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
   const bool values = __builtin_amdgcn_readfirstlane(tid >> 8) != 0;
@@ -606,7 +608,7 @@ extern "C" int zp_launch_attn_fwd(const zp_attn_params *p, int d, int partial, i
   p = &q;
   (void)block_rows;
   if (q.pair) {
-    const int pair_grid = ((units + 7) / 8) * 8 * p->grp;
+    const int pair_grid = ((units + 7) / 8) * 8 * p->grp * (q.pair == ZP_PAIR_HALVES ? 2 : 1);
     zp_prof_begin(partial ? "attn_fwd_partial_pair" : "attn_fwd_pair", stream);
 #define ZP_FWD_PAIR(D, PART) hipLaunchKernelGGL((attn_fwd_pair_kernel<D, PART>), dim3(pair_grid), dim3(512), pair_lds<D>(), stream, q)
     if (d == 128) {

@@ -110,6 +110,22 @@ __device__ __forceinline__ int zp_item_of_block(const zp_work_split &ws, int *sl
   return __builtin_amdgcn_readfirstlane(*slot);
 }
 
+// The kernels that put two waves on every 16 query rows work on 64 rows at a time. Their table is in the launch arguments, as
+// tiles of 64 rows (ordered by cost, none empty) where that many fit, else as the tiles of 128, whose halves are two workgroups.
+enum zp_pair_mode { ZP_PAIR_NONE = 0, ZP_PAIR_TILES = 1, ZP_PAIR_HALVES = 2 };
+// The item of this workgroup (halves: both on one XCD, the later rows first) and, of its tile, the 64 rows.
+__device__ __forceinline__ int zp_pair_item(int mode, int &half) {
+  const int b = blockIdx.x, y = b >> 3;
+  half = mode == ZP_PAIR_HALVES ? 1 - (y & 1) : 0;
+  return mode == ZP_PAIR_HALVES ? (y >> 1) * 8 + (b & 7) : b;
+}
+__device__ __forceinline__ bool zp_pair_rows(zp_tile &t, int half) {
+  if (64 * half >= t.q_rows) return false;
+  t.q_tok0 += 64 * half; t.q_pos0 += 64 * half; t.out_row0 += 64 * half;
+  t.q_rows = min(64, t.q_rows - 64 * half);
+  return true;
+}
+
 // Parameters shared by the attention kernels. Strides are token strides in elements.
 struct zp_attn_params {
   const __bf16 *q, *k, *v;
@@ -124,7 +140,7 @@ struct zp_attn_params {
   float *lse;        // [Hq][lse_stride]
   int64_t lse_stride;
   int32_t update;    // partial kernel only: merge the result into the running (o, lse) found at the output rows
-  int32_t pair;      // by the kernel for launches that leave much of the chip idle: tiles of 64 rows, in the launch arguments
+  int32_t pair;      // by the kernel for launches that leave much of the chip idle: zp_pair_mode
   zp_work_split work;  // which workgroups take their item by number and which claim one (set by the launcher)
   zp_inline_tiles inl; // the tile table if `tiles` is null
 };
@@ -144,7 +160,7 @@ struct zp_bwd_params {
   float scale_log2, scale;
   __bf16 *dq, *dk, *dv;      // outputs (bf16, overwritten) ...
   int64_t dq_stride, dkv_stride;
-  int32_t dq_pair;           // dQ by the kernel for launches that leave much of the chip idle: tiles of 64 rows, in the launch arguments
+  int32_t dq_pair;           // dQ by the kernel for launches that leave much of the chip idle: zp_pair_mode
   int32_t kv_pair;           // dK/dV at head dimension 128 by workgroups of two groups of four waves
   int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
@@ -321,7 +337,7 @@ struct zp_stager {
   // extra: a wave-uniform element offset added to every source address (e.g. head * D)
   __device__ __forceinline__ void issue(char *lds_tile, int row0, int rows_total, int64_t extra = 0) const {
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(zp_lds_addr(lds_tile));
-    if (row0 + 64 <= rows_total) {
+    if (__builtin_expect(row0 + 64 <= rows_total, 1)) {  // (the rest behind the loop around it)
       const void *sb = zp_uniform_ptr(base + (int64_t)row0 * stride + extra);
 #pragma unroll
       for (int n = 0; n < PER_WAVE; n++) zp_dma16_so(sb, off[n], lds0 + dest(n));

@@ -54,32 +54,46 @@ inline float zp_pair_estimate(const zp_pair_cost &c, const int *cost, int n, int
   return head + (pairs ? std::max(most, 1.03f * sum + 0.5f * dur(items - 1)) : std::max(most + c.share * dur(256), sum * 0.5f * (1.f + c.share)));
 }
 
-// Turns the table of a launch (n tiles of 128 rows in the launch arguments, `behind` tiles of another launch behind them) into
-// the one of the kernel with two waves per 16 rows where that is the faster one; false: the table stays as it is. With a CU
-// for every workgroup it always is, the launch being its longest chain; beyond, its estimate has to be below `margin` of the
-// other kernel's.
-inline bool zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int Hkv, int grp, const zp_pair_cost &whole, const zp_pair_cost &pair,
-                          float margin) {
+// Whether a launch (n tiles of 128 rows in the launch arguments, `behind` tiles of another launch behind them) takes the kernel
+// with two waves per 16 rows, and how its table is laid out then. With a CU for every workgroup that is always the faster
+// one, the launch being its longest chain; beyond, its estimate has to be below `margin` of the other kernel's, by a tenth more
+// where the table does not fit and so is not in order of cost.
+inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int Hkv, int grp, const zp_pair_cost &whole, const zp_pair_cost &pair,
+                                  float margin) {
   const int heads = Hkv * grp;
   zp_tile *tiles = inl.t;
-  if (n > ZP_INLINE_TILES || (int64_t)n * heads > 1024) return false;
+  if (n < 1 || n > ZP_INLINE_TILES || (int64_t)n * heads > 1024) return ZP_PAIR_NONE;
   int m = 0;
   for (int i = 0; i < n; i++) m += tiles[i].q_rows > 64 ? 2 : 1;
-  if (m + behind > ZP_INLINE_TILES || m * heads > 1024) return false;
+  if (m * heads > 1024) return ZP_PAIR_NONE;
+  const bool fits = m + behind <= ZP_INLINE_TILES;
   zp_inline_tiles half;
-  if ((m * Hkv + 7) / 8 * grp <= 32) {
-    zp_halve_tiles(tiles, n, half, nullptr);
+  if (((fits ? m : 2 * n) * Hkv + 7) / 8 * grp <= 32) {
+    if (fits) zp_halve_tiles(tiles, n, half, nullptr);
   } else {
-    int cost64[ZP_INLINE_TILES], cost128[ZP_INLINE_TILES];
-    zp_halve_tiles(tiles, n, half, cost64);
+    int cost64[2 * ZP_INLINE_TILES], cost128[ZP_INLINE_TILES], k = 0;
     for (int i = 0; i < n; i++) cost128[i] = zp_key_tiles(tiles[i]);
+    if (fits) {
+      zp_halve_tiles(tiles, n, half, cost64);
+    } else {
+      for (int i = 0; i < n; i++) {
+        cost64[k++] = cost128[i];
+        if (tiles[i].q_rows > 64) {
+          zp_tile t = tiles[i];
+          t.q_rows = 64;
+          cost64[k++] = zp_key_tiles(t);
+        }
+      }
+      std::sort(cost64, cost64 + m, [](int a, int b) { return a > b; });
+    }
     std::sort(cost128, cost128 + n, [](int a, int b) { return a > b; });
-    if (!(zp_pair_estimate(pair, cost64, m, heads, true) < margin * zp_pair_estimate(whole, cost128, n, heads, false))) return false;
+    if (!(zp_pair_estimate(pair, cost64, m, heads, true) < (fits ? margin : margin - 0.1f) * zp_pair_estimate(whole, cost128, n, heads, false))) return ZP_PAIR_NONE;
   }
+  if (!fits) return ZP_PAIR_HALVES;
   std::memmove(tiles + m, tiles + n, (size_t)behind * sizeof(zp_tile));
   std::memcpy(tiles, half.t, (size_t)m * sizeof(zp_tile));
   n = m;
-  return true;
+  return ZP_PAIR_TILES;
 }
 
 // The forward's two kernels. Constants fitted to 850 launches whose tables fit (4/2 to 64/8 and 8/1 heads; equal, ragged and
@@ -91,6 +105,8 @@ inline bool zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int Hkv, int
 //    64   4/4   4000   n =  1:  51.9 / 33.5    64/8, L =  762, n = 2:  17.7 / 24.2
 //   128   4/4   1000   n =  4:  23.2 / 15.4    64/8, L =  894, n = 2:  27.8 / 35.1
 //   128   8/2   2085   n =  1:  41.4 / 27.1    16/4, L =  200, n = 20: 21.9 / 26.2
+// Of 370 ragged batches of 2000 to 20000 tokens under 1 to 16 heads, whose tables fit or not, 216 take the pairs at one margin for
+// both, for 0.76 of the time in the mean; the tenth keeps out those that lost (six sequences of 10943 tokens, 4/4 heads, d = 64: 45.4 -> 42.0; one of 2931 and others, 9860 tokens, 2/1, d = 128: 54.5 -> 39.4).
 inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
   static const zp_pair_cost whole[2] = {{2.95f, 0.769f, 1.74f, 0.0023f, 0.345f}, {2.20f, 1.074f, 3.19f, 0.0032f, 0.536f}};
   static const zp_pair_cost pair[2] = {{2.03f, 0.471f, 1.95f, 0.0022f, 1.f}, {2.63f, 0.660f, 1.64f, 0.0027f, 1.f}};
@@ -105,5 +121,5 @@ inline void zp_plan_dq_pair(zp_bwd_params &p, int d) {
   static const zp_pair_cost whole[2] = {{2.5f, 0.817f, 1.4f, 0.0023f, 0.345f}, {2.8f, 1.20f, 2.8f, 0.0032f, 0.536f}};
   static const zp_pair_cost pair[2] = {{2.5f, 0.655f, -0.6f, 0.0022f, 1.f}, {3.2f, 0.945f, -0.2f, 0.0027f, 1.f}};
   if (p.dq_tiles == nullptr)
-    p.dq_pair = p.n_dq_tiles > 0 && zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.85f);
+    p.dq_pair = zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.85f);
 }

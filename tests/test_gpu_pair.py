@@ -12,7 +12,9 @@ from paper_2509_21841_amd import synth
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 BATCHES = [([1], 1, 1), ([15, 16, 17, 0, 31, 32, 33], 2, 1), ([63, 64, 65], 3, 3), ([127, 128, 129, 1, 191, 192, 193], 4, 2),
-           ([255, 257, 320], 8, 1), ([449, 2], 6, 3), ([1100], 5, 1), ([2000], 4, 4)]
+           ([255, 257, 320], 8, 1), ([449, 2], 6, 3), ([1100], 5, 1), ([2000], 4, 4),
+           ([2931, 2500, 64, 65, 1900, 1, 1283], 2, 1)]   # the last one's 64-row tiles do not fit the launch arguments,
+DQ_BATCHES = BATCHES[:-1] + [([2900, 1900, 64, 65, 1, 1283], 2, 1)]   # nor this one's beside the dK/dV tiles
 
 
 def bits(t):
@@ -96,7 +98,7 @@ def test_nothing_visible_is_not_poisoned():
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("lengths,Hq,Hkv", BATCHES)
+@pytest.mark.parametrize("lengths,Hq,Hkv", DQ_BATCHES)
 def test_dq_is_the_same_bits(lengths, Hq, Hkv, d):
     n, all_lengths = sum(lengths), lengths + filler(Hq)
     T = sum(all_lengths)
