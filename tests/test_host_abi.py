@@ -252,3 +252,39 @@ def test_scratch_of_captured_calls_is_not_shared(monkeypatch):
     capturing[0] = False
     assert B.workspace(5000, "cpu", "fwd") is eager
     assert B.workspace(100, "cpu", "bwd") is not fresh
+
+
+def test_cached_scratch_is_handed_out_before_its_size_is_asked(monkeypatch):
+    """Calls of 5000, 3000, 9000 bytes, one that fails, one that is captured: the size is asked only where nothing cached is enough."""
+    capturing, asked, seen = [False], [], []
+    monkeypatch.setattr(B, "_ws_cache", {})
+    monkeypatch.setattr(B, "_stream_ptr", lambda stream=None: 7)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
+
+    def run(nbytes, ws=None, rc=0):
+        def call(w):
+            if w.numel() < nbytes:
+                return B.E_WORKSPACE
+            seen.append(w)
+            return rc
+
+        def need():
+            asked.append(nbytes)
+            return nbytes
+
+        B._with_scratch(call, ws, "cpu", "fwd", None, need)
+
+    for n in (5000, 3000, 9000, 5000):
+        run(n)
+    assert asked == [5000, 9000] and seen[0] is seen[1] and seen[2] is seen[3] and seen[2].numel() >= 9000
+    with pytest.raises(B.ZpError):
+        run(100, rc=-1)
+    with pytest.raises(B.ZpError):
+        run(100, ws=torch.empty(99, dtype=torch.uint8))   # the caller's own is never replaced
+    assert asked == [5000, 9000]
+    capturing[0] = True
+    run(100)
+    assert asked == [5000, 9000, 100] and seen[-1] is not seen[2]
+    capturing[0] = False
+    run(100)
+    assert asked == [5000, 9000, 100] and seen[-1] is seen[2]
