@@ -219,6 +219,22 @@ def kernel_flops(job, label: str) -> float:
             "attn_bwd_dq": 3 * per_gemm_all, "attn_bwd_dkdv": 4 * per_gemm_all}.get(label, 0.0)
 
 
+def kernel_of(label: str) -> str:
+    """The launch a profile label stands for: the kernels for launches that leave part of the chip idle do the same work."""
+    for suffix in ("_pair", "_split"):
+        label = label.removesuffix(suffix)
+    return label
+
+
+def kernel_table(recs, steps: int):
+    """Profile records (label, ms) of `steps` steps -> launches and times of each kernel."""
+    by = {}
+    for label, ms in recs:
+        by.setdefault(kernel_of(label), []).append(ms)
+    return {k: {"launches_per_step": len(v) // steps, "avg_ms": float(np.mean(v)), "ms_per_step": float(np.sum(v)) / steps}
+            for k, v in by.items()}
+
+
 def cpu_baseline(job: Job, target_s: float = 15.0):
     """Times the fp64 oracle (forward + backward, as it stands) on the shortest sequences of the batch."""
     import oracle
@@ -297,13 +313,7 @@ def measure(job, steps: int, warmup: int):
     ms_step = ev0.elapsed_time(ev1) / steps
     recs = B.profile_records()
     B.profile_enable(False)
-    by = {}
-    for label, ms in recs:
-        # the same work by the kernel for launches that leave most of the chip idle
-        by.setdefault("attn_bwd_dkdv" if label == "attn_bwd_dkdv_split" else label, []).append(ms)
-    kern = {k: {"launches_per_step": len(v) // steps, "avg_ms": float(np.mean(v)), "ms_per_step": float(np.sum(v)) / steps}
-            for k, v in by.items()}
-    return ms_step, wall, kern
+    return ms_step, wall, kernel_table(recs, steps)
 
 
 def fwd_bwd_rates(job, kern):

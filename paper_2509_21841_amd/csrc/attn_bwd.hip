@@ -1319,7 +1319,7 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
     if (e != hipSuccess) return (int)e;
   }
   if (kv_units > 0) {
-    zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : "attn_bwd_dkdv", stream);
+    zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : p->kv_pair && d == 128 ? "attn_bwd_dkdv_pair" : "attn_bwd_dkdv", stream);
     if (p->kv_split) {
       const dim3 grid(((kv_units + 7) / 8) * 8 * 4);
       if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(512), split_lds<128>(), stream, *p);

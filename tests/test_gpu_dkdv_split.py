@@ -59,7 +59,7 @@ def test_both_sides_of_the_rule(n, d):
         for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
             assert_close(name, widen(a[sl]), b, maxabs=MAXABS, rell2=RELL2)
     if n <= 8 or n >= 40:
-        assert dkdv_labels(do, q, k, v, o, lse, cu) == {"attn_bwd_dkdv_split" if n <= 8 else "attn_bwd_dkdv"}
+        assert (dkdv_labels(do, q, k, v, o, lse, cu) == {"attn_bwd_dkdv_split"}) == (n <= 8)
 
 
 def dkdv_labels(*call):
@@ -82,4 +82,4 @@ def test_the_faster_kernel_is_taken(d, Hq, Hkv, L, n, split):
     q, k, v, do = synth.make_qkv(L * n, Hq, Hkv, d, 107, DEV, with_dout=True)
     cu = synth.cu_seqlens([L] * n)
     o, lse = B.varlen_attn_fwd(q, k, v, cu)
-    assert dkdv_labels(do, q, k, v, o, lse, cu) == {"attn_bwd_dkdv_split" if split else "attn_bwd_dkdv"}
+    assert (dkdv_labels(do, q, k, v, o, lse, cu) == {"attn_bwd_dkdv_split"}) == split

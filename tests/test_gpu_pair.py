@@ -164,7 +164,8 @@ def test_dkdv_of_two_groups(lengths, Hq, Hkv):
     cu = synth.cu_seqlens(lengths)
     o, lse = B.varlen_attn_fwd(q, k, v, cu)
     call = lambda: B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
-    got = call()
+    got, names = labels(call)
+    assert names[-1] == "attn_bwd_dkdv_pair"
     for a, b in zip(got, call()):
         assert torch.equal(bits(a), bits(b))
     for i in {0, 2, len(lengths) - 1}:
@@ -178,7 +179,8 @@ def test_dkdv_of_two_groups(lengths, Hq, Hkv):
             assert float((a - b).norm()) <= (5e-3 if lengths[i] > 100 else 1.5e-2) * float(b.norm()) + 1e-3
     acc = [torch.zeros(x.shape, dtype=torch.float32, device=DEV) for x in (q, k, v)]
     pairs = [dict(q_tok0=int(cu[i]), q_len=n, k_tok0=int(cu[i]), k_len=n, q_pos0=0, k_pos0=0, out_row0=0) for i, n in enumerate(lengths)]
-    B.chunk_attn_partial_bwd(do, q, k, v, o, lse, pairs, *acc)
+    _, names = labels(lambda: B.chunk_attn_partial_bwd(do, q, k, v, o, lse, pairs, *acc))
+    assert names[-1] == "attn_bwd_dkdv_pair"
     for a, b in zip(acc, got):   # the written results are these, rounded once (their launches number the key blocks alike)
         a, b = a.to(torch.bfloat16).float(), b.float()
         assert bool(((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-4).all())
