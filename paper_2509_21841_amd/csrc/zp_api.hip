@@ -276,91 +276,131 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   return upload_tiles(tiles, ws, stream);
 }
 // Which dK/dV kernel a launch takes, by estimates of their times in microseconds; an iteration is a (32-query tile, head). All deal
-// the units (tile, KV head) to the XCDs by turns, and the XCD that ends last decides.
-//  - whole: one workgroup of four waves per key block. The first 32 units of an XCD get a CU each, the next 32 share those in
-//    the same order; an iteration beside another workgroup takes 1.35 to 1.39 times as long. The longest chain with its
-//    companion's share; behind two workgroups per CU, no less than all iterations and a part of those that start last.
-//  - pair (d = 128): one workgroup of two groups of four waves per key block and CU, half the chain. The longest one, or all of
-//    them over 32 CUs and a part of those that start last.
-//  - split: four workgroups of four groups of two waves per key block (those without keys cost a prologue as well), a quarter
-//    of the chain. One per CU at d = 128, two at 64. The longest one while 32 CUs hold all of an XCD's, else their time over
-//    the CUs and a part of those that start last, no more than the longest per round.
-// More than 1024 units always take the first: their number evens out what the others gain. The constants are fitted to some 875
-// launches of 4/4 to 64/8 and 8/1 heads (equal, ragged and lognormal lengths of 100 to 100000 tokens in all); the
-// estimates are 5 to 8 % off in the mean, so the split is taken when its is 5 % below (at d = 64 18 % behind
-// 128 units, where two of its workgroups share a CU) and the pair when its is 3 % below. On 870 other launches the kernel taken
-// is 1 % behind the fastest in the mean; none is more than 12 % behind the first one. n sequences,
-// us, whole / pair / split:
+// the units (tile, KV head) to the XCDs by turns. An XCD hands its workgroups in order and by turns to four engines of eight
+// CUs; one waits for its engine, whatever room the others have. (Sequences of four key blocks so put every longest chain on
+// one engine: 17 of 405 tokens, 64/8 heads, d = 128, 260 us where their sum would make 175.)
+//  - whole: one workgroup of four waves per key block. Two share a CU, 32 units apart, and an iteration beside another workgroup
+//    takes 1.35 to 1.37 times as long. The longest pair of chains; behind two workgroups per CU, no less than all of the fullest
+//    engine and a part of those that start last. Iterations on the diagonal count more (masks), and d = 64 takes 64 queries at a time.
+//  - pair (d = 128): one workgroup of two groups of four waves per key block and CU, half the chain.
+//  - split: four workgroups of four groups of two waves per key block, some of them without keys, a quarter of the chain. One
+//    per CU at d = 128. Two share a CU at 64: the longest one while 32 CUs hold all of an XCD's, else their time over the CUs
+//    and a part of those that start last, no more than the longest per round; those without keys cost 2 us.
+// Pair and split at d = 128 are placed workgroup by workgroup, those of the XCD with the most iterations (0.1 us of host
+// time in the mean, 2.5 at most; not where their sum is longer already). More than 1024 units always take the first: their number evens out what the
+// others gain.
+//
+// The constants are fitted to 3900 launches of 2/1 to 64/8 heads (equal, ragged and lognormal lengths, 16 to 40000 tokens);
+// the estimates are 3 to 5 % off in the mean. The split has to be 3 % below at d = 64 and the pair 2 %. Of all 4500 launches
+// (with dQ in front) 10 are more than 5 % behind the fastest of the three, 0.06 % in the mean, and none more than 3 % behind
+// the first. n sequences, us, whole / pair / split:
 //    d   heads   tokens                              taken
-//    64   8/1    3722, longest 2315, n =  3:  329.8 /     - /  119.2   split
-//    64   8/8   26831, longest 3762, n = 20:  149.9 /     - /  210.6   whole
-//   128   4/4    6434, longest 2665, n =  5:   92.3 /  71.4 /   57.7   split
-//   128   8/8    6813, longest 2453, n =  9:   91.1 /  69.0 /   96.3   pair
-//   128  32/8    8547, longest 5430, n =  2:  779.0 / 632.6 /  878.4   pair
-//   128  32/32  12000, longest 3074, n = 11:  384.9 / 424.7 /  766.3   whole
+//    64  64/8    1698, longest   98, n = 39:   33.7 /     - /   27.9   split
+//    64  16/16    312, equal,        n =  8:    5.1 /     - /    6.9   whole
+//    64  16/16   7923, longest 2641, n =  3:  101.7 /     - /  136.9   whole
+//   128  16/4     919, longest  100, n = 18:   24.2 /  19.8 /   11.5   split
+//   128   8/8    2456, longest 1493, n =  2:   55.0 /  43.8 /   32.7   split
+//   128   8/8    7721, longest 2502, n = 14:   96.1 /  71.8 /  106.8   pair
+//   128  32/32   3037,               n =  1:  137.1 / 151.1 /  242.2   whole
+//   128   8/8   14745, equal,        n = 15:  101.0 / 113.5 /  160.0   whole
 struct KvCost {
-  float whole, whole_it, whole_head, share, rate, whole_tail;  // fixed, per iteration, per head; of the companion's; all of them, of the last
-  float pair, pair_wg, pair_it, pair_tail;                     // per launch; per workgroup: fixed, per iteration of a group; share of the last
-  float split, split_wg, split_it, split_tail, empty, beside;  // the same; a workgroup without keys; what a second one on the CU adds
+  float whole, whole_it, share, rate, whole_tail, whole_wg, mask;  // fixed, per iteration; in iterations: of the companion's, all of them, of the last; per workgroup, masked one
+  float split, split_wg, split_it;                                 // per launch; per workgroup: fixed, per iteration of a group
 };
 enum KvKernel { KV_WHOLE, KV_PAIR, KV_SPLIT };
+// Workgroups of one XCD with a CU each, in order: when the last one ends.
+struct KvPlacement {
+  float busy[4][8] = {}, end = 0.f;
+  int next = 0;
+  void start(float time) {
+    float *b = busy[next++ & 3];
+    int at = 0;
+    for (int i = 1; i < 8; i++) at = b[i] < b[at] ? i : at;
+    b[at] += time;
+    end = std::max(end, b[at]);
+  }
+};
 KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int grp) {
-  static const KvCost cost[2] = {{7.07f, 0.541f, 1.142f, 0.393f, 0.951f, 0.991f, 0.f, 0.f, 0.f, 0.f, 4.13f, 2.0f, 0.809f, 0.703f, 2.18f, 0.549f},
-                                 {8.19f, 1.011f, 0.370f, 0.346f, 0.968f, 0.509f, 2.77f, 6.50f, 1.51f, 0.917f, 2.58f, 5.03f, 1.267f, 0.444f, 4.22f, 1.f}};
+  static const KvCost cost[2] = {{2.12f, 0.565f, 0.371f, 0.841f, 0.136f, 3.08f, 0.375f, 2.46f, 1.86f, 0.831f},
+                                 {0.49f, 1.029f, 0.349f, 0.740f, 0.586f, 4.30f, 0.154f, 1.69f, 2.82f, 1.255f}};
   const KvCost &c = cost[d == 128];
   const int64_t units = (int64_t)kt.size() * Hkv;
   if (units > 1024) return KV_WHOLE;
   struct Xcd {
-    int n = 0, wg = 0, last_wg = 0;      // units; workgroups of the split with keys, those of them that start last (about 32)
-    float it = 0.f, split_it = 0.f, last_it = 0.f, last32 = 0.f;  // iterations; of the split's workgroups' groups; of its last; of the last 32 units
-    float chain[128];
+    int n = 0, parts[128];                  // units; of each: its 32-row parts with keys,
+    float its[128], chain[128], all = 0.f;  // its iterations, the same with what else the whole kernel spends; of all units
   } xcd[8];
-  int64_t longest = 0;
-  int u = (int)units;
-  for (size_t i = kt.size(); i-- > 0;) {
-    const int64_t its = (int64_t)((kt[i].t.q_rows + 31) / 32) * grp, per_group = (its + 3) / 4;
-    const int parts = (kt[i].t.k_len + 31) / 32;
+  int u = 0;
+  float longest = 0.f;
+  for (const CostTile &k : kt) {
+    const float its = (float)((k.t.q_rows + 31) / 32) * (float)grp, wide = d == 64 ? (float)((k.t.q_rows + 63) / 64 * 2) * (float)grp : its;
     longest = std::max(longest, its);
-    for (int g = 0; g < Hkv; g++) {
-      Xcd &x = xcd[--u & 7];
-      x.chain[u >> 3] = (float)its;
-      if (x.n < 32) x.last32 += (float)its / 32.f;
-      if (x.last_wg < 32) {
-        x.last_wg += parts;
-        x.last_it += (float)(parts * per_group);
-      }
-      x.n++;
-      x.wg += parts;
-      x.it += (float)its;
-      x.split_it += (float)(parts * per_group);
+    for (int g = 0; g < Hkv; g++, u++) {
+      Xcd &x = xcd[u & 7];
+      x.parts[x.n] = (k.t.k_len + 31) / 32;
+      x.its[x.n] = its;
+      x.chain[x.n++] = wide + c.mask * std::min(wide, 4.f * (float)grp) + c.whole_wg;
+      x.all += its;
     }
   }
-  const bool two = d == 64;  // workgroups of the split on a CU
-  const float top = c.split_wg + c.split_it * (float)((longest + 3) / 4), slow = two ? 1.f + c.beside : 1.f;
-  const int places = two ? 64 : 32;
-  int64_t split_wgs = 0;
-  float whole_its = 0.f, pair = c.pair_wg + c.pair_it * (float)((longest + 1) / 2), split = top;
+  float whole = 0.f;
+  const Xcd *most = xcd;
   for (const Xcd &x : xcd) {
-    split_wgs += x.wg;
-    for (int i = 0; i < std::min(32, x.n); i++)
-      whole_its = std::max(whole_its, x.chain[i] + (i + 32 < x.n ? c.share * x.chain[i + 32] : 0.f));
-    if (x.n > 64) whole_its = std::max(whole_its, x.it / 32.f * c.rate + c.whole_tail * x.last32);
-    if (x.n > 32)
-      pair = std::max(pair, (c.pair_wg * (float)x.n + c.pair_it * 0.5f * x.it) / 32.f + c.pair_tail * (c.pair_wg + c.pair_it * 0.5f * x.last32));
-    if (x.n > 8) {
-      const float all = c.split_wg * (float)x.wg + c.empty * (float)(4 * x.n - x.wg) + c.split_it * x.split_it;
-      const float fill = all * slow / (float)places + c.split_tail * (c.split_wg + c.split_it * x.last_it / (float)x.last_wg);
-      split = std::max(split, std::min(fill, top * slow * (float)((4 * x.n + places - 1) / places)));
+    if (x.all > most->all) most = &x;
+    for (int i = 0; i < std::min(32, x.n); i++) {
+      const float beside = i + 32 < x.n ? x.chain[i + 32] : 0.f;
+      whole = std::max(whole, std::max(x.chain[i], beside) + c.share * std::min(x.chain[i], beside));
+    }
+    if (x.n > 64) {
+      float engine[4] = {}, last = 0.f;
+      for (int i = 0; i < x.n; i++) {
+        engine[i & 3] += x.chain[i];
+        if (i >= x.n - 32) last += x.chain[i];
+      }
+      const float fullest = std::max(std::max(engine[0], engine[1]), std::max(engine[2], engine[3]));
+      whole = std::max(whole, fullest / 8.f * c.rate + c.whole_tail * last / 32.f);
     }
   }
-  const float t_whole = c.whole + c.whole_it * whole_its + c.whole_head * (float)grp;
-  const float t_pair = d == 128 ? c.pair + pair : t_whole, t_split = c.split + split;
-  // sequences under 64 keys leave most of the split's workgroups without any; behind one per CU it then loses up to a fifth, but
-  // for heads that share a short chain at d = 64 (thirteen sequences of 10 tokens, 64/8: 16.8 us whole, 9.3 split)
-  const bool empty = units > 64 && split_wgs < 2 * units && (d == 128 || grp == 1);
-  const float margin = d == 64 && units > 128 ? 0.82f : 0.95f;
-  if (t_split < margin * std::min(t_whole, t_pair) && !empty) return KV_SPLIT;
-  return t_pair < 0.97f * t_whole ? KV_PAIR : KV_WHOLE;
+  const float t_whole = c.whole + c.whole_it * whole;
+  if (d == 64) {
+    const float top = c.split_wg + c.split_it * floorf((longest + 3.f) / 4.f), slow = 1.519f;
+    float split = top;
+    for (const Xcd &x : xcd) {
+      if (x.n <= 8) continue;
+      float wgs = 0.f, its = 0.f, last_wgs = 0.f, last_its = 0.f;
+      for (int i = x.n; i-- > 0;) {
+        const float p = (float)x.parts[i], it = floorf((x.its[i] + 3.f) / 4.f) * p;
+        if (last_wgs < 32.f) { last_wgs += p; last_its += it; }
+        wgs += p; its += it;
+      }
+      const float all = c.split_wg * wgs + 2.01f * ((float)(4 * x.n) - wgs) + c.split_it * its;
+      const float fill = all * slow / 64.f + 0.923f * (c.split_wg + c.split_it * last_its / std::max(1.f, last_wgs));
+      split = std::max(split, std::min(fill, top * slow * (float)((4 * x.n + 63) / 64)));
+    }
+    return c.split + split < 0.97f * t_whole ? KV_SPLIT : KV_WHOLE;
+  }
+
+  constexpr float PAIR = 1.04f, PAIR_WG = 3.61f, PAIR_IT = 1.533f, SPLIT_MASK = 0.514f;
+  const float least = PAIR_IT * 0.5f * most->all / 32.f, longest_pair = PAIR_WG + floorf((longest + 1.f) / 2.f);
+  float t_pair = t_whole;
+  if (PAIR + std::max(least, PAIR_IT * longest_pair) < 0.98f * t_whole) {
+    KvPlacement on;
+    for (int i = 0; i < most->n; i++) on.start(PAIR_WG + floorf((most->its[i] + 1.f) / 2.f));
+    t_pair = PAIR + PAIR_IT * std::max(on.end, longest_pair);
+  }
+  const bool pair = t_pair < 0.98f * t_whole;
+  const float other = std::min(t_whole, t_pair), masked = SPLIT_MASK * (float)((grp + 3) / 4);
+  float all = 0.f;
+  for (int i = 0; i < most->n; i++) all += (float)most->parts[i] * (c.split_wg + masked + floorf((most->its[i] + 3.f) / 4.f));
+  if (c.split + c.split_it * all / 32.f < other) {
+    KvPlacement on;
+    for (int i = 0; i < most->n; i++) {
+      const float time = c.split_wg + masked + floorf((most->its[i] + 3.f) / 4.f);
+      for (int part = 0; part < 4; part++) on.start(part < most->parts[i] ? time : 0.f);
+    }
+    if (c.split + c.split_it * on.end < other) return KV_SPLIT;
+  }
+  return pair ? KV_PAIR : KV_WHOLE;
 }
 // work items of a launch over n tiles: (tile, KV head) units padded to one per XCD, times the heads in a group
 int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7) / 8 * 8 * grp; }
