@@ -56,10 +56,10 @@ inline float zp_pair_estimate(const zp_pair_cost &c, const int *cost, int n, int
 
 // Whether a launch (n tiles of 128 rows in the launch arguments, `behind` tiles of another launch behind them) takes the kernel
 // with two waves per 16 rows, and how its table is laid out then. With a CU for every workgroup that is always the faster
-// one, the launch being its longest chain; beyond, its estimate has to be below `margin` of the other kernel's, by a tenth more
-// where the table does not fit and so is not in order of cost.
+// one, the launch being its longest chain; beyond, its estimate has to be below `margin` of the other kernel's, or below
+// `halves` where the table does not fit and so is not in order of cost.
 inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int Hkv, int grp, const zp_pair_cost &whole, const zp_pair_cost &pair,
-                                  float margin) {
+                                  float margin, float halves) {
   const int heads = Hkv * grp;
   zp_tile *tiles = inl.t;
   if (n < 1 || n > ZP_INLINE_TILES || (int64_t)n * heads > 1024) return ZP_PAIR_NONE;
@@ -87,7 +87,7 @@ inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int 
       std::sort(cost64, cost64 + m, [](int a, int b) { return a > b; });
     }
     std::sort(cost128, cost128 + n, [](int a, int b) { return a > b; });
-    if (!(zp_pair_estimate(pair, cost64, m, heads, true) < (fits ? margin : margin - 0.1f) * zp_pair_estimate(whole, cost128, n, heads, false))) return ZP_PAIR_NONE;
+    if (!(zp_pair_estimate(pair, cost64, m, heads, true) < (fits ? margin : halves) * zp_pair_estimate(whole, cost128, n, heads, false))) return ZP_PAIR_NONE;
   }
   if (!fits) return ZP_PAIR_HALVES;
   std::memmove(tiles + m, tiles + n, (size_t)behind * sizeof(zp_tile));
@@ -110,16 +110,22 @@ inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int 
 inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
   static const zp_pair_cost whole[2] = {{2.95f, 0.769f, 1.74f, 0.0023f, 0.345f}, {2.20f, 1.074f, 3.19f, 0.0032f, 0.536f}};
   static const zp_pair_cost pair[2] = {{2.03f, 0.471f, 1.95f, 0.0022f, 1.f}, {2.63f, 0.660f, 1.64f, 0.0027f, 1.f}};
-  if (p.tiles == nullptr) p.pair = zp_take_pairs(p.inl, p.n_tiles, 0, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.93f);
+  if (p.tiles == nullptr) p.pair = zp_take_pairs(p.inl, p.n_tiles, 0, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.93f, 0.83f);
 }
 
-// The dQ kernels, whose tiles have the dK/dV tiles behind them. Of 610 such launches the 429 that take the pairs are at most 4 %
-// slower with them (eight 11-token sequences, 64/8 heads); the whole backward takes 0.94 of the time in the mean of all. One
-// sequence of L tokens, 4 heads, dQ alone, us, whole / pairs: L = 1000, d = 128: 25.0 / 18.1, d = 64: 17.2 / 12.6; L = 4000: 81.4 / 62.2
-// and 55.6 / 43.4.
+// The dQ kernels, whose tiles have the dK/dV tiles behind them. Constants fitted to 3446 launches (2/1 to 64/8 heads; equal,
+// ragged and lognormal lengths, 16 to 7000 tokens); the estimates are 4 to 5 % off in the mean. Of the 2642 launches that take the
+// pairs 3 are 2 to 3 % slower with them and none is more; all 3446 take 0.86 of the time (geometric mean). n sequences, us, whole / pairs:
+//    d   heads   tokens                              taken: pairs      not taken
+//    64   4/4     954,               n =  1:   17.7 / 14.3
+//    64   4/4    3780,               n =  1:   55.6 / 44.5
+//   128   4/4     983,               n =  1:   26.3 / 20.5
+//   128   4/4    3907,               n =  1:   84.8 / 67.5
+//   128  16/16    830, longest   88, n = 17:                      9.8 / 11.5
+//   128   4/4    5677, equal,        n =  7:                     23.7 / 29.0   (as halves)
 inline void zp_plan_dq_pair(zp_bwd_params &p, int d) {
-  static const zp_pair_cost whole[2] = {{2.5f, 0.817f, 1.4f, 0.0023f, 0.345f}, {2.8f, 1.20f, 2.8f, 0.0032f, 0.536f}};
-  static const zp_pair_cost pair[2] = {{2.5f, 0.655f, -0.6f, 0.0022f, 1.f}, {3.2f, 0.945f, -0.2f, 0.0027f, 1.f}};
+  static const zp_pair_cost whole[2] = {{-0.273f, 0.864f, 4.78f, 0.00305f, 0.584f}, {1.36f, 1.29f, 4.29f, 0.00569f, 0.592f}};
+  static const zp_pair_cost pair[2] = {{2.18f, 0.691f, 1.42f, 0.0015f, 1.f}, {3.62f, 1.02f, 1.34f, 0.00266f, 1.f}};
   if (p.dq_tiles == nullptr)
-    p.dq_pair = zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.85f);
+    p.dq_pair = zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.91f, 0.76f);
 }

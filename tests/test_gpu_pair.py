@@ -119,6 +119,17 @@ def test_dq_is_the_same_bits(lengths, Hq, Hkv, d):
         assert torch.equal(bits(a), bits(b))
 
 
+# Launches whose dQ is slower with two waves per 16 query rows: one-tile chains that share CUs, tables that do not fit (us, one
+# wave / two: 17 sequences of up to 88 tokens 9.8 / 11.5, seven of 811 23.7 / 29.0).
+@pytest.mark.parametrize("lengths,Hq,Hkv,d", [([88] * 7 + [60] * 10, 16, 16, 128), ([88] * 2 + [60] * 8, 32, 32, 128), ([811] * 7, 4, 4, 128),
+                                              ([98] * 14 + [60] * 36, 4, 4, 64)])
+def test_the_faster_dq_is_taken(lengths, Hq, Hkv, d):
+    q, k, v, do = synth.make_qkv(sum(lengths), Hq, Hkv, d, 139, DEV, with_dout=True)
+    cu = synth.cu_seqlens(lengths)
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    assert labels(lambda: B.varlen_attn_bwd(do, q, k, v, o, lse, cu))[1][0] == "attn_bwd_dq"
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("q_pos0,k_pos0,q_len,k_len", [(0, 0, 128, 128), (40, 70, 128, 130), (64, 1, 17, 127), (5, 64, 113, 65), (0, 127, 128, 1),
                                                        (300, 0, 65, 299), (33, 0, 15, 512)])
