@@ -286,14 +286,17 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
 //  - split: four workgroups of four groups of two waves per key block, some of them without keys, a quarter of the chain. One
 //    per CU at d = 128. Two share a CU at 64: the longest one while 32 CUs hold all of an XCD's, else their time over the CUs
 //    and a part of those that start last, no more than the longest per round; those without keys cost 2 us.
-// Pair and split at d = 128 are placed workgroup by workgroup, those of the XCD with the most iterations (0.1 us of host
-// time in the mean, 2.5 at most; not where their sum is longer already). More than 1024 units always take the first: their number evens out what the
-// others gain.
+// Pair and split at d = 128 are placed workgroup by workgroup, those of the XCD with the most iterations (0.1 us of host time in
+// the mean, 3.5 at most; not where their sum is longer already). More than 1024 units always take the first: their number
+// evens out what the others gain.
 //
 // The constants are fitted to 3900 launches of 2/1 to 64/8 heads (equal, ragged and lognormal lengths, 16 to 40000 tokens);
-// the estimates are 3 to 5 % off in the mean. The split has to be 3 % below at d = 64 and the pair 2 %. Of all 4500 launches
-// (with dQ in front) 10 are more than 5 % behind the fastest of the three, 0.06 % in the mean, and none more than 3 % behind
-// the first. n sequences, us, whole / pair / split:
+// the estimates are 3 to 5 % off in the mean. The split has to be 3 % below at d = 64, and at d = 128 the pair 2 %. Beyond
+// 200 us, where the clock falls with what the CUs have to do, the split has to be 8 % below (six sequences, 6705 tokens, 64/8:
+// 729 us estimated against 736 for the pair; backward 1210 against 1073), and the pair may be 4 % above if heads share a
+// KV head (ten sequences of 2628 tokens, 16/4: 575 against 569 for the first; 998 against 1072). Of all 4500 launches (with dQ in front)
+// 11 are more than 5 % behind the fastest of the three, 0.06 % in the mean, and none more than 3 % behind the first. n
+// sequences, us, whole / pair / split:
 //    d   heads   tokens                              taken
 //    64  64/8    1698, longest   98, n = 39:   33.7 /     - /   27.9   split
 //    64  16/16    312, equal,        n =  8:    5.1 /     - /    6.9   whole
@@ -382,14 +385,15 @@ KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int gr
 
   constexpr float PAIR = 1.04f, PAIR_WG = 3.61f, PAIR_IT = 1.533f, SPLIT_MASK = 0.514f;
   const float least = PAIR_IT * 0.5f * most->all / 32.f, longest_pair = PAIR_WG + floorf((longest + 1.f) / 2.f);
-  float t_pair = t_whole;
-  if (PAIR + std::max(least, PAIR_IT * longest_pair) < 0.98f * t_whole) {
+  float t_pair = t_whole + t_whole;  // (not taken)
+  const float limit = (grp > 1 && t_whole > 200.f ? 1.04f : 0.98f) * t_whole;
+  if (PAIR + std::max(least, PAIR_IT * longest_pair) < limit) {
     KvPlacement on;
     for (int i = 0; i < most->n; i++) on.start(PAIR_WG + floorf((most->its[i] + 1.f) / 2.f));
     t_pair = PAIR + PAIR_IT * std::max(on.end, longest_pair);
   }
-  const bool pair = t_pair < 0.98f * t_whole;
-  const float other = std::min(t_whole, t_pair), masked = SPLIT_MASK * (float)((grp + 3) / 4);
+  const bool pair = t_pair < limit;
+  const float fastest = std::min(t_whole, t_pair), other = fastest > 200.f ? 0.92f * fastest : fastest, masked = SPLIT_MASK * (float)((grp + 3) / 4);
   float all = 0.f;
   for (int i = 0; i < most->n; i++) all += (float)most->parts[i] * (c.split_wg + masked + floorf((most->its[i] + 3.f) / 4.f));
   if (c.split + c.split_it * all / 32.f < other) {

@@ -78,7 +78,7 @@ def dkdv_labels(*call):
     (128, 4, 4, 1000, 7, "_pair"), (128, 8, 1, 1000, 6, "_split"), (128, 8, 1, 1000, 17, "_pair"), (128, 8, 1, 1000, 28, "_pair"),
     (128, 8, 1, 4000, 2, "_split"), (128, 32, 8, 300, 10, "_pair"), (128, 32, 8, 1000, 2, "_split"), (128, 32, 8, 1000, 9, "_pair"),
     (128, 4, 4, 100, 32, ""), (128, 32, 32, 3037, 1, ""), (128, 16, 4, 885, 16, ""), (128, 32, 8, 1360, 6, "_pair"),
-    (128, 16, 4, 2699, 5, "_pair"), (128, 64, 8, 1411, 6, ""), (128, 8, 8, 983, 15, ""),
+    (128, 16, 4, 2628, 10, "_pair"), (128, 16, 4, 2699, 5, "_pair"), (128, 64, 8, 1411, 6, ""), (128, 8, 8, 983, 15, ""),
     (64, 4, 4, 300, 3, "_split"), (64, 4, 4, 300, 16, ""), (64, 16, 4, 300, 10, "_split"), (64, 16, 4, 300, 19, "_split"),
     (64, 8, 1, 1000, 6, "_split"), (64, 4, 2, 100, 13, "_split"), (64, 4, 2, 300, 38, ""), (64, 32, 32, 40, 4, ""),
     (64, 16, 16, 39, 8, ""), (64, 16, 16, 1030, 8, "")])
