@@ -13,23 +13,26 @@ inline int zp_key_tiles(const zp_tile &t) {
   return (int)((n + 63) / 64);
 }
 
-// Cuts the 128-row tiles of a table in the launch arguments into tiles of 64 rows (they fit), the later rows of a block first;
-// with `cost`, all of them heaviest first.
-inline void zp_halve_tiles(const zp_tile *in, int n, zp_inline_tiles &out, int *cost) {
-  int m = 0;
-  for (int i = 0; i < n; i++)
-    for (int r0 = (in[i].q_rows - 1) / 64 * 64; r0 >= 0; r0 -= 64) {
-      zp_tile t = in[i];
-      t.q_tok0 += r0; t.q_pos0 += r0; t.out_row0 += r0;
-      t.q_rows = std::min(64, t.q_rows - r0);
-      int at = m++;
-      if (cost) {
-        const int c = zp_key_tiles(t);
-        for (; at > 0 && cost[at - 1] < c; at--) { out.t[at] = out.t[at - 1]; cost[at] = cost[at - 1]; }
-        cost[at] = c;
-      }
-      out.t[at] = t;
-    }
+// The later (half = 1) or earlier 64 rows of a tile.
+inline zp_tile zp_half_tile(zp_tile t, int half) {
+  t.q_tok0 += 64 * half; t.q_pos0 += 64 * half; t.out_row0 += 64 * half;
+  t.q_rows = std::min(64, t.q_rows - 64 * half);
+  return t;
+}
+
+// Order of n tiles by cost, heaviest first, equal ones as they come.
+inline void zp_by_cost(const int *cost, int n, int *order) {
+  constexpr int MOST = 255;
+  int at[MOST + 2] = {}, most = 0;
+  for (int i = 0; i < n; i++) most = std::max(most, cost[i]);
+  if (most > MOST) {
+    for (int i = 0; i < n; i++) order[i] = i;
+    std::sort(order, order + n, [&](int a, int b) { return cost[a] != cost[b] ? cost[a] > cost[b] : a < b; });
+    return;
+  }
+  for (int i = 0; i < n; i++) at[most - cost[i] + 1]++;
+  for (int c = 0; c < most; c++) at[c + 1] += at[c];
+  for (int i = 0; i < n; i++) order[at[most - cost[i]]++] = i;
 }
 
 // Estimated time of a launch in microseconds, from its tiles' costs (descending, each `heads` times): one workgroup per CU up to
@@ -45,7 +48,17 @@ inline float zp_pair_estimate(const zp_pair_cost &c, const int *cost, int n, int
   float most = dur(0);
   if (items <= 256) return head + most;
   if (items <= 512) {
-    for (int k = 0; k < items - 256; k++) most = std::max(most, pairs ? dur(255 - k) + dur(256 + k) : dur(k) + c.share * dur(256 + k));
+    // tiles of item k or 255 - k, and of item 256 + k, and what is left of their heads
+    const int step = pairs ? -1 : 1;
+    int a = pairs ? 255 / heads : 0, a_left = pairs ? 255 % heads + 1 : heads, b = 256 / heads, b_left = heads - 256 % heads;
+    for (int k = 256; k < items;) {
+      const float da = c.wg + c.tile * (float)cost[a], db = c.wg + c.tile * (float)cost[b];
+      most = std::max(most, pairs ? da + db : da + c.share * db);
+      const int run = std::min(a_left, b_left);
+      k += run;
+      if ((a_left -= run) == 0) { a += step; a_left = heads; }
+      if ((b_left -= run) == 0) { b++; b_left = heads; }
+    }
     return head + most;
   }
   float sum = 0.f;
@@ -67,31 +80,32 @@ inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int 
   for (int i = 0; i < n; i++) m += tiles[i].q_rows > 64 ? 2 : 1;
   if (m * heads > 1024) return ZP_PAIR_NONE;
   const bool fits = m + behind <= ZP_INLINE_TILES;
-  zp_inline_tiles half;
-  if (((fits ? m : 2 * n) * Hkv + 7) / 8 * grp <= 32) {
-    if (fits) zp_halve_tiles(tiles, n, half, nullptr);
+  // the 64-row tiles, the later rows of a block first: 2 * tile + half
+  int half[2 * ZP_INLINE_TILES], order[2 * ZP_INLINE_TILES];
+  for (int i = 0, k = 0; i < n; i++) {
+    if (tiles[i].q_rows > 64) half[k++] = 2 * i + 1;
+    half[k++] = 2 * i;
+  }
+  if (((fits ? m : 2 * n) * Hkv + 7) / 8 * grp > 32) {
+    // decided by the costs alone: the table is written where the pairs are taken (28 sequences of 256 tokens, 4/2 heads, which
+    // are not: 3.9 us with a table sorted beforehand, 1.0 now)
+    int cost[2 * ZP_INLINE_TILES], sorted[2 * ZP_INLINE_TILES], order128[ZP_INLINE_TILES];
+    for (int i = 0; i < n; i++) cost[i] = zp_key_tiles(tiles[i]);
+    zp_by_cost(cost, n, order128);
+    for (int i = 0; i < n; i++) sorted[i] = cost[order128[i]];
+    const float other = zp_pair_estimate(whole, sorted, n, heads, false);
+    for (int k = 0; k < m; k++) cost[k] = zp_key_tiles(zp_half_tile(tiles[half[k] / 2], half[k] & 1));
+    zp_by_cost(cost, m, order);
+    for (int k = 0; k < m; k++) sorted[k] = cost[order[k]];
+    if (!(zp_pair_estimate(pair, sorted, m, heads, true) < (fits ? margin : halves) * other)) return ZP_PAIR_NONE;
   } else {
-    int cost64[2 * ZP_INLINE_TILES], cost128[ZP_INLINE_TILES], k = 0;
-    for (int i = 0; i < n; i++) cost128[i] = zp_key_tiles(tiles[i]);
-    if (fits) {
-      zp_halve_tiles(tiles, n, half, cost64);
-    } else {
-      for (int i = 0; i < n; i++) {
-        cost64[k++] = cost128[i];
-        if (tiles[i].q_rows > 64) {
-          zp_tile t = tiles[i];
-          t.q_rows = 64;
-          cost64[k++] = zp_key_tiles(t);
-        }
-      }
-      std::sort(cost64, cost64 + m, [](int a, int b) { return a > b; });
-    }
-    std::sort(cost128, cost128 + n, [](int a, int b) { return a > b; });
-    if (!(zp_pair_estimate(pair, cost64, m, heads, true) < (fits ? margin : halves) * zp_pair_estimate(whole, cost128, n, heads, false))) return ZP_PAIR_NONE;
+    for (int k = 0; k < m; k++) order[k] = k;
   }
   if (!fits) return ZP_PAIR_HALVES;
+  zp_tile table[ZP_INLINE_TILES];
+  for (int k = 0; k < m; k++) table[k] = zp_half_tile(tiles[half[order[k]] / 2], half[order[k]] & 1);
   std::memmove(tiles + m, tiles + n, (size_t)behind * sizeof(zp_tile));
-  std::memcpy(tiles, half.t, (size_t)m * sizeof(zp_tile));
+  std::memcpy(tiles, table, (size_t)m * sizeof(zp_tile));
   n = m;
   return ZP_PAIR_TILES;
 }
