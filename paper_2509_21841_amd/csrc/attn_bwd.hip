@@ -1279,7 +1279,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
   __bf16 *out = which ? p.dv : p.dk;
   const int64_t at = ((int64_t)t.k_tok0 + kb) * p.dkv_stride + (int64_t)g * D + ch * (D / 2);
   if (!p.accumulate) zp_store_rows<D / 2>(smem + wave * ZP_ROWS_LDS_OF(D / 2), sum, mul, out + at, p.dkv_stride, t.k_len - kb, lane);
-  else if (krow < t.k_len) add_acc_rows<D / 2>((float *)out + at + c16 * p.dkv_stride + q4, sum, mul);
+  else {
+    int first = kb;
+    asm volatile("" : "+s"(first));  // krow worked out again: a register of its own through the loop was one too many at D = 64
+    if (first + c16 < t.k_len) add_acc_rows<D / 2>((float *)out + at + c16 * p.dkv_stride + q4, sum, mul);
+  }
 }
 
 template <int D>
