@@ -380,7 +380,10 @@ KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int gr
       const float fill = all * slow / 64.f + 0.923f * (c.split_wg + c.split_it * last_its / std::max(1.f, last_wgs));
       split = std::max(split, std::min(fill, top * slow * (float)((4 * x.n + 63) / 64)));
     }
-    return c.split + split < 0.97f * t_whole ? KV_SPLIT : KV_WHOLE;
+    // one key block each, all of it on the diagonal, beyond one workgroup per CU: up to 30 % behind the estimate (49 sequences of up
+    // to 99 tokens, 32/8 heads: 19.8 us estimated, 26.5 measured; 56 of up to 100, 64/8: 34.6 us whole, 40.8 split)
+    const bool diagonal = units > 256 && longest <= 4.f * (float)grp;
+    return c.split + split < (diagonal ? 0.8f : 0.97f) * t_whole ? KV_SPLIT : KV_WHOLE;
   }
 
   constexpr float PAIR = 1.04f, PAIR_WG = 3.61f, PAIR_IT = 1.533f, SPLIT_MASK = 0.514f;

@@ -86,11 +86,12 @@ def test_the_fastest_kernel_is_taken(d, Hq, Hkv, L, n, kernel):
     check_kernel(d, Hq, Hkv, [L] * n, kernel)
 
 
-# Ragged sequences under 100 tokens leave many workgroups of the split without keys, and it is the fastest by far: 24.2 us one
-# workgroup per key block, 19.8 two groups, 11.5 split; 33.0, 25.2 and 14.7.
+# Ragged sequences of up to 100 tokens leave many workgroups of the split without keys, and at d = 128 it is the fastest by far:
+# 24.2 us one workgroup per key block, 19.8 two groups, 11.5 split; 33.0, 25.2 and 14.7. The third: 34.6 and 40.8 split.
 @pytest.mark.parametrize("d,Hq,Hkv,lengths,kernel", [
     (128, 16, 4, [100, 97, 93, 90, 88, 61, 55, 50, 47, 45, 40, 33, 30, 28, 21, 20, 12, 9], "_split"),
-    (128, 64, 8, [87, 80, 75, 60, 52, 33, 21, 15, 10, 4], "_split")])
+    (128, 64, 8, [87, 80, 75, 60, 52, 33, 21, 15, 10, 4], "_split"),
+    (64, 64, 8, [20 + i * 37 % 81 for i in range(56)], "")])
 def test_short_ragged_sequences(d, Hq, Hkv, lengths, kernel):
     check_kernel(d, Hq, Hkv, lengths, kernel)
 
