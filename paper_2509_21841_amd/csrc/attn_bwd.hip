@@ -916,7 +916,8 @@ __device__ __forceinline__ void dkdv_add_groups(const zp_bwd_params &p, const zp
 // G = 2: both of a CU's workgroups become groups of one, which go through the iterations of ONE key block by turns and add up
 // their accumulators at the end. The same work per CU and half the chain, at the price of a prologue and an end that
 // nothing else runs beside (9.3 us per workgroup) and of meeting at one barrier: for launches of a few waves of workgroups, in which the
-// longest chains and the last wave decide. 8000 ragged tokens, 32/8 heads: 500 -> 360 us, 10709 tokens, 8/8: 121 -> 88; 64K lognormal MHA
+// longest chains and the last wave decide. (Its scalar registers are five short: three are read back from lanes of a vector
+// register per two tiles.) 8000 ragged tokens, 32/8 heads: 500 -> 360 us, 10709 tokens, 8/8: 121 -> 88; 64K lognormal MHA
 // 2315 -> 2818.
 template <int G>
 __global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv128_kernel(zp_bwd_params p) {
@@ -1142,7 +1143,7 @@ constexpr int split_own() { return 8 * zp_pad16<D>::R16 + 1024; }
 // its own (140 KB of LDS in all at D = 128), and the two waves of a group, on one SIMD, share the tile and do 16 key rows
 // each. The groups' accumulators are added up at the end, through LDS, in their order.
 //
-// One workgroup per CU at d = 128, two at 64 (70 KB of LDS, 128 registers: what a second one adds is worth a third).
+// One workgroup per CU at d = 128, two at 64 (70 KB of LDS, all of 128 registers: what a second one adds is worth a third).
 // Bound: a group's chain of iterations: 1.21 us each at d = 128, 0.81 at 64 (2850 and 1900 cycles, of which the MFMAs of a SIMD's
 // two waves are 1024 and 512, their arithmetic under MFMAs about as much, hand-over and addresses 600); with one wave per
 // group and 32 key rows per wave, whose operations issue one after the other, 1.50 and 0.86. 1000 tokens, 4/2 heads, d = 128:
@@ -1217,7 +1218,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
   on(next_i0, next_hh);
   auto query_tile = [&](int it, auto BUF) {
     constexpr int buf = decltype(BUF)::value;
-    // the tile has landed; both waves of the group are done with the one before
+    // the tile has landed; both waves of the group are done with the one before (and, the barrier being the workgroup's, so are
+    // the other groups', which need not be)
     zp_wait_async();
     __syncthreads();
     const int qpos0 = t.q_pos0 + i0;

@@ -432,7 +432,7 @@ __device__ __forceinline__ void fwd_pair_values(f32x4 (&o_acc)[D / 16], const bf
   __builtin_amdgcn_sched_barrier(0);
 }
 
-constexpr int PAIR_BUFS = 4;  // staged K and V tiles: 158 KB of LDS at d = 128
+constexpr int PAIR_BUFS = 4;  // staged K and V tiles: 136 KB of the 156 KB of LDS at d = 128
 template <int D>
 constexpr size_t pair_lds() { return 2 * PAIR_BUFS * 4 * (size_t)zp_pad16<D>::R16 + 2 * 4 * 2048 + 4 * 4 * 256 + 2 * 4 * 16; }
 

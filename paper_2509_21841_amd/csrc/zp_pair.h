@@ -110,17 +110,17 @@ inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int 
   return ZP_PAIR_TILES;
 }
 
-// The forward's two kernels. Constants fitted to 850 launches whose tables fit (4/2 to 64/8 and 8/1 heads; equal, ragged and
-// lognormal lengths of 64 to 16000 tokens in all): the estimates are 4 and 5 % off in the mean. Of the 669 launches that take
-// the pairs none is more than 1.1 % slower with them, and all 850 together take 0.79 of the time (geometric mean). n
-// sequences of L tokens, us, whole / pairs:
-//    d   heads    L    taken: pairs            not taken
+// The forward's two kernels. Constants fitted to 850 launches whose tables fit; the estimates are 4 and 5 % off in the mean of 3996 others
+// (2/1 to 64/8 heads; equal, ragged and lognormal lengths, 16 to 13600 tokens). Of the 3361 launches of these that take the pairs 12 are 2
+// to 8 % slower with them; all 3996 take 0.78 of the time (geometric mean), and the 121 of the 3361 whose tables do not
+// fit 0.77. A limit of 0.91 leaves 8 such losses but gives up 2 to 9 % in 11 launches at d = 128 alone. n sequences of L tokens, us,
+// whole / pairs:
+//    d   heads    L    taken: pairs                      not taken
 //    64   4/4    300   n =  1:   8.0 /  6.1
-//    64   4/4   4000   n =  1:  51.9 / 33.5    64/8, L =  762, n = 2:  17.7 / 24.2
-//   128   4/4   1000   n =  4:  23.2 / 15.4    64/8, L =  894, n = 2:  27.8 / 35.1
-//   128   8/2   2085   n =  1:  41.4 / 27.1    16/4, L =  200, n = 20: 21.9 / 26.2
-// Of 370 ragged batches of 2000 to 20000 tokens under 1 to 16 heads, whose tables fit or not, 216 take the pairs at one margin for
-// both, for 0.76 of the time in the mean; the tenth keeps out those that lost (six sequences of 10943 tokens, 4/4 heads, d = 64: 45.4 -> 42.0; one of 2931 and others, 9860 tokens, 2/1, d = 128: 54.5 -> 39.4).
+//    64   4/4   4000   n =  1:  51.9 / 33.5              64/8, L =  762, n = 2:  17.7 / 24.2
+//   128   4/4   1000   n =  4:  23.2 / 15.4              64/8, L =  894, n = 2:  27.8 / 35.1
+//   128   8/2   2085   n =  1:  41.4 / 27.1              16/4, L =  200, n = 20: 21.9 / 26.2
+//   128   4/4   1623   n =  5:  34.8 / 37.7 (as halves, the worst)
 inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
   static const zp_pair_cost whole[2] = {{2.95f, 0.769f, 1.74f, 0.0023f, 0.345f}, {2.20f, 1.074f, 3.19f, 0.0032f, 0.536f}};
   static const zp_pair_cost pair[2] = {{2.03f, 0.471f, 1.95f, 0.0022f, 1.f}, {2.63f, 0.660f, 1.64f, 0.0027f, 1.f}};
