@@ -13,11 +13,6 @@ namespace {
 
 constexpr int BN = 64;  // keys per LDS tile
 
-template <int D, int NW>
-struct FwdCfg {
-  static constexpr int TILEB = BN * D * 2;  // bytes per K (or V) tile
-};
-
 // The partial sum of a lane's probabilities of a tile above which the reference maximum of its rows has to move.
 constexpr float P_SUM_MAX = 4096.0f;
 
@@ -37,114 +32,220 @@ __device__ __forceinline__ float fwd_move_reference(uint64_t far, float m, float
   return alpha;
 }
 
-// One 64-key tile for one wave of two 16-query sub-blocks. Kb, Vb: byte offsets of the K and V tile from the LDS base
-// that the lane offsets in `lo` carry (compile-time at the call sites, so every read is a register plus an immediate).
-// ONLY1: no query of sub-block 0 sees a key of this tile. Both products run as fenced steps of one LDS operand and the
-// two MFMAs it feeds, operands requested two (K) and three (V) steps ahead, the first two V operands in front of the
-// softmax arithmetic. With PIECES, `piece(integral_constant<int, n>)` is called in every second step of the score
-// product: the caller issues one asynchronous copy of the next tile there, far enough apart that none waits for the
-// address unit behind the copies of the other waves.
-//
-// Bound: the power limit. The 16x16x32 MFMA accumulates twice as many products per accumulator access as the 32x32x16;
-// a register-only loop on random operands holds 1885-1956 TFLOP/s with it (zp_mfma_probe) against 1520-1800, at the price of twice the
-// issue slots. On four 16384-token sequences (GQA 32/8, d = 128) the 32x32x16 form of this kernel took 7.66 ms and
-// this one takes 7.11 (on zeros, where power does not bind, 5.72 and 5.91: it issues more and waits more).
+// Asynchronous copies of the [64][D] tiles of one run of keys, tile by tile (see zp_stager). Neighbouring loads of a wave that
+// differ by whole rows share a lane offset, and the rows are added to the scalar base.
+template <int D, bool TURNS>
+struct fwd_stager {
+  typedef zp_pad16<D> L;
+  static constexpr int PW = 64 * D * 2 / 1024 / 4, SHARE = TURNS ? PW / 2 : 1, ROWS = D == 128 ? 4 : 8;  // loads per wave and tile; per offset; rows of a load
+  unsigned off[PW / SHARE];
+  unsigned row_bytes;
+  const char *tile;  // the next one
+  int w;
+  __device__ __forceinline__ void init(const __bf16 *first, int64_t tok_stride, int lane, int wave) {
+    w = __builtin_amdgcn_readfirstlane(wave);
+    row_bytes = (unsigned)tok_stride * 2;
+    tile = (const char *)first;
+#pragma unroll
+    for (int i = 0; i < PW / SHARE; i++) off[i] = lane_offset(i * SHARE, lane, 64);
+  }
+  // of load n, for a tile of n_rows valid rows; the rows behind repeat the last one
+  __device__ __forceinline__ unsigned lane_offset(int n, int lane, int n_rows) const {
+    const int r = (w * PW + n) * ROWS + lane / (D / 8);
+    return (unsigned)min(r, n_rows - 1) * row_bytes + (((lane & (D / 8 - 1)) ^ L::mask(r)) << 4);
+  }
+  // load N of a tile of 64 valid rows
+  template <int N>
+  __device__ __forceinline__ void piece(unsigned lds_tile) const {
+    zp_dma16_so(zp_uniform_ptr(tile + (uint64_t)(N % SHARE * ROWS) * row_bytes), off[N / SHARE], __builtin_amdgcn_readfirstlane(lds_tile + L::group(w * PW + N)));
+  }
+  // the tile after the next one is the next one
+  __device__ __forceinline__ void move() { tile += (uint64_t)64 * row_bytes; }
+  // all loads of a tile of n_rows (64 or more: 64) valid rows
+  __device__ __forceinline__ void issue(unsigned lds_tile, int n_rows) const {
+    if (__builtin_expect(n_rows >= 64, 1)) {
+      zp_static_for<PW>([&](auto n) { piece<decltype(n)::value>(lds_tile); });
+    } else {
+#pragma unroll
+      for (int n = 0; n < PW; n++) {
+        int ln = threadIdx.x & 63;
+        asm volatile("" : "+v"(ln));  // keeps the rare path's offsets out of the registers of the loop around it
+        zp_dma16_so(zp_uniform_ptr(tile), lane_offset(n, ln, n_rows), __builtin_amdgcn_readfirstlane(lds_tile + L::group(w * PW + n)));
+      }
+    }
+  }
+};
+
+// The scores of NKB blocks of 16 keys from block KB0 of a tile on (at byte offset Kb) for one wave of two 16-query sub-blocks, as
+// fenced steps of one LDS operand and the MFMAs it feeds (sub-blocks QB0 to QB1 - 1), operands requested two steps ahead.
+// `piece(integral_constant<int, n>)` is called after step n.
+template <int D, bool MASK, int QB0, int QB1, int KB0, int NKB, class Piece>
+__device__ __forceinline__ void fwd_scores(int Kb, const bf16x8 (&qreg)[2][D / 32], f32x4 (&s)[2][NKB], int j0, int q4,
+                                           const int (&nvis_lane)[2], const zp_pad16_addr<D> &la, Piece &&piece) {
+  constexpr int N = NKB * (D / 32);  // operand n: key block n % NKB, k-step n / NKB
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[N];
+  a[0] = la.rows(Kb, KB0, 0);
+  a[1] = la.rows(Kb, KB0 + 1, 0);
+  zp_static_for<N>([&](auto nn) {
+    constexpr int n = nn.value, kb = n % NKB, k = n / NKB;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qb = QB0; qb < QB1; qb++)
+      s[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], qreg[qb][k], k == 0 ? zero : s[qb][kb], 0, 0, 0);
+    if constexpr (n + 2 < N) a[n + 2] = la.rows(Kb, KB0 + (n + 2) % NKB, (n + 2) / NKB);
+    piece(nn);
+  });
+  __builtin_amdgcn_sched_barrier(0);
+  if (MASK) {
+#pragma unroll
+    for (int qb = QB0; qb < QB1; qb++)
+#pragma unroll
+      for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+          if (j0 + 16 * (KB0 + kb) + q4 + r >= nvis_lane[qb]) s[qb][kb][r] = -INFINITY;
+  }
+}
+
+// Probabilities of NKB blocks of 16 keys: the B operands pb of their part of the second product, and the lane's sums over the keys
+// of even (ta) and odd (tb) blocks.
+template <int NKB>
+__device__ __forceinline__ void fwd_take(const f32x4 (&s)[NKB], float c_log2, float ref, bf16x8 *pb, float &ta, float &tb) {
+#pragma unroll
+  for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const float p = zp_exp2(__builtin_fmaf(s[kb][r], c_log2, ref));
+      // the row sum is taken over the unrounded probabilities: LSE has to hold to 1e-3 also for rows with few keys
+      if (kb & 1) tb += p; else ta += p;
+      pb[kb >> 1][(kb & 1) * 4 + r] = (__bf16)p;
+    }
+}
+template <int NKB>
+__device__ __forceinline__ float fwd_max(const f32x4 (&s)[NKB], float m) {
+#pragma unroll
+  for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) m = fmaxf(m, s[kb][r]);
+  return m;
+}
+
+// Scores and probabilities of one 64-key tile (K at byte offset Kb from the base the lane addresses carry, compile-time at the call
+// sites) for one wave of two 16-query sub-blocks. ONLY1: no query of sub-block 0 sees a key of this tile. WHOLE: all scores first,
+// else 32 keys at a time, which needs 16 registers less. FIRST: the rows' first tile (o_acc holds nothing yet), which gives them
+// their reference. `between` is called in front of the softmax arithmetic of WHOLE and FIRST.
 //
 // The probabilities are taken against the reference the rows already have, nm = -(reference) in scaled log2 units, and
 // only their sum is looked at: a maximum per tile costs 20 of 136 vector operations and puts a cross-lane exchange in
 // front of the first exp2, while all that it protects against is a reference so far below the scores that the
 // probabilities grow out of range. When the 16 probabilities of one of a row's four lanes add up to more than P_SUM_MAX
-// (or to NaN), the row's maximum is worked out and its probabilities of the tile taken again. A row without a reference
-// has nm = +inf, which makes its first tile end there. The other rows of the wave keep their reference, so that no bit of
-// a row depends on the tokens behind it. Probabilities, sums and O are floating point throughout, so the reference's
-// distance from the row maximum costs no precision.
-template <int D, bool MASK, bool ONLY1, bool PIECES, class Piece>
-__device__ __forceinline__ void fwd_tile(int Kb, int Vb, const bf16x8 (&qreg)[2][D / 32], f32x4 (&o_acc)[2][D / 16],
-                                         float (&nm)[2], float (&l_sum)[2], float c_log2, int j0, int q4,
-                                         const int (&nvis_lane)[2], const zp_lds16<D> &lo, Piece &&piece) {
-  constexpr int KK = D / 32, DB = D / 16, QB0 = ONLY1 ? 1 : 0;
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 s[2][4];
-  {
-    constexpr int N = 4 * KK;  // operand n: key block n % 4, k-step n / 4
-    bf16x8 a[N];
-    a[0] = lo.rows_at(Kb, 0, 0);
-    a[1] = lo.rows_at(Kb, 1, 0);
-    zp_static_for<N>([&](auto nn) {
-      constexpr int n = nn.value, kb = n % 4, k = n / 4;
-      __builtin_amdgcn_sched_barrier(0);
+// (or to NaN), the row's maximum is worked out and its probabilities of the tile taken again (32 keys at a time: from scores
+// multiplied out again, those of the first half are gone). A row that has seen no key yet has nm = +inf, which ends there. The
+// other rows of the wave keep their reference, so that no bit of a row depends on the tokens behind it. Probabilities, sums and O
+// are floating point throughout, so the reference's distance from the row maximum costs no precision.
+//
+// Bound: the power limit and the vector issue port. The 16x16x32 MFMA accumulates twice as many products per accumulator access as
+// the 32x32x16; a register-only loop on random operands holds 1885-1956 TFLOP/s with it (zp_mfma_probe) against 1520-1800, at the
+// price of twice the issue slots. On four 16384-token sequences (GQA 32/8, d = 128) the 32x32x16 form took 7.66 ms and this one 7.11.
+template <int D, bool WHOLE, bool FIRST, bool MASK, bool ONLY1, class Piece, class Between>
+__device__ __forceinline__ void fwd_tile_scores(int Kb, const bf16x8 (&qreg)[2][D / 32], bf16x8 (&pb)[2][2], f32x4 (&o_acc)[2][D / 16],
+                                                float (&nm)[2], float (&l_sum)[2], float c_log2, int j0, int q4, const int (&nvis_lane)[2],
+                                                const zp_pad16_addr<D> &la, Piece &&piece, Between &&between) {
+  constexpr int DB = D / 16, QB0 = ONLY1 ? 1 : 0, N = 2 * (D / 32);
+  auto no_piece = [](auto) {};
+  auto second = [&](auto nn) { piece(std::integral_constant<int, N + decltype(nn)::value>{}); };
+  float ta[2] = {0.f, 0.f}, tb[2] = {0.f, 0.f};
+  if constexpr (WHOLE || FIRST) {
+    f32x4 s[2][4];
+    fwd_scores<D, MASK, QB0, 2, 0, 4>(Kb, qreg, s, j0, q4, nvis_lane, la, piece);
+    between();
+    auto take = [&](int qb, float ref) {
+      ta[qb] = tb[qb] = 0.f;
+      fwd_take(s[qb], c_log2, ref, pb[qb], ta[qb], tb[qb]);
+    };
+    uint64_t far[2] = {~0ull, ~0ull};  // lanes of out-of-range sums
+    if constexpr (!FIRST) {
 #pragma unroll
-      for (int qb = QB0; qb < 2; qb++)
-        s[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], qreg[qb][k], k == 0 ? zero : s[qb][kb], 0, 0, 0);
-      if constexpr (n + 2 < N) a[n + 2] = lo.rows_at(Kb, (n + 2) % 4, (n + 2) / 4);
-      if constexpr (PIECES && n % 2 == 0) piece(std::integral_constant<int, n / 2>{});
-    });
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  bf16x8 va[2 * DB];  // operand n of the second product: 32 keys n / DB, 16 columns n % DB
-  va[0] = lo.tr_at(Vb, 0, 0);
-  va[1] = lo.tr_at(Vb, 0, 1);
-  __builtin_amdgcn_sched_barrier(0);
-  if (MASK) {
+      for (int qb = QB0; qb < 2; qb++) take(qb, nm[qb]);
 #pragma unroll
-    for (int qb = QB0; qb < 2; qb++)
+      for (int qb = QB0; qb < 2; qb++) far[qb] = __builtin_amdgcn_ballot_w64(!(ta[qb] + tb[qb] <= P_SUM_MAX));
+    }
+    // (unlikely: behind the loop's own code, which a short sequence's few tiles have to fetch as well)
+    if (FIRST || __builtin_expect((far[QB0] | far[1]) != 0, 0)) {
 #pragma unroll
-      for (int kb = 0; kb < 4; kb++)
+      for (int qb = QB0; qb < 2; qb++) {
+        float ref;
+        const float alpha = fwd_move_reference(far[qb], fwd_max(s[qb], -INFINITY), c_log2, nm[qb], ref);
+        if constexpr (!FIRST) {
+          l_sum[qb] *= alpha;
 #pragma unroll
-        for (int r = 0; r < 4; r++)
-          if (j0 + 16 * kb + q4 + r >= nvis_lane[qb]) s[qb][kb][r] = -INFINITY;
-  }
-  // probabilities as the B operands of the second product: operand kp covers key blocks 2 kp and 2 kp + 1
-  bf16x8 pb[2][2];
-  float t[2] = {0.f, 0.f};
-  auto take = [&](int qb, float ref) {
-    float ta = 0.f, tb = 0.f;
+          for (int i = 0; i < DB; i++)
 #pragma unroll
-    for (int kb = 0; kb < 4; kb++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const float p = zp_exp2(__builtin_fmaf(s[qb][kb][r], c_log2, ref));
-        // the row sum is taken over the unrounded probabilities: LSE has to hold to 1e-3 also for rows with few keys
-        if (kb & 1) tb += p; else ta += p;
-        pb[qb][kb >> 1][(kb & 1) * 4 + r] = (__bf16)p;
+            for (int r = 0; r < 4; r++) o_acc[qb][i][r] *= alpha;
+        }
+        take(qb, ref);
       }
-    t[qb] = ta + tb;
-  };
+    }
+  } else {
+    f32x4 s[2][2];
+    fwd_scores<D, MASK, QB0, 2, 0, 2>(Kb, qreg, s, j0, q4, nvis_lane, la, piece);
 #pragma unroll
-  for (int qb = QB0; qb < 2; qb++) take(qb, nm[qb]);
-  uint64_t far[2];  // lanes of out-of-range sums
+    for (int qb = QB0; qb < 2; qb++) fwd_take(s[qb], c_log2, nm[qb], pb[qb], ta[qb], tb[qb]);
+    fwd_scores<D, MASK, QB0, 2, 2, 2>(Kb, qreg, s, j0, q4, nvis_lane, la, second);
 #pragma unroll
-  for (int qb = QB0; qb < 2; qb++) far[qb] = __builtin_amdgcn_ballot_w64(!(t[qb] <= P_SUM_MAX));
-  // (unlikely: behind the loop's own code, which a short sequence's few tiles have to fetch as well)
-  if (__builtin_expect((far[QB0] | far[1]) != 0, 0)) {
+    for (int qb = QB0; qb < 2; qb++) fwd_take(s[qb], c_log2, nm[qb], pb[qb] + 1, ta[qb], tb[qb]);
+    uint64_t far[2];  // lanes of out-of-range sums
 #pragma unroll
-    for (int qb = QB0; qb < 2; qb++) {
-      float m = s[qb][0][0];
+    for (int qb = QB0; qb < 2; qb++) far[qb] = __builtin_amdgcn_ballot_w64(!(ta[qb] + tb[qb] <= P_SUM_MAX));
+    // (unlikely: behind the loop's own code, which a short sequence's few tiles have to fetch as well)
+    if (__builtin_expect((far[QB0] | far[1]) != 0, 0)) {
+      zp_static_for<2 - QB0>([&](auto q) {
+        constexpr int qb = QB0 + decltype(q)::value;
+        if (far[qb] == 0) return;
+        float m = -INFINITY, ref;
+        zp_static_for<2>([&](auto half) {
+          fwd_scores<D, MASK, qb, qb + 1, 2 * decltype(half)::value, 2>(Kb, qreg, s, j0, q4, nvis_lane, la, no_piece);
+          m = fwd_max(s[qb], m);
+        });
+        const float alpha = fwd_move_reference(far[qb], m, c_log2, nm[qb], ref);
+        l_sum[qb] *= alpha;
+        ta[qb] = tb[qb] = 0.f;
 #pragma unroll
-      for (int kb = 0; kb < 4; kb++)
+        for (int i = 0; i < DB; i++)
 #pragma unroll
-        for (int r = 0; r < 4; r++) m = fmaxf(m, s[qb][kb][r]);
-      float ref;
-      const float alpha = fwd_move_reference(far[qb], m, c_log2, nm[qb], ref);
-      l_sum[qb] *= alpha;
-#pragma unroll
-      for (int i = 0; i < DB; i++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) o_acc[qb][i][r] *= alpha;
-      take(qb, ref);
+          for (int r = 0; r < 4; r++) o_acc[qb][i][r] *= alpha;
+        zp_static_for<2>([&](auto half) {
+          fwd_scores<D, MASK, qb, qb + 1, 2 * decltype(half)::value, 2>(Kb, qreg, s, j0, q4, nvis_lane, la, no_piece);
+          fwd_take(s[qb], c_log2, ref, pb[qb] + decltype(half)::value, ta[qb], tb[qb]);
+        });
+      });
     }
   }
 #pragma unroll
-  for (int qb = QB0; qb < 2; qb++) l_sum[qb] += t[qb];
-  va[2] = lo.tr_at(Vb, 0, 2);
+  for (int qb = QB0; qb < 2; qb++) l_sum[qb] += ta[qb] + tb[qb];  // (zero before the first tile)
+}
+
+// The second product of the tile, V at byte offset Vb, operands three steps ahead.
+template <int D, bool FIRST, bool ONLY1, class Piece>
+__device__ __forceinline__ void fwd_tile_values(int Vb, const bf16x8 (&pb)[2][2], f32x4 (&o_acc)[2][D / 16], const zp_pad16_addr<D> &la,
+                                                const bf16x8 (&ahead)[3], Piece &&piece) {
+  constexpr int DB = D / 16, QB0 = ONLY1 ? 1 : 0;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  bf16x8 va[2 * DB];  // operand n: 32 keys n / DB, 16 columns n % DB
+#pragma unroll
+  for (int n = 0; n < 3; n++) va[n] = ahead[n];
   zp_static_for<2 * DB>([&](auto nn) {
     constexpr int n = nn.value, kp = n / DB, db = n % DB;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int qb = QB0; qb < 2; qb++)
-      o_acc[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[n], pb[qb][kp], o_acc[qb][db], 0, 0, 0);
-    if constexpr (n + 3 < 2 * DB) va[n + 3] = lo.tr_at(Vb, (n + 3) / DB, (n + 3) % DB);
+      o_acc[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[n], pb[qb][kp], FIRST && kp == 0 ? zero : o_acc[qb][db], 0, 0, 0);
+    if constexpr (n + 3 < 2 * DB) va[n + 3] = la.cols(Vb + 2 * ((n + 3) / DB) * zp_pad16<D>::R16, (n + 3) % DB);
+    piece(nn);
   });
+  if constexpr (FIRST && ONLY1)
+    for (int i = 0; i < DB; i++) o_acc[0][i] = zero;
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -201,17 +302,25 @@ __device__ __forceinline__ void fwd_finish(const zp_attn_params &p, const zp_til
   }
 }
 
-// Two workgroups per CU at head dimension 128 (64 KB of LDS, up to 256 registers), three at 64 (32 KB, up to 168: 8
-// sequences of 4096 tokens, GQA 32/8: 631 us with two, 568 with three; a fourth does not fit the registers).
-template <int D, int NW, bool PARTIAL>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2))) void attn_fwd_kernel(zp_attn_params p) {
-  using C = FwdCfg<D, NW>;
-  static_assert(NW == 4, "the tile stager is laid out for four waves");
+// One workgroup of four waves per 128 query rows. Two forms:
+//  - K and V of a tile and of the next one in four buffers, the next tile's copies spread over the score product, one barrier per tile;
+//    two workgroups per CU at d = 128 (68 KB of LDS, 206 registers), three at 64 (32 KB, 154; 8 sequences of 4096 tokens, GQA 32/8:
+//    631 us with two, 568 with three).
+//  - TURNS (d = 128): three buffers by turns (51 KB), scores 32 keys at a time (168 registers), three workgroups per CU. The next K
+//    tile comes in during the scores, the next V tile goes, behind a second barrier, where K was. A third wave on the SIMD fills what
+//    the other two leave of its issue slots, above all while one of them starts or ends an item; a wave alone takes 15 % longer.
+// A row's first tile has a body of its own: no probabilities against a reference that is not there yet, no zeros to add to.
+// Two workgroups -> TURNS, us: 64K lognormal tokens MHA 1329 -> 1284, 64 x 1K MHA 729 -> 686, four sequences of 16384 7120 -> 7090,
+// 700 of up to 59 tokens, 64/8 heads: 502 (without the first tile's body) -> 445 -> 353; one of 14351 among 33137 tokens, 4 heads:
+// 289 -> 344. See zp_fwd_turns for which is taken. The results are the same bits.
+template <int D, bool TURNS>
+constexpr size_t fwd_lds() { return (TURNS ? 3 : 4) * 4 * (size_t)zp_pad16<D>::R16 + 16; }
+template <int D, bool TURNS, bool PARTIAL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TURNS || D == 64 ? 3 : 2, TURNS || D == 64 ? 3 : 2))) void attn_fwd_kernel(zp_attn_params p) {
+  constexpr int TILEB = 4 * zp_pad16<D>::R16;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char *Ks = smem;                  // [2][BN][D] bf16
-  char *Vs = smem + 2 * C::TILEB;   // [2][BN][D] bf16
 
-  const int item = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work, (int *)(smem + 4 * C::TILEB)));
+  const int item = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work, (int *)(smem + (TURNS ? 3 : 4) * TILEB)));
   if (item < 0) return;
   int unit, hh;
   zp_block_to_unit(item, p.grp, p.m_grp, unit, hh);
@@ -220,7 +329,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
   const int h = g * p.grp + hh;
   const zp_tile t = ZP_TILE(p.tiles, p.inl, 0, tile_idx);
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
   // A wave's two sub-blocks of 16 query rows are the w-th from the front and the w-th from the back of the block, so
   // that all four waves see about the same number of keys and meet the barriers together.
@@ -252,79 +361,138 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64
   // prologue overlap; the explicit wait in front of the first barrier covers both (and tells the compiler that the
   // register operands have arrived: a wait of its own inside the key loop would drain the copies in flight).
 
-  zp_stager<D> kst, vst;
-  kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
-  vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
-  zp_lds16<D> lo;
-  lo.init_abs(lane, smem);
+  typedef fwd_stager<D, TURNS> stager;
+  constexpr int PW = stager::PW;
+  stager kst, vst;
+  kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, lane, w);
+  vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, lane, w);
+  zp_pad16_addr<D> la;
+  la.init(lane, smem);
+  const unsigned lds0 = zp_lds_addr(smem);
 
   f32x4 o_acc[2][D / 16];
-#pragma unroll
-  for (int qb = 0; qb < 2; qb++)
-#pragma unroll
-    for (int i = 0; i < D / 16; i++) o_acc[qb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   float nm[2] = {INFINITY, INFINITY};  // minus the running reference maximum, in scaled log2 units
   float l_sum[2] = {0.f, 0.f};         // this lane's share of the row sums
   const float c_log2 = p.scale_log2;
 
   if (n_kt > 0) {
-    kst.issue(Ks, 0, t.k_len);
-    vst.issue(Vs, 0, t.k_len);
+    kst.issue(lds0, t.k_len);
+    vst.issue(lds0 + TILEB, t.k_len);
   }
+  kst.move();
+  vst.move();
   zp_wait_async();
   __syncthreads();
 
-  constexpr int PW = zp_stager<D>::PER_WAVE;
-  // one key tile out of LDS buffer BUF (a compile-time constant, so every LDS address is register + immediate)
-  auto key_tile = [&](int it, auto BUF) {
-    constexpr int buf = decltype(BUF)::value;
+  auto no_output = [&] {
+#pragma unroll
+    for (int qb = 0; qb < 2; qb++)
+#pragma unroll
+      for (int i = 0; i < D / 16; i++) o_acc[qb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // one key tile, K in LDS buffer KB (a compile-time constant, so every LDS address is register + immediate), V in VB, the next K
+  // and V to KN and VN
+  auto key_tile = [&](int it, auto KB, auto VB, auto KN, auto VN, auto first) {
+    constexpr int Kb = decltype(KB)::value * TILEB, Vb = decltype(VB)::value * TILEB;
+    constexpr bool FIRST = decltype(first)::value;
+    const unsigned k_next = lds0 + decltype(KN)::value * TILEB, v_next = lds0 + decltype(VN)::value * TILEB;
     const int j0 = it * BN;
     // which sub-blocks have a row that sees a key of this tile, and whether some row sees only a part of it
     const bool act0 = j0 < nvis0_max, act1 = j0 < nvis1_max;
-    const bool compute = act0 || act1;
     const bool masked = j0 + BN > (act0 ? nvis0_min : nvis1_min);
-    // the next tile is fetched inside this tile's score MFMAs when it has 64 valid keys and this wave computes an
-    // unmasked tile (the common case), else in front of it
+    // the next tiles are fetched inside the products when they have 64 valid keys and this wave computes an unmasked tile (the
+    // common case), else in front of them
     const bool fetch = it + 1 < n_kt;
     const bool fused = fetch && act0 && !masked && j0 + 2 * BN <= t.k_len;
-    if (__builtin_expect(fetch && !fused, 0)) {  // (behind the loop's own code: 2.5 % of a launch with one workgroup per CU)
-      kst.issue(Ks + (buf ^ 1) * C::TILEB, j0 + BN, t.k_len);
-      vst.issue(Vs + (buf ^ 1) * C::TILEB, j0 + BN, t.k_len);
+    if (__builtin_expect(fetch && !fused, 0)) {
+      kst.issue(k_next, t.k_len - j0 - BN);
+      if constexpr (!TURNS) vst.issue(v_next, t.k_len - j0 - BN);
     }
-    // the same copies one load at a time, K and V alternating (2 * PW loads = one per k-step); the sources are worked
-    // out unconditionally: a value defined under a branch would not stay in scalar registers
-    const void *pc_k = zp_uniform_ptr(kst.base + (int64_t)(j0 + BN) * kst.stride);
-    const void *pc_v = zp_uniform_ptr(vst.base + (int64_t)(j0 + BN) * vst.stride);
-    auto stage_piece = [&](auto n) {
-      constexpr int N = decltype(n)::value, i = N / 2;
-      static_assert(2 * PW == 2 * (D / 32), "one copy per two K operands");
-      if constexpr (N % 2 == 0)
-        zp_dma16_so(pc_k, kst.off[i], __builtin_amdgcn_readfirstlane(zp_lds_addr(Ks + (buf ^ 1) * C::TILEB) + (kst.w * PW + i) * 1024));
-      else
-        zp_dma16_so(pc_v, vst.off[i], __builtin_amdgcn_readfirstlane(zp_lds_addr(Vs + (buf ^ 1) * C::TILEB) + (vst.w * PW + i) * 1024));
+    constexpr int EVERY = 4 * (D / 32) / PW / (TURNS ? 1 : 2);
+    auto k_piece = [&](auto n) {
+      constexpr int N = decltype(n)::value / EVERY;
+      if constexpr (decltype(n)::value % EVERY != 0) return;
+      else if constexpr (TURNS) kst.template piece<N>(k_next);
+      else if constexpr (N % 2 == 0) kst.template piece<N / 2>(k_next);
+      else vst.template piece<N / 2>(v_next);
     };
-    if (compute) {
-      constexpr int Kb = buf * C::TILEB, Vb = (2 + buf) * C::TILEB;  // byte offsets of the tiles from smem
-      if (!act0) fwd_tile<D, true, true, false>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
-      else if (masked) fwd_tile<D, true, false, false>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
-      else if (fused) fwd_tile<D, false, false, true>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
-      else fwd_tile<D, false, false, false>(Kb, Vb, qreg, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, lo, stage_piece);
+    auto v_piece = [&](auto n) {
+      if constexpr (TURNS && decltype(n)::value % EVERY == 0) vst.template piece<decltype(n)::value / EVERY>(v_next);
+    };
+    auto no_piece = [](auto) {};
+    bf16x8 pb[2][2], va[3];
+    auto v_first = [&] {
+#pragma unroll
+      for (int n = 0; n < 3; n++) va[n] = la.cols(Vb, n);
+    };
+    auto v_ahead = [&] {
+      if constexpr (!TURNS) v_first();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto scores = [&](auto mask, auto only1, auto &&piece) {
+      fwd_tile_scores<D, !TURNS, FIRST, decltype(mask)::value, decltype(only1)::value>(Kb, qreg, pb, o_acc, nm, l_sum, c_log2, j0, q4, nvis_lane, la, piece, v_ahead);
+    };
+    auto values = [&](auto only1, auto &&piece) { fwd_tile_values<D, FIRST, decltype(only1)::value>(Vb, pb, o_acc, la, va, piece); };
+    const std::true_type yes;
+    const std::false_type no;
+    if constexpr (TURNS) {
+      if (!act0) { if (act1) scores(yes, yes, no_piece); }
+      else if (masked) scores(yes, no, no_piece);
+      else if (fused) scores(no, no, k_piece);
+      else scores(no, no, no_piece);
+      kst.move();
+      // V of this tile has landed (the next K may be in flight), and everybody is done with K
+      if (fetch) zp_wait_async_upto<PW>();
+      else zp_wait_async();
+      __syncthreads();
+      if (__builtin_expect(fetch && !fused, 0)) vst.issue(v_next, t.k_len - j0 - BN);
+      v_first();
+      if (!act0) { if (act1) values(yes, no_piece); else if (FIRST) no_output(); }
+      else if (fused) values(no, v_piece);
+      else values(no, no_piece);
+    } else {
+      if (!act0) {
+        if (act1) { scores(yes, yes, no_piece); values(yes, no_piece); }
+        else if (FIRST) no_output();
+      } else if (masked) { scores(yes, no, no_piece); values(no, no_piece); }
+      else if (fused) { scores(no, no, k_piece); values(no, no_piece); }
+      else { scores(no, no, no_piece); values(no, no_piece); }
+      kst.move();
     }
-    zp_wait_async();
-    __syncthreads();
+    vst.move();
+    // the next K (and V, or it may be in flight) has landed, and everybody is done with V
+    if (TURNS && fetch) zp_wait_async_upto<PW>();
+    else zp_wait_async();
+    if (!TURNS || fetch) __syncthreads();
   };
-  for (int it = 0; it < n_kt; it += 2) {
-    key_tile(it, std::integral_constant<int, 0>{});
-    if (it + 1 < n_kt) key_tile(it + 1, std::integral_constant<int, 1>{});
+#define ZP_N(n) std::integral_constant<int, n>{}
+  if (n_kt == 0) {
+    no_output();
+  } else if constexpr (TURNS) {
+    key_tile(0, ZP_N(0), ZP_N(1), ZP_N(2), ZP_N(0), std::true_type{});
+    for (int it = 1; it < n_kt; it += 3) {
+      key_tile(it, ZP_N(2), ZP_N(0), ZP_N(1), ZP_N(2), std::false_type{});
+      if (it + 1 < n_kt) key_tile(it + 1, ZP_N(1), ZP_N(2), ZP_N(0), ZP_N(1), std::false_type{});
+      if (it + 2 < n_kt) key_tile(it + 2, ZP_N(0), ZP_N(1), ZP_N(2), ZP_N(0), std::false_type{});
+    }
+  } else {
+    key_tile(0, ZP_N(0), ZP_N(1), ZP_N(2), ZP_N(3), std::true_type{});
+    for (int it = 1; it < n_kt; it += 2) {
+      key_tile(it, ZP_N(2), ZP_N(3), ZP_N(0), ZP_N(1), std::false_type{});
+      if (it + 1 < n_kt) key_tile(it + 1, ZP_N(0), ZP_N(1), ZP_N(2), ZP_N(3), std::false_type{});
+    }
   }
-
-  fwd_finish<D, PARTIAL, 2>(p, t, h, lane, rb, o_acc, nm, l_sum, smem + w * ZP_ROWS_LDS);
+#undef ZP_N
+  if (TURNS) __syncthreads();  // the rows go out through the tiles' LDS
+  int ln = threadIdx.x & 63;
+  asm volatile("" : "+v"(ln));  // worked out again: what depends on the lane would keep registers through the loop
+  fwd_finish<D, PARTIAL, 2>(p, t, h, ln, rb, o_acc, nm, l_sum, smem + w * ZP_ROWS_LDS);
 }
 
 // ---- launches that leave much of the chip idle: two waves per 16 query rows ---------------------------------------
 // The score wave of a pair: softmax arithmetic of a tile (SM, s -> pn; 2: masked) with the score product of the next one (SC:
 // K at lk, into sn) spread over it. Returns the lanes whose rows' reference moved; their O is then to be multiplied by alpha.
-// What a row computes, and in which order, is what fwd_tile computes: the results are the same bits.
+// What a row computes, and in which order, is what attn_fwd_kernel computes: the results are the same bits.
 // ahead: the first K operands, requested by the step before; on return those of the tile behind (lk moves there by `step`).
 constexpr int PAIR_KA = 4;
 template <int D, int SM, bool SC>
@@ -620,17 +788,20 @@ extern "C" int zp_launch_attn_fwd(const zp_attn_params *p, int d, int partial, i
     zp_prof_end(stream);
     return (int)hipGetLastError();
   }
-#define ZP_FWD_LAUNCH(D, NW, PART)                                                                      \
+#define ZP_FWD_LAUNCH(D, TURNS, PART)                                                                   \
   do {                                                                                                  \
-    size_t lds = 4 * (size_t)FwdCfg<D, NW>::TILEB + 16;                                                    \
     zp_prof_begin(PART ? "attn_fwd_partial" : "attn_fwd", stream);                                      \
-    hipLaunchKernelGGL((attn_fwd_kernel<D, NW, PART>), dim3(grid), dim3(NW * 64), lds, stream, *p);     \
+    hipLaunchKernelGGL((attn_fwd_kernel<D, TURNS, PART>), dim3(grid), dim3(256), (fwd_lds<D, TURNS>()), stream, *p); \
     zp_prof_end(stream);                                                                                \
   } while (0)
   if (d == 128) {
-    if (partial) ZP_FWD_LAUNCH(128, 4, true); else ZP_FWD_LAUNCH(128, 4, false);
+    if (p->turns) {
+      if (partial) ZP_FWD_LAUNCH(128, true, true); else ZP_FWD_LAUNCH(128, true, false);
+    } else {
+      if (partial) ZP_FWD_LAUNCH(128, false, true); else ZP_FWD_LAUNCH(128, false, false);
+    }
   } else {
-    if (partial) ZP_FWD_LAUNCH(64, 4, true); else ZP_FWD_LAUNCH(64, 4, false);
+    if (partial) ZP_FWD_LAUNCH(64, false, true); else ZP_FWD_LAUNCH(64, false, false);
   }
 #undef ZP_FWD_LAUNCH
   return (int)hipGetLastError();

@@ -246,6 +246,13 @@ int dyn_div_of(const std::vector<CostTile> &tiles, size_t first, size_t n, int w
   return sum * weight >= (int64_t)n * 32 ? 2 : 8;
 }
 
+// (the costs are key tiles)
+bool fwd_turns(const std::vector<CostTile> &tiles, const zp_shape *sh) {
+  int64_t sum = 0, longest = 0;
+  for (const CostTile &c : tiles) { sum += c.cost; longest = std::max<int64_t>(longest, c.cost); }
+  return zp_fwd_turns(sh->d, sum, (int64_t)tiles.size(), longest, sh->Hq);
+}
+
 int upload_tiles(const std::vector<CostTile> &tiles, void *ws, hipStream_t stream) {
   if (tiles.empty()) return ZP_OK;
   const size_t bytes = WS_HEADER + tiles.size() * sizeof(zp_tile);
@@ -528,6 +535,7 @@ int varlen_attn_fwd(const void *q, const void *k, const void *v, int64_t q_strid
   p.n_tiles = (int32_t)tiles.size(); p.work.dyn_div = dyn_div_of(tiles, 0, tiles.size(), 1);
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
   zp_plan_fwd_pair(p, sh->d);
+  p.turns = fwd_turns(tiles, sh);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o; p.o_stride = o_stride; p.lse = lse; p.lse_stride = sh->T;
   hipError_t e = (hipError_t)zp_launch_attn_fwd(&p, sh->d, 0, bm, (hipStream_t)stream);
@@ -584,6 +592,7 @@ int chunk_attn_partial(const void *q, const void *k, const void *v, int64_t q_st
   p.n_tiles = (int32_t)tiles.size(); p.work.dyn_div = dyn_div_of(tiles, 0, tiles.size(), 1);
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
   zp_plan_fwd_pair(p, sh->d);
+  p.turns = fwd_turns(tiles, sh);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o_part; p.o_stride = (int64_t)sh->Hq * sh->d; p.lse = lse_part; p.lse_stride = part_rows;
   hipError_t e = (hipError_t)zp_launch_attn_fwd(&p, sh->d, 1, bm, (hipStream_t)stream);
@@ -644,6 +653,7 @@ int chunk_attn_update(const void *q, const void *k, const void *v, int64_t q_str
   p.n_tiles = (int32_t)tiles.size(); p.work.dyn_div = dyn_div_of(tiles, 0, tiles.size(), 1);
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
   zp_plan_fwd_pair(p, sh->d);
+  p.turns = fwd_turns(tiles, sh);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o_run; p.o_stride = (int64_t)sh->Hq * sh->d; p.lse = lse_run; p.lse_stride = sh->T;
   p.update = 1;

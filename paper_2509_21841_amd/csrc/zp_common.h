@@ -141,6 +141,7 @@ struct zp_attn_params {
   int64_t lse_stride;
   int32_t update;    // partial kernel only: merge the result into the running (o, lse) found at the output rows
   int32_t pair;      // by the kernel for launches that leave much of the chip idle: zp_pair_mode
+  int32_t turns;     // head dimension 128: by the kernel of three workgroups per CU
   zp_work_split work;  // which workgroups take their item by number and which claim one (set by the launcher)
   zp_inline_tiles inl; // the tile table if `tiles` is null
 };

@@ -4,6 +4,7 @@
 // a serving loop that forbids hipMalloc. The attention kernel itself is the one varlen_attn_fwd launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -155,11 +156,14 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
   PlanArgs a;
   a.S = sh->S;
   for (size_t i = 0; i < sizeof(a.skip_bits) / sizeof(a.skip_bits[0]); i++) a.skip_bits[i] = 0;
-  int64_t n_tiles = 0;
+  int64_t n_tiles = 0, sum = 0, longest = 0;  // query blocks; key tiles they see, the last block of the longest sequence
   for (int s = 0; s <= sh->S; s++) a.cu[s] = cu[s];
   for (int s = 0; s < sh->S; s++) {
     if (seq_skip && seq_skip[s]) { a.skip_bits[s >> 5] |= 1u << (s & 31); continue; }
-    n_tiles += ((int64_t)cu[s + 1] - cu[s] + BM - 1) / BM;
+    const int64_t nb = ((int64_t)cu[s + 1] - cu[s] + BM - 1) / BM, last = ((int64_t)cu[s + 1] - cu[s] + 63) / 64;
+    n_tiles += nb;
+    sum += nb > 0 ? nb * (nb - 1) + last : 0;  // 2, 4, ... and the last block
+    longest = std::max(longest, last);
   }
   if (n_tiles > ZP_NOALLOC_MAX_TILES) return ZP_ETOOLARGE;
   if (n_tiles == 0) return ZP_OK;
@@ -188,6 +192,7 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv;
   zp_plan_fwd_pair(p, sh->d);
+  p.turns = zp_fwd_turns(sh->d, sum, n_tiles, longest, sh->Hq);
   p.scale = sh->scale > 0.f ? sh->scale : 1.0f / std::sqrt((float)sh->d);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   p.o = o; p.o_stride = o_stride; p.lse = lse; p.lse_stride = sh->T;

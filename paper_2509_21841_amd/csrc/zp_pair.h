@@ -143,3 +143,13 @@ inline void zp_plan_dq_pair(zp_bwd_params &p, int d) {
   if (p.dq_tiles == nullptr)
     p.dq_pair = zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.91f, 0.76f);
 }
+
+// Whether a forward launch at head dimension 128 (n query blocks that see `sum` key tiles of 64 in all, one of them `longest`, each
+// `heads` times) takes the kernel of three workgroups per CU. A CU does more with three, and each of them is slower: it pays where a
+// CU's share of the launch is several times the longest item, so that nothing waits for that one. Of 278 random launches (2/1 to 64/8
+// heads, 600 to 131072 tokens) with a share of 4 and more of the longest 155 take it, 1.06 times faster in the mean; 4 are 1 to 2 %
+// slower. From 2 to 4 it is 0.6 % faster in the mean and up to 12 % slower, below 6 % slower in the mean. An item's fixed costs count
+// as three key tiles.
+inline bool zp_fwd_turns(int d, int64_t sum, int64_t n, int64_t longest, int heads) {
+  return d == 128 && (sum + 3 * n) * heads >= 4 * 256 * (longest + 3);
+}
