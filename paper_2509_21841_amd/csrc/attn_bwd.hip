@@ -26,14 +26,17 @@ __device__ __forceinline__ void add_acc_rows(float *dst, const f32x4 (&acc)[D / 
   }
 }
 
-// D = dO . O of a lane's row, whose four lanes hold 8 consecutive head-dim elements of every 32 each
+// D = dO . O of a lane's row, whose four lanes hold 8 consecutive head-dim elements of every 32 each. The dot instruction rounds once
+// per two products: 32 of N(0, 1) values are off by 1.90e-7 (rms, against 64 bits), 1.97e-7 as a chain of fused multiply-adds, for
+// a sixth of the vector operations.
 template <int D>
 __device__ __forceinline__ float row_d(const bf16x8 (&doreg)[D / 32], const bf16x8 (&oreg)[D / 32]) {
   float sum = 0.f;
 #pragma unroll
   for (int kk = 0; kk < D / 32; kk++)
 #pragma unroll
-    for (int e = 0; e < 8; e++) sum = __builtin_fmaf((float)doreg[kk][e], (float)oreg[kk][e], sum);
+    for (int e = 0; e < 8; e += 2)
+      sum = __builtin_amdgcn_fdot2_f32_bf16((bf16x2){doreg[kk][e], doreg[kk][e + 1]}, (bf16x2){oreg[kk][e], oreg[kk][e + 1]}, sum, false);
   return zp_quad_sum(sum);
 }
 
@@ -362,19 +365,19 @@ constexpr size_t dq_pair_lds() { return 2 * PAIR_BUFS * 4 * (size_t)zp_pad16<D>:
 // attn_bwd_dq_kernel alone on a CU and 2250 here at d = 128, 1930 and 1550 at d = 64; MFMAs alone take 1070 of the 2250, the
 // arithmetic between them 800, operand reads and copies the rest. Forward and backward of 1218 tokens, GQA 4/2, d = 128:
 // dQ 14.0 -> 11.6 us; zp_plan_dq_pair has more figures and the rule.
-template <int D>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_pair_kernel(zp_bwd_params p) {
+// block: of the kernel's own. PRE: D and -LSE / scale have been worked out (attn_bwd_rows_kernel).
+template <int D, bool PRE>
+__device__ __forceinline__ void dq_pair_rows(const zp_bwd_params &p, int block, char *smem) {
   constexpr int TILEB = 4 * zp_pad16<D>::R16, NB = PAIR_BUFS;
   typedef zp_stager<D, 8, true> stager;
   constexpr int PW = stager::PER_WAVE;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
   char *Ks = smem;                   // [NB][64][D]: tile j in buffer j % NB
   char *Vs = smem + NB * TILEB;      // [NB][64][D]
   char *Ss = smem + 2 * NB * TILEB;  // [2][4][2][64 x 16 bytes]: a tile's dS, pair by pair, half by half
 
   int unit, hh;
   int part;
-  zp_block_to_unit(zp_pair_item(p.dq_pair, part), p.grp, p.m_grp, unit, hh);
+  zp_block_to_unit(zp_pair_item(p.dq_pair, block, part), p.grp, p.m_grp, unit, hh);
   if (unit >= p.n_dq_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
@@ -397,15 +400,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   kst.init(p.k + (int64_t)t.k_tok0 * p.k_stride + (int64_t)g * D, p.k_stride, tid);
   vst.init(p.v + (int64_t)t.k_tok0 * p.v_stride + (int64_t)g * D, p.v_stride, tid);
   // row operands first, the first two tiles' copies right behind them (see attn_bwd_dq_kernel)
-  bf16x8 qreg[D / 32], doreg[D / 32], oreg[D / 32];
+  bf16x8 qreg[D / 32], doreg[D / 32], oreg[D / 32];  // (PRE: not O)
   const int64_t tok = (int64_t)t.q_tok0 + rowc;
 #pragma unroll
   for (int kk = 0; kk < D / 32; kk++) {
     qreg[kk] = *(const bf16x8 *)(p.q + tok * p.q_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
     doreg[kk] = *(const bf16x8 *)(p.dout + tok * p.do_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
-    oreg[kk] = *(const bf16x8 *)(p.o + tok * p.o_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
+    if (!PRE) oreg[kk] = *(const bf16x8 *)(p.o + tok * p.o_stride + (int64_t)h * D + 2 * q4 + 32 * kk);
   }
   const float lse_nat = p.lse[(int64_t)h * p.T + tok];
+  const float minus_d = PRE ? p.dvec[(int64_t)h * p.T + tok] : 0.f;
 #pragma unroll
   for (int j = 0; j < 2; j++)
     if (j < n_kt) {
@@ -415,7 +419,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   dq_pair_addr<D> la;
   la.init(lane, half, Ks, Vs);
   const unsigned own = zp_lds_addr(Ss) + w * 2048 + lane * 16;
-  const float Dq = row_d<D>(doreg, oreg), lse2 = lse_nat * LOG2E;
+  const float Dq = PRE ? -minus_d : row_d<D>(doreg, oreg), lse2 = lse_nat * LOG2E;
   const f32x4 negD = {-Dq, -Dq, -Dq, -Dq};
   f32x4 dq_acc[D / 32];
 #pragma unroll
@@ -455,7 +459,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int i = 0; i < D / 32; i++) la.t[i] += step_t;
   }
 
-  if (half == 0 && row < t.q_rows && q4 == 0) {
+  if (!PRE && half == 0 && row < t.q_rows && q4 == 0) {
     const int64_t r = (int64_t)h * p.T + t.q_tok0 + row;
     p.dvec[r] = -Dq;
     p.lse2[r] = -lse_nat / p.scale;
@@ -464,6 +468,37 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int64_t at = ((int64_t)t.q_tok0 + rb) * p.dq_stride + (int64_t)h * D + half * (D / 2);
   if (!p.accumulate) zp_store_rows<D / 2>(Vs + (half * 4 + w) * ZP_ROWS_LDS_OF(D / 2), dq_acc, p.scale, p.dq + at, p.dq_stride, t.q_rows - rb, lane);
   else if (row < t.q_rows) add_acc_rows<D / 2>((float *)p.dq + at + c16 * p.dq_stride + q4, dq_acc, p.scale);
+}
+
+template <int D, bool PRE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_pair_kernel(zp_bwd_params p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  dq_pair_rows<D, PRE>(p, blockIdx.x, smem);
+}
+
+// -D and -LSE / scale of the rows of the dQ kernel's tiles, bit for bit what it would leave: 64 rows of a head per workgroup.
+template <int D>
+__global__ __launch_bounds__(256) void attn_bwd_rows_kernel(zp_bwd_params p) {
+  int unit, hh, part;
+  zp_block_to_unit(zp_pair_item(p.dq_pair, blockIdx.x, part), p.grp, p.m_grp, unit, hh);
+  if (unit >= p.n_dq_tiles * p.Hkv) return;
+  const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), h = (unit - tile_idx * p.Hkv) * p.grp + hh;
+  zp_tile t = ZP_TILE((const zp_tile *)nullptr, p.inl, 0, tile_idx);
+  if (!zp_pair_rows(t, part)) return;
+  const int lane = threadIdx.x & 63, c16 = lane & 15, q4 = 4 * (lane >> 4), row = 16 * (threadIdx.x >> 6) + c16;
+  const int64_t tok = (int64_t)t.q_tok0 + min(row, t.q_rows - 1);
+  const __bf16 *dop = p.dout + tok * p.do_stride + (int64_t)h * D + 2 * q4, *op = p.o + tok * p.o_stride + (int64_t)h * D + 2 * q4;
+  bf16x8 doreg[D / 32], oreg[D / 32];
+#pragma unroll
+  for (int kk = 0; kk < D / 32; kk++) {
+    doreg[kk] = *(const bf16x8 *)(dop + 32 * kk);
+    oreg[kk] = *(const bf16x8 *)(op + 32 * kk);
+  }
+  const float lse_nat = p.lse[(int64_t)h * p.T + tok], Dq = row_d<D>(doreg, oreg);
+  if (row < t.q_rows && q4 == 0) {
+    p.dvec[(int64_t)h * p.T + tok] = -Dq;
+    p.lse2[(int64_t)h * p.T + tok] = -lse_nat / p.scale;
+  }
 }
 
 // ------------------------------------------------------------------------------------------- dK, dV
@@ -1086,11 +1121,11 @@ __global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2
 // operand and its MFMA, operands requested AHEAD steps ahead. exp2 runs under the dP product, dS = P dP under the dV product.
 // Q_OFF, O_OFF, seed, D_OFF: as for dkdv_block. V fits the registers here. `piece(integral_constant<int, n>)`, n = 0 .. D / 16, is
 // called every third step: the caller's copies of a later tile go there one by one.
-template <int D, int Q_OFF, int O_OFF, int D_OFF, bool MASK, class Piece>
+template <int D, int AHEAD, int Q_OFF, int O_OFF, int D_OFF, bool MASK, class Piece>
 __device__ __forceinline__ void dkdv_half_block(unsigned seed, const bf16x8 (&kreg)[D / 32], const bf16x8 (&vreg)[D / 32], f32x4 (&dk_acc)[D / 16],
                                                 f32x4 (&dv_acc)[D / 16], int qpos0, int kpos, int qpos_end, float c_log2,
                                                 const zp_pad16_addr<D> &la, Piece &&piece) {
-  constexpr int N = D / 16, EPS = 8 / N, AHEAD = D == 64 ? 3 : 6;  // steps of a product; elements of P or dS per step
+  constexpr int N = D / 16, EPS = 8 / N;  // steps of a product; elements of P or dS per step
   f32x4 s[2], dp[2], ls[2], ds[2];
 #pragma unroll
   for (int rb = 0; rb < 2; rb++) {  // -LSE/scale and -D of the 4 query rows this lane holds of each 16
@@ -1148,20 +1183,19 @@ constexpr int split_own() { return 8 * zp_pad16<D>::R16 + 1024; }
 // two waves are 1024 and 512, their arithmetic under MFMAs about as much, hand-over and addresses 600); with one wave per
 // group and 32 key rows per wave, whose operations issue one after the other, 1.50 and 0.86. 1000 tokens, 4/2 heads, d = 128:
 // one wave per group 31.7 us, two 27.1; 4000 tokens 105.6 and 85.5 (61.8 and 58.6 at d = 64). See dkdv_kernel_for for when it is used.
+// block: of the kernel's own
 template <int D>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2, D == 64 ? 4 : 2))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
-  constexpr int QT = 32;
+__device__ __forceinline__ void dkdv_split_rows(const zp_bwd_params &p, int block, char *smem) {
+  constexpr int QT = 32, AHEAD = D == 64 ? 3 : 6;
   typedef zp_pad16<D> L;
   constexpr int TILEB = 2 * L::R16;                // a staged tile: 32 query rows
-  constexpr int OWN = split_own<D>();
-  extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave & 3, half = wave >> 2;
-  char *own = smem + group * OWN;
+  char *own = smem + group * split_own<D>();
   float *Ls = (float *)(own + 4 * TILEB);          // [2][2][64]: see attn_bwd_dkdv128_kernel
 
   // the four workgroups of a key block on one XCD
-  const int x = blockIdx.x & 7, y = blockIdx.x >> 3, part = y & 3, unit = (y >> 2) * 8 + x;
+  const int x = block & 7, y = block >> 3, part = y & 3, unit = (y >> 2) * 8 + x;
   if (unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
@@ -1240,11 +1274,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
     auto no_piece = [](auto) {};
     if (compute) {
       if (masked)
-        dkdv_half_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+        dkdv_half_block<D, AHEAD, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, true>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
       else if (D == 128 && fused)
-        dkdv_half_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
+        dkdv_half_block<D, AHEAD, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, stage_piece);
       else
-        dkdv_half_block<D, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
+        dkdv_half_block<D, AHEAD, 2 * buf * TILEB, (2 * buf + 1) * TILEB, 256, false>(seed + buf * 512, kreg, vreg, dk_acc, dv_acc, qpos0, kpos, qpos_end_l, c_log2, la, no_piece);
     }
     i0 = next_i0;
     on(next_i0, next_hh);
@@ -1289,6 +1323,25 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
 }
 
 template <int D>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2, D == 64 ? 4 : 2))) void attn_bwd_dkdv_split_kernel(zp_bwd_params p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  dkdv_split_rows<D>(p, blockIdx.x, smem);
+}
+
+// dQ and dK/dV in one launch, where both would take the kernels for launches that leave part of the chip idle: the first p.both
+// workgroups do what attn_bwd_dkdv_split_kernel does, the others what attn_bwd_dq_pair_kernel does. Neither then needs anything of the
+// other's: attn_bwd_rows_kernel works out -D and -LSE / scale in front. (Worked out in the dK/dV workgroups instead, tile by tile, they
+// took more of a CU's 64 bytes per cycle from L2 than Q and dO leave: an iteration 2.6 us instead of 1.2.) Bound: the longer of the two
+// longest chains, and 3 us for the rows. Backward of 1218 tokens in eight sequences, GQA 4/2, d = 128: 23.8 -> 16.6 us, passes one
+// after the other; zp_take_both has more figures and the rule.
+template <int D>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_both_kernel(zp_bwd_params p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int block = blockIdx.x;
+  if (block < p.both) dkdv_split_rows<D>(p, block, smem);
+  else dq_pair_rows<D, true>(p, block - p.both, smem);
+}
+template <int D>
 constexpr size_t split_lds() {
   constexpr size_t loop = 4 * (size_t)split_own<D>(), end = 16 * (D / 16) * 64 * 16;
   return loop > end ? loop : end;
@@ -1298,6 +1351,7 @@ constexpr size_t split_lds() {
 
 extern "C" void zp_prof_begin(const char *name, hipStream_t stream);
 extern "C" void zp_prof_end(hipStream_t stream);
+extern "C" int zp_prof_enabled(void);
 
 extern "C" int zp_attn_bwd_block_rows(int d, int which) { (void)d; (void)which; return 128; }
 
@@ -1312,12 +1366,32 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   int32_t *c = p->work_dq.counters;
   const int dq_grid = zp_plan_work_split(p->work_dq, c, ((dq_units + 7) / 8) * 8 * p->grp);
   const int kv_grid = zp_plan_work_split(p->work_kv, c ? c + ZP_COUNTER_BYTES / 4 : nullptr, ((kv_units + 7) / 8) * 8);
+  const dim3 pair_grid(((dq_units + 7) / 8) * 8 * p->grp * (p->dq_pair == ZP_PAIR_HALVES ? 2 : 1)), split_grid(((kv_units + 7) / 8) * 8 * 4);
+  // (the profile tells dQ and dK/dV apart; the results are the same bits)
+  const bool both = p->both && dq_units > 0 && kv_units > 0, merged = both && !zp_prof_enabled();
+#define ZP_BOTH_ROWS()                                                                                             \
+  do {                                                                                                             \
+    if (d == 128) hipLaunchKernelGGL(attn_bwd_rows_kernel<128>, pair_grid, dim3(256), 0, stream, *p);              \
+    else hipLaunchKernelGGL(attn_bwd_rows_kernel<64>, pair_grid, dim3(256), 0, stream, *p);                        \
+  } while (0)
+  if (merged) {
+    ZP_BOTH_ROWS();
+    const dim3 grid(split_grid.x + pair_grid.x);
+    p->both = (int)split_grid.x;
+    const size_t lds128 = std::max(dq_pair_lds<128>(), split_lds<128>()), lds64 = std::max(dq_pair_lds<64>(), split_lds<64>());
+    if (d == 128) hipLaunchKernelGGL(attn_bwd_both_kernel<128>, grid, dim3(512), lds128, stream, *p);
+    else hipLaunchKernelGGL(attn_bwd_both_kernel<64>, grid, dim3(512), lds64, stream, *p);
+    return (int)hipGetLastError();
+  }
   if (dq_units > 0) {
     zp_prof_begin(p->dq_pair ? "attn_bwd_dq_pair" : "attn_bwd_dq", stream);
     if (p->dq_pair) {
-      const dim3 grid(((dq_units + 7) / 8) * 8 * p->grp * (p->dq_pair == ZP_PAIR_HALVES ? 2 : 1));
-      if (d == 128) hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<128>, grid, dim3(512), dq_pair_lds<128>(), stream, *p);
-      else hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<64>, grid, dim3(512), dq_pair_lds<64>(), stream, *p);
+      if (both) ZP_BOTH_ROWS();
+#define ZP_DQ_PAIR(D, PRE) hipLaunchKernelGGL((attn_bwd_dq_pair_kernel<D, PRE>), pair_grid, dim3(512), dq_pair_lds<D>(), stream, *p)
+      if (d == 128) { if (both) ZP_DQ_PAIR(128, true); else ZP_DQ_PAIR(128, false); }
+      else if (both) ZP_DQ_PAIR(64, true);
+      else ZP_DQ_PAIR(64, false);
+#undef ZP_DQ_PAIR
     } else if (d == 128) hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 128 * 2 + 16, stream, *p);
     else hipLaunchKernelGGL((attn_bwd_dq_kernel<64>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 64 * 2 + 16, stream, *p);
     zp_prof_end(stream);
@@ -1327,9 +1401,8 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   if (kv_units > 0) {
     zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : p->kv_pair && d == 128 ? "attn_bwd_dkdv_pair" : "attn_bwd_dkdv", stream);
     if (p->kv_split) {
-      const dim3 grid(((kv_units + 7) / 8) * 8 * 4);
-      if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, grid, dim3(512), split_lds<128>(), stream, *p);
-      else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, grid, dim3(512), split_lds<64>(), stream, *p);
+      if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, split_grid, dim3(512), split_lds<128>(), stream, *p);
+      else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, split_grid, dim3(512), split_lds<64>(), stream, *p);
     } else if (d == 128) {
       constexpr size_t R16 = zp_pad16<128>::R16;
       if (p->kv_pair) hipLaunchKernelGGL(attn_bwd_dkdv128_kernel<2>, dim3(kv_grid), dim3(2 * BWD_NT), std::max(24 * R16 + 2 * 1024 + 16, (size_t)131072), stream, *p);

@@ -630,7 +630,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))) voi
 
   int unit, hh;
   int half;
-  zp_block_to_unit(zp_pair_item(p.pair, half), p.grp, p.m_grp, unit, hh);
+  zp_block_to_unit(zp_pair_item(p.pair, blockIdx.x, half), p.grp, p.m_grp, unit, hh);
   if (unit >= p.n_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;

@@ -436,6 +436,10 @@ void zp_prof_end(hipStream_t stream) {
   if (!g_prof_on || g_prof.empty()) return;
   (void)hipEventRecord(g_prof.back().b, stream);
 }
+int zp_prof_enabled(void) {
+  std::lock_guard<std::mutex> lk(g_prof_mu);
+  return g_prof_on;
+}
 int zp_profile_enable(int on) {
   std::lock_guard<std::mutex> lk(g_prof_mu);
   for (auto &r : g_prof) {
@@ -829,6 +833,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv; p.T = sh->T;
   zp_plan_dq_pair(p, sh->d);
+  p.both = zp_take_both(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.dq = (__bf16 *)dq; p.dk = (__bf16 *)dk; p.dv = (__bf16 *)dv;
   p.dq_stride = dq_stride; p.dkv_stride = dkv_stride;
@@ -925,6 +930,7 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.n_dq_tiles = (int32_t)qt.size(); p.n_kv_tiles = (int32_t)kt.size();
   p.Hq = sh->Hq; p.Hkv = sh->Hkv; p.grp = sh->Hq / sh->Hkv; p.T = sh->T;
   zp_plan_dq_pair(p, sh->d);
+  p.both = zp_take_both(p, sh->d);
   p.scale = eff_scale(sh); p.scale_log2 = p.scale * 1.4426950408889634f;
   p.dq = (__bf16 *)dq_acc; p.dk = (__bf16 *)dk_acc; p.dv = (__bf16 *)dv_acc;
   p.dq_stride = (int64_t)sh->Hq * sh->d; p.dkv_stride = (int64_t)sh->Hkv * sh->d;

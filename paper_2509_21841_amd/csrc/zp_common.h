@@ -113,9 +113,9 @@ __device__ __forceinline__ int zp_item_of_block(const zp_work_split &ws, int *sl
 // The kernels that put two waves on every 16 query rows work on 64 rows at a time. Their table is in the launch arguments, as
 // tiles of 64 rows (ordered by cost, none empty) where that many fit, else as the tiles of 128, whose halves are two workgroups.
 enum zp_pair_mode { ZP_PAIR_NONE = 0, ZP_PAIR_TILES = 1, ZP_PAIR_HALVES = 2 };
-// The item of this workgroup (halves: both on one XCD, the later rows first) and, of its tile, the 64 rows.
-__device__ __forceinline__ int zp_pair_item(int mode, int &half) {
-  const int b = blockIdx.x, y = b >> 3;
+// The item of workgroup b (halves: both on one XCD, the later rows first) and, of its tile, the 64 rows.
+__device__ __forceinline__ int zp_pair_item(int mode, int b, int &half) {
+  const int y = b >> 3;
   half = mode == ZP_PAIR_HALVES ? 1 - (y & 1) : 0;
   return mode == ZP_PAIR_HALVES ? (y >> 1) * 8 + (b & 7) : b;
 }
@@ -164,6 +164,7 @@ struct zp_bwd_params {
   int32_t dq_pair;           // dQ by the kernel for launches that leave much of the chip idle: zp_pair_mode
   int32_t kv_pair;           // dK/dV at head dimension 128 by workgroups of two groups of four waves
   int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
+  int32_t both;              // that and dq_pair in one launch (there: the workgroups of dK/dV, which come first)
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to
   zp_work_split work_dq, work_kv;  // work hand-out of the two launches (counters set by the C ABI, the rest by the launcher)
   zp_inline_tiles inl;  // the dQ tiles and, behind them, the dK/dV tiles if dq_tiles and kv_tiles are null

@@ -144,6 +144,45 @@ inline void zp_plan_dq_pair(zp_bwd_params &p, int d) {
     p.dq_pair = zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.91f, 0.76f);
 }
 
+// Whether dQ and dK/dV, which take the kernels for launches that leave part of the chip idle (their tiles in the launch arguments), go
+// in one launch behind a small one for the row terms: the two leave different parts of the chip idle, and each waits for its longest
+// chain. Workgroups take a CU each there. With a CU for all of them it is faster (one key tile at d = 64 and more than 160 workgroups:
+// 9.7 / 10.5 us); beyond, where the longest chain is a third longer than a CU's share of all. At d = 128 also with shares of 9 us and more; at 64, where two workgroups of the dK/dV
+// kernel by itself share a CU, not. Constants: dQ as above, dK/dV as in dkdv_kernel_for. Of 270 random launches (2/1 to 64/8 heads, 100 to
+// 14000 tokens) 240 take it, for 0.77 of the time in the mean, one of them 1.5 % slower. n sequences, us, two launches / one and the small one:
+//    d   heads   tokens                              taken              not taken
+//    64   4/2    1511,               n =  1:   42.4 / 26.3
+//    64   2/1    4919, longest 3033, n =  3:   77.1 / 46.3
+//    64  32/32    322, longest  126, n =  4:                      13.1 / 15.7
+//    64   8/8    4002, longest 2876, n =  2:                      77.7 / 88.1
+//   128   4/2    1218, longest  329, n =  8:   23.8 / 16.6
+//   128   2/1    4001, longest 3681, n =  4:  135.7 / 79.4
+//   128  16/4     272, longest   17, n = 16:                      12.3 / 13.4
+inline bool zp_take_both(const zp_bwd_params &p, int d) {
+  if (!p.dq_pair || !p.kv_split || p.dq_tiles != nullptr) return false;
+  static const float dq_wg[2] = {2.18f, 3.62f}, dq_tile[2] = {0.691f, 1.02f}, kv_wg[2] = {1.55f, 2.82f}, kv_it[2] = {0.831f, 1.255f};
+  const int c = d == 128;
+  float longest = 0.f, sum = 0.f;
+  int64_t n = 0;
+  for (int i = 0; i < p.n_dq_tiles; i++)
+    for (int half = 0; half < (p.dq_pair == ZP_PAIR_HALVES && p.inl.t[i].q_rows > 64 ? 2 : 1); half++) {
+      const float t = dq_wg[c] + dq_tile[c] * (float)zp_key_tiles(p.dq_pair == ZP_PAIR_HALVES ? zp_half_tile(p.inl.t[i], half) : p.inl.t[i]);
+      longest = std::max(longest, t);
+      sum += t * (float)p.Hq;
+      n += p.Hq;
+    }
+  for (int i = 0; i < p.n_kv_tiles; i++) {
+    const zp_tile &k = p.inl.t[p.n_dq_tiles + i];
+    const int parts = (k.k_len + 31) / 32, its = ((k.q_rows + 31) / 32 * p.grp + 3) / 4;
+    const float t = kv_wg[c] + kv_it[c] * (float)its;
+    longest = std::max(longest, t);
+    sum += t * (float)(parts * p.Hkv);
+    n += parts * p.Hkv;
+  }
+  const float share = sum / 256.f;
+  return n <= (longest < 3.f ? 160 : 256) || (n > 256 && share <= 0.75f * longest) || (d == 128 && share >= 9.f);
+}
+
 // Whether a forward launch at head dimension 128 (n query blocks that see `sum` key tiles of 64 in all, one of them `longest`, each
 // `heads` times) takes the kernel of three workgroups per CU. A CU does more with three, and each of them is slower: it pays where a
 // CU's share of the launch is several times the longest item, so that nothing waits for that one. Of 278 random launches (2/1 to 64/8
