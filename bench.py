@@ -221,7 +221,7 @@ def kernel_flops(job, label: str) -> float:
 
 def kernel_of(label: str) -> str:
     """The launch a profile label stands for: the kernels for launches that leave part of the chip idle do the same work."""
-    for suffix in ("_pair", "_split"):
+    for suffix in ("_pair", "_split", "_shares"):
         label = label.removesuffix(suffix)
     return label
 

@@ -631,6 +631,52 @@ __device__ __forceinline__ void dkdv_tile(unsigned seed, const bf16x8 (&kreg)[2]
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The end of a workgroup that has gone through one share of its block's iterations: its sums go to scratch memory, and the share that
+// is done last adds all of them up, in their order whichever it is (no workgroup waits for another). Returns whether this is the one
+// (dk_acc, dv_acc then hold the block's sums). slot: an int of LDS that nobody needs any more. Bound: memory, 128 KB per share written and read
+// at d = 128, 64 KB at 64 -- 256 shares at a time take some 14 and 7 us, 4.8 TB/s.
+template <int D>
+__device__ __forceinline__ bool dkdv_join_parts(const zp_bwd_params &p, const zp_part &part, int g, int tid, int *slot, f32x4 (&dk_acc)[2][D / 16],
+                                                f32x4 (&dv_acc)[2][D / 16]) {
+  constexpr int64_t SLOT = 128 * D * 2;  // floats
+  constexpr int ONE = 2 * (D / 16) * 64 * 4;  // of a wave and sum
+  const int at = (tid >> 6) * 2 * ONE + (tid & 63) * 4;
+  auto of = [&](int i) { return p.parts + ((int64_t)(part.slot + i) * p.Hkv + g) * SLOT + at; };
+  {
+    float *own = of(part.part);
+#pragma unroll
+    for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+      for (int i = 0; i < D / 16; i++) {
+        *(f32x4 *)(own + (cb * (D / 16) + i) * 256) = dk_acc[cb][i];
+        *(f32x4 *)(own + ONE + (cb * (D / 16) + i) * 256) = dv_acc[cb][i];
+      }
+  }
+  zp_wait_async();  // this wave's have been written
+  __syncthreads();  // everybody's
+  if (tid == 0) *slot = __hip_atomic_fetch_add(p.part_done + (int64_t)part.slot * p.Hkv + g, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*slot) != part.n - 1) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  for (int n = 0; n < part.n; n++) {
+    const float *in = of(n);
+#pragma unroll
+    for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+      for (int i = 0; i < D / 16; i++) {
+        const f32x4 a = *(const f32x4 *)(in + (cb * (D / 16) + i) * 256), b = *(const f32x4 *)(in + ONE + (cb * (D / 16) + i) * 256);
+        if (n == 0) {
+          dk_acc[cb][i] = a;
+          dv_acc[cb][i] = b;
+        } else {
+          dk_acc[cb][i] += a;
+          dv_acc[cb][i] += b;
+        }
+      }
+  }
+  return true;
+}
+
 __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv64_kernel(zp_bwd_params p) {
   constexpr int D = 64;
   constexpr int TILEB = 64 * D * 2;
@@ -676,7 +722,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const float c_log2 = p.scale_log2;
 
   const int n_qt = (t.q_rows + 63) / 64;
-  const int n_it = n_qt * p.grp;  // iterations: query tiles outermost (last tile first), heads of the group innermost
+  // iterations: query tiles outermost (last tile first), heads of the group innermost; of the block, and of this workgroup's share
+  const zp_part part = zp_part_of(t.part);
+  const int n_all = n_qt * p.grp, it0 = part.part * p.share_its, n_it = part.part + 1 < part.n ? p.share_its : n_all - it0;
 
   zp_stager<D> qst, ost;
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
@@ -687,7 +735,9 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   // Iteration order: query tiles from the END of the sequence backwards, the heads of the group innermost.
   // Workgroups of one sequence that start together then read the same (tile, head) at the same time and
   // share it in L2; the diagonal (masked) tiles come last.
-  int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
+  const int qt0 = zp_udiv(it0, p.grp, p.m_grp);
+  int st_hh = it0 - qt0 * p.grp, st_qt = n_qt - 1 - qt0;  // head and query tile of the next tile to request
+  int buf = 0, cur_qt = st_qt, cur_hh = st_hh;
   auto staged = [&] { if (++st_hh == p.grp) { st_hh = 0; st_qt--; } };
   auto stage = [&](int buf) {
     const int hh = st_hh, i0 = st_qt * 64;
@@ -736,7 +786,6 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int qpos_end_l = qpos_end - q4;
   constexpr int D_OFF = NBUF * 256;
 
-  int buf = 0, cur_qt = n_qt - 1, cur_hh = 0;
   for (int it = 0; it < n_it; it++) {
     const int i0 = cur_qt * 64;
     if (++cur_hh == p.grp) { cur_hh = 0; cur_qt--; }
@@ -779,6 +828,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     lo.move(buf ? 2 * TILEB : -2 * (NBUF - 1) * TILEB);
     seed += buf ? 256 : -(NBUF - 1) * 256;
   }
+  if (part.n && !dkdv_join_parts<D>(p, part, g, tid, (int *)(Ds + NBUF * 64), dk_acc, dv_acc)) return;
 
 #pragma unroll
   for (int cb = 0; cb < 2; cb++) {
@@ -999,7 +1049,9 @@ __global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2
   const float c_log2 = p.scale_log2;
 
   const int n_qt = (t.q_rows + QT - 1) / QT;
-  const int n_it = n_qt * p.grp;  // iterations: query tiles outermost (last tile first), heads of the group innermost
+  // iterations: query tiles outermost (last tile first), heads of the group innermost; of the block, and (G = 1) of this workgroup's share
+  const zp_part part = zp_part_of(G == 1 ? t.part : 0);
+  const int n_all = n_qt * p.grp, it0 = part.part * p.share_its, n_it = part.part + 1 < part.n ? p.share_its : n_all - it0;
 
   stager qst, ost;
   qst.init(p.q + (int64_t)t.q_tok0 * p.q_stride + (int64_t)g * p.grp * D, p.q_stride, tid);
@@ -1017,7 +1069,8 @@ __global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int i = 0; i < by; i++)
       if (++hh == p.grp) { hh = 0; qt--; }
   };
-  int st_hh = 0, st_qt = n_qt - 1;  // head and query tile of the next tile to request
+  const int qt0 = G == 1 ? zp_udiv(it0, p.grp, p.m_grp) : 0;
+  int st_hh = it0 - qt0 * p.grp, st_qt = n_qt - 1 - qt0;  // head and query tile of the next tile to request
   on(st_hh, st_qt, group);
   int cur_qt = st_qt, cur_hh = st_hh;
   auto staged = [&] { on(st_hh, st_qt, G); };
@@ -1102,6 +1155,7 @@ __global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2
     dkdv_add_groups<D>(p, t, g, group, w, lane, kb, dk_acc, dv_acc, smem);
     return;
   }
+  if (part.n && !dkdv_join_parts<D>(p, part, g, tid, (int *)Ls, dk_acc, dv_acc)) return;
 
 #pragma unroll
   for (int cb = 0; cb < 2; cb++) {
@@ -1399,7 +1453,7 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
     if (e != hipSuccess) return (int)e;
   }
   if (kv_units > 0) {
-    zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : p->kv_pair && d == 128 ? "attn_bwd_dkdv_pair" : "attn_bwd_dkdv", stream);
+    zp_prof_begin(p->kv_split ? "attn_bwd_dkdv_split" : p->kv_pair && d == 128 ? "attn_bwd_dkdv_pair" : p->share_its ? "attn_bwd_dkdv_shares" : "attn_bwd_dkdv", stream);
     if (p->kv_split) {
       if (d == 128) hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<128>, split_grid, dim3(512), split_lds<128>(), stream, *p);
       else hipLaunchKernelGGL(attn_bwd_dkdv_split_kernel<64>, split_grid, dim3(512), split_lds<64>(), stream, *p);

@@ -253,15 +253,17 @@ bool fwd_turns(const std::vector<CostTile> &tiles, const zp_shape *sh) {
   return zp_fwd_turns(sh->d, sum, (int64_t)tiles.size(), longest, sh->Hq);
 }
 
-int upload_tiles(const std::vector<CostTile> &tiles, void *ws, hipStream_t stream) {
+// (zeros: so many 32-bit zeros behind the table)
+int upload_tiles(const std::vector<CostTile> &tiles, size_t zeros, void *ws, hipStream_t stream) {
   if (tiles.empty()) return ZP_OK;
-  const size_t bytes = WS_HEADER + tiles.size() * sizeof(zp_tile);
+  const size_t bytes = WS_HEADER + tiles.size() * sizeof(zp_tile) + zeros * sizeof(int32_t);
   Upload u;
   int rc = upload_begin(bytes, stream, u);
   if (rc) return rc;
   std::memset(u.host, 0, WS_HEADER);
   zp_tile *h = (zp_tile *)((char *)u.host + WS_HEADER);
   for (size_t i = 0; i < tiles.size(); i++) h[i] = tiles[i].t;
+  std::memset((void *)(h + tiles.size()), 0, zeros * sizeof(int32_t));
   return upload_send(u, ws, bytes, stream);
 }
 
@@ -270,9 +272,10 @@ int upload_tiles(const std::vector<CostTile> &tiles, void *ws, hipStream_t strea
 // device memory; then *dev and *counters are null. Eight sequences of 1218 tokens in all, one call after the other:
 // forward (4 heads, d = 64) 23.1 us with the upload, 19.1 without (the host is the bound), forward and backward (GQA 4/2,
 // d = 128) 70.1 and 57.6.
+bool tiles_inline(size_t n, int64_t max_items) { return n <= ZP_INLINE_TILES && max_items < ZP_CLAIM_MIN_ITEMS; }
 int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline_tiles &inl, void *ws, hipStream_t stream,
-                const zp_tile **dev, int32_t **counters) {
-  if (tiles.size() <= ZP_INLINE_TILES && max_items < ZP_CLAIM_MIN_ITEMS) {
+                const zp_tile **dev, int32_t **counters, size_t zeros = 0) {
+  if (tiles_inline(tiles.size(), max_items)) {
     for (size_t i = 0; i < tiles.size(); i++) inl.t[i] = tiles[i].t;
     *dev = nullptr;
     *counters = nullptr;
@@ -280,7 +283,7 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   }
   *dev = ws_tiles(ws);
   *counters = ws_counters(ws);
-  return upload_tiles(tiles, ws, stream);
+  return upload_tiles(tiles, zeros, ws, stream);
 }
 // Which dK/dV kernel a launch takes, by estimates of their times in microseconds; an iteration is a (32-query tile, head). All deal
 // the units (tile, KV head) to the XCDs by turns. An XCD hands its workgroups in order and by turns to four engines of eight
@@ -330,11 +333,13 @@ struct KvPlacement {
     end = std::max(end, b[at]);
   }
 };
-KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int grp) {
-  static const KvCost cost[2] = {{2.12f, 0.565f, 0.371f, 0.841f, 0.136f, 3.08f, 0.375f, 2.46f, 1.86f, 0.831f},
-                                 {0.49f, 1.029f, 0.349f, 0.740f, 0.586f, 4.30f, 0.154f, 1.69f, 2.82f, 1.255f}};
-  const KvCost &c = cost[d == 128];
+const KvCost kv_cost[2] = {{2.12f, 0.565f, 0.371f, 0.841f, 0.136f, 3.08f, 0.375f, 2.46f, 1.86f, 0.831f},
+                           {0.49f, 1.029f, 0.349f, 0.740f, 0.586f, 4.30f, 0.154f, 1.69f, 2.82f, 1.255f}};
+// *estimate: its time; 0 beyond 1024 units
+KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int grp, float *estimate) {
+  const KvCost &c = kv_cost[d == 128];
   const int64_t units = (int64_t)kt.size() * Hkv;
+  *estimate = 0.f;
   if (units > 1024) return KV_WHOLE;
   struct Xcd {
     int n = 0, parts[128];                  // units; of each: its 32-row parts with keys,
@@ -390,7 +395,9 @@ KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int gr
     // one key block each, all of it on the diagonal, beyond one workgroup per CU: up to 30 % behind the estimate (49 sequences of up
     // to 99 tokens, 32/8 heads: 19.8 us estimated, 26.5 measured; 56 of up to 100, 64/8: 34.6 us whole, 40.8 split)
     const bool diagonal = units > 256 && longest <= 4.f * (float)grp;
-    return c.split + split < (diagonal ? 0.8f : 0.97f) * t_whole ? KV_SPLIT : KV_WHOLE;
+    const bool taken = c.split + split < (diagonal ? 0.8f : 0.97f) * t_whole;
+    *estimate = taken ? c.split + split : t_whole;
+    return taken ? KV_SPLIT : KV_WHOLE;
   }
 
   constexpr float PAIR = 1.04f, PAIR_WG = 3.61f, PAIR_IT = 1.533f, SPLIT_MASK = 0.514f;
@@ -412,12 +419,137 @@ KvKernel dkdv_kernel_for(const std::vector<CostTile> &kt, int d, int Hkv, int gr
       const float time = c.split_wg + masked + floorf((most->its[i] + 3.f) / 4.f);
       for (int part = 0; part < 4; part++) on.start(part < most->parts[i] ? time : 0.f);
     }
-    if (c.split + c.split_it * on.end < other) return KV_SPLIT;
+    *estimate = c.split + c.split_it * on.end;
+    if (*estimate < other) return KV_SPLIT;
   }
+  *estimate = pair ? t_pair : t_whole;
   return pair ? KV_PAIR : KV_WHOLE;
 }
 // work items of a launch over n tiles: (tile, KV head) units padded to one per XCD, times the heads in a group
 int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7) / 8 * 8 * grp; }
+
+// ---- dK/dV: shares of key blocks
+// The whole kernels' launch lasts at least as long as its longest chain of iterations, that of the first key block of the longest
+// sequence with all heads of its group, however little the others have to do. Blocks of many iterations are therefore cut into shares,
+// a workgroup each, whose sums the last one to end adds up (dkdv_join_parts). The shares of a sequence's blocks cover the same query
+// tiles, counted from its end, so that they still find each other's Q and dO rows in L2 (shares of a block's own iterations that are equally
+// long: 39059 tokens, 8/2 heads, d = 64, 5.1 ms instead of 4.7). A share costs a prologue and its sums' way to memory and back, 7 us of a CU at d = 64
+// and 14 at 128, so it is a fifth or a quarter of a CU's load long, and the shares are taken where the estimate of their launch is
+// 7 % (d = 128: 5 %) below that of the other kernels. The estimate is fitted to 340 launches of up to 4 ms (of 4/4 to 64/8 heads, 5000 to 131072
+// tokens; 5 % off in the mean). Of 85 random backwards whose longest chain is a third of a CU's load and more 42 take them: 1.06 times
+// faster in the mean of all at d = 64 and 1.023 at 128; none of the 42 is slower. Backward, us, before / with shares:
+//    d   heads   tokens                        taken             not taken
+//    64  16/4    24001, longest  3802          482 / 448
+//    64   8/2    39059, longest 39059         5256 / 4660
+//   128   8/2    24001, longest 11048         1504 / 1235
+//   128   4/4    34415, longest  7173          434 / 373
+//   128   4/2    11503, longest  3643                            160 / 168
+//    64   4/2    26485, longest  3837                            192 / 202
+struct KvShares {
+  int32_t its = 0;    // iterations of a share, 0: no block is shared
+  int64_t slots = 0;  // shares of shared blocks (times KV heads: sums in scratch memory)
+};
+struct KvShareCost {
+  float of_load, least;            // a share: of a CU's load, and at least so many iterations of 32 queries
+  float launch, it, slot, share;   // per launch; per CU: iteration, share; per iteration of a share
+  float margin;
+};
+const KvShareCost kv_share_cost[2] = {{0.2f, 48.f, 11.2f, 0.385f, 7.43f, 0.408f, 0.93f}, {0.25f, 64.f, 8.84f, 0.691f, 14.2f, 0.803f, 0.95f}};
+// iterations of a block of keys that `rows` queries see (d = 64: of 64 queries)
+inline int64_t kv_iterations(int64_t rows, int d, int grp) { return (d == 64 ? (rows + 63) / 64 : (rows + 31) / 32) * grp; }
+// shares of a block: the last one has between 3/8 and 11/8 of the others' iterations
+inline int64_t kv_shares_of(int64_t its, int64_t share) { return std::max<int64_t>(1, (its + share * 5 / 8) / share); }
+struct KvLoad {
+  float sum = 0.f;  // iterations of 32 queries, fixed ones of a workgroup among them
+  int64_t longest = 0, blocks = 0;
+  void add(int64_t its, int d) {
+    sum += (d == 64 ? 2.f : 1.f) * (float)its + kv_cost[d == 128].whole_wg;
+    longest = std::max(longest, its);
+    blocks++;
+  }
+};
+// How long a share would be and how many there would be at most: from all sequences, flagged ones too, as the workspace's size is.
+KvShares plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk) {
+  KvShares r;
+  const int grp = sh->Hq / sh->Hkv, c = sh->d == 128;
+  const float unit = sh->d == 64 ? 2.f : 1.f;
+  KvLoad all;
+  for (int s = 0; s < sh->S; s++)
+    for (int64_t L = (int64_t)cu[s + 1] - cu[s]; L > 0; L -= bnk) all.add(kv_iterations(L, sh->d, grp), sh->d);
+  if (tiles_inline(2 * (size_t)all.blocks, launch_items((size_t)all.blocks, sh->Hkv, grp))) return r;
+  const float load = kv_cost[c].rate * all.sum * (float)sh->Hkv / 256.f;
+  if (unit * (float)all.longest < 0.5f * load) return r;
+  int64_t share = (int64_t)(std::max(kv_share_cost[c].of_load * load, kv_share_cost[c].least) / unit);
+  // no more than 2048 sums (d = 128: 256 MB)
+  for (;; share += share / 8) {
+    share = (share + grp - 1) / grp * grp;
+    int64_t slots = 0, most = 0;
+    for (int s = 0; s < sh->S; s++)
+      for (int64_t L = (int64_t)cu[s + 1] - cu[s]; L > 0; L -= bnk) {
+        const int64_t n = kv_shares_of(kv_iterations(L, sh->d, grp), share);
+        if (n == 1) break;  // nor do the sequence's blocks behind it have more
+        slots += n;
+        most = std::max(most, n);
+      }
+    if (slots == 0) return r;
+    if (most <= ZP_PART_MAX && slots * sh->Hkv <= 2048) {
+      r.its = (int32_t)share;
+      r.slots = slots;
+      return r;
+    }
+  }
+}
+// Whether the blocks of `kt` are shared, in place of a kernel estimated at `other` us (0: the whole one, not estimated).
+bool take_kv_shares(const KvShares &shares, const std::vector<CostTile> &kt, int d, int Hkv, int grp, float other) {
+  if (shares.its == 0) return false;
+  const KvCost &w = kv_cost[d == 128];
+  const KvShareCost &c = kv_share_cost[d == 128];
+  const float unit = d == 64 ? 2.f : 1.f, heads = (float)Hkv / 256.f;
+  KvLoad all;
+  int64_t slots = 0;
+  for (const CostTile &k : kt) {
+    const int64_t its = kv_iterations(k.t.q_rows, d, grp), n = kv_shares_of(its, shares.its);
+    all.add(its, d);
+    if (n > 1) slots += n;
+  }
+  if (other == 0.f) other = w.whole + w.whole_it * std::max(w.rate * all.sum * heads, (1.f + w.share) * unit * (float)all.longest);
+  const float time = c.launch + c.it * all.sum * heads + c.slot * (float)slots * heads + c.share * unit * (float)shares.its;
+  return slots > 0 && time < c.margin * other;
+}
+// Puts the shares of the blocks of `kt` (sequence by sequence, blocks in position order) in their place: the first shares of a sequence's blocks, the
+// second ones, and so on. Returns how many shares of shared blocks there are.
+int32_t share_blocks(std::vector<CostTile> &kt, int d, int grp, int64_t share) {
+  std::vector<CostTile> out;
+  out.reserve(kt.size() * 2);
+  int32_t slots = 0;
+  for (size_t a = 0, b; a < kt.size(); a = b) {
+    for (b = a + 1; b < kt.size() && kt[b].t.k_pos0 > 0;) b++;
+    const int32_t slot0 = slots;
+    const int most = (int)kv_shares_of(kv_iterations(kt[a].t.q_rows, d, grp), share);
+    for (int part = 0; part < most; part++) {
+      int32_t slot = slot0;
+      for (size_t i = a; i < b; i++) {
+        const int64_t its = kv_iterations(kt[i].t.q_rows, d, grp);
+        const int n = (int)kv_shares_of(its, share);
+        if (part >= n) break;  // nor have the blocks behind it this many
+        CostTile c = kt[i];
+        if (n > 1) {
+          c.t.part = zp_part_code(part, n, slot);
+          c.cost = (int32_t)(c.cost * (part + 1 < n ? share : its - part * share) / its);
+          slot += n;
+        }
+        out.push_back(c);
+      }
+      slots = std::max(slots, slot);
+    }
+  }
+  kt.swap(out);
+  return slots;
+}
+size_t kv_share_bytes(const KvShares &s, const zp_shape *sh) {
+  return align256((size_t)s.slots * (size_t)sh->Hkv * sizeof(int32_t)) + (size_t)s.slots * (size_t)sh->Hkv * 128 * 2 * (size_t)sh->d * sizeof(float);
+}
+
 
 }  // namespace
 
@@ -506,7 +638,9 @@ size_t zp_workspace_bytes(int which_fn, const zp_shape *sh, const int32_t *cu, i
       if (check_cu(cu, sh) != ZP_OK) return 0;
       const size_t tiles = (size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 0)) +
                            (size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 1));
-      return tile_table_bytes(tiles) + 2 * align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float)) + 512;
+      const KvShares shares = plan_kv_shares(cu, sh, zp_attn_bwd_block_rows(sh->d, 1));
+      return tile_table_bytes(tiles + (size_t)shares.slots) + 2 * align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float)) +
+             kv_share_bytes(shares, sh) + 768;
     }
     default: return 0;
   }
@@ -809,15 +943,31 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
     }
   }
   if (qt.empty() && kt.empty()) return ZP_OK;
-  const size_t tile_bytes = tile_table_bytes(qt.size() + kt.size());
+  const int grp = sh->Hq / sh->Hkv;
+  float kv_time;
+  KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, grp, &kv_time);
+  int32_t slots = 0, share = 0;
+  if (!tiles_inline(qt.size() + kt.size(), launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp))) {
+    const KvShares shares = plan_kv_shares(cu, sh, bnk);
+    if (take_kv_shares(shares, kt, sh->d, sh->Hkv, grp, kv_time)) {
+      kv = KV_WHOLE;
+      share = shares.its;
+      slots = share_blocks(kt, sh->d, grp, share);
+    }
+  }
+  const size_t done = (size_t)slots * (size_t)sh->Hkv, done_at = WS_HEADER + (qt.size() + kt.size()) * sizeof(zp_tile);
+  const size_t tile_bytes = align256(done_at + done * sizeof(int32_t));
   const size_t dvec_bytes = align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float));
-  if ((rc = check_ws(ws, ws_bytes, tile_bytes + 2 * dvec_bytes))) return rc;
+  if ((rc = check_ws(ws, ws_bytes, tile_bytes + 2 * dvec_bytes + done * 128 * 2 * (size_t)sh->d * sizeof(float)))) return rc;
   std::vector<CostTile> all(qt);
   all.insert(all.end(), kt.begin(), kt.end());
   zp_bwd_params p{};
-  if ((rc = place_tiles(all, launch_items(std::max(qt.size(), kt.size()), sh->Hkv, sh->Hq / sh->Hkv), p.inl, ws, (hipStream_t)stream,
-                        &p.dq_tiles, &p.work_dq.counters)))
+  if ((rc = place_tiles(all, launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp), p.inl, ws, (hipStream_t)stream,
+                        &p.dq_tiles, &p.work_dq.counters, done)))
     return rc;
+  p.part_done = (int32_t *)((char *)ws + done_at);
+  p.parts = (float *)((char *)ws + tile_bytes + 2 * dvec_bytes);
+  p.share_its = share;
   p.q = (const __bf16 *)q; p.k = (const __bf16 *)k; p.v = (const __bf16 *)v; p.o = (const __bf16 *)o;
   p.dout = (const __bf16 *)dout;
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride; p.o_stride = o_stride; p.do_stride = do_stride;
@@ -825,7 +975,6 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
-  const KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
   p.kv_pair = kv == KV_PAIR;
   p.kv_split = kv == KV_SPLIT;
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);
@@ -922,7 +1071,8 @@ extern "C" int chunk_attn_partial_bwd(const void *dout, const void *q, const voi
   p.dvec = (float *)((char *)ws + tile_bytes);
   p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
-  const KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv);
+  float kv_time;
+  const KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, sh->Hq / sh->Hkv, &kv_time);
   p.kv_pair = kv == KV_PAIR;
   p.kv_split = kv == KV_SPLIT;
   p.work_dq.dyn_div = dyn_div_of(all, 0, qt.size(), 1);

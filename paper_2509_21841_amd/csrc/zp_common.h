@@ -26,8 +26,17 @@ struct zp_tile {
   int32_t k_len;     // keys in the run
   int32_t k_pos0;    // position of the first key inside the sequence
   int32_t out_row0;  // first output row (packed token, or partial-result row)
-  int32_t unused;    // a record is 32 bytes
+  int32_t part;      // dK/dV: which share of the block's iterations (zp_part_of); 0: all of them. A record is 32 bytes
 };
+
+// dK/dV of a block of keys whose iterations several workgroups share: share `part` of `n`, whose sums lie at `slot` + part among
+// all shares of the launch.
+#define ZP_PART_MAX 63
+struct zp_part {
+  int part, n, slot;
+};
+inline int32_t zp_part_code(int part, int n, int slot) { return part | n << 6 | slot << 12; }
+__device__ __forceinline__ zp_part zp_part_of(int32_t code) { return {code & 63, code >> 6 & 63, code >> 12}; }
 
 // n / d for a wave-uniform n (any 32-bit value) on the scalar unit; m = zp_div_magic(d). The estimate falls short by one at
 // most. (The compiler's division runs on the vector unit: some 30 dependent instructions in front of the tile record.)
@@ -44,7 +53,7 @@ template <class P>
 __device__ __forceinline__ zp_tile zp_load_tile(P p) {
   zp_tile t;
 #define ZP_U(f) t.f = __builtin_amdgcn_readfirstlane(p->f)
-  ZP_U(q_tok0); ZP_U(q_rows); ZP_U(q_pos0); ZP_U(k_tok0); ZP_U(k_len); ZP_U(k_pos0); ZP_U(out_row0);
+  ZP_U(q_tok0); ZP_U(q_rows); ZP_U(q_pos0); ZP_U(k_tok0); ZP_U(k_len); ZP_U(k_pos0); ZP_U(out_row0); ZP_U(part);
 #undef ZP_U
   return t;
 }
@@ -154,6 +163,8 @@ struct zp_bwd_params {
   const float *lse;   // [Hq][T]
   float *dvec;        // [Hq][T] scratch: -D_i = -(dO_i . O_i)
   float *lse2;        // [Hq][T] scratch: -LSE_i / scale
+  float *parts;       // scratch: sums of the shares of shared blocks, [slot][Hkv][dK, dV of 128 rows]
+  int32_t *part_done; // [slot][Hkv], zero before the launch: shares of the block that are done (at its first slot)
   const zp_tile *dq_tiles;
   const zp_tile *kv_tiles;
   int32_t n_dq_tiles, n_kv_tiles, Hq, Hkv, grp, T;
@@ -163,6 +174,7 @@ struct zp_bwd_params {
   int64_t dq_stride, dkv_stride;
   int32_t dq_pair;           // dQ by the kernel for launches that leave much of the chip idle: zp_pair_mode
   int32_t kv_pair;           // dK/dV at head dimension 128 by workgroups of two groups of four waves
+  int32_t share_its;         // iterations of a share of a shared block (its last one takes what is left)
   int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
   int32_t both;              // that and dq_pair in one launch (there: the workgroups of dK/dV, which come first)
   int32_t accumulate;        // ... or, when set, float accumulators of the same shapes that the results are ADDED to

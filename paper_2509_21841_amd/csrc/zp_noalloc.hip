@@ -84,7 +84,7 @@ __global__ __launch_bounds__(256) void plan_fwd_tiles_kernel(PlanArgs a, int32_t
   t.k_len = L;
   t.k_pos0 = 0;
   t.out_row0 = t.q_tok0;
-  t.unused = 0;
+  t.part = 0;
   tiles[slot] = t;
 }
 
