@@ -122,7 +122,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(D == 64 
   if (unit >= p.n_dq_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = ZP_TILE(p.dq_tiles, p.inl, 0, tile_idx);
+  const zp_tile t = ZP_TILE_OF(p.dq_tiles, p.inl, p.n_seq, 0, false, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Ds + NBUF * 64)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
-  const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
+  const zp_tile t = ZP_TILE_OF(p.kv_tiles, p.inl, p.n_seq, p.n_dq_tiles, true, tile_idx);
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(G * BWD_NT) __attribute__((amdgpu_waves_per_eu(2, 2
   const int unit = __builtin_amdgcn_readfirstlane(zp_item_of_block(p.work_kv, (int *)(Vs + 8 * zp_pad16<128>::R16 + G * 4 * 64 * 4)));
   if (unit < 0 || unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
-  const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
+  const zp_tile t = ZP_TILE_OF(p.kv_tiles, p.inl, p.n_seq, p.n_dq_tiles, true, tile_idx);
 
   const int tid = G == 1 ? threadIdx.x : threadIdx.x & 255, lane = tid & 63, w = tid >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);
@@ -1252,7 +1252,7 @@ __device__ __forceinline__ void dkdv_split_rows(const zp_bwd_params &p, int bloc
   const int x = block & 7, y = block >> 3, part = y & 3, unit = (y >> 2) * 8 + x;
   if (unit >= p.n_kv_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
-  const zp_tile t = ZP_TILE(p.kv_tiles, p.inl, p.n_dq_tiles, tile_idx);
+  const zp_tile t = ZP_TILE_OF(p.kv_tiles, p.inl, p.n_seq, p.n_dq_tiles, true, tile_idx);
   if (32 * part >= t.k_len) return;
 
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);

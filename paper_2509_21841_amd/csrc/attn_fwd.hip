@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TURNS || D 
   if (unit >= p.n_tiles * p.Hkv) return;
   const int tile_idx = zp_udiv(unit, p.Hkv, p.m_hkv), g = unit - tile_idx * p.Hkv;
   const int h = g * p.grp + hh;
-  const zp_tile t = ZP_TILE(p.tiles, p.inl, 0, tile_idx);
+  const zp_tile t = ZP_TILE_OF(p.tiles, p.inl, p.n_seq, 0, false, tile_idx);
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int c16 = lane & 15, q4 = 4 * (lane >> 4);

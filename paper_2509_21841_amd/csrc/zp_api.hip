@@ -285,6 +285,22 @@ int place_tiles(const std::vector<CostTile> &tiles, int64_t max_items, zp_inline
   *counters = ws_counters(ws);
   return upload_tiles(tiles, zeros, ws, stream);
 }
+// Whether the sequences of a call on whole ones (their query blocks: `tiles`) go into the launch arguments, where its tile table would have
+// to be uploaded otherwise: zp_seqs_pay, with the call's limit.
+bool seqs_in_arguments(const std::vector<CostTile> &tiles, const zp_shape *sh, float most, zp_inline_tiles &inl, int32_t &n_seq) {
+  int64_t sum = 0;
+  int32_t n = 0;
+  for (const CostTile &c : tiles) {
+    sum += c.cost;
+    n += c.t.q_pos0 == 0;
+  }
+  if (!zp_seqs_fit(n, (int64_t)tiles.size()) || !zp_seqs_pay(sum, sh->Hq, sh->d, most)) return false;
+  n_seq = n;
+  int i = 0, block = 0;
+  for (const CostTile &c : tiles)
+    if (c.t.q_pos0 == 0) block = zp_put_seq(inl, n, i++, block, c.t.k_tok0, c.t.k_len);
+  return true;
+}
 // Which dK/dV kernel a launch takes, by estimates of their times in microseconds; an iteration is a (32-query tile, head). All deal
 // the units (tile, KV head) to the XCDs by turns. An XCD hands its workgroups in order and by turns to four engines of eight
 // CUs; one waits for its engine, whatever room the others have. (Sequences of four key blocks so put every longest chain on
@@ -665,8 +681,9 @@ int varlen_attn_fwd(const void *q, const void *k, const void *v, int64_t q_strid
   if (tiles.empty()) return ZP_OK;
   if ((rc = check_ws(ws, ws_bytes, tile_table_bytes(tiles.size())))) return rc;
   zp_attn_params p{};
-  if ((rc = place_tiles(tiles, launch_items(tiles.size(), sh->Hkv, sh->Hq / sh->Hkv), p.inl, ws, (hipStream_t)stream, &p.tiles,
-                        &p.work.counters)))
+  const int64_t items = launch_items(tiles.size(), sh->Hkv, sh->Hq / sh->Hkv);
+  if ((tiles_inline(tiles.size(), items) || !seqs_in_arguments(tiles, sh, ZP_SEQS_FWD, p.inl, p.n_seq)) &&
+      (rc = place_tiles(tiles, items, p.inl, ws, (hipStream_t)stream, &p.tiles, &p.work.counters)))
     return rc;
   p.q = (const __bf16 *)q; p.k = (const __bf16 *)k; p.v = (const __bf16 *)v;
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride;
@@ -947,7 +964,8 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   float kv_time;
   KvKernel kv = dkdv_kernel_for(kt, sh->d, sh->Hkv, grp, &kv_time);
   int32_t slots = 0, share = 0;
-  if (!tiles_inline(qt.size() + kt.size(), launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp))) {
+  const bool inline_tiles = tiles_inline(qt.size() + kt.size(), launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp));
+  if (!inline_tiles) {
     const KvShares shares = plan_kv_shares(cu, sh, bnk);
     if (take_kv_shares(shares, kt, sh->d, sh->Hkv, grp, kv_time)) {
       kv = KV_WHOLE;
@@ -962,8 +980,9 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   std::vector<CostTile> all(qt);
   all.insert(all.end(), kt.begin(), kt.end());
   zp_bwd_params p{};
-  if ((rc = place_tiles(all, launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp), p.inl, ws, (hipStream_t)stream,
-                        &p.dq_tiles, &p.work_dq.counters, done)))
+  if ((slots || inline_tiles || !seqs_in_arguments(qt, sh, ZP_SEQS_BWD, p.inl, p.n_seq)) &&
+      (rc = place_tiles(all, launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp), p.inl, ws, (hipStream_t)stream, &p.dq_tiles,
+                        &p.work_dq.counters, done)))
     return rc;
   p.part_done = (int32_t *)((char *)ws + done_at);
   p.parts = (float *)((char *)ws + tile_bytes + 2 * dvec_bytes);

@@ -62,13 +62,45 @@ __device__ __forceinline__ zp_tile zp_load_tile(P p) {
 #define ZP_TILE(tiles, inl, first, idx)                                                                            \
   ((tiles) ? zp_load_tile((const __attribute__((address_space(4))) zp_tile *)(uintptr_t)(tiles) + (idx))           \
            : zp_load_tile((inl).t + (first) + (idx)))
+// The same for a launch that may have its sequences in its arguments (n_seq of them): the tile of their idx-th block of query rows, the
+// last block of a sequence first, or of keys, the first block first.
+#define ZP_TILE_OF(tiles, inl, n_seq, first, keys, idx) ((n_seq) ? zp_seq_tile((inl).words, n_seq, idx, keys) : ZP_TILE(tiles, inl, first, idx))
 
 // A launch's tile table where it is short: in the launch arguments themselves (4 KB at most in all), so that nothing is
 // uploaded in front of the launch.
 #define ZP_INLINE_TILES 112
 struct zp_inline_tiles {
-  zp_tile t[ZP_INLINE_TILES];
+  union {
+    zp_tile t[ZP_INLINE_TILES];
+    // or the sequences themselves (zp_put_seqs): three words of each, then, 16 bits each, the sequence of every block
+    uint32_t words[ZP_INLINE_TILES * 8];
+  };
 };
+
+// Whole sequences, longest first, in launch arguments: their blocks of 128 rows are numbered through, and a workgroup works out the record
+// of its own from the sequence's first token, length and first block.
+#define ZP_SEQ_BLOCK 128
+inline bool zp_seqs_fit(int64_t n_seq, int64_t n_blocks) { return n_seq * 12 + (n_blocks + 1) / 2 * 4 <= (int64_t)sizeof(zp_inline_tiles); }
+// Host side: the i-th of n_seq sequences; returns the number of the first block behind it.
+inline int zp_put_seq(zp_inline_tiles &inl, int n_seq, int i, int first, int32_t tok0, int32_t len) {
+  uint32_t *w = inl.words + 3 * i;
+  w[0] = (uint32_t)tok0; w[1] = (uint32_t)len; w[2] = (uint32_t)first;
+  const int end = first + (len + ZP_SEQ_BLOCK - 1) / ZP_SEQ_BLOCK;
+  for (int b = first; b < end; b++) inl.words[3 * n_seq + b / 2] |= (uint32_t)i << 16 * (b & 1);
+  return end;
+}
+__device__ __forceinline__ zp_tile zp_seq_tile(const uint32_t *words, int n_seq, int block, bool keys) {
+  const uint32_t two = __builtin_amdgcn_readfirstlane(words[3 * n_seq + (block >> 1)]);
+  const uint32_t *w = words + 3 * ((block & 1) ? two >> 16 : two & 0xffff);
+  const int tok0 = __builtin_amdgcn_readfirstlane(w[0]), len = __builtin_amdgcn_readfirstlane(w[1]);
+  const int nth = block - __builtin_amdgcn_readfirstlane(w[2]), last = (len - 1) / ZP_SEQ_BLOCK;
+  const int r0 = (keys ? nth : last - nth) * ZP_SEQ_BLOCK, rows = min(ZP_SEQ_BLOCK, len - r0);
+  zp_tile t;
+  t.q_tok0 = tok0 + r0; t.q_rows = keys ? len - r0 : rows; t.q_pos0 = r0;
+  t.k_tok0 = keys ? tok0 + r0 : tok0; t.k_len = keys ? rows : len; t.k_pos0 = keys ? r0 : 0;
+  t.out_row0 = tok0 + r0; t.part = 0;
+  return t;
+}
 
 // How a launch hands its work items to workgroups. The XCDs of a chip do not run equally fast (on the cards measured
 // the same four finish an equal share 4-8 % later than the other four), and the hardware deals workgroups to them
@@ -150,6 +182,7 @@ struct zp_attn_params {
   int64_t lse_stride;
   int32_t update;    // partial kernel only: merge the result into the running (o, lse) found at the output rows
   int32_t pair;      // by the kernel for launches that leave much of the chip idle: zp_pair_mode
+  int32_t n_seq;     // sequences in `inl`; 0: tiles
   int32_t turns;     // head dimension 128: by the kernel of three workgroups per CU
   zp_work_split work;  // which workgroups take their item by number and which claim one (set by the launcher)
   zp_inline_tiles inl; // the tile table if `tiles` is null
@@ -174,6 +207,7 @@ struct zp_bwd_params {
   int64_t dq_stride, dkv_stride;
   int32_t dq_pair;           // dQ by the kernel for launches that leave much of the chip idle: zp_pair_mode
   int32_t kv_pair;           // dK/dV at head dimension 128 by workgroups of two groups of four waves
+  int32_t n_seq;             // sequences in `inl`; 0: tiles
   int32_t share_its;         // iterations of a share of a shared block (its last one takes what is left)
   int32_t kv_split;          // dK/dV by the kernel for launches that leave most of the chip idle
   int32_t both;              // that and dq_pair in one launch (there: the workgroups of dK/dV, which come first)

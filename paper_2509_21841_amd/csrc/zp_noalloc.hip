@@ -106,6 +106,17 @@ void fill_inline(const PlanArgs &a, zp_inline_tiles &inl) {
   }
 }
 
+// The sequences themselves in the same order (zp_seqs_fit has looked at their number).
+void fill_seqs(const PlanArgs &a, int n_seq, zp_inline_tiles &inl) {
+  int order[sizeof(zp_inline_tiles) / 12], n = 0;
+  auto len = [&](int s) { return a.cu[s + 1] - a.cu[s]; };
+  for (int s = 0; s < a.S; s++)
+    if (!((a.skip_bits[s >> 5] >> (s & 31)) & 1u) && len(s) > 0) order[n++] = s;
+  std::sort(order, order + n, [&](int x, int y) { return len(x) != len(y) ? len(x) > len(y) : x < y; });
+  int block = 0;
+  for (int i = 0; i < n; i++) block = zp_put_seq(inl, n_seq, i, block, a.cu[order[i]], len(order[i]));
+}
+
 std::mutex g_mu;
 constexpr int MAX_DEVICES = 64;
 void *g_scratch_ptr[MAX_DEVICES] = {};
@@ -156,12 +167,14 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
   PlanArgs a;
   a.S = sh->S;
   for (size_t i = 0; i < sizeof(a.skip_bits) / sizeof(a.skip_bits[0]); i++) a.skip_bits[i] = 0;
+  int n_seq = 0;
   int64_t n_tiles = 0, sum = 0, longest = 0;  // query blocks; key tiles they see, the last block of the longest sequence
   for (int s = 0; s <= sh->S; s++) a.cu[s] = cu[s];
   for (int s = 0; s < sh->S; s++) {
     if (seq_skip && seq_skip[s]) { a.skip_bits[s >> 5] |= 1u << (s & 31); continue; }
     const int64_t nb = ((int64_t)cu[s + 1] - cu[s] + BM - 1) / BM, last = ((int64_t)cu[s + 1] - cu[s] + 63) / 64;
     n_tiles += nb;
+    n_seq += nb > 0;
     sum += nb > 0 ? nb * (nb - 1) + last : 0;  // 2, 4, ... and the last block
     longest = std::max(longest, last);
   }
@@ -175,6 +188,9 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
   if (n_tiles <= ZP_INLINE_TILES && items < ZP_CLAIM_MIN_ITEMS) {
     // a short table goes into the launch arguments (and the shared array is not touched)
     fill_inline(a, p.inl);
+  } else if (zp_seqs_fit(n_seq, n_tiles) && zp_seqs_pay(sum, sh->Hq, sh->d, ZP_SEQS_NOALLOC)) {
+    fill_seqs(a, n_seq, p.inl);
+    p.n_seq = n_seq;
   } else {
     void *tiles = nullptr;
     const int rc = scratch_for_current_device(&tiles);

@@ -6,6 +6,22 @@
 
 #include "zp_common.h"
 
+// Whether a launch's sequences go into its arguments (zp_put_seq) where they fit and the table of its tiles does not, or would be
+// written to device memory for the sake of the work counters only. That saves the launch in front that writes the table (3.5 us where
+// it is uploaded, 4 to 13 where it is worked out on the device), and gives up claimed items, which launches of 200 us and more
+// lose more by. `sum`: key tiles of 64 that the query blocks of 128 see; the limits are on key tiles x heads x head dimension. Of 60
+// random batches (3000 to 96000 tokens, 4/2 to 64/8 heads) the 23 forwards under the limit and over 112 tiles or 1024 items are 2 to 7 % faster,
+// the 26 without allocation up to 10 % (one 0.3 % slower), the 11 backwards up to 5 %; the next ones
+// above the limits lose up to 4 %. us, table / arguments:
+//    d   heads   tokens            in arguments                                           not
+//    64   8/2    26191             forward 97.6 / 94.0, without allocation 98.9 / 94.0
+//    64   4/4    90755             forward 137.0 / 133.3, without allocation 147.0 / 133.3
+//   128   4/2     8895             backward 147.4 / 143.6
+//    64  32/32   12599             forward 116.9 / 113.0                                  backward 353.6 / 367.4
+//    64  32/8    39879                                                                    forward 427.1 / 437.2
+constexpr float ZP_SEQS_FWD = 5.3e6f, ZP_SEQS_NOALLOC = 1e7f, ZP_SEQS_BWD = 1.5e6f;
+inline bool zp_seqs_pay(int64_t sum, int Hq, int d, float most) { return (float)sum * (float)Hq * (float)d <= most; }
+
 // key tiles of 64 that a tile's last row sees
 inline int zp_key_tiles(const zp_tile &t) {
   int64_t n = (int64_t)t.q_pos0 + t.q_rows - t.k_pos0;
@@ -124,7 +140,7 @@ inline zp_pair_mode zp_take_pairs(zp_inline_tiles &inl, int &n, int behind, int 
 inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
   static const zp_pair_cost whole[2] = {{2.95f, 0.769f, 1.74f, 0.0023f, 0.345f}, {2.20f, 1.074f, 3.19f, 0.0032f, 0.536f}};
   static const zp_pair_cost pair[2] = {{2.03f, 0.471f, 1.95f, 0.0022f, 1.f}, {2.63f, 0.660f, 1.64f, 0.0027f, 1.f}};
-  if (p.tiles == nullptr) p.pair = zp_take_pairs(p.inl, p.n_tiles, 0, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.93f, 0.83f);
+  if (p.tiles == nullptr && p.n_seq == 0) p.pair = zp_take_pairs(p.inl, p.n_tiles, 0, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.93f, 0.83f);
 }
 
 // The dQ kernels, whose tiles have the dK/dV tiles behind them. Constants fitted to 3446 launches (2/1 to 64/8 heads; equal,
@@ -140,7 +156,7 @@ inline void zp_plan_fwd_pair(zp_attn_params &p, int d) {
 inline void zp_plan_dq_pair(zp_bwd_params &p, int d) {
   static const zp_pair_cost whole[2] = {{-0.273f, 0.864f, 4.78f, 0.00305f, 0.584f}, {1.36f, 1.29f, 4.29f, 0.00569f, 0.592f}};
   static const zp_pair_cost pair[2] = {{2.18f, 0.691f, 1.42f, 0.0015f, 1.f}, {3.62f, 1.02f, 1.34f, 0.00266f, 1.f}};
-  if (p.dq_tiles == nullptr)
+  if (p.dq_tiles == nullptr && p.n_seq == 0)
     p.dq_pair = zp_take_pairs(p.inl, p.n_dq_tiles, p.n_kv_tiles, p.Hkv, p.grp, whole[d == 128], pair[d == 128], 0.91f, 0.76f);
 }
 
