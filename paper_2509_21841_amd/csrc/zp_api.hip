@@ -453,7 +453,9 @@ int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7)
 // and 14 at 128, so it is a fifth or a quarter of a CU's load long, and the shares are taken where the estimate of their launch is
 // 7 % (d = 128: 5 %) below that of the other kernels. The estimate is fitted to 340 launches of up to 4 ms (of 4/4 to 64/8 heads, 5000 to 131072
 // tokens; 5 % off in the mean). Of 85 random backwards whose longest chain is a third of a CU's load and more 42 take them: 1.06 times
-// faster in the mean of all at d = 64 and 1.023 at 128; none of the 42 is slower. Backward, us, before / with shares:
+// faster in the mean of all at d = 64 and 1.023 at 128; none of the 42 is slower. Sequences of one length fill the chip more evenly, and
+// the estimate is up to 14 % low for them (28 of 1000 tokens, 8/1 heads, d = 128: backward 341 us, 349 with shares): they are left to
+// the other kernels up to 550 us. Backward, us, before / with shares:
 //    d   heads   tokens                        taken             not taken
 //    64  16/4    24001, longest  3802          482 / 448
 //    64   8/2    39059, longest 39059         5256 / 4660
@@ -477,8 +479,9 @@ inline int64_t kv_iterations(int64_t rows, int d, int grp) { return (d == 64 ? (
 inline int64_t kv_shares_of(int64_t its, int64_t share) { return std::max<int64_t>(1, (its + share * 5 / 8) / share); }
 struct KvLoad {
   float sum = 0.f;  // iterations of 32 queries, fixed ones of a workgroup among them
-  int64_t longest = 0, blocks = 0;
+  int64_t its = 0, longest = 0, blocks = 0;
   void add(int64_t its, int d) {
+    this->its += its;
     sum += (d == 64 ? 2.f : 1.f) * (float)its + kv_cost[d == 128].whole_wg;
     longest = std::max(longest, its);
     blocks++;
@@ -530,7 +533,9 @@ bool take_kv_shares(const KvShares &shares, const std::vector<CostTile> &kt, int
   }
   if (other == 0.f) other = w.whole + w.whole_it * std::max(w.rate * all.sum * heads, (1.f + w.share) * unit * (float)all.longest);
   const float time = c.launch + c.it * all.sum * heads + c.slot * (float)slots * heads + c.share * unit * (float)shares.its;
-  return slots > 0 && time < c.margin * other;
+  // (equal sequences: the longest block has less than twice the iterations of the average one)
+  const bool uneven = all.longest * all.blocks > 2 * all.its;
+  return slots > 0 && (uneven || other > 550.f) && time < c.margin * other;
 }
 // Puts the shares of the blocks of `kt` (sequence by sequence, blocks in position order) in their place: the first shares of a sequence's blocks, the
 // second ones, and so on. Returns how many shares of shared blocks there are.
