@@ -44,19 +44,42 @@ __device__ __forceinline__ void seq_blocks(const PlanArgs &a, int s, int &L, int
 // (equal lengths: lower index first), inside a sequence the last query block first. Tile (s, b) therefore sits behind
 // all blocks of the sequences ordered before s and behind the later blocks of s -- a closed form, so no sort and no
 // atomics, and the table is the same on every call.
-__global__ __launch_bounds__(256) void plan_fwd_tiles_kernel(PlanArgs a, int32_t *counters, zp_tile *tiles) {
-  __shared__ int first_tile[ZP_NOALLOC_MAX_SEQS + 1];
+static_assert(ZP_NOALLOC_MAX_SEQS % 4 == 0, "lengths are read four at a time");
+constexpr int PLAN_NT = 256;
+__global__ __launch_bounds__(PLAN_NT) void plan_fwd_tiles_kernel(PlanArgs a, int32_t *counters, zp_tile *tiles) {
+  constexpr int PER = (ZP_NOALLOC_MAX_SEQS + PLAN_NT - 1) / PLAN_NT;
+  __shared__ int __align__(16) length[ZP_NOALLOC_MAX_SEQS], first_tile[ZP_NOALLOC_MAX_SEQS + 1], wave_sum[PLAN_NT / 64];
   // the attention kernel's work counters start from zero on every call
   if (blockIdx.x == 0 && threadIdx.x < 8) counters[threadIdx.x * ZP_COUNTER_STRIDE] = 0;
-  for (int s = threadIdx.x; s < a.S; s += blockDim.x) {
-    int L, nb;
-    seq_blocks(a, s, L, nb);
-    first_tile[s + 1] = nb;
+  // A running sum over the sequences, PER of them per thread: over a wave's lanes, then over the waves. The lengths go to LDS, from where
+  // every tile compares four with its own at a time. Bound: that loop's chain (read from the launch arguments one sequence after the other,
+  // and with the sum by one thread, 768 sequences kept the attention kernel waiting for some 90 us: 57928 tokens, 32/8 heads, d = 128,
+  // the whole call 427 us, now 376; with the table from the host 335).
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, s0 = threadIdx.x * PER;
+  int blocks[PER], mine = 0;
+#pragma unroll
+  for (int j = 0; j < PER; j++) {
+    int L = 0;
+    blocks[j] = 0;
+    if (s0 + j < a.S) seq_blocks(a, s0 + j, L, blocks[j]);
+    if (s0 + j < ZP_NOALLOC_MAX_SEQS) length[s0 + j] = blocks[j] ? L : 0;
+    mine += blocks[j];
   }
+  int sum = mine;
+#pragma unroll
+  for (int by = 1; by < 64; by *= 2) {
+    const int before = __shfl_up(sum, by);
+    if (lane >= by) sum += before;
+  }
+  if (lane == 63) wave_sum[w] = sum;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    first_tile[0] = 0;
-    for (int s = 0; s < a.S; s++) first_tile[s + 1] += first_tile[s];
+  sum -= mine;
+  for (int i = 0; i < w; i++) sum += wave_sum[i];
+  if (threadIdx.x == 0) first_tile[0] = 0;
+#pragma unroll
+  for (int j = 0; j < PER; j++) {
+    sum += blocks[j];
+    if (s0 + j < a.S) first_tile[s0 + j + 1] = sum;
   }
   __syncthreads();
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -71,10 +94,13 @@ __global__ __launch_bounds__(256) void plan_fwd_tiles_kernel(PlanArgs a, int32_t
   int L, nb;
   seq_blocks(a, s, L, nb);
   int slot = nb - 1 - b;
-  for (int s2 = 0; s2 < a.S; s2++) {
-    int L2, nb2;
-    seq_blocks(a, s2, L2, nb2);
-    if (L2 > L || (L2 == L && s2 < s)) slot += nb2;
+#pragma unroll 8  // (reads of several steps in flight)
+  for (int s4 = 0; s4 < a.S; s4 += 4) {
+    const int4 l4 = *(const int4 *)(length + s4);
+    const int l[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      if (l[j] > L || (l[j] == L && s4 + j < s)) slot += (l[j] + BM - 1) / BM;
   }
   zp_tile t;
   t.q_tok0 = a.cu[s] + b * BM;
@@ -197,7 +223,7 @@ extern "C" int varlen_attn_fwd_noalloc(const void *q, const void *k, const void 
     if (rc) return rc;
     // Every slot the attention kernel reads is rewritten by the planning kernel of the same call, on the same stream,
     // and so are the work counters in front of the table: nothing of an earlier call survives into this one.
-    hipLaunchKernelGGL(plan_fwd_tiles_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, (hipStream_t)stream, a,
+    hipLaunchKernelGGL(plan_fwd_tiles_kernel, dim3((unsigned)((n_tiles + PLAN_NT - 1) / PLAN_NT)), dim3(PLAN_NT), 0, (hipStream_t)stream, a,
                        (int32_t *)tiles, (zp_tile *)((char *)tiles + ZP_COUNTER_BYTES));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return zp_report_hip_error((int)e, "plan_fwd_tiles launch");
