@@ -972,7 +972,10 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   const bool inline_tiles = tiles_inline(qt.size() + kt.size(), launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp));
   if (!inline_tiles) {
     const KvShares shares = plan_kv_shares(cu, sh, bnk);
-    if (take_kv_shares(shares, kt, sh->d, sh->Hkv, grp, kv_time)) {
+    // (not in a workspace that was sized for another batch, which may have needed none for sums)
+    const size_t need = tile_table_bytes(qt.size() + kt.size() + (size_t)shares.slots) + 2 * align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float)) +
+                        kv_share_bytes(shares, sh);
+    if (ws_bytes >= need && take_kv_shares(shares, kt, sh->d, sh->Hkv, grp, kv_time)) {
       kv = KV_WHOLE;
       share = shares.its;
       slots = share_blocks(kt, sh->d, grp, share);
