@@ -194,7 +194,8 @@ def _with_scratch(call, ws, device, tag: str, stream, need, ask: bool = False) -
     """call(ws) -> return code, with the caller's scratch or with the stream's cached one. The library looks at the size before it
     enqueues anything, so need() -- a call of its own; a forward of 1218 tokens, 4 heads,
     d = 64, one after the other: 11.3 us with it and 9.6 without -- is asked only where there is no cached scratch or it turns
-    out too small, or first (`ask`) by calls that do with less than they would use."""
+    out too small, or first (`ask`) by calls that do with less than they would use: which kernels those take must not follow from
+    what an earlier call has left."""
     if ws is not None:
         return _check(call(ws))
     if ask:
@@ -252,6 +253,14 @@ def varlen_attn_fwd_noalloc(q, k, v, cu_seqlens, o, lse, scale=0.0, stream=None,
     return o, lse
 
 
+def _bwd_may_share(T: int, S: int, Hq: int, Hkv: int) -> bool:
+    """False: the tile table of a backward is in its launch arguments (at most 112 tiles, half of them dQ's, and under 1024 work
+    items), and nothing of such a launch is shared among workgroups, so that its workspace holds no sums. S sequences of T tokens are
+    at most T // 128 + S blocks; their units (block, KV head) are padded to one per XCD."""
+    blocks = T // 128 + S
+    return blocks > 56 or (blocks * Hkv + 7) // 8 * 8 * (Hq // Hkv) >= 1024
+
+
 def varlen_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, dq=None, dk=None, dv=None, scale=0.0, ws=None, stream=None,
                     seq_skip=None):
     """-> (dq [T,Hq,d], dk [T,Hkv,d], dv [T,Hkv,d]) bf16. Rows of sequences flagged in seq_skip are not written."""
@@ -264,15 +273,12 @@ def varlen_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, dq=None, dk=None, dv=None
     dv = torch.empty_like(v) if dv is None else dv
     assert _tok_stride(dk) == _tok_stride(dv)
     skip, skp = _skip_ptr(seq_skip, cu)
-    # (the tables of smaller batches are in the launch arguments, and nothing of theirs is shared among workgroups)
-    blocks = T // 128 + len(cu) - 1
-    ask = blocks > 56 or blocks * Hq >= 1024
     _with_scratch(lambda w: lib().varlen_attn_bwd(dout.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                                   lse.data_ptr(), _tok_stride(dout), _tok_stride(q), _tok_stride(k),
                                                   _tok_stride(v), _tok_stride(o), _cu_ptr(cu), skp, dq.data_ptr(),
                                                   dk.data_ptr(), dv.data_ptr(), _tok_stride(dq), _tok_stride(dk),
                                                   ctypes.byref(sh), w.data_ptr(), w.numel(), _stream_ptr(stream)),
-                  ws, q.device, "bwd", stream, lambda: workspace_bytes(FN_BWD, sh, cu), ask)
+                  ws, q.device, "bwd", stream, lambda: workspace_bytes(FN_BWD, sh, cu), _bwd_may_share(T, len(cu) - 1, Hq, Hkv))
     return dq, dk, dv
 
 

@@ -1,0 +1,56 @@
+"""Scratch memory of the backward: a call that would share key blocks among workgroups needs room for their sums, and does without
+sharing in a smaller workspace. The binding's cached scratch must therefore never decide: it asks for the size wherever there may be sums."""
+import random
+
+import pytest
+import torch
+
+from paper_2509_21841_amd import binding as B
+from paper_2509_21841_amd import synth
+
+DEV = "cuda:0"
+HEADS = [(4, 1), (8, 2), (8, 8), (16, 1), (32, 1), (32, 8), (48, 1), (64, 1), (64, 2), (64, 8), (18, 6), (33, 11)]
+
+
+def scratch(lengths, Hq, Hkv, d):
+    return B.workspace_bytes(B.FN_BWD, B.make_shape(sum(lengths), len(lengths), Hq, Hkv, d), synth.cu_seqlens(lengths))
+
+
+def without_sums(lengths, Hq):
+    """A tile table, two values per row and head, and a few kilobytes of counters and padding."""
+    return 64 * sum(-(-n // 128) for n in lengths) + 2 * 4 * Hq * sum(lengths) + 8192
+
+
+def test_the_binding_asks_wherever_there_may_be_sums():
+    """One sequence of 1900 tokens, 64/1 heads, is 15 blocks, whose units are padded to 16 before they count as 1024 work items."""
+    rng = random.Random(3)
+    batches = [([1900], 64, 1, 128), ([1900], 64, 2, 64), ([2500], 48, 1, 128), ([3900], 32, 1, 64)]
+    for _ in range(2000):
+        lengths = [int(20 * 300 ** rng.random()) for _ in range(rng.choice([1, 1, 2, 3, 8, 40]))]
+        batches.append((lengths, *rng.choice(HEADS), rng.choice([64, 128])))
+    some = 0
+    for lengths, Hq, Hkv, d in batches:
+        if scratch(lengths, Hq, Hkv, d) > without_sums(lengths, Hq):
+            assert B._bwd_may_share(sum(lengths), len(lengths), Hq, Hkv), (lengths, Hq, Hkv, d)
+            some += 1
+    assert some > 100
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("length,Hq,Hkv,d", [(1900, 64, 1, 128), (2500, 48, 1, 128), (1900, 64, 2, 64)])
+def test_the_same_bits_after_a_smaller_call(length, Hq, Hkv, d):
+    def backward(n):
+        q, k, v, do = synth.make_qkv(n, Hq, Hkv, d, 231, DEV, with_dout=True)
+        cu = synth.cu_seqlens([n])
+        o, lse = B.varlen_attn_fwd(q, k, v, cu)
+        return B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
+
+    for key in [key for key in B._ws_cache if key[1] == "bwd"]:
+        del B._ws_cache[key]
+    B.workspace(2 << 20, torch.device(DEV), "bwd")   # room for everything but sums
+    backward(300)
+    after = backward(length)
+    for key in [key for key in B._ws_cache if key[1] == "bwd"]:
+        del B._ws_cache[key]
+    for a, b in zip(after, backward(length)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
