@@ -198,16 +198,19 @@ int64_t count_blocks(const int32_t *cu, int S, int bm) {
   for (int s = 0; s < S; s++) n += ((int64_t)cu[s + 1] - cu[s] + bm - 1) / bm;
   return n;
 }
+std::vector<int> longest_first(const int32_t *cu, int S) {
+  std::vector<int> order(S);
+  for (int s = 0; s < S; s++) order[s] = s;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
+  return order;
+}
 // Tiles of whole sequences: sequence by sequence, longest sequence first, and inside a sequence the last query block
 // (the most expensive one) first. The heaviest tiles of the batch still start first and the cheap ones fill the tail,
 // as a plain sort by cost would have it, but the query blocks of one (sequence, KV head) now run next to each other on
 // one XCD and find the sequence's K/V rows in its L2 instead of re-reading them from HBM -- with many short sequences
 // and one KV head per query head that re-reading, not the arithmetic, bounded the kernels.
 void plan_whole(const int32_t *cu, int S, int bm, std::vector<CostTile> &out, const uint8_t *skip = nullptr) {
-  std::vector<int> seq_order(S);
-  for (int s = 0; s < S; s++) seq_order[s] = s;
-  std::stable_sort(seq_order.begin(), seq_order.end(), [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
-  for (int s : seq_order) {
+  for (int s : longest_first(cu, S)) {
     if (skip && skip[s]) continue;
     const int32_t L = cu[s + 1] - cu[s];
     for (int32_t r0 = ((L - 1) / bm) * bm; L > 0 && r0 >= 0; r0 -= bm) {
@@ -220,6 +223,28 @@ void plan_whole(const int32_t *cu, int S, int bm, std::vector<CostTile> &out, co
       c.t.k_pos0 = 0;
       c.t.out_row0 = cu[s] + r0;
       c.cost = tile_cost(c.t);
+      out.push_back(c);
+    }
+  }
+}
+// Key-block tiles go sequence by sequence, longest sequence first, blocks in position order (descending
+// cost inside the sequence): workgroups that run side by side then walk the same Q/dO rows a few tiles
+// apart and find them in L2, and the cheap blocks of the short sequences still come last.
+void plan_whole_keys(const int32_t *cu, int S, int bnk, std::vector<CostTile> &out, const uint8_t *skip = nullptr) {
+  out.reserve((size_t)count_blocks(cu, S, bnk));
+  for (int s : longest_first(cu, S)) {
+    if (skip && skip[s]) continue;
+    const int32_t L = cu[s + 1] - cu[s];
+    for (int32_t j0 = 0; j0 < L; j0 += bnk) {
+      CostTile c{};
+      c.t.k_tok0 = cu[s] + j0;
+      c.t.k_len = std::min(bnk, L - j0);
+      c.t.k_pos0 = j0;
+      c.t.q_tok0 = cu[s] + j0;  // first query that sees the block's first key
+      c.t.q_rows = L - j0;
+      c.t.q_pos0 = j0;
+      c.t.out_row0 = cu[s] + j0;
+      c.cost = (c.t.q_rows + 63) / 64;
       out.push_back(c);
     }
   }
@@ -463,10 +488,6 @@ int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7)
 //   128   4/4    34415, longest  7173          434 / 373
 //   128   4/2    11503, longest  3643                            160 / 168
 //    64   4/2    26485, longest  3837                            192 / 202
-struct KvShares {
-  int32_t its = 0;    // iterations of a share, 0: no block is shared
-  int64_t slots = 0;  // shares of shared blocks (times KV heads: sums in scratch memory)
-};
 struct KvShareCost {
   float of_load, least;            // a share: of a CU's load, and at least so many iterations of 32 queries
   float launch, it, slot, share;   // per launch; per CU: iteration, share; per iteration of a share
@@ -487,17 +508,16 @@ struct KvLoad {
     blocks++;
   }
 };
-// How long a share would be and how many there would be at most: from all sequences, flagged ones too, as the workspace's size is.
-KvShares plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk) {
-  KvShares r;
+// How many iterations a share of a batch's blocks would have; 0: no block would be shared.
+int32_t plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk) {
   const int grp = sh->Hq / sh->Hkv, c = sh->d == 128;
   const float unit = sh->d == 64 ? 2.f : 1.f;
   KvLoad all;
   for (int s = 0; s < sh->S; s++)
     for (int64_t L = (int64_t)cu[s + 1] - cu[s]; L > 0; L -= bnk) all.add(kv_iterations(L, sh->d, grp), sh->d);
-  if (tiles_inline(2 * (size_t)all.blocks, launch_items((size_t)all.blocks, sh->Hkv, grp))) return r;
+  if (tiles_inline(2 * (size_t)all.blocks, launch_items((size_t)all.blocks, sh->Hkv, grp))) return 0;
   const float load = kv_cost[c].rate * all.sum * (float)sh->Hkv / 256.f;
-  if (unit * (float)all.longest < 0.5f * load) return r;
+  if (unit * (float)all.longest < 0.5f * load) return 0;
   int64_t share = (int64_t)(std::max(kv_share_cost[c].of_load * load, kv_share_cost[c].least) / unit);
   // no more than 2048 sums (d = 128: 256 MB)
   for (;; share += share / 8) {
@@ -510,29 +530,26 @@ KvShares plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk) {
         slots += n;
         most = std::max(most, n);
       }
-    if (slots == 0) return r;
-    if (most <= ZP_PART_MAX && slots * sh->Hkv <= 2048) {
-      r.its = (int32_t)share;
-      r.slots = slots;
-      return r;
-    }
+    if (slots == 0) return 0;
+    if (most <= ZP_PART_MAX && slots * sh->Hkv <= 2048) return (int32_t)share;
   }
 }
-// Whether the blocks of `kt` are shared, in place of a kernel estimated at `other` us (0: the whole one, not estimated).
-bool take_kv_shares(const KvShares &shares, const std::vector<CostTile> &kt, int d, int Hkv, int grp, float other) {
-  if (shares.its == 0) return false;
+// Whether the blocks of `kt` are taken in shares of `share` iterations, in place of a kernel estimated at `other` us (0: the whole one,
+// not estimated).
+bool take_kv_shares(int32_t share, const std::vector<CostTile> &kt, int d, int Hkv, int grp, float other) {
+  if (share == 0) return false;
   const KvCost &w = kv_cost[d == 128];
   const KvShareCost &c = kv_share_cost[d == 128];
   const float unit = d == 64 ? 2.f : 1.f, heads = (float)Hkv / 256.f;
   KvLoad all;
   int64_t slots = 0;
   for (const CostTile &k : kt) {
-    const int64_t its = kv_iterations(k.t.q_rows, d, grp), n = kv_shares_of(its, shares.its);
+    const int64_t its = kv_iterations(k.t.q_rows, d, grp), n = kv_shares_of(its, share);
     all.add(its, d);
     if (n > 1) slots += n;
   }
   if (other == 0.f) other = w.whole + w.whole_it * std::max(w.rate * all.sum * heads, (1.f + w.share) * unit * (float)all.longest);
-  const float time = c.launch + c.it * all.sum * heads + c.slot * (float)slots * heads + c.share * unit * (float)shares.its;
+  const float time = c.launch + c.it * all.sum * heads + c.slot * (float)slots * heads + c.share * unit * (float)share;
   // (equal sequences: the longest block has less than twice the iterations of the average one)
   const bool uneven = all.longest * all.blocks > 2 * all.its;
   return slots > 0 && (uneven || other > 550.f) && time < c.margin * other;
@@ -567,10 +584,33 @@ int32_t share_blocks(std::vector<CostTile> &kt, int d, int grp, int64_t share) {
   kt.swap(out);
   return slots;
 }
-size_t kv_share_bytes(const KvShares &s, const zp_shape *sh) {
-  return align256((size_t)s.slots * (size_t)sh->Hkv * sizeof(int32_t)) + (size_t)s.slots * (size_t)sh->Hkv * 128 * 2 * (size_t)sh->d * sizeof(float);
+// What a backward keeps in its workspace: counters and tile table, of every sum a count of the shares that are done (zeros behind the table), D and
+// -LSE / scale of the rows, sums of shares. `sums`: shares of shared blocks x KV heads.
+struct BwdScratch {
+  size_t done_at, dvec_at, lse2_at, parts_at, bytes;
+};
+BwdScratch bwd_scratch(size_t tiles, size_t sums, const zp_shape *sh) {
+  const size_t rows = align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float));
+  BwdScratch w;
+  w.done_at = WS_HEADER + tiles * sizeof(zp_tile);
+  w.dvec_at = align256(w.done_at + sums * sizeof(int32_t));
+  w.lse2_at = w.dvec_at + rows;
+  w.parts_at = w.lse2_at + rows;
+  w.bytes = w.parts_at + sums * 128 * 2 * (size_t)sh->d * sizeof(float);
+  return w;
 }
-
+// Iterations of a share as a call on the whole batch takes them, which the size of its workspace is asked for; 0: no shares. (Calls with
+// flagged sequences take them only where that one does, and of the same length: the size is asked without flags, and room that
+// happens to be there must not decide.) kt: the batch's dK/dV tiles, where there are shares.
+int32_t batch_kv_share(const int32_t *cu, const zp_shape *sh, int bnk, std::vector<CostTile> &kt) {
+  const int32_t share = plan_kv_shares(cu, sh, bnk);
+  if (share == 0) return 0;
+  const int grp = sh->Hq / sh->Hkv;
+  plan_whole_keys(cu, sh->S, bnk, kt);
+  float time;
+  (void)dkdv_kernel_for(kt, sh->d, sh->Hkv, grp, &time);
+  return take_kv_shares(share, kt, sh->d, sh->Hkv, grp, time) ? share : 0;
+}
 
 }  // namespace
 
@@ -657,11 +697,12 @@ size_t zp_workspace_bytes(int which_fn, const zp_shape *sh, const int32_t *cu, i
     }
     case ZP_FN_BWD: {
       if (check_cu(cu, sh) != ZP_OK) return 0;
-      const size_t tiles = (size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 0)) +
-                           (size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 1));
-      const KvShares shares = plan_kv_shares(cu, sh, zp_attn_bwd_block_rows(sh->d, 1));
-      return tile_table_bytes(tiles + (size_t)shares.slots) + 2 * align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float)) +
-             kv_share_bytes(shares, sh) + 768;
+      const int bnk = zp_attn_bwd_block_rows(sh->d, 1);
+      std::vector<CostTile> kt;
+      const int32_t share = batch_kv_share(cu, sh, bnk, kt);
+      const size_t slots = share ? (size_t)share_blocks(kt, sh->d, sh->Hq / sh->Hkv, share) : 0;
+      const size_t blocks = share ? kt.size() : (size_t)count_blocks(cu, sh->S, bnk);
+      return bwd_scratch((size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 0)) + blocks, slots * (size_t)sh->Hkv, sh).bytes + 512;
     }
     default: return 0;
   }
@@ -940,30 +981,7 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   std::vector<CostTile> qt, kt;
   qt.reserve((size_t)count_blocks(cu, sh->S, bmq));
   plan_whole(cu, sh->S, bmq, qt, seq_skip);
-  kt.reserve((size_t)count_blocks(cu, sh->S, bnk));
-  // Key-block tiles go sequence by sequence, longest sequence first, blocks in position order (descending
-  // cost inside the sequence): workgroups that run side by side then walk the same Q/dO rows a few tiles
-  // apart and find them in L2, and the cheap blocks of the short sequences still come last.
-  std::vector<int> seq_order(sh->S);
-  for (int s = 0; s < sh->S; s++) seq_order[s] = s;
-  std::stable_sort(seq_order.begin(), seq_order.end(),
-                   [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
-  for (int s : seq_order) {
-    if (seq_skip && seq_skip[s]) continue;
-    const int32_t L = cu[s + 1] - cu[s];
-    for (int32_t j0 = 0; j0 < L; j0 += bnk) {
-      CostTile c{};
-      c.t.k_tok0 = cu[s] + j0;
-      c.t.k_len = std::min(bnk, L - j0);
-      c.t.k_pos0 = j0;
-      c.t.q_tok0 = cu[s] + j0;  // first query that sees the block's first key
-      c.t.q_rows = L - j0;
-      c.t.q_pos0 = j0;
-      c.t.out_row0 = cu[s] + j0;
-      c.cost = (c.t.q_rows + 63) / 64;
-      kt.push_back(c);
-    }
-  }
+  plan_whole_keys(cu, sh->S, bnk, kt, seq_skip);
   if (qt.empty() && kt.empty()) return ZP_OK;
   const int grp = sh->Hq / sh->Hkv;
   float kv_time;
@@ -971,36 +989,38 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   int32_t slots = 0, share = 0;
   const bool inline_tiles = tiles_inline(qt.size() + kt.size(), launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp));
   if (!inline_tiles) {
-    const KvShares shares = plan_kv_shares(cu, sh, bnk);
-    // (not in a workspace that was sized for another batch, which may have needed none for sums)
-    const size_t need = tile_table_bytes(qt.size() + kt.size() + (size_t)shares.slots) + 2 * align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float)) +
-                        kv_share_bytes(shares, sh);
-    if (ws_bytes >= need && take_kv_shares(shares, kt, sh->d, sh->Hkv, grp, kv_time)) {
+    std::vector<CostTile> cut;
+    share = seq_skip ? batch_kv_share(cu, sh, bnk, cut) : plan_kv_shares(cu, sh, bnk);
+    if (take_kv_shares(share, kt, sh->d, sh->Hkv, grp, kv_time)) {
+      cut = kt;
+      slots = share_blocks(cut, sh->d, grp, share);
+      // (not in a workspace that was sized for another batch, which may have needed none for sums)
+      if (ws_bytes < bwd_scratch(qt.size() + cut.size(), (size_t)slots * (size_t)sh->Hkv, sh).bytes) slots = 0;
+    }
+    if (slots) {
       kv = KV_WHOLE;
-      share = shares.its;
-      slots = share_blocks(kt, sh->d, grp, share);
+      kt.swap(cut);
     }
   }
-  const size_t done = (size_t)slots * (size_t)sh->Hkv, done_at = WS_HEADER + (qt.size() + kt.size()) * sizeof(zp_tile);
-  const size_t tile_bytes = align256(done_at + done * sizeof(int32_t));
-  const size_t dvec_bytes = align256((size_t)sh->Hq * (size_t)sh->T * sizeof(float));
-  if ((rc = check_ws(ws, ws_bytes, tile_bytes + 2 * dvec_bytes + done * 128 * 2 * (size_t)sh->d * sizeof(float)))) return rc;
+  const size_t sums = (size_t)slots * (size_t)sh->Hkv;
+  const BwdScratch at = bwd_scratch(qt.size() + kt.size(), sums, sh);
+  if ((rc = check_ws(ws, ws_bytes, at.bytes))) return rc;
   std::vector<CostTile> all(qt);
   all.insert(all.end(), kt.begin(), kt.end());
   zp_bwd_params p{};
   if ((slots || inline_tiles || !seqs_in_arguments(qt, sh, ZP_SEQS_BWD, p.inl, p.n_seq)) &&
       (rc = place_tiles(all, launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp), p.inl, ws, (hipStream_t)stream, &p.dq_tiles,
-                        &p.work_dq.counters, done)))
+                        &p.work_dq.counters, sums)))
     return rc;
-  p.part_done = (int32_t *)((char *)ws + done_at);
-  p.parts = (float *)((char *)ws + tile_bytes + 2 * dvec_bytes);
-  p.share_its = share;
+  p.part_done = (int32_t *)((char *)ws + at.done_at);
+  p.parts = (float *)((char *)ws + at.parts_at);
+  p.share_its = slots ? share : 0;
   p.q = (const __bf16 *)q; p.k = (const __bf16 *)k; p.v = (const __bf16 *)v; p.o = (const __bf16 *)o;
   p.dout = (const __bf16 *)dout;
   p.q_stride = q_stride; p.k_stride = k_stride; p.v_stride = v_stride; p.o_stride = o_stride; p.do_stride = do_stride;
   p.lse = lse;
-  p.dvec = (float *)((char *)ws + tile_bytes);
-  p.lse2 = (float *)((char *)ws + tile_bytes + dvec_bytes);
+  p.dvec = (float *)((char *)ws + at.dvec_at);
+  p.lse2 = (float *)((char *)ws + at.lse2_at);
   p.kv_tiles = p.dq_tiles ? p.dq_tiles + qt.size() : nullptr;
   p.kv_pair = kv == KV_PAIR;
   p.kv_split = kv == KV_SPLIT;

@@ -36,6 +36,48 @@ def test_the_binding_asks_wherever_there_may_be_sums():
     assert some > 100
 
 
+# Launches that are not shared (an even load, or a chain that other kernels go through faster) and launches that are
+WHOLE = [([1, 0, 3000, 900, 2500, 120, 700, 780], 32, 8, 128), ([1000] * 28, 8, 1, 128), ([7400], 8, 2, 128), ([544] * 12, 16, 1, 128),
+         ([2000, 7000, 6000, 1000] * 6, 8, 8, 64), ([1660] * 5, 32, 8, 64)]
+SHARED = [([3001] + [1] * 40, 8, 2, 128), ([1900], 64, 1, 128), ([24001 - 11048, 11048], 8, 2, 128), ([3802, 900, 3100, 40, 2500, 3300], 16, 4, 64)]
+
+
+def test_room_for_sums_only_where_there_are_any():
+    for batch in WHOLE:
+        assert without_sums(batch[0], batch[1]) - 8192 <= scratch(*batch) <= without_sums(batch[0], batch[1]), batch
+    for lengths, Hq, Hkv, d in SHARED:   # (dK and dV of 128 keys each in float, of two shares and more)
+        assert scratch(lengths, Hq, Hkv, d) > without_sums(lengths, Hq) + 2 * 2 * 128 * 4 * d * Hkv
+
+
+def last_label(call):
+    B.profile_enable(True)
+    call()
+    torch.cuda.synchronize()
+    name = B.profile_records()[-1][0]
+    B.profile_enable(False)
+    return name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch", WHOLE + SHARED)
+def test_exactly_the_stated_size_decides(batch):
+    """Shares where the size has room for them and only there, in a workspace of that size as in a larger one; with flagged sequences the
+    same bits in both."""
+    lengths, Hq, Hkv, d = batch
+    q, k, v, do = synth.make_qkv(sum(lengths), Hq, Hkv, d, 233, DEV, with_dout=True)
+    cu = synth.cu_seqlens(lengths)
+    o, lse = B.varlen_attn_fwd(q, k, v, cu)
+    ws = torch.empty(scratch(*batch), dtype=torch.uint8, device=DEV)
+    large = torch.empty(ws.numel() + (256 << 20), dtype=torch.uint8, device=DEV)
+    shares = {w: last_label(lambda: B.varlen_attn_bwd(do, q, k, v, o, lse, cu, ws=w)) == "attn_bwd_dkdv_shares" for w in (ws, large)}
+    assert set(shares.values()) == {batch in SHARED}
+    first = [1] + [0] * (len(lengths) - 1)
+    for skip in (first, [1 - x for x in first]):
+        runs = [B.varlen_attn_bwd(do, q, k, v, o, lse, cu, *map(torch.zeros_like, (q, k, v)), ws=w, seq_skip=skip) for w in (ws, large)]
+        for a, b in zip(*runs):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("length,Hq,Hkv,d", [(1900, 64, 1, 128), (2500, 48, 1, 128), (1900, 64, 2, 64)])
 def test_the_same_bits_after_a_smaller_call(length, Hq, Hkv, d):
