@@ -478,9 +478,12 @@ int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7)
 // and 14 at 128, so it is a fifth or a quarter of a CU's load long, and the shares are taken where the estimate of their launch is
 // 7 % (d = 128: 5 %) below that of the other kernels. The estimate is fitted to 340 launches of up to 4 ms (of 4/4 to 64/8 heads, 5000 to 131072
 // tokens; 5 % off in the mean). Of 85 random backwards whose longest chain is a third of a CU's load and more 42 take them: 1.06 times
-// faster in the mean of all at d = 64 and 1.023 at 128; none of the 42 is slower. Sequences of one length fill the chip more evenly, and
-// the estimate is up to 14 % low for them (28 of 1000 tokens, 8/1 heads, d = 128: backward 341 us, 349 with shares): they are left to
-// the other kernels up to 550 us. Backward, us, before / with shares:
+// faster in the mean of all at d = 64 and 1.023 at 128; none of the 42 is slower. Batches whose blocks have much the same number of iterations
+// (single sequences and equal ones: the longest block less than twice the average) are not in that fit, and the estimate favours shares
+// there: up to 550 us they are taken where it is 20 % below. Of 262 such backwards 169 take them, in 0.85 of the time in the mean, two of
+// them 2 and 4 % slower; with 15 % below it were 216, seven of them slower, by 12 % at most. (Beyond 550 us the margins of the others
+// hold: of 48 such backwards 36 take shares, all of them faster.) Tables in the launch arguments are left out, since the counts of shares that are done travel
+// with an uploaded table. Backward, us, before / with shares:
 //    d   heads   tokens                        taken             not taken
 //    64  16/4    24001, longest  3802          482 / 448
 //    64   8/2    39059, longest 39059         5256 / 4660
@@ -488,6 +491,10 @@ int64_t launch_items(size_t n, int Hkv, int grp) { return ((int64_t)n * Hkv + 7)
 //   128   4/4    34415, longest  7173          434 / 373
 //   128   4/2    11503, longest  3643                            160 / 168
 //    64   4/2    26485, longest  3837                            192 / 202
+//    64  64/2     1900                             429 / 164
+//   128   8/1    17 of 1000                        295 / 213
+//   128   8/1    28 of 1000                                        341 / 345
+//   128   8/2     9000                             671 / 644
 struct KvShareCost {
   float of_load, least;            // a share: of a CU's load, and at least so many iterations of 32 queries
   float launch, it, slot, share;   // per launch; per CU: iteration, share; per iteration of a share
@@ -550,9 +557,8 @@ bool take_kv_shares(int32_t share, const std::vector<CostTile> &kt, int d, int H
   }
   if (other == 0.f) other = w.whole + w.whole_it * std::max(w.rate * all.sum * heads, (1.f + w.share) * unit * (float)all.longest);
   const float time = c.launch + c.it * all.sum * heads + c.slot * (float)slots * heads + c.share * unit * (float)share;
-  // (equal sequences: the longest block has less than twice the iterations of the average one)
-  const bool uneven = all.longest * all.blocks > 2 * all.its;
-  return slots > 0 && (uneven || other > 550.f) && time < c.margin * other;
+  const bool even = all.longest * all.blocks <= 2 * all.its;
+  return slots > 0 && time < (even && other <= 550.f ? 0.8f : c.margin) * other;
 }
 // Puts the shares of the blocks of `kt` (sequence by sequence, blocks in position order) in their place: the first shares of a sequence's blocks, the
 // second ones, and so on. Returns how many shares of shared blocks there are.

@@ -39,7 +39,8 @@ def test_the_binding_asks_wherever_there_may_be_sums():
 # Launches that are not shared (an even load, or a chain that other kernels go through faster) and launches that are
 WHOLE = [([1, 0, 3000, 900, 2500, 120, 700, 780], 32, 8, 128), ([1000] * 28, 8, 1, 128), ([7400], 8, 2, 128), ([544] * 12, 16, 1, 128),
          ([2000, 7000, 6000, 1000] * 6, 8, 8, 64), ([1660] * 5, 32, 8, 64)]
-SHARED = [([3001] + [1] * 40, 8, 2, 128), ([1900], 64, 1, 128), ([24001 - 11048, 11048], 8, 2, 128), ([3802, 900, 3100, 40, 2500, 3300], 16, 4, 64)]
+# (also one sequence by itself, and equal ones)
+SHARED = [([1000] * 17, 8, 1, 128), ([9000], 8, 2, 128), ([3000] * 3, 16, 2, 128), ([8000], 16, 2, 64), ([1900], 64, 2, 64), ([3001] + [1] * 40, 8, 2, 128), ([1900], 64, 1, 128), ([24001 - 11048, 11048], 8, 2, 128), ([3802, 900, 3100, 40, 2500, 3300], 16, 4, 64)]
 
 
 def test_room_for_sums_only_where_there_are_any():
