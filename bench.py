@@ -216,7 +216,7 @@ def kernel_flops(job, label: str) -> float:
     per_gemm_all = 2 * d * Hq * job.pairs_total
     per_gemm_long = 2 * d * Hq * job.pairs_long
     return {"attn_fwd": 2 * (per_gemm_all - per_gemm_long), "attn_fwd_partial": 2 * per_gemm_long,
-            "attn_bwd_dq": 3 * per_gemm_all, "attn_bwd_dkdv": 4 * per_gemm_all}.get(label, 0.0)
+            "attn_bwd_dq": 3 * per_gemm_all, "attn_bwd_dkdv": 4 * per_gemm_all, "attn_bwd_both": 7 * per_gemm_all}.get(label, 0.0)
 
 
 def kernel_of(label: str) -> str:
@@ -318,7 +318,7 @@ def measure(job, steps: int, warmup: int):
 
 def fwd_bwd_rates(job, kern):
     fwd_ms = sum(kern[k]["ms_per_step"] for k in ("attn_fwd", "attn_fwd_partial", "lse_merge") if k in kern)
-    bwd_ms = sum(kern[k]["ms_per_step"] for k in ("attn_bwd_dq", "attn_bwd_dkdv") if k in kern)
+    bwd_ms = sum(kern[k]["ms_per_step"] for k in ("attn_bwd_dq", "attn_bwd_dkdv", "attn_bwd_both") if k in kern)
     return (job.flops_fwd / (fwd_ms * 1e-3) / 1e12 if fwd_ms else None,
             job.flops_bwd / (bwd_ms * 1e-3) / 1e12 if bwd_ms else None)
 

@@ -25,7 +25,8 @@ int zp_mfma_probe(float *out, int32_t iters, int32_t random_operands, void *stre
 
 /* Measurement aid: per-kernel durations from hipEvents recorded on the launch stream.
  * zp_profile_enable(1) clears the records and starts recording every kernel the library launches (one
- * record per launch, in launch order); zp_profile_enable(0) stops and clears. zp_profile_get() waits for
+ * record per launch, in launch order; the small launch for the row terms of a short backward is part of the record of the one
+ * behind it); the calls launch what they would without it; zp_profile_enable(0) stops and clears. zp_profile_get() waits for
  * record i to finish and returns its kernel label (truncated to name_cap-1 chars) and duration in ms.
  * Event creation is a host-side allocation: keep it off in production loops. */
 int zp_profile_enable(int on);

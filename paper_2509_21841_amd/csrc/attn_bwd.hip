@@ -470,10 +470,10 @@ __device__ __forceinline__ void dq_pair_rows(const zp_bwd_params &p, int block, 
   else if (row < t.q_rows) add_acc_rows<D / 2>((float *)p.dq + at + c16 * p.dq_stride + q4, dq_acc, p.scale);
 }
 
-template <int D, bool PRE>
+template <int D>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_pair_kernel(zp_bwd_params p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  dq_pair_rows<D, PRE>(p, blockIdx.x, smem);
+  dq_pair_rows<D, false>(p, blockIdx.x, smem);
 }
 
 // -D and -LSE / scale of the rows of the dQ kernel's tiles, bit for bit what it would leave: 64 rows of a head per workgroup.
@@ -1405,7 +1405,6 @@ constexpr size_t split_lds() {
 
 extern "C" void zp_prof_begin(const char *name, hipStream_t stream);
 extern "C" void zp_prof_end(hipStream_t stream);
-extern "C" int zp_prof_enabled(void);
 
 extern "C" int zp_attn_bwd_block_rows(int d, int which) { (void)d; (void)which; return 128; }
 
@@ -1421,31 +1420,25 @@ extern "C" int zp_launch_attn_bwd(const zp_bwd_params *p_in, int d, hipStream_t 
   const int dq_grid = zp_plan_work_split(p->work_dq, c, ((dq_units + 7) / 8) * 8 * p->grp);
   const int kv_grid = zp_plan_work_split(p->work_kv, c ? c + ZP_COUNTER_BYTES / 4 : nullptr, ((kv_units + 7) / 8) * 8);
   const dim3 pair_grid(((dq_units + 7) / 8) * 8 * p->grp * (p->dq_pair == ZP_PAIR_HALVES ? 2 : 1)), split_grid(((kv_units + 7) / 8) * 8 * 4);
-  // (the profile tells dQ and dK/dV apart; the results are the same bits)
-  const bool both = p->both && dq_units > 0 && kv_units > 0, merged = both && !zp_prof_enabled();
-#define ZP_BOTH_ROWS()                                                                                             \
-  do {                                                                                                             \
-    if (d == 128) hipLaunchKernelGGL(attn_bwd_rows_kernel<128>, pair_grid, dim3(256), 0, stream, *p);              \
-    else hipLaunchKernelGGL(attn_bwd_rows_kernel<64>, pair_grid, dim3(256), 0, stream, *p);                        \
-  } while (0)
-  if (merged) {
-    ZP_BOTH_ROWS();
+  if (p->both && dq_units > 0 && kv_units > 0) {
     const dim3 grid(split_grid.x + pair_grid.x);
     p->both = (int)split_grid.x;
-    const size_t lds128 = std::max(dq_pair_lds<128>(), split_lds<128>()), lds64 = std::max(dq_pair_lds<64>(), split_lds<64>());
-    if (d == 128) hipLaunchKernelGGL(attn_bwd_both_kernel<128>, grid, dim3(512), lds128, stream, *p);
-    else hipLaunchKernelGGL(attn_bwd_both_kernel<64>, grid, dim3(512), lds64, stream, *p);
+    zp_prof_begin("attn_bwd_both", stream);
+    if (d == 128) {
+      hipLaunchKernelGGL(attn_bwd_rows_kernel<128>, pair_grid, dim3(256), 0, stream, *p);
+      hipLaunchKernelGGL(attn_bwd_both_kernel<128>, grid, dim3(512), std::max(dq_pair_lds<128>(), split_lds<128>()), stream, *p);
+    } else {
+      hipLaunchKernelGGL(attn_bwd_rows_kernel<64>, pair_grid, dim3(256), 0, stream, *p);
+      hipLaunchKernelGGL(attn_bwd_both_kernel<64>, grid, dim3(512), std::max(dq_pair_lds<64>(), split_lds<64>()), stream, *p);
+    }
+    zp_prof_end(stream);
     return (int)hipGetLastError();
   }
   if (dq_units > 0) {
     zp_prof_begin(p->dq_pair ? "attn_bwd_dq_pair" : "attn_bwd_dq", stream);
     if (p->dq_pair) {
-      if (both) ZP_BOTH_ROWS();
-#define ZP_DQ_PAIR(D, PRE) hipLaunchKernelGGL((attn_bwd_dq_pair_kernel<D, PRE>), pair_grid, dim3(512), dq_pair_lds<D>(), stream, *p)
-      if (d == 128) { if (both) ZP_DQ_PAIR(128, true); else ZP_DQ_PAIR(128, false); }
-      else if (both) ZP_DQ_PAIR(64, true);
-      else ZP_DQ_PAIR(64, false);
-#undef ZP_DQ_PAIR
+      if (d == 128) hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<128>, pair_grid, dim3(512), dq_pair_lds<128>(), stream, *p);
+      else hipLaunchKernelGGL(attn_bwd_dq_pair_kernel<64>, pair_grid, dim3(512), dq_pair_lds<64>(), stream, *p);
     } else if (d == 128) hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 128 * 2 + 16, stream, *p);
     else hipLaunchKernelGGL((attn_bwd_dq_kernel<64>), dim3(dq_grid), dim3(BWD_NT), 4 * 64 * 64 * 2 + 16, stream, *p);
     zp_prof_end(stream);

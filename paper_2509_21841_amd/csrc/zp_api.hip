@@ -137,8 +137,9 @@ int upload_send(Upload &u, void *dev, size_t bytes, hipStream_t stream) {
 }
 
 // ---- per-kernel timing (measurement aid) -----------------------------------------------------------
-// When enabled, every kernel launch is bracketed by a pair of hipEvents on the launch stream; the bench reads
-// the elapsed times after it has synchronised. Off by default: no events are created or recorded.
+// When enabled, every kernel launch (the row terms of a short backward with the launch behind them) is bracketed by a pair of hipEvents on
+// the launch stream; the bench reads the elapsed times after it has synchronised. Which kernels a call takes does not depend on it. Off by
+// default: no events are created or recorded.
 struct ProfRec {
   const char *name;
   hipEvent_t a, b;
@@ -634,10 +635,6 @@ void zp_prof_end(hipStream_t stream) {
   std::lock_guard<std::mutex> lk(g_prof_mu);
   if (!g_prof_on || g_prof.empty()) return;
   (void)hipEventRecord(g_prof.back().b, stream);
-}
-int zp_prof_enabled(void) {
-  std::lock_guard<std::mutex> lk(g_prof_mu);
-  return g_prof_on;
 }
 int zp_profile_enable(int on) {
   std::lock_guard<std::mutex> lk(g_prof_mu);

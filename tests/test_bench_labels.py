@@ -6,7 +6,8 @@ from types import SimpleNamespace
 import bench
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-KERNELS = {"attn_fwd": 2 * 300, "attn_fwd_partial": 2 * 700, "attn_bwd_dq": 3 * 1000, "attn_bwd_dkdv": 4 * 1000}   # products x pairs
+KERNELS = {"attn_fwd": 2 * 300, "attn_fwd_partial": 2 * 700, "attn_bwd_dq": 3 * 1000, "attn_bwd_dkdv": 4 * 1000,
+           "attn_bwd_both": 7 * 1000}   # products x pairs
 
 
 def source_labels():
@@ -20,7 +21,7 @@ def source_labels():
 
 def test_every_attention_label_is_credited():
     labels = source_labels()
-    assert {"attn_fwd", "attn_fwd_pair", "attn_bwd_dq_pair", "attn_bwd_dkdv_split", "attn_bwd_dkdv_pair"} <= labels
+    assert {"attn_fwd", "attn_fwd_pair", "attn_bwd_dq_pair", "attn_bwd_dkdv_split", "attn_bwd_dkdv_pair", "attn_bwd_both"} <= labels
     job = SimpleNamespace(w=dict(d=64, Hq=2), pairs_total=1000, pairs_long=700)
     for label in labels:
         kernel = bench.kernel_of(label)

@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2509_21841_amd import binding as B
 from paper_2509_21841_amd import synth
-from util import Checks, assert_close, widen
+from util import Checks, assert_close, kernels_of, widen
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -66,7 +66,7 @@ def dkdv_labels(*call):
     B.profile_enable(True)
     B.varlen_attn_bwd(*call)
     torch.cuda.synchronize()
-    labels = {name for name, _ in B.profile_records() if name.startswith("attn_bwd_dkdv")}
+    labels = {name for name in kernels_of(B.profile_records()) if name.startswith("attn_bwd_dkdv")}
     B.profile_enable(False)
     return labels
 

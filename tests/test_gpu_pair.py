@@ -8,6 +8,7 @@ import torch
 
 from paper_2509_21841_amd import binding as B
 from paper_2509_21841_amd import synth
+from util import kernels_of
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -25,7 +26,7 @@ def labels(call):
     B.profile_enable(True)
     out = call()
     torch.cuda.synchronize()
-    names = [name for name, _ in B.profile_records()]
+    names = kernels_of(B.profile_records())
     B.profile_enable(False)
     return out, names
 

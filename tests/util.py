@@ -99,3 +99,9 @@ def assert_lse_close(name, got, ref):
     if (~inf).any():
         err = float(np.abs(got[~inf] - ref[~inf]).max())
         assert err <= LSE_MAXABS, f"{name}: LSE max-abs {err:.3e}"
+
+
+def kernels_of(records):
+    """Labels of profile records; the launch that does dQ and dK/dV counts as the two kernels whose work it is."""
+    both = {"attn_bwd_both": ["attn_bwd_dq_pair", "attn_bwd_dkdv_split"]}
+    return [kernel for name, _ in records for kernel in both.get(name, [name])]
