@@ -220,8 +220,8 @@ def kernel_flops(job, label: str) -> float:
 
 
 def kernel_of(label: str) -> str:
-    """The launch a profile label stands for: the kernels for launches that leave part of the chip idle do the same work."""
-    for suffix in ("_pair", "_split", "_shares"):
+    """The launch a profile label stands for: the kernels for launches that fill or leave idle more of the chip do the same work."""
+    for suffix in ("_pair", "_split", "_shares", "_turns"):
         label = label.removesuffix(suffix)
     return label
 

@@ -790,7 +790,7 @@ extern "C" int zp_launch_attn_fwd(const zp_attn_params *p, int d, int partial, i
   }
 #define ZP_FWD_LAUNCH(D, TURNS, PART)                                                                   \
   do {                                                                                                  \
-    zp_prof_begin(PART ? "attn_fwd_partial" : "attn_fwd", stream);                                      \
+    zp_prof_begin(PART ? (TURNS ? "attn_fwd_partial_turns" : "attn_fwd_partial") : TURNS ? "attn_fwd_turns" : "attn_fwd", stream); \
     hipLaunchKernelGGL((attn_fwd_kernel<D, TURNS, PART>), dim3(grid), dim3(256), (fwd_lds<D, TURNS>()), stream, *p); \
     zp_prof_end(stream);                                                                                \
   } while (0)

@@ -21,7 +21,8 @@ def source_labels():
 
 def test_every_attention_label_is_credited():
     labels = source_labels()
-    assert {"attn_fwd", "attn_fwd_pair", "attn_bwd_dq_pair", "attn_bwd_dkdv_split", "attn_bwd_dkdv_pair", "attn_bwd_both"} <= labels
+    assert {"attn_fwd", "attn_fwd_turns", "attn_fwd_partial_turns", "attn_fwd_pair", "attn_bwd_dq_pair", "attn_bwd_dkdv_split", "attn_bwd_dkdv_pair",
+            "attn_bwd_both"} <= labels
     job = SimpleNamespace(w=dict(d=64, Hq=2), pairs_total=1000, pairs_long=700)
     for label in labels:
         kernel = bench.kernel_of(label)

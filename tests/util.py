@@ -102,6 +102,7 @@ def assert_lse_close(name, got, ref):
 
 
 def kernels_of(records):
-    """Labels of profile records; the launch that does dQ and dK/dV counts as the two kernels whose work it is."""
+    """Labels of profile records; the launch that does dQ and dK/dV counts as the two kernels whose work it is, the two forms of the forward
+    of full launches as one."""
     both = {"attn_bwd_both": ["attn_bwd_dq_pair", "attn_bwd_dkdv_split"]}
-    return [kernel for name, _ in records for kernel in both.get(name, [name])]
+    return [kernel for name, _ in records for kernel in both.get(name, [name.removesuffix("_turns")])]
