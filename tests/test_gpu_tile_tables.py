@@ -12,6 +12,8 @@ from paper_2509_21841_amd import synth
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+# behind a batch: more sequences than the launch arguments hold (298), so that its tables are in memory
+MANY = [1] * 300
 
 
 def bits(t):
@@ -51,8 +53,8 @@ def test_short_tables_equal_long_ones(tiles, Hq, Hkv, d):
 
 def test_uploaded_tables_in_a_captured_graph():
     """Replays of a graph that uploads tables, between other calls that use the staging buffers."""
-    lengths = [130] * 64
-    Hq, Hkv, d, T = 8, 2, 128, 130 * 64
+    lengths = [130] * 64 + MANY
+    Hq, Hkv, d, T = 8, 2, 128, sum(lengths)
     cu = synth.cu_seqlens(lengths)
     q, k, v, do = synth.make_qkv(T, Hq, Hkv, d, 91, DEV, with_dout=True)
     o, lse = B.varlen_attn_fwd(q, k, v, cu)
@@ -86,7 +88,7 @@ def test_uploaded_tables_in_a_captured_graph():
 
 
 def test_noalloc_with_a_long_table_replays_from_a_captured_graph():
-    lengths = [900, 129, 0, 1, 2049] * 8
+    lengths = [900, 129, 0, 1, 2049] * 8 + MANY
     Hq, Hkv, d, T = 8, 2, 128, sum(lengths)
     cu = synth.cu_seqlens(lengths)
     q, k, v = synth.make_qkv(T, Hq, Hkv, d, 95, DEV)
@@ -138,7 +140,7 @@ def test_captures_need_no_staging_buffers():
     Hq, Hkv, d = 8, 2, 128
     side = torch.cuda.Stream()
     graphs = []
-    for seed, lengths in ((97, [130] * 64), (98, [8192, 40, 1, 3000])):
+    for seed, lengths in ((97, [130] * 64 + MANY), (98, [8192, 40, 1, 3000])):
         x, outs, call = uploading_calls(lengths, Hq, Hkv, d, seed)
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
@@ -166,7 +168,7 @@ def test_a_graph_outlives_the_scratch_of_its_stream():
     that stream's cached scratch) and new tensors: replays give the right results and write to nobody else's memory."""
     Hq, Hkv, d = 8, 2, 128
     side = torch.cuda.Stream()
-    small, large = [130] * 64, [700] * 64
+    small, large = [130] * 64 + MANY, [700] * 64 + MANY
 
     def call(x, outs, cu):
         q, k, v, do = x
@@ -216,7 +218,7 @@ def test_scratch_of_a_given_stream_is_allocated_for_it():
     """stream= other than the current one: the cached scratch belongs to that stream for the allocator too, so that one which
     is outgrown is handed out again only behind the calls that still use it."""
     side = torch.cuda.Stream()
-    lengths = [130] * 64
+    lengths = [130] * 64 + MANY
     q, k, v = synth.make_qkv(sum(lengths), 4, 2, 64, 111, DEV)
     want = B.varlen_attn_fwd(q, k, v, synth.cu_seqlens(lengths))
     side.wait_stream(torch.cuda.current_stream())

@@ -48,6 +48,26 @@ def test_noalloc_at_its_limits():
     _run_both([int(x) for x in rng.integers(0, 300, size=B.NOALLOC_MAX_SEQS)], 2, 1, 64, 2106)
 
 
+def ragged(n, most, seed):
+    """n sequences, empty ones and equal ones among them, and flags of a quarter of them (a whole run and the last one too). What is left
+    does not fit the launch arguments (298 sequences): the table is worked out on the device."""
+    rng = np.random.default_rng(seed)
+    lengths = [int(x) for x in rng.integers(0, most, size=n)]
+    lengths[10:20], lengths[30:40] = [0] * 10, [lengths[30]] * 10
+    skip = (rng.random(n) < 0.25).astype(np.uint8)
+    skip[50:70], skip[-1] = 1, 1
+    assert sum(x > 0 and not f for x, f in zip(lengths, skip)) > 298
+    return lengths, skip
+
+
+@pytest.mark.parametrize("n", [513, 514, 515, 516, B.NOALLOC_MAX_SEQS])   # lengths are compared four at a time
+def test_noalloc_of_flagged_sequences_with_a_table(n):
+    lengths, skip = ragged(n, 300, 2107)
+    _run_both(lengths, 4, 2, 64, 2107, skip=skip)
+    lengths, skip = ragged(n, 150, 2108)
+    _run_both(lengths, 4, 2, 128, 2108, skip=skip)
+
+
 def test_noalloc_limits_are_errors():
     dev = "cuda:0"
     lengths = [1] * (B.NOALLOC_MAX_SEQS + 1)
@@ -63,23 +83,30 @@ def test_noalloc_forward_replays_from_a_captured_graph():
     """What the entry point is for: one call recorded into a HIP graph (nothing in it allocates, uploads or clears
     memory with a memset node), replayed on new contents of the same buffers, each replay against an eager
     varlen_attn_fwd of the same inputs, with the program's own eager work and synchronisations in between."""
+    _replays([900, 129, 0, 1, 2049, 64, 300], None)
+
+
+def test_noalloc_with_flags_and_a_table_replays_from_a_captured_graph():
+    _replays(*ragged(500, 200, 2202))
+
+
+def _replays(lengths, skip):
     dev = "cuda:0"
-    lengths = [900, 129, 0, 1, 2049, 64, 300]
     Hq, Hkv, d = 8, 2, 128
     T = int(sum(lengths))
     cu = np.asarray(synth.cu_seqlens(lengths))
     q, k, v = synth.make_qkv(T, Hq, Hkv, d, 2201, dev)
     o = torch.full_like(q, 7.0)
     lse = torch.full((Hq, T), 7.0, dtype=torch.float32, device=dev)
-    B.varlen_attn_fwd_noalloc(q, k, v, cu, o, lse)      # first call on the device: looks up the array's address
+    B.varlen_attn_fwd_noalloc(q, k, v, cu, o, lse, seq_skip=skip)      # first call on the device: looks up the array's address
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        B.varlen_attn_fwd_noalloc(q, k, v, cu, o, lse)  # on the capture stream (torch's current stream here)
+        B.varlen_attn_fwd_noalloc(q, k, v, cu, o, lse, seq_skip=skip)  # on the capture stream (torch's current stream here)
     for rep in range(3):
         q2, k2, v2 = synth.make_qkv(T, Hq, Hkv, d, 2300 + rep, dev)
         q.copy_(q2); k.copy_(k2); v.copy_(v2)
-        o_ref, lse_ref = B.varlen_attn_fwd(q, k, v, cu)
+        o_ref, lse_ref = B.varlen_attn_fwd(q, k, v, cu, o=torch.full_like(q, 7.0), lse=torch.full_like(lse, 7.0), seq_skip=skip)
         o.fill_(7.0); lse.fill_(7.0)
         torch.cuda.synchronize()
         graph.replay()
