@@ -258,7 +258,7 @@ def _bwd_may_share(T: int, S: int, Hq: int, Hkv: int) -> bool:
     items), and nothing of such a launch is shared among workgroups, so that its workspace holds no sums. S sequences of T tokens are
     at most T // 128 + S blocks; their units (block, KV head) are padded to one per XCD."""
     blocks = T // 128 + S
-    return blocks > 56 or (blocks * Hkv + 7) // 8 * 8 * (Hq // Hkv) >= 1024
+    return blocks > 56 or (blocks * Hkv + 7) // 8 * 8 * Hq >= 1024 * Hkv
 
 
 def varlen_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, dq=None, dk=None, dv=None, scale=0.0, ws=None, stream=None,

@@ -34,6 +34,7 @@ def test_the_binding_asks_wherever_there_may_be_sums():
             assert B._bwd_may_share(sum(lengths), len(lengths), Hq, Hkv), (lengths, Hq, Hkv, d)
             some += 1
     assert some > 100
+    assert B._bwd_may_share(100, 1, 4, 0)   # (not this function's to refuse: the library does)
 
 
 # Launches that are not shared (an even load, or a chain that other kernels go through faster) and launches that are
