@@ -111,9 +111,11 @@ int varlen_attn_fwd_noalloc(const void *q, const void *k, const void *v, int64_t
  * P_ij = exp(scale q_i.k_j - LSE_i), D_i = dO_i.O_i, dS_ij = P_ij (dO_i.v_j - D_i):
  *   dQ_i = scale sum_{j<=i} dS_ij k_j ;  dK_j = scale sum_{h in group} sum_{i>=j} dS_ij q_i ;
  *   dV_j = sum_{h in group} sum_{i>=j} P_ij dO_i.
- * Deterministic (no atomics): one kernel owns key/value rows, one owns query rows. O, LSE and dQ of a sequence are the same
+ * Deterministic: no result is added to by atomics, and the same call gives the same bits. O, LSE and dQ of a sequence are the same
  * bits whatever else is in the batch; dK and dV up to the order of their float32 sums, which follows how full the batch
- * makes the launch.
+ * makes the launch. Where the longest blocks of keys are shared among workgroups, their partial sums lie in `ws` and
+ * zp_workspace_bytes has room for them (256 MB at most); a smaller `ws` that holds the rest does, without shares, and so in
+ * another order of the sums.
  * seq_skip_host: NULL, or host [S] flags; the dQ/dK/dV rows of a flagged sequence are not written (the caller runs
  * it as chunk pairs with chunk_attn_partial_bwd instead).
  * dq/dk/dv token strides are dq_stride (= for dQ) and dkv_stride (for dK and dV). */

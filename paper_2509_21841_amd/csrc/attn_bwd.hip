@@ -1,4 +1,6 @@
-// Backward of causal varlen attention, deterministic and atomics-free: two kernels.
+// Backward of causal varlen attention, two kernels. Deterministic: no result is added to by atomics. (Shares of a block of keys count
+// themselves done by an atomic, which decides who adds their sums up, not in which order: dkdv_join_parts.) Short launches do both
+// kernels' work in one, behind a small one for the row terms (attn_bwd_both_kernel).
 //   attn_bwd_dq   owns a block of query rows, walks the visible key tiles:  S^T = K Q^T, dP^T = V dO^T,
 //                 dS^T = P^T o (dP^T - D), dQ^T += K^T dS^T.  Also computes D_i = dO_i . O_i and stores it.
 //   attn_bwd_dkdv owns a block of key rows, walks the query tiles at or after it and the query heads of its
@@ -1386,7 +1388,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
 // workgroups do what attn_bwd_dkdv_split_kernel does, the others what attn_bwd_dq_pair_kernel does. Neither then needs anything of the
 // other's: attn_bwd_rows_kernel works out -D and -LSE / scale in front. (Worked out in the dK/dV workgroups instead, tile by tile, they
 // took more of a CU's 64 bytes per cycle from L2 than Q and dO leave: an iteration 2.6 us instead of 1.2.) Bound: the longer of the two
-// longest chains, and 3 us for the rows. Backward of 1218 tokens in eight sequences, GQA 4/2, d = 128: 23.8 -> 16.6 us, passes one
+// longest chains, and 4 us for the rows. Backward of 1218 tokens in eight sequences, GQA 4/2, d = 128: 23.8 -> 16.6 us, passes one
 // after the other; zp_take_both has more figures and the rule.
 template <int D>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_both_kernel(zp_bwd_params p) {

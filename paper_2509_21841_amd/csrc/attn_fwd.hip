@@ -5,7 +5,7 @@
 // query (column l%16) and 4 keys per 16-key block (rows 4(l/16) + c). A wave owns two 16-query sub-blocks, so every K
 // operand read from LDS feeds two MFMAs. The bf16 probabilities are already laid out as the B operand of
 // O^T += V^T P^T (k-slots 0-3 of a lane are its keys of one 16-key block, 4-7 those of the next), and V^T comes from
-// the row-major V tile in LDS through the transposing LDS read with the matching key order (zp_lds16).
+// the row-major V tile in LDS through the transposing LDS read with the matching key order (zp_pad16_addr).
 #include <type_traits>
 #include "zp_common.h"
 
@@ -308,7 +308,9 @@ __device__ __forceinline__ void fwd_finish(const zp_attn_params &p, const zp_til
 //    631 us with two, 568 with three).
 //  - TURNS (d = 128): three buffers by turns (51 KB), scores 32 keys at a time (168 registers), three workgroups per CU. The next K
 //    tile comes in during the scores, the next V tile goes, behind a second barrier, where K was. A third wave on the SIMD fills what
-//    the other two leave of its issue slots, above all while one of them starts or ends an item; a wave alone takes 15 % longer.
+//    the other two leave of its issue slots, above all while one of them starts or ends an item; a wave alone takes 15 % longer. 64K
+//    lognormal tokens MHA, by counter, two -> three: SQ_ACTIVE_INST_ANY per SQ_BUSY_CU_CYCLES 0.82 -> 0.96, matrix pipe busy 0.49 -> 0.54 of
+//    the cycles, which are 10 % fewer, at 1.85 instead of 1.91 GHz.
 // A row's first tile has a body of its own: no probabilities against a reference that is not there yet, no zeros to add to.
 // Two workgroups -> TURNS, us: 64K lognormal tokens MHA 1329 -> 1284, 64 x 1K MHA 729 -> 686, four sequences of 16384 7120 -> 7090,
 // 700 of up to 59 tokens, 64/8 heads: 502 (without the first tile's body) -> 445 -> 353; one of 14351 among 33137 tokens, 4 heads:

@@ -72,7 +72,7 @@ __device__ __forceinline__ zp_tile zp_load_tile(P p) {
 struct zp_inline_tiles {
   union {
     zp_tile t[ZP_INLINE_TILES];
-    // or the sequences themselves (zp_put_seqs): three words of each, then, 16 bits each, the sequence of every block
+    // or the sequences themselves (zp_put_seq): three words of each, then, 16 bits each, the sequence of every block
     uint32_t words[ZP_INLINE_TILES * 8];
   };
 };
