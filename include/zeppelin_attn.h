@@ -115,7 +115,7 @@ int varlen_attn_fwd_noalloc(const void *q, const void *k, const void *v, int64_t
  * bits whatever else is in the batch; dK and dV up to the order of their float32 sums, which follows how full the batch
  * makes the launch. Where the longest blocks of keys are shared among workgroups, their partial sums lie in `ws` and
  * zp_workspace_bytes has room for them (256 MB at most); a smaller `ws` that holds the rest does, without shares, and so in
- * another order of the sums.
+ * another order of the sums. (With flagged sequences: that size and the one of the batch without them together have the room.)
  * seq_skip_host: NULL, or host [S] flags; the dQ/dK/dV rows of a flagged sequence are not written (the caller runs
  * it as chunk pairs with chunk_attn_partial_bwd instead).
  * dq/dk/dv token strides are dq_stride (= for dQ) and dkv_stride (for dK and dV). */

@@ -261,6 +261,15 @@ def _bwd_may_share(T: int, S: int, Hq: int, Hkv: int) -> bool:
     return blocks > 56 or (blocks * Hkv + 7) // 8 * 8 * Hq >= 1024 * Hkv
 
 
+def _bwd_workspace_bytes(sh: ZpShape, cu: np.ndarray, skip) -> int:
+    """With room for the sums that the call takes: those of the unflagged sequences are in the size of the batch without the others."""
+    need = workspace_bytes(FN_BWD, sh, cu)
+    if skip is None:
+        return need
+    own = np.concatenate(([0], np.cumsum(np.where(skip, 0, np.diff(cu))))).astype(np.int32)
+    return need + workspace_bytes(FN_BWD, make_shape(own[-1], sh.S, sh.Hq, sh.Hkv, sh.d, sh.scale), own)
+
+
 def varlen_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, dq=None, dk=None, dv=None, scale=0.0, ws=None, stream=None,
                     seq_skip=None):
     """-> (dq [T,Hq,d], dk [T,Hkv,d], dv [T,Hkv,d]) bf16. Rows of sequences flagged in seq_skip are not written."""
@@ -278,7 +287,7 @@ def varlen_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, dq=None, dk=None, dv=None
                                                   _tok_stride(v), _tok_stride(o), _cu_ptr(cu), skp, dq.data_ptr(),
                                                   dk.data_ptr(), dv.data_ptr(), _tok_stride(dq), _tok_stride(dk),
                                                   ctypes.byref(sh), w.data_ptr(), w.numel(), _stream_ptr(stream)),
-                  ws, q.device, "bwd", stream, lambda: workspace_bytes(FN_BWD, sh, cu), _bwd_may_share(T, len(cu) - 1, Hq, Hkv))
+                  ws, q.device, "bwd", stream, lambda: _bwd_workspace_bytes(sh, cu, skip), _bwd_may_share(T, len(cu) - 1, Hq, Hkv))
     return dq, dk, dv
 
 

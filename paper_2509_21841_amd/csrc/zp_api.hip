@@ -516,13 +516,14 @@ struct KvLoad {
     blocks++;
   }
 };
-// How many iterations a share of a batch's blocks would have; 0: no block would be shared.
-int32_t plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk) {
+// How many iterations a share of the blocks of a batch's unflagged sequences would have; 0: no block would be shared.
+int32_t plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk, const uint8_t *skip = nullptr) {
+  auto tokens = [&](int s) { return skip && skip[s] ? 0 : (int64_t)cu[s + 1] - cu[s]; };
   const int grp = sh->Hq / sh->Hkv, c = sh->d == 128;
   const float unit = sh->d == 64 ? 2.f : 1.f;
   KvLoad all;
   for (int s = 0; s < sh->S; s++)
-    for (int64_t L = (int64_t)cu[s + 1] - cu[s]; L > 0; L -= bnk) all.add(kv_iterations(L, sh->d, grp), sh->d);
+    for (int64_t L = tokens(s); L > 0; L -= bnk) all.add(kv_iterations(L, sh->d, grp), sh->d);
   if (tiles_inline(2 * (size_t)all.blocks, launch_items((size_t)all.blocks, sh->Hkv, grp))) return 0;
   const float load = kv_cost[c].rate * all.sum * (float)sh->Hkv / 256.f;
   if (unit * (float)all.longest < 0.5f * load) return 0;
@@ -532,7 +533,7 @@ int32_t plan_kv_shares(const int32_t *cu, const zp_shape *sh, int bnk) {
     share = (share + grp - 1) / grp * grp;
     int64_t slots = 0, most = 0;
     for (int s = 0; s < sh->S; s++)
-      for (int64_t L = (int64_t)cu[s + 1] - cu[s]; L > 0; L -= bnk) {
+      for (int64_t L = tokens(s); L > 0; L -= bnk) {
         const int64_t n = kv_shares_of(kv_iterations(L, sh->d, grp), share);
         if (n == 1) break;  // nor do the sequence's blocks behind it have more
         slots += n;
@@ -605,18 +606,6 @@ BwdScratch bwd_scratch(size_t tiles, size_t sums, const zp_shape *sh) {
   w.parts_at = w.lse2_at + rows;
   w.bytes = w.parts_at + sums * 128 * 2 * (size_t)sh->d * sizeof(float);
   return w;
-}
-// Iterations of a share as a call on the whole batch takes them, which the size of its workspace is asked for; 0: no shares. (Calls with
-// flagged sequences take them only where that one does, and of the same length: the size is asked without flags, and room that
-// happens to be there must not decide.) kt: the batch's dK/dV tiles, where there are shares.
-int32_t batch_kv_share(const int32_t *cu, const zp_shape *sh, int bnk, std::vector<CostTile> &kt) {
-  const int32_t share = plan_kv_shares(cu, sh, bnk);
-  if (share == 0) return 0;
-  const int grp = sh->Hq / sh->Hkv;
-  plan_whole_keys(cu, sh->S, bnk, kt);
-  float time;
-  (void)dkdv_kernel_for(kt, sh->d, sh->Hkv, grp, &time);
-  return take_kv_shares(share, kt, sh->d, sh->Hkv, grp, time) ? share : 0;
 }
 
 }  // namespace
@@ -700,12 +689,20 @@ size_t zp_workspace_bytes(int which_fn, const zp_shape *sh, const int32_t *cu, i
     }
     case ZP_FN_BWD: {
       if (check_cu(cu, sh) != ZP_OK) return 0;
-      const int bnk = zp_attn_bwd_block_rows(sh->d, 1);
-      std::vector<CostTile> kt;
-      const int32_t share = batch_kv_share(cu, sh, bnk, kt);
-      const size_t slots = share ? (size_t)share_blocks(kt, sh->d, sh->Hq / sh->Hkv, share) : 0;
-      const size_t blocks = share ? kt.size() : (size_t)count_blocks(cu, sh->S, bnk);
-      return bwd_scratch((size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 0)) + blocks, slots * (size_t)sh->Hkv, sh).bytes + 512;
+      // (room for sums only where the call takes shares)
+      const int bnk = zp_attn_bwd_block_rows(sh->d, 1), grp = sh->Hq / sh->Hkv;
+      size_t tiles = (size_t)count_blocks(cu, sh->S, bnk), sums = 0;
+      if (const int32_t share = plan_kv_shares(cu, sh, bnk)) {
+        std::vector<CostTile> kt;
+        plan_whole_keys(cu, sh->S, bnk, kt);
+        float time;
+        (void)dkdv_kernel_for(kt, sh->d, sh->Hkv, grp, &time);
+        if (take_kv_shares(share, kt, sh->d, sh->Hkv, grp, time)) {
+          sums = (size_t)share_blocks(kt, sh->d, grp, share) * (size_t)sh->Hkv;
+          tiles = kt.size();
+        }
+      }
+      return bwd_scratch((size_t)count_blocks(cu, sh->S, zp_attn_bwd_block_rows(sh->d, 0)) + tiles, sums, sh).bytes + 512;
     }
     default: return 0;
   }
@@ -992,17 +989,16 @@ extern "C" int varlen_attn_bwd(const void *dout, const void *q, const void *k, c
   int32_t slots = 0, share = 0;
   const bool inline_tiles = tiles_inline(qt.size() + kt.size(), launch_items(std::max(qt.size(), kt.size()), sh->Hkv, grp));
   if (!inline_tiles) {
-    std::vector<CostTile> cut;
-    share = seq_skip ? batch_kv_share(cu, sh, bnk, cut) : plan_kv_shares(cu, sh, bnk);
+    share = plan_kv_shares(cu, sh, bnk, seq_skip);
     if (take_kv_shares(share, kt, sh->d, sh->Hkv, grp, kv_time)) {
-      cut = kt;
+      std::vector<CostTile> cut = kt;
       slots = share_blocks(cut, sh->d, grp, share);
-      // (not in a workspace that was sized for another batch, which may have needed none for sums)
+      // (not in a workspace that was sized for another batch or without the flags, which may have needed none for sums)
       if (ws_bytes < bwd_scratch(qt.size() + cut.size(), (size_t)slots * (size_t)sh->Hkv, sh).bytes) slots = 0;
-    }
-    if (slots) {
-      kv = KV_WHOLE;
-      kt.swap(cut);
+      else {
+        kv = KV_WHOLE;
+        kt.swap(cut);
+      }
     }
   }
   const size_t sums = (size_t)slots * (size_t)sh->Hkv;

@@ -63,8 +63,7 @@ def last_label(call):
 @pytest.mark.gpu
 @pytest.mark.parametrize("batch", WHOLE + SHARED)
 def test_exactly_the_stated_size_decides(batch):
-    """Shares where the size has room for them and only there, in a workspace of that size as in a larger one; with flagged sequences the
-    same bits in both."""
+    """Shares where the size has room for them and only there, in a workspace of that size as in a larger one."""
     lengths, Hq, Hkv, d = batch
     q, k, v, do = synth.make_qkv(sum(lengths), Hq, Hkv, d, 233, DEV, with_dout=True)
     cu = synth.cu_seqlens(lengths)
@@ -73,11 +72,35 @@ def test_exactly_the_stated_size_decides(batch):
     large = torch.empty(ws.numel() + (256 << 20), dtype=torch.uint8, device=DEV)
     shares = {w: last_label(lambda: B.varlen_attn_bwd(do, q, k, v, o, lse, cu, ws=w)) == "attn_bwd_dkdv_shares" for w in (ws, large)}
     assert set(shares.values()) == {batch in SHARED}
-    first = [1] + [0] * (len(lengths) - 1)
-    for skip in (first, [1 - x for x in first]):
-        runs = [B.varlen_attn_bwd(do, q, k, v, o, lse, cu, *map(torch.zeros_like, (q, k, v)), ws=w, seq_skip=skip) for w in (ws, large)]
-        for a, b in zip(*runs):
-            assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+def forget_scratch():
+    for key in [key for key in B._ws_cache if key[1] == "bwd"]:
+        del B._ws_cache[key]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rest,Hq,Hkv,d", [([3001] + [1] * 40, 8, 2, 128), ([3802, 900, 3100, 40, 2500, 3300], 16, 4, 64)])
+def test_what_is_left_of_a_flagged_batch_is_shared(rest, Hq, Hkv, d):
+    """Eight flagged sequences of 9000 tokens, with which the batch would not be shared: the others are, whatever scratch there is, and
+    give the bits that they give by themselves."""
+    lengths, skip = [9000] * 4 + rest + [9000] * 4, [1] * 4 + [0] * len(rest) + [1] * 4
+    assert scratch(lengths, Hq, Hkv, d) <= without_sums(lengths, Hq)
+    own = slice(36000, 36000 + sum(rest))
+    q, k, v, do = synth.make_qkv(sum(lengths), Hq, Hkv, d, 235, DEV, with_dout=True)
+    cut = [x[own] for x in (do, q, k, v)]
+    o, lse = torch.zeros_like(q), torch.zeros((Hq, len(q)), device=DEV)
+    o[own], lse[:, own] = B.varlen_attn_fwd(*cut[1:], synth.cu_seqlens(rest))
+    want = B.varlen_attn_bwd(*cut, o[own], lse[:, own].contiguous(), synth.cu_seqlens(rest))
+    for room in (4096, 8 << 20, 512 << 20):
+        forget_scratch()
+        B.workspace(room, torch.device(DEV), "bwd")
+        got = []
+        call = lambda: got.append(B.varlen_attn_bwd(do, q, k, v, o, lse, synth.cu_seqlens(lengths), seq_skip=skip))
+        assert last_label(call) == "attn_bwd_dkdv_shares"
+        for x, y in zip(got[0], want):
+            assert torch.equal(x[own].view(torch.int16), y.view(torch.int16))
+    forget_scratch()
 
 
 @pytest.mark.gpu
@@ -89,12 +112,10 @@ def test_the_same_bits_after_a_smaller_call(length, Hq, Hkv, d):
         o, lse = B.varlen_attn_fwd(q, k, v, cu)
         return B.varlen_attn_bwd(do, q, k, v, o, lse, cu)
 
-    for key in [key for key in B._ws_cache if key[1] == "bwd"]:
-        del B._ws_cache[key]
+    forget_scratch()
     B.workspace(2 << 20, torch.device(DEV), "bwd")   # room for everything but sums
     backward(300)
     after = backward(length)
-    for key in [key for key in B._ws_cache if key[1] == "bwd"]:
-        del B._ws_cache[key]
+    forget_scratch()
     for a, b in zip(after, backward(length)):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
